@@ -21,8 +21,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Wno-unused-command-line-argument"]
 # Per-file additions.  dsgc.hip: keep the MFMA accumulators in ordinary vector registers (the kernel
 # has registers to spare); otherwise the compiler parks them in accumulation registers and copies
-# all of them back and forth on every trip of the inner loop.
-EXTRA_FLAGS = {"dsgc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# all of them back and forth on every trip of the inner loop.  And leave its LDS counter's atomic add to one lane as
+# it is written: the optimizer for atomics on one address turns it into a sum over the wave whose result is waited
+# for on the spot, an LDS round trip per iteration.
+EXTRA_FLAGS = {"dsgc.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
 
 
 def _stale(obj: str, deps) -> bool:

@@ -36,6 +36,7 @@ __host__ __device__ inline int odd_pitch(int granules) { return (granules & 1) ?
 // the "row exists" test of the epilogue is the same for every lane.
 template <bool DGRAD, int MT, int NTW, bool UNI>
 __global__ __launch_bounds__(256) void band_kernel(const IgemmArgs a, int BP, int nbands_h, int nbands) {
+    raise_wave_priority();
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const int Cg16 = a.Ca >> 4;
     const int G = a.R * a.S * Cg16;          // reduction granules
@@ -254,6 +255,7 @@ struct BandRegTab {
 template <bool DGRAD, int NKS>
 __global__ __launch_bounds__(256, 2) void band_reg_kernel(const IgemmArgs a, int BP, int nbands_h, int nbands,
                                                           const BandRegTab tab) {
+    raise_wave_priority();
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const int Cg16 = a.Ca >> 4;
     constexpr int G = 2 * NKS;                // = R * S * Cg16 (host)

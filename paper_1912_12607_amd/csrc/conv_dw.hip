@@ -19,6 +19,7 @@ constexpr int DW_MAX_TAPS = 64;   // R*S limit of the depthwise kernels
 // NT: threads per block (64, 128 or 256 by plane size, dw_threads()).
 template <bool DGRAD, int ST, int NT>
 __global__ __launch_bounds__(NT) void dw_conv_kernel(const DwArgs a) {
+    raise_wave_priority();
     const int stride_h = ST ? ST : a.stride_h, stride_w = ST ? ST : a.stride_w;
     extern __shared__ __attribute__((aligned(16))) int8_t plane[];
     __shared__ int wtap[DW_MAX_TAPS];
@@ -285,6 +286,7 @@ constexpr int DW_MAX_PPB = 32;        // planes per block of the fast path, at m
 // further right as well.
 template <bool DGRAD, int SD, int NT, int ST = 1, int OFF = 0>    // SD = dwords of packed weights per filter row (S <= 4*SD)
 __global__ __launch_bounds__(NT) void dw_conv_fast_kernel(const DwArgs a, int pitch, int rows, int ppb) {
+    raise_wave_priority();
     static_assert(ST == 1 || (ST == 2 && !DGRAD), "the strided form is the forward pass at stride 2");
     extern __shared__ __attribute__((aligned(16))) int8_t plane[];
     __shared__ uint32_t wrow[DW_MAX_PPB][DW_FAST_MAXR][SD];

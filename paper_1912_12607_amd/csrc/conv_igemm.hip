@@ -406,6 +406,7 @@ __global__ __launch_bounds__(128 * WM, WM == 2 ? (ALLC ? 2 : (BNT == 128 && KG =
     constexpr int NL = NLA + NLB;
     static_assert(NSTAGE == 2 || NL == 6 || NL == 4, "vmcnt waits below are written for these");
     extern __shared__ __attribute__((aligned(16))) uint4 ring[];   // [NSTAGE][STAGE_SLOTS]
+    raise_wave_priority();
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;

@@ -9,6 +9,12 @@ namespace int8t {
 
 constexpr int kWave = 64;            // CDNA wavefront width
 
+// Raises the wave's issue priority.  For the kernels that may run on a second stream beside the clip search: they wait for
+// memory most of the time and issue little, the search's waves issue all the time, and at equal priority the older waves
+// -- the search's -- go first (64 -> 256 1x1 layer at 56 x 56, batch 256: step 1233 -> 1124 us; 7x7 stem, batch 64: 365 ->
+// 336).  Without such a neighbour all waves of a compute unit have the same priority and nothing changes.
+__device__ __forceinline__ void raise_wave_priority() { __builtin_amdgcn_s_setprio(3); }
+
 // ---------------------------------------------------------------------------
 // Wavefront / block reductions (64-wide shuffles, then one LDS hop per wave).
 // ---------------------------------------------------------------------------
@@ -138,40 +144,6 @@ __device__ __forceinline__ int stoch_fixed(float x, float inv24, float uf) {
     asm("v_cvt_i32_f32 %0, %1" : "=v"(X) : "v"(t));
     return X;
 }
-// same with the scale in a scalar register
-__device__ __forceinline__ int stoch_fixed_s(float x, float inv24_uniform, float uf) {
-    float t;
-    int X;
-    asm volatile("v_fma_f32 %0, |%1|, %2, %3" : "=v"(t) : "v"(x), "s"(inv24_uniform), "v"(uf));
-    asm("v_cvt_i32_f32 %0, %1" : "=v"(X) : "v"(t));
-    return X;
-}
-
-// Four elements against one (uniform) scale: the four magnitudes min(127, floor(|x_e| * inv + u_e)), u_e in [0, 1),
-// packed as bytes [m0, m1, m2, m3].  The caller passes inv2 = 2 * inv and uf2 = 2 * u_e (both exact): in the
-// round-down mode the fused multiply-add never crosses an integer, the float -> byte convert-and-pack follows the
-// wave's rounding mode (so it floors) and saturates at 255, and floor(2t) >> 1 = floor(t) with 255 >> 1 = 127.
-// Ten instructions for four codes; one instruction block, so they stay together and in this order.
-__device__ __forceinline__ uint32_t stoch_codes4(const float x[4], float inv2_uniform, const float uf2[4]) {
-    uint32_t a;
-    float t0, t1, t2, t3;
-    asm volatile(
-        "v_fma_f32 %1, |%5|, %9, %10\n\t"
-        "v_fma_f32 %2, |%6|, %9, %11\n\t"
-        "v_fma_f32 %3, |%7|, %9, %12\n\t"
-        "v_fma_f32 %4, |%8|, %9, %13\n\t"
-        "v_cvt_pk_u8_f32 %0, %1, 0, 0\n\t"
-        "v_cvt_pk_u8_f32 %0, %2, 1, %0\n\t"
-        "v_cvt_pk_u8_f32 %0, %3, 2, %0\n\t"
-        "v_cvt_pk_u8_f32 %0, %4, 3, %0\n\t"
-        "v_lshrrev_b32 %0, 1, %0\n\t"
-        "v_and_b32 %0, %14, %0"
-        : "=&v"(a), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(inv2_uniform), "v"(uf2[0]), "v"(uf2[1]), "v"(uf2[2]),
-          "v"(uf2[3]), "s"(0x7f7f7f7fu));
-    return a;
-}
-
 // One code, with NaN -> 0.  STOCH needs fp32_round_down_mode() and inv = inv24.
 template <bool STOCH>
 __device__ __forceinline__ int quantize_one(float x, float inv, uint32_t seed_lo, uint32_t seed_hi_mul,

@@ -7,24 +7,38 @@
 // once per element and shared by all candidates -- the same draw the later quantize call uses,
 // so the search scores exactly the codes that will be produced.
 //
-// The sweep is bound by the plain vector ALUs, not by HBM (4 bytes per element against several
+// The sweep is bound by the vector ALUs, not by HBM (4 bytes per element against several
 // operations per element AND candidate), so the arithmetic is arranged to need few instructions:
 //   * codes are sign(g) * m with m the rounded magnitude, so g*q = |g|*m and q^2 = m^2: the whole
 //     search runs on magnitudes and never looks at a sign;
-//   * m = floor(2 (|g| * inv + u)) >> 1: one round-down fused multiply-add and one convert that floors,
-//     saturates and drops its byte into the dword of four elements, then one shift and one mask per dword
-//     (see device_common.h).  These 2.5 instructions per element and candidate are all the vector ALU
-//     does per evaluation;
+//   * m = floor(|g| * inv + u): one round-down fused multiply-add and one convert that floors,
+//     saturates at 255 and drops its byte into the dword of four elements.  The clip at 127 costs a shift and a
+//     mask per dword more (floor(2t) >> 1 = floor(t), 255 >> 1 = 127) and is left out for the eights of candidates
+//     none of which clips any of the wave's 256 elements: with the heavy tails of a gradient that is three
+//     of the four eights of the default grid nearly always (205 M elements: 22 us of 478);
 //   * |g| is turned, once per element, into a 44-bit fixed-point integer relative to max|g|
-//     (H * 2^22 + L, H, L <= 2^22), and both halves into three balanced (signed) byte digits;
+//     (H * 2^22 + L, H, L <= 2^22), and both halves into three byte digits.  In the round-down mode adding
+//     2^23 leaves floor(.) in the low mantissa bits, so the halves cost adds instead of floor / round / convert;
 //   * the sums A_j = sum |g| m_j (six digit sums) and B_j = sum m_j^2 are int8 x int8 products
 //     with int32 accumulation, i.e. matrix products [digits x elements] * [elements x candidates]
 //     and [candidates x elements] * [elements x candidates] (diagonal): they go to the matrix
 //     cores.  A lane computes the codes of ITS four elements for all candidates, but an MFMA
-//     operand wants one candidate's codes of 16 elements in a lane, so the code dwords take a trip
-//     through a wave-private LDS tile (one byte per evaluation), which is cheap next to the ALU
-//     work.  No barriers: a wave only reads what it wrote itself, and LDS serves a wave's
-//     instructions in order.
+//     operand wants one candidate's codes of 16 elements: the code dwords pass through a wave-private
+//     LDS tile (no barriers needed: a wave reads only what it wrote), sixteen candidates at a time.
+//
+// What an instruction costs here (one SIMD, many waves, cycles per wave instruction): 2 - 2.5 for fp32 add / multiply /
+// fused multiply-add, integer add, right shift and the bitwise operations on vector registers, 4 - 4.5 for
+// everything else (conversions, byte permutes, min / max, 24-bit and full integer multiplies, left shifts, and any of the first
+// group with a scalar operand) -- two pipes, of which one does everything.  About 400 instructions per 256 elements at
+// 2.5 cycles each, 16 MFMAs and their operand reads (a fifth of the time) are what the loop now consists of.
+//
+// One block of 16 waves per compute unit: a compute unit issues from its oldest waves first, so of three equal
+// blocks that share one the first was done in half the time of the last, and the last ran alone (205 M elements: blocks
+// between 237 and 448 us).  The waves of a block therefore take their wave-iterations from a counter in LDS as
+// they come.  616 -> 466 us at 205 M elements, 161 -> 118 at 51 M, 47.6 -> 38.6 at 12.8 M, 21.4 -> 18.3 at 3.2 M.
+// The block leaves half the wave slots, 66 KB of LDS and 7/16 of the registers to kernels of another stream; those raise their
+// waves' priority (they are bound by HBM and issue little), which is what lets them run beside this kernel.
+//
 // The integer sums are exact and order independent; the only error against an fp64 evaluation is
 // the fixed-point rounding of |g|, |delta| <= max|g| * 2^-44 per element, i.e. at most
 // 2^-44 * sqrt(n) in d_j (Cauchy-Schwarz), far below the resolution the search needs.
@@ -44,32 +58,22 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int DSGC_JC = 32;        // candidates per block: the 32 columns of one MFMA tile
 constexpr int DSGC_JPAD = 64;      // row pitch of the partial arrays (= INT8T_MAX_CANDIDATES)
-// Three blocks per compute unit.  A fourth would fit (LDS 4 x 40 KB, 4 waves per SIMD) and is about
-// 2 us faster when the sweep has the GPU to itself, but three leave 40 KB of LDS and half the wave
-// slots to kernels of another stream: the sweep is bound by the vector ALUs, so HBM-bound kernels
-// (quantizers, a forward convolution) can run beside it.
-constexpr int DSGC_MAX_BLOCKS = 768;
+constexpr int DSGC_MAX_BLOCKS = 256;         // one per compute unit
+constexpr int DSGC_MAX_THREADS = 1024;
 constexpr int DSGC_GROUPS = 32;     // accumulator sets the blocks spread their atomics over
-constexpr int DSGC_ROWS = DSGC_JC + 6;   // 32 code rows, then the 6 digit rows
+constexpr int DSGC_JH = 16;                 // candidates per pass through the LDS tile: the columns of one MFMA
+constexpr int DSGC_ROWS = DSGC_JH + 6;      // 16 code rows, then the 6 digit rows
 // A wave's LDS tile holds 256 elements x DSGC_ROWS byte rows, stored by 16-element granule:
-// [granule 0..15][row][16 bytes], with the granule pitch padded to 39 rows.  An MFMA operand read
-// (32 lanes = 32 consecutive rows of one granule) is then 512 contiguous bytes, and the 16 granules
-// a store instruction touches (4 lanes each) start 156 banks apart, i.e. in 16 different groups of
-// 4 banks -- both free of bank conflicts, and 2.5 KB smaller per wave than padded rows, which is what
-// lets a fourth block fit a compute unit.
-constexpr int DSGC_GPITCH = (DSGC_ROWS + 1) * 16;   // 624 bytes
-constexpr int DSGC_TILE = 16 * DSGC_GPITCH;         // 9984 bytes per wave
+// [granule 0..15][row][16 bytes], with the granule pitch padded to 23 rows.  An MFMA operand read
+// (16 lanes = 16 consecutive rows of one granule) is then 256 contiguous bytes, and the 16 granules
+// a store instruction touches (4 lanes each) start 92 banks apart, i.e. in 16 different groups of
+// 4 banks -- both free of bank conflicts.
+constexpr int DSGC_GPITCH = (DSGC_ROWS + 1) * 16;   // 368 bytes
+constexpr int DSGC_TILE = 16 * DSGC_GPITCH;         // 5888 bytes per wave
 // int32 accumulators: |digit * code| <= 128 * 127 per element and lane sum; flushed well before 2^31
-// (the bound is 256 iterations: 256 x 256 elements x 16256 < 2^31; 16 keeps the flush path in use at
-// the benchmark sizes -- 12 to 28 iterations per block -- at a cost of under 1 % of the loop)
-constexpr int DSGC_FLUSH_ITERS = 16;
+// (64 iterations: 64 x 256 elements x 16256 < 2^28.1)
+constexpr int DSGC_FLUSH_ITERS = 64;
 
-// bytes [a.b3, b.b3, c.b3, d.b3]: the top bytes of four 32-bit values
-__device__ __forceinline__ uint32_t top_bytes(int a, int b, int c, int d) {
-    const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0703u);   // a.b3 b.b3 0 0
-    const uint32_t hi = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x07030c0cu);   // 0 0 c.b3 d.b3
-    return lo | hi;
-}
 // bytes [a.b0, b.b0, c.b0, d.b0]
 __device__ __forceinline__ uint32_t low_bytes(int a, int b, int c, int d) {
     const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
@@ -77,92 +81,124 @@ __device__ __forceinline__ uint32_t low_bytes(int a, int b, int c, int d) {
     return lo | hi;
 }
 
-// Balanced byte digits of four integers 0 <= v <= 2^22:  v = d0 + 256 d1 + 65536 d2 with
-// -128 <= d < 128 (the bytes of v + 0x808080, each minus 128).  plane[b] packs digit b of the
-// four values as signed bytes.
-__device__ __forceinline__ void digit_planes(const uint32_t v[4], uint32_t plane[3]) {
-    uint32_t y[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = v[e] + 0x808080u;
+// Byte digits of four integers 0 <= v <= 2^22, handed in as y = v + 0x8080 in the low 24 bits (the top byte is
+// ignored): v = d0 + 256 d1 + 65536 d2 with -128 <= d0, d1 < 128 (bytes 0 and 1 of y, each minus 128) and
+// 0 <= d2 <= 64.  plane[b] packs digit b of the four values as signed bytes.
+__device__ __forceinline__ void digit_planes(const uint32_t y[4], uint32_t plane[3]) {
     const uint32_t t0 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u);  // y0.b0 y1.b0 y0.b1 y1.b1
     const uint32_t t1 = __builtin_amdgcn_perm(y[1], y[0], 0x0c0c0602u);  // y0.b2 y1.b2 0 0
     const uint32_t t2 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
     const uint32_t t3 = __builtin_amdgcn_perm(y[3], y[2], 0x06020c0cu);  // 0 0 y2.b2 y3.b2
     plane[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100u) ^ 0x80808080u;
     plane[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ 0x80808080u;
-    plane[2] = (t1 | t3) ^ 0x80808080u;
+    plane[2] = t1 | t3;
+}
+
+// 2 v of a positive scale (or of an infinite one: the reciprocal of a very small clip value), on the scalar unit: the
+// exponent plus one.  (0 becomes a tiny number, which only meets elements that are 0 and candidates that do not exist.)
+// Volatile, so that the doubled scales of all candidates are not kept, and spilled, across the loop.
+__device__ __forceinline__ float twice(float v) {
+    int b;
+    asm volatile("s_add_u32 %0, %1, 0x800000\n\ts_min_u32 %0, %0, 0x7f800000" : "=&s"(b) : "s"(v) : "scc");
+    return __int_as_float(b);
+}
+
+// Two candidates against four elements: the magnitudes floor(|x_e| * inv + u_e) of both as bytes (saturated at 255).
+// The two chains are interleaved: a convert-and-pack depends on the one before it.
+__device__ __forceinline__ void stoch_codes4x2(const float x[4], float ia, float ib, const float uf[4], uint32_t& a, uint32_t& b) {
+    float t0, t1, t2, t3, s0, s1, s2, s3;
+    asm volatile(
+        "v_fma_f32 %2, |%10|, %14, %16\n\t"
+        "v_fma_f32 %6, |%10|, %15, %16\n\t"
+        "v_fma_f32 %3, |%11|, %14, %17\n\t"
+        "v_cvt_pk_u8_f32 %0, %2, 0, 0\n\t"
+        "v_fma_f32 %7, |%11|, %15, %17\n\t"
+        "v_cvt_pk_u8_f32 %1, %6, 0, 0\n\t"
+        "v_fma_f32 %4, |%12|, %14, %18\n\t"
+        "v_cvt_pk_u8_f32 %0, %3, 1, %0\n\t"
+        "v_fma_f32 %8, |%12|, %15, %18\n\t"
+        "v_cvt_pk_u8_f32 %1, %7, 1, %1\n\t"
+        "v_fma_f32 %5, |%13|, %14, %19\n\t"
+        "v_cvt_pk_u8_f32 %0, %4, 2, %0\n\t"
+        "v_fma_f32 %9, |%13|, %15, %19\n\t"
+        "v_cvt_pk_u8_f32 %1, %8, 2, %1\n\t"
+        "v_cvt_pk_u8_f32 %0, %5, 3, %0\n\t"
+        "v_cvt_pk_u8_f32 %1, %9, 3, %1"
+        : "=&v"(a), "=&v"(b), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3), "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3)
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(ia), "s"(ib), "v"(uf[0]), "v"(uf[1]), "v"(uf[2]), "v"(uf[3]));
 }
 
 template <bool STOCH>
-__global__ __launch_bounds__(256) void dsgc_sweep_kernel(
+__global__ __launch_bounds__(DSGC_MAX_THREADS) void dsgc_sweep_kernel(
     const float* __restrict__ g, size_t n, const float* __restrict__ ratios, int n_cand,
     const float* __restrict__ absmax_part, int nparts, uint32_t seed_lo, uint32_t seed_hi_mul,
     unsigned long long* __restrict__ acc, unsigned int* __restrict__ ticket, const double* __restrict__ partG,
     float* __restrict__ clip_out, double* __restrict__ dev_out, double* __restrict__ dev_all_out) {
-    constexpr int JC = DSGC_JC;
+    constexpr int JC = DSGC_JC, JH = DSGC_JH;
     __shared__ float lds4[4];
-    __shared__ float s_inv[JC];
     __shared__ unsigned int s_last;
-    __shared__ __attribute__((aligned(16))) unsigned char s_tile[4][DSGC_TILE];
-    // the block reductions after the sweep re-use the tiles' memory
-    long long (*const s_red)[JC][3] = reinterpret_cast<long long (*)[JC][3]>(&s_tile[0][0]);
-    static_assert(sizeof(long long) * 4 * JC * 3 <= sizeof(s_tile), "reduction scratch fits the tiles");
+    __shared__ unsigned long long s_tot[JC * 3];
+    __shared__ int s_next;
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_tile[];     // one tile per wave
+    const int nwaves = (int)blockDim.x >> 6;
 
     const int j0 = blockIdx.y * JC;
     const int jn = (n_cand - j0 < JC) ? (n_cand - j0) : JC;
     // Everything the prologue fetches is requested before the first wait: the absmax partials, the ratios and
-    // the block's first 16 bytes per lane of g (one memory round trip instead of three in a row, about 1 us
+    // the wave's first 16 bytes per lane of g (one memory round trip instead of three in a row, about 1 us
     // of a sweep that takes 10 us on a small tensor).
     absmax_partials_begin(absmax_part, nparts, lds4);
     const size_t n4 = n >> 2;
     const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
-    const size_t i_first = (size_t)blockIdx.x * 256 + threadIdx.x;
+    // the wave-iterations (64 float4 each) of a block: blockIdx.x + k * gridDim.x, k = 0, 1, ..; its waves take them as they come
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const size_t i_first = ((size_t)w * gridDim.x + blockIdx.x) * 64 + lane;
     const float4 f_first = (i_first < n4) ? g4[i_first] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float ratio_j = ratios[j0 + ((int)threadIdx.x < jn ? (int)threadIdx.x : 0)];
+    const float ratio_j = ratios[j0 + (lane < jn ? lane : 0)];
+    if (threadIdx.x < 3 * JC) s_tot[threadIdx.x] = 0ull;
+    if (threadIdx.x == 0) s_next = nwaves;
     const float M = absmax_partials_end(lds4);
-    if (threadIdx.x < JC) {
-        const int j = threadIdx.x;
-        const float c = (j < jn) ? __fmul_rn(M, ratio_j) : 0.0f;
-        // the stochastic sweep works on twice the scaled value (exact power-of-two factor; stoch_codes4)
-        s_inv[j] = STOCH ? __fmul_rn(inv_scale_of(c), 2.0f) : inv_scale_of(c);
-    }
-    __syncthreads();
     // fixed point: max|g| < 2^e, |g| * 2^(22-e) <= 2^22
     int e2 = 0;
     float mant = frexpf(M, &e2);
+    // lane j < 32 of every wave: candidate j's clip value, scale and -- a little below the clip value -- the largest |g|
+    // it surely does not clip; of the latter the smallest of every eight candidates.  A candidate that does not exist has
+    // scale 0; one whose scale overflows sends its eight to the clipping form.
+    const float clip_j = lane < jn ? __fmul_rn(M, ratio_j) : 0.0f;
+    const float inv_j = inv_scale_of(clip_j);
+    float thr_j = inv_j == 0.0f ? __builtin_huge_valf() : inv_j < __builtin_huge_valf() ? 0.99f * clip_j : 0.0f;
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) thr_j = fminf(thr_j, __shfl_xor(thr_j, o, kWave));
+    float inv[JC], thr[JC / 8];
+#pragma unroll
+    for (int j = 0; j < JC; ++j) inv[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_j), j));
+#pragma unroll
+    for (int q = 0; q < JC / 8; ++q) thr[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(thr_j), 8 * q));
     float e2f = (float)e2;
-    // From here on every fp32 operation of the stochastic sweep is either exact or the one
-    // round-down multiply-add; the candidates' scales above were computed (by other lanes, before
-    // the barrier) in the default mode.
+    // From here on every fp32 operation of the stochastic sweep is either exact or meant to round down; the candidates'
+    // scales above are in scalar registers by now, computed in the default mode.
+#pragma unroll
+    for (int j = 0; j < JC; ++j) asm volatile("" : "+s"(inv[j]));
     if (STOCH) fp32_round_down_mode(mant, e2f);
     const int shift = 22 - (int)e2f;
-    float inv[JC];
-#pragma unroll
-    for (int j = 0; j < JC; ++j)
-        inv[j] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_inv[j])));
 
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int l16 = lane & 15, kg = lane >> 4;
-    unsigned char* __restrict__ const tile = s_tile[w];
+    unsigned char* __restrict__ const tile = s_tile + (size_t)w * DSGC_TILE;
     // this lane's four elements live in granule lane / 4, bytes 4 * (lane % 4) ..; + 16 * row
     uint32_t* __restrict__ const wr = reinterpret_cast<uint32_t*>(tile + (lane >> 2) * DSGC_GPITCH + 4 * (lane & 3));
     // MFMA operands of this lane (16 x 16 x 64 tiles: a lane supplies 16 reduction bytes of one row):
-    // codes of candidate l16 (+ 16 for the second candidate group) / digit row min(l16, 5), granule
-    // 4 * step + kg
+    // codes of candidate l16 of the half in the tile / digit row min(l16, 5), granule 4 * step + kg
     const unsigned char* __restrict__ const rd_code = tile + kg * DSGC_GPITCH + l16 * 16;
-    const unsigned char* __restrict__ const rd_dig = tile + kg * DSGC_GPITCH + (JC + (l16 < 5 ? l16 : 5)) * 16;
+    const unsigned char* __restrict__ const rd_dig = tile + kg * DSGC_GPITCH + (JH + (l16 < 5 ? l16 : 5)) * 16;
 
-    // per candidate group h: [digit row][candidate] (rows 0..5 used) and [candidate][candidate] (diagonal
-    // used).  The 16-row tiles waste far fewer rows on the six digit rows than 32-row ones would.
+    // per candidate half h: [digit row][candidate] (rows 0..5 used) and [candidate][candidate] (diagonal used)
     v4i accA[2], accB[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int v = 0; v < 4; ++v) accA[h][v] = accB[h][v] = 0;
-    // lanes 0..15: totals so far (flushed part) of candidates l16 and 16 + l16: sum H*m, sum L*m, sum m^2
-    long long runH[2] = {0, 0}, runL[2] = {0, 0}, runB[2] = {0, 0};
 
-    // int32 tiles -> 64-bit per-candidate totals in lanes 0..15, accumulators cleared
+    // int32 tiles -> the block's 64-bit per-candidate totals, accumulators cleared
     auto flush = [&]() {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -175,89 +211,123 @@ __global__ __launch_bounds__(256) void dsgc_sweep_kernel(
             } else if (kg == 1) {
                 pl = 256LL * accA[h][0] + 65536LL * accA[h][1];
             }
-            pl += __shfl_xor(pl, 16, kWave);
-            runH[h] += ph;       // meaningful in lanes 0..15 only
-            runL[h] += pl;
+            unsigned long long* const t = s_tot + (16 * h + l16) * 3;
+            if (kg == 0) __hip_atomic_fetch_add(t + 0, (unsigned long long)ph, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (kg < 2) __hip_atomic_fetch_add(t + 1, (unsigned long long)pl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             // accB[h]: the diagonal element of column l16 is row l16 = 4*kg + v
             int diag = 0;
 #pragma unroll
             for (int v = 0; v < 4; ++v) diag = (v == (l16 & 3)) ? accB[h][v] : diag;
-            long long bd = ((l16 >> 2) == kg) ? (long long)diag : 0LL;
-            bd += __shfl_xor(bd, 16, kWave);
-            bd += __shfl_xor(bd, 32, kWave);
-            runB[h] += bd;
+            if ((l16 >> 2) == kg) __hip_atomic_fetch_add(t + 2, (unsigned long long)(long long)diag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
             for (int v = 0; v < 4; ++v) accA[h][v] = accB[h][v] = 0;
         }
     };
+    // constants of the loop in vector registers: with a literal or scalar operand the adds take twice as long
+    float cmag = 8388608.0f + 32896.0f, c22 = 4194304.0f, cm24 = 0x1p-24f;
+    uint32_t mask7 = 0x7f7f7f7fu;
+    asm volatile("" : "+v"(cmag), "+v"(c22), "+v"(cm24), "+v"(mask7));
 
     // one wave iteration: 256 consecutive elements, four per lane
     auto group = [&](const float x[4], uint32_t index0) {
         float uf[4] = {0.f, 0.f, 0.f, 0.f};
         uint32_t H[4], L[4];
+        const uint32_t ix = index0 ^ seed_lo;            // index0 is a multiple of 4: (index0 + e) ^ key = ix ^ e
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (STOCH) uf[e] = (float)rng24(seed_lo, seed_hi_mul, index0 + e) * 0x1p-23f;   // 2 u, u in [0, 1): exact
             const float xs = ldexpf(fabsf(x[e]), shift);     // exact, 0 .. 2^22
-            const float h = floorf(xs);
-            H[e] = (uint32_t)h;
-            L[e] = (uint32_t)rintf((xs - h) * 4194304.0f);   // remainder * 2^22: exact before rint
+            if (STOCH) {
+                uf[e] = (float)(rng_mix32((ix ^ (uint32_t)e) + seed_hi_mul) >> 8) * cm24;
+                // round-down mode: 2^23 + 0x8080 + floor(xs), i.e. floor(xs) + 0x8080 in the low mantissa bits; then the
+                // remainder times 2^22, rounded to nearest (floor of it plus a half; every step but the last exact)
+                const float hs = xs + cmag;
+                const float ls = __builtin_fmaf(xs - (hs - cmag), c22, 0.5f) + cmag;
+                H[e] = __float_as_uint(hs);
+                L[e] = __float_as_uint(ls);
+            } else {
+                const float h = floorf(xs);
+                H[e] = (uint32_t)h + 0x8080u;          // (digit_planes' offset)
+                L[e] = (uint32_t)rintf((xs - h) * 4194304.0f) + 0x8080u;
+            }
         }
         uint32_t pH[3], pL[3];
         digit_planes(H, pH);
         digit_planes(L, pL);
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
-            wr[(JC + b) * 4] = pH[b];
-            wr[(JC + 3 + b) * 4] = pL[b];
+            wr[(JH + b) * 4] = pH[b];
+            wr[(JH + 3 + b) * 4] = pL[b];
         }
+        const float xm = STOCH ? fmaxf(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fabsf(x[2])), fabsf(x[3])) : 0.0f;
 #pragma unroll
-        for (int j = 0; j < JC; ++j) {
-            uint32_t rp;
-            if (STOCH) {
-                rp = stoch_codes4(x, inv[j], uf);
-            } else {
-                rp = low_bytes(round_nearest_code(fabsf(x[0]), inv[j]), round_nearest_code(fabsf(x[1]), inv[j]),
-                               round_nearest_code(fabsf(x[2]), inv[j]), round_nearest_code(fabsf(x[3]), inv[j]));
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int q = 2 * h; q < 2 * h + 2; ++q) {
+                uint32_t* const wq = wr + (8 * q - JH * h) * 4;
+                if (!STOCH) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        wq[4 * j] = low_bytes(round_nearest_code(fabsf(x[0]), inv[8 * q + j]), round_nearest_code(fabsf(x[1]), inv[8 * q + j]),
+                                              round_nearest_code(fabsf(x[2]), inv[8 * q + j]), round_nearest_code(fabsf(x[3]), inv[8 * q + j]));
+                } else if (!__any(xm >= thr[q])) {
+#pragma unroll
+                    for (int j = 0; j < 8; j += 2) {
+                        uint32_t a, b;
+                        stoch_codes4x2(x, inv[8 * q + j], inv[8 * q + j + 1], uf, a, b);
+                        wq[4 * j] = a;
+                        wq[4 * j + 4] = b;
+                    }
+                } else {
+                    float u2[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) u2[e] = uf[e] + uf[e];
+#pragma unroll
+                    for (int j = 0; j < 8; j += 2) {
+                        uint32_t a, b;
+                        stoch_codes4x2(x, twice(inv[8 * q + j]), twice(inv[8 * q + j + 1]), u2, a, b);
+                        wq[4 * j] = (a >> 1) & mask7;
+                        wq[4 * j + 4] = (b >> 1) & mask7;
+                    }
+                }
             }
-            wr[j * 4] = rp;
-        }
-        __builtin_amdgcn_wave_barrier();   // keep the tile's stores ahead of its loads
+            __builtin_amdgcn_wave_barrier();   // keep the tile's stores ahead of its loads
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const uint4 td = *reinterpret_cast<const uint4*>(rd_dig + 4 * DSGC_GPITCH * s);
-            const v4i fd = v4i{(int)td.x, (int)td.y, (int)td.z, (int)td.w};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint4 tc = *reinterpret_cast<const uint4*>(rd_code + 4 * DSGC_GPITCH * s + 256 * h);
-                const v4i fc = v4i{(int)tc.x, (int)tc.y, (int)tc.z, (int)tc.w};
+            for (int s = 0; s < 4; ++s) {
+                const v4i fd = *reinterpret_cast<const v4i*>(rd_dig + 4 * DSGC_GPITCH * s);
+                const v4i fc = *reinterpret_cast<const v4i*>(rd_code + 4 * DSGC_GPITCH * s);
                 accA[h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fd, fc, accA[h], 0, 0, 0);
                 accB[h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fc, fc, accB[h], 0, 0, 0);
             }
+            __builtin_amdgcn_wave_barrier();   // and the next stores behind these loads
         }
-        __builtin_amdgcn_wave_barrier();   // and the next iteration's stores behind these loads
     };
 
-    const size_t stride = (size_t)gridDim.x * 256;
     {
         // Wave-uniform trip count (the MFMAs need the whole wave): lanes beyond the end carry zeros,
         // which add nothing to A or B.  The next iteration's 16 bytes are requested before this
-        // iteration's arithmetic starts.  The int32 tiles are turned into 64-bit totals after every
-        // DSGC_FLUSH_ITERS iterations, outside the inner loop, so inside it only MFMAs touch them.
-        size_t i = i_first;
-        size_t ibase = (size_t)blockIdx.x * 256 + 64 * w;      // the wave's first float4
+        // iteration's arithmetic starts.
+        const int units = (int)((n4 + 63) >> 6);
+        int u = w * (int)gridDim.x + (int)blockIdx.x;      // this wave's current wave-iteration
         float4 f = f_first;
-        while (ibase < n4) {
-            for (int it = 0; it < DSGC_FLUSH_ITERS && ibase < n4; ++it) {
-                const size_t inext = i + stride;
+        // (waits for the first data here: inside the loop the wait would be for the load just issued)
+        asm volatile("" : "+v"(f.x), "+v"(f.y), "+v"(f.z), "+v"(f.w));
+        int knext = 0;                                     // (lane 0) the number of the one after it, asked for an iteration ahead
+        auto draw = [&]() {
+            if (lane == 0) knext = __hip_atomic_fetch_add(&s_next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        draw();
+        while (u < units) {
+            for (int it = 0; it < DSGC_FLUSH_ITERS && u < units; ++it) {
+                const int un = __builtin_amdgcn_readfirstlane(knext) * (int)gridDim.x + (int)blockIdx.x;
+                const size_t inext = (size_t)un * 64 + lane;
                 const float4 fn = (inext < n4) ? g4[inext] : make_float4(0.f, 0.f, 0.f, 0.f);
+                draw();
                 const float vv[4] = {f.x, f.y, f.z, f.w};
-                group(vv, (uint32_t)(4 * i));
+                group(vv, (uint32_t)u * 256u + 4u * (uint32_t)lane);
                 f = fn;
-                i = inext;
-                ibase += stride;
+                u = un;
             }
-            flush();
+            if (u < units) flush();
         }
     }
     if (blockIdx.x == 0 && w == 0 && (n & 3)) {
@@ -266,26 +336,16 @@ __global__ __launch_bounds__(256) void dsgc_sweep_kernel(
         if (lane == 0)
             for (int e = 0; e < (int)(n & 3); ++e) vv[e] = g[(n4 << 2) + e];
         group(vv, (uint32_t)(n4 << 2) + 4u * (uint32_t)lane);
-        flush();
     }
+    flush();
 
     // block totals -> one of the accumulator sets
-    __syncthreads();   // every wave is done with its tile: the memory now serves the reductions
-    if (lane < 16) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            s_red[w][16 * h + lane][0] = runH[h];
-            s_red[w][16 * h + lane][1] = runL[h];
-            s_red[w][16 * h + lane][2] = runB[h];
-        }
-    }
     __syncthreads();
     if (threadIdx.x < 3 * JC) {
         const int j = threadIdx.x / 3, q = threadIdx.x - 3 * j;
         if (j < jn) {
-            const long long t = (s_red[0][j][q] + s_red[1][j][q]) + (s_red[2][j][q] + s_red[3][j][q]);
             const int grp = (int)(blockIdx.x % DSGC_GROUPS);
-            __hip_atomic_fetch_add(&acc[((size_t)grp * DSGC_JPAD + j0 + j) * 3 + q], (unsigned long long)t,
+            __hip_atomic_fetch_add(&acc[((size_t)grp * DSGC_JPAD + j0 + j) * 3 + q], s_tot[threadIdx.x],
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
@@ -311,11 +371,12 @@ __global__ __launch_bounds__(256) void dsgc_sweep_kernel(
 
     // ---- last block: sum the sets, Eq.6 per candidate, smallest deviation (ties: smallest j, i.e.
     // the largest clip value for decreasing ratios).  Every addition is in a fixed order. ----------
-    long long (*const f_part)[DSGC_JPAD][3] = reinterpret_cast<long long (*)[DSGC_JPAD][3]>(&s_tile[0][0]);
-    double* const f_g = reinterpret_cast<double*>(&s_tile[0][0] + sizeof(long long) * 4 * DSGC_JPAD * 3);
-    static_assert(sizeof(long long) * 4 * DSGC_JPAD * 3 + sizeof(double) * 4 <= sizeof(s_tile), "fits the tiles");
+    long long (*const f_part)[DSGC_JPAD][3] = reinterpret_cast<long long (*)[DSGC_JPAD][3]>(s_tile);
+    double* const f_g = reinterpret_cast<double*>(s_tile + sizeof(long long) * 4 * DSGC_JPAD * 3);
+    static_assert(sizeof(long long) * 4 * DSGC_JPAD * 3 + sizeof(double) * 4 <= 4 * DSGC_TILE, "fits the tiles of the smallest block");
     {
         const int j = threadIdx.x & 63, part = threadIdx.x >> 6;
+        if (part < 4) {
         long long t[3] = {0, 0, 0};
         if (j < n_cand) {
             long long v[DSGC_GROUPS / 4][3];
@@ -337,6 +398,7 @@ __global__ __launch_bounds__(256) void dsgc_sweep_kernel(
         for (int i = threadIdx.x; i < nparts; i += 256) gs += partG[i];
         gs = wave_sum(gs);
         if (j == 0) f_g[part] = gs;
+        }
     }
     __syncthreads();
     if (threadIdx.x < 64) {
@@ -376,34 +438,36 @@ __global__ __launch_bounds__(256) void dsgc_sweep_kernel(
     }
 }
 
-// Blocks of the sweep: one per 1024 elements up to one per compute unit, then a quarter of that up to three per
-// compute unit.  Every block ends with 96 device-scope atomic additions and a ticket, which the blocks of a
-// mid-sized tensor all issue at the same moment: with 768 blocks of one or two iterations each that hand-over
-// took 6 - 7 us of a 16 us sweep (0.8 M elements: 16.4 us with 768 blocks, 13.2 with 256; 1.6 M: 18.2 -> 16.7
-// with 392; from 3 M elements on the full grid is fastest).
-int dsgc_blocks(size_t n) {
-    const size_t units = (n / 4 + 255) / 256;
-    size_t want = units <= 256 ? units : (units / 4 < 256 ? 256 : units / 4);
-    return (int)(want < 1 ? 1 : (want > (size_t)DSGC_MAX_BLOCKS ? (size_t)DSGC_MAX_BLOCKS : want));
-}
+// Threads per block and blocks.  Up to 1024 wave-iterations (262 K elements) a wave has one of them and the sweep is a chain of
+// memory round trips: blocks of four waves spread them over more compute units (65 K elements: 9.8 us, 12.4 with 16
+// waves per block).  Above, 16 waves per block, one block per compute unit: fewer blocks also leave fewer atomic
+// additions and tickets at the end (0.8 M elements: 17.0 us with four waves per block, 13.7 with 16).
+static int dsgc_threads(size_t units) { return units <= 1024 ? 256 : DSGC_MAX_THREADS; }
 
 hipError_t launch_dsgc(const float* g, size_t n, const float* ratios, int n_cand, int stochastic,
                        uint64_t seed, const DsgcWs& ws, int nparts_absmax, float* clip_out,
                        double* dev_out, double* dev_all_out, hipStream_t st) {
     const int nchunks = (n_cand + DSGC_JC - 1) / DSGC_JC;
-    // about three blocks per compute unit in total; every candidate chunk walks the same x-grid
-    int blocks = dsgc_blocks(n);
-    const int cap = (DSGC_MAX_BLOCKS + nchunks - 1) / nchunks;
-    if (blocks > cap) blocks = cap;
+    const size_t units = (n / 4 + 63) / 64;
+    const int threads = dsgc_threads(units), waves = threads / 64;
+    // every candidate chunk walks the same x-grid
+    const size_t cap = (DSGC_MAX_BLOCKS + nchunks - 1) / nchunks;
+    size_t blocks = (units + waves - 1) / waves;
+    blocks = blocks < 1 ? 1 : blocks > cap ? cap : blocks;
     const uint32_t slo = seed_key_x(seed), shi = seed_key_a(seed);
-    dim3 grid(blocks, nchunks);
+    const size_t lds = (size_t)waves * DSGC_TILE;
+    dim3 grid((unsigned)blocks, nchunks);
+    static std::atomic<unsigned long long> done_st, done_nr;
+    const hipError_t e = raise_dynamic_lds(stochastic ? (const void*)dsgc_sweep_kernel<true> : (const void*)dsgc_sweep_kernel<false>,
+                                           DSGC_MAX_THREADS / 64 * DSGC_TILE, stochastic ? done_st : done_nr);
+    if (e != hipSuccess) return e;
     KernelTimer kt(KID_DSGC_SWEEP, st);
     if (stochastic)
-        launch_timed(kt, (dsgc_sweep_kernel<true>), grid, dim3(256), 0, st, g, n, ratios, n_cand,
+        launch_timed(kt, (dsgc_sweep_kernel<true>), grid, dim3(threads), lds, st, g, n, ratios, n_cand,
                            ws.absmax_part, nparts_absmax, slo, shi, ws.acc, ws.ticket, ws.partG, clip_out,
                            dev_out, dev_all_out);
     else
-        launch_timed(kt, (dsgc_sweep_kernel<false>), grid, dim3(256), 0, st, g, n, ratios, n_cand,
+        launch_timed(kt, (dsgc_sweep_kernel<false>), grid, dim3(threads), lds, st, g, n, ratios, n_cand,
                            ws.absmax_part, nparts_absmax, slo, shi, ws.acc, ws.ticket, ws.partG, clip_out,
                            dev_out, dev_all_out);
     return hipGetLastError();

@@ -106,7 +106,6 @@ struct DsgcWs {
     unsigned int* ticket;
     double* partG;               // [kMaxPartials]: per-block sums of g^2 from the absmax pass
 };
-int dsgc_blocks(size_t n);
 // 64-bit accumulator words of the sweep: 32 sets x 64 candidates x {sum H*m, sum L*m, sum m^2}
 constexpr size_t kDsgcAccWords = (size_t)32 * 64 * 3;
 size_t dsgc_acc_words();             // == kDsgcAccWords

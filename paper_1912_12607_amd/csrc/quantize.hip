@@ -96,6 +96,7 @@ __global__ __launch_bounds__(AM_THREADS) void absmax_kernel(const float* __restr
 
 // several tensors in one launch: block b serves the tensor whose block range holds it
 __global__ __launch_bounds__(AM_THREADS) void absmax_batch_kernel(const AbsmaxBatch b) {
+    raise_wave_priority();
     int i = 0;
     while (i + 1 < b.count && (int)blockIdx.x >= b.it[i].block0 + b.it[i].nblocks) ++i;
     const AbsmaxBatchItem& t = b.it[i];
@@ -665,6 +666,7 @@ __global__ __launch_bounds__(256) void quantize_wgt_kernel(
 // W is a kernel of its own, so that it keeps its register count beside the clip search.
 template <bool ANYSTOCH>
 __global__ __launch_bounds__(256) void quantize_batch_kernel(const QuantBatch b) {
+    raise_wave_priority();
     // one LDS area for whichever pass this block runs, sized by the host for the tensors of this launch
     // (a 3x3 weight tensor needs 2.3 KB of tile, not the 16 KB of the largest case: the kernel then fits
     // beside other kernels' blocks on a compute unit)

@@ -31,6 +31,7 @@ __device__ __forceinline__ uint4 s2d_pack(const uint32_t px[4], int C) {
 // One thread per output pixel; it reads the first four bytes of four input pixels.
 __global__ __launch_bounds__(256) void s2d_repack_kernel(const int8_t* __restrict__ x, int8_t* __restrict__ xs,
                                                          int N, int H, int W, int C) {
+    raise_wave_priority();
     const int H2 = (H + 1) >> 1, W2 = (W + 1) >> 1;
     const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (size_t)N * H2 * W2) return;
@@ -49,6 +50,7 @@ __global__ __launch_bounds__(256) void s2d_repack_kernel(const int8_t* __restric
 // of the layer's own filter in the same channel order; taps outside it are zero.
 __global__ __launch_bounds__(256) void s2d_weights_kernel(const int8_t* __restrict__ w, int8_t* __restrict__ ws,
                                                           int K, int R, int S, int C, S2dGeo g) {
+    raise_wave_priority();
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= K * g.R2 * g.S2) return;
     const int s2 = t % g.S2, r2 = (t / g.S2) % g.R2, k = t / (g.S2 * g.R2);

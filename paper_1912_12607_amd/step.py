@@ -33,6 +33,15 @@ def two_stream_default(L: Layer) -> bool:
     return L.N * L.K * L.P * L.Q >= (6 << 20)
 
 
+def two_stream_mode(L: Layer) -> int:
+    """The schedule (run()'s overlap) of a layer two_stream_default() sends to two streams.  4 lets the backward passes start
+    before the forward pass is done: its wide tiles fill a compute unit's LDS and wait for the search to end where the
+    reduction is long (1x7 on 768 channels, 17 x 17, batch 64: 362 us with 1, 349 with 4); a short forward pass is
+    done beside the search, and the backward passes then have the chip to themselves (3x3 on 64 channels, 56 x 56:
+    141.7 with 1, 143.0 with 4)."""
+    return 4 if (L.C // L.groups) * L.R * L.S >= 1024 else 1
+
+
 _SIDE_STREAMS: dict = {}
 
 
@@ -215,11 +224,12 @@ class LayerStep:
           4          as 1, but the backward passes wait for the codes of a and W only, not for the forward pass
                      behind them (with 1 each convolution has the chip to itself).
         A step that keeps the clip has no search to hide anything behind: any non-zero value means 2.
-        overlap=None follows tune() if it has run, else two_stream_default() in steps that search
+        overlap=None follows tune() if it has run, else two_stream_default() and two_stream_mode() in steps that search
         and one stream in steps that do not."""
         if overlap is None:
             if search:
-                overlap = self._tuned_overlap if self._tuned_overlap is not None else two_stream_default(self.L)
+                overlap = (self._tuned_overlap if self._tuned_overlap is not None
+                           else two_stream_mode(self.L) if two_stream_default(self.L) else 0)
             else:
                 overlap = self._tuned_fork or 0
         mode = int(overlap)
