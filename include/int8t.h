@@ -322,6 +322,50 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc *desc,
                                    void *ws_dev, size_t ws_bytes, void *stream);
 
 /*
+ * The calls of one layer's training step (Sec.3.4) in one: what int8t_quantize_batch_prepare, int8t_dsgc_search,
+ * int8t_quantize of g_z and the three convolutions write, bit for bit, in fewer launches -- calls that do not depend on
+ * one another share a launch, and a step of a small layer is a chain of launches before it is anything else.
+ *   parts   which of the calls run, an OR of the values below; each needs the results of the ones named with it from this
+ *           or an earlier call.  A caller with two streams deals the parts to them; everything else passes INT8T_STEP_ALL
+ *           (search and input gradient left out where they are not wanted).
+ *   b       device pointers as in the calls of the same argument names; y_acc, dx_acc, dw_acc, dev_all and dev_final
+ *           may be NULL (dev_final: d_c of Eq.6 of the codes of g_z, as int8t_quantize reports it), those that no part of
+ *           this call uses as well.  Read before the call returns.
+ *   ws_quant     3 x int8t_quantize_batch_workspace_bytes(1, ..) bytes: the absmax partials of a and W, kept between
+ *                INT8T_STEP_ABSMAX and INT8T_STEP_QUANT_XW
+ *   ws_dy        max(int8t_workspace_bytes(INT8T_OP_DSGC, ..), int8t_quantize_workspace_bytes(dims of g_z)) bytes
+ *   ws_fwd, ws_bwd_data    as for int8t_conv_fwd / int8t_conv_bwd_data (optional);  ws_bwd_weight: required by that part
+ * Errors as for the calls; arguments are checked before anything is launched.
+ */
+typedef enum {
+    INT8T_STEP_ABSMAX = 1,       /* max|a|, max|W|; with INT8T_STEP_PREPARE also the first pass of the clip search, same launch */
+    INT8T_STEP_PREPARE = 2,
+    INT8T_STEP_SEARCH = 4,       /* the sweep over the candidates (after PREPARE) */
+    INT8T_STEP_QUANT_XW = 8,     /* codes of a and W (after ABSMAX) */
+    INT8T_STEP_QUANT_G = 16,     /* codes of g_z, stochastic rounding, with the clip value at `clip` */
+    INT8T_STEP_FWD = 32,         /* (after QUANT_XW) */
+    INT8T_STEP_BWD_DATA = 64,    /* (after QUANT_XW, QUANT_G) */
+    INT8T_STEP_BWD_WEIGHT = 128, /* (after QUANT_XW, QUANT_G) */
+    INT8T_STEP_ALL = 255,
+    INT8T_STEP_MAX_ENUM = 0x7fffffff
+} int8t_step_part;
+typedef struct int8t_layer_buffers {
+    const float *x, *w, *dy;
+    int8_t *xq, *wq, *dyq;
+    float *sx, *sw, *sdy;
+    const float *ratios;
+    float *clip;
+    double *dev_search, *dev_all, *dev_final;
+    float *y, *dx, *dw;
+    int32_t *y_acc, *dx_acc, *dw_acc;
+    void *ws_quant, *ws_dy, *ws_fwd, *ws_bwd_data, *ws_bwd_weight;
+    size_t ws_quant_bytes, ws_dy_bytes, ws_fwd_bytes, ws_bwd_data_bytes, ws_bwd_weight_bytes;
+    int n_cand;
+} int8t_layer_buffers;
+int8t_status int8t_layer_step(const int8t_conv_desc *desc, const int8t_layer_buffers *b, int parts, uint64_t seed,
+                              void *stream);
+
+/*
  * Choice of the kernel per layer by measurement "before training" (Suppl. "INT8 Convolution", last
  * paragraph: the paper picks between its two convolution algorithms per layer; here the choice is
  * among this library's kernels for a pass).  Every variant computes the same integer sums, so the

@@ -29,7 +29,7 @@ EXPORTS = ["int8t_status_string", "int8t_code_bytes", "int8t_unpack_codes", "int
            "int8t_quantize_workspace_bytes", "int8t_quantize", "int8t_quantize_batch_workspace_bytes",
            "int8t_quantize_batch", "int8t_quantize_batch_prepare", "int8t_dsgc_clip", "int8t_dsgc_clip_static", "int8t_dsgc_prepare", "int8t_dsgc_search", "int8t_conv_fwd", "int8t_conv_fwd_fused",
            "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_dclr_scale",
-           "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
+           "int8t_layer_step", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
            "int8t_profile_start", "int8t_profile_start_sampled", "int8t_profile_stop", "int8t_profile_mfma_ceiling"]
 
 
@@ -40,6 +40,20 @@ class KernelTime(C.Structure):
 class QuantizeItem(C.Structure):
     _fields_ = [("x_dev", C.c_void_p), ("dims", C.c_int * 4), ("kind", C.c_int), ("clip_dev", C.c_void_p),
                 ("q_dev", C.c_void_p), ("scale_dev", C.c_void_p), ("mode", C.c_int), ("seed", C.c_uint64)]
+
+
+(STEP_ABSMAX, STEP_PREPARE, STEP_SEARCH, STEP_QUANT_XW, STEP_QUANT_G, STEP_FWD, STEP_BWD_DATA,
+ STEP_BWD_WEIGHT) = (1 << k for k in range(8))
+STEP_ALL = 255
+
+
+class LayerBuffers(C.Structure):
+    """int8t_layer_buffers: field names are the header's."""
+    _fields_ = ([(n, C.c_void_p) for n in
+                 ("x", "w", "dy", "xq", "wq", "dyq", "sx", "sw", "sdy", "ratios", "clip", "dev_search", "dev_all", "dev_final",
+                  "y", "dx", "dw", "y_acc", "dx_acc", "dw_acc", "ws_quant", "ws_dy", "ws_fwd", "ws_bwd_data", "ws_bwd_weight")]
+                + [(n + "_bytes", C.c_size_t) for n in ("ws_quant", "ws_dy", "ws_fwd", "ws_bwd_data", "ws_bwd_weight")]
+                + [("n_cand", C.c_int)])
 
 
 class ConvDesc(C.Structure):
@@ -91,6 +105,8 @@ def _load():
         f.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.int8t_conv_fwd_fused.restype = i32
     L.int8t_conv_fwd_fused.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    L.int8t_layer_step.restype = i32
+    L.int8t_layer_step.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp]
     L.int8t_conv_variant_ok.restype = i32
     L.int8t_conv_variant_ok.argtypes = [i32, dp, i32]
     L.int8t_conv_select_variant.restype = i32
@@ -132,8 +148,14 @@ def _nbytes(t):
     return 0 if t is None else t.numel() * t.element_size()
 
 
+# The current stream's handle without building torch's stream object, which costs the host as much as a launch (3 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
         return C.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return C.c_void_p(stream)
@@ -264,6 +286,23 @@ def int8t_conv_bwd_data(desc, dyq, sdy, wq, sw, dx, acc=None, ws=None, stream=No
 def int8t_conv_bwd_weight(desc, xq, sx, dyq, sdy, dw, acc=None, ws=None, stream=None):
     _check(lib.int8t_conv_bwd_weight(C.byref(desc), _ptr(xq), _ptr(sx), _ptr(dyq), _ptr(sdy), _ptr(dw),
                                      _ptr(acc), _ptr(ws), _nbytes(ws), _stream(stream)))
+
+
+def layer_buffers(**fields) -> LayerBuffers:
+    """A LayerBuffers of tensors (or None); every ws_* also fills its ws_*_bytes."""
+    b = LayerBuffers()
+    for name, t in fields.items():
+        if name == "n_cand":
+            b.n_cand = int(t)
+            continue
+        setattr(b, name, _ptr(t))
+        if name.startswith("ws_"):
+            setattr(b, name + "_bytes", _nbytes(t))
+    return b
+
+
+def int8t_layer_step(desc, buffers: LayerBuffers, parts: int = STEP_ALL, seed: int = 0, stream=None):
+    _check(lib.int8t_layer_step(C.byref(desc), C.byref(buffers), parts, seed, _stream(stream)))
 
 
 def int8t_conv_variant_ok(op: int, desc: ConvDesc, variant: int) -> bool:

@@ -347,9 +347,10 @@ size_t int8t_quantize_batch_workspace_bytes(int count, const int8t_quantize_item
 
 namespace {
 DsgcWs dsgc_ws_layout(void* ws_dev);
-// int8t_quantize_batch, and with g_dev also the first phase of a clip search on g in the same absmax launch
-int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, void* ws_dev, size_t ws_bytes,
-                                 const float* g_dev, size_t g_n, void* dsgc_ws_dev, size_t dsgc_ws_size, void* stream) {
+
+// Argument checks of a batch of tensors (and of the tensor of a clip search beside them).
+int8t_status quantize_batch_check(int count, const int8t_quantize_item* items, const void* ws_dev, size_t ws_bytes,
+                                  const float* g_dev, size_t g_n, const void* dsgc_ws_dev, size_t dsgc_ws_size) {
     if (!items) return INT8T_ERR_NULL;
     if (count < 1 || count > INT8T_MAX_BATCH) return INT8T_ERR_ARG;
     if (g_dev) {
@@ -358,10 +359,6 @@ int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, vo
         if (!aligned16(g_dev) || !aligned16(dsgc_ws_dev)) return INT8T_ERR_ARG;
         if (dsgc_ws_size < dsgc_ws_bytes(g_n)) return INT8T_ERR_WORKSPACE;
     }
-    AbsmaxBatch ab{};
-    QuantBatch qb{};
-    qb.count = count;
-    long long ablocks = 0, qblocks = 0;
     bool any_absmax = false;
     for (int i = 0; i < count; ++i) {
         const int8t_quantize_item& it = items[i];
@@ -382,30 +379,62 @@ int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, vo
         if (ws_bytes < int8t_quantize_batch_workspace_bytes(count, items)) return INT8T_ERR_WORKSPACE;
         if (!aligned16(ws_dev)) return INT8T_ERR_ARG;
     }
-    // Block ranges are dealt smallest tensor first: the dispatcher hands out blocks in order, so the
-    // few blocks of a small tensor run beside the first blocks of a large one instead of after its last.
-    int order[INT8T_MAX_BATCH];
-    size_t sizes[INT8T_MAX_BATCH];
+    return INT8T_OK;
+}
+
+// Block ranges are dealt smallest tensor first: the dispatcher hands out blocks in order, so the
+// few blocks of a small tensor run beside the first blocks of a large one instead of after its last.
+void batch_order(int count, const int8t_quantize_item* items, int order[INT8T_MAX_BATCH], size_t sizes[INT8T_MAX_BATCH]) {
     for (int i = 0; i < count; ++i) {
         order[i] = i;
         (void)dims_ok(items[i].dims, &sizes[i]);
     }
     for (int i = 1; i < count; ++i)
         for (int j = i; j > 0 && sizes[order[j]] < sizes[order[j - 1]]; --j) { const int t = order[j]; order[j] = order[j - 1]; order[j - 1] = t; }
+}
+float* batch_partials(void* ws_dev, int i) { return (float*)((char*)ws_dev + (size_t)i * align256(kMaxPartials * sizeof(float))); }
+
+// First launch of a batch: the absmax partials of the items without a clip value and, with g_dev, the first phase of a
+// clip search on g.  (checked arguments)
+hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_dev, const float* g_dev, size_t g_n, void* dsgc_ws_dev,
+                        hipStream_t st) {
+    AbsmaxBatch ab{};
+    long long ablocks = 0;
+    int order[INT8T_MAX_BATCH];
+    size_t sizes[INT8T_MAX_BATCH];
+    batch_order(count, items, order, sizes);
+    for (int oi = 0; oi < count; ++oi) {
+        const int i = order[oi];
+        if (items[i].clip_dev) continue;
+        AbsmaxBatchItem& a = ab.it[ab.count++];
+        a.x = items[i].x_dev; a.n = sizes[i]; a.part = batch_partials(ws_dev, i); a.block0 = (int)ablocks; a.nblocks = absmax_blocks(sizes[i]);
+        ablocks += a.nblocks;
+    }
+    if (g_dev) {
+        const DsgcWs dws = dsgc_ws_layout(dsgc_ws_dev);
+        AbsmaxBatchItem& a = ab.it[ab.count++];
+        a.x = g_dev; a.n = g_n; a.part = dws.absmax_part; a.block0 = (int)ablocks; a.nblocks = absmax_blocks(g_n);
+        a.sumsq = dws.partG; a.zero = dws.acc; a.nzero = (int)dsgc_acc_words() + 1;
+        ablocks += a.nblocks;
+    }
+    return ab.count ? launch_absmax_batch(ab, (int)ablocks, st) : hipSuccess;
+}
+
+// Second launch: the codes and scales, from the clip values and the partials of the first.  (checked arguments)
+int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_dev, hipStream_t st) {
+    QuantBatch qb{};
+    qb.count = count;
+    long long qblocks = 0;
+    int order[INT8T_MAX_BATCH];
+    size_t sizes[INT8T_MAX_BATCH];
+    batch_order(count, items, order, sizes);
     for (int oi = 0; oi < count; ++oi) {
         const int i = order[oi];
         const int8t_quantize_item& it = items[i];
-        const size_t n = sizes[i];
-        float* part = any_absmax ? (float*)((char*)ws_dev + (size_t)i * align256(kMaxPartials * sizeof(float))) : nullptr;
-        const int nb = it.clip_dev ? 0 : absmax_blocks(n);
-        if (nb) {
-            AbsmaxBatchItem& a = ab.it[ab.count++];
-            a.x = it.x_dev; a.n = n; a.part = part; a.block0 = (int)ablocks; a.nblocks = nb;
-            ablocks += nb;
-        }
         QuantBatchItem& q = qb.it[oi];
         q.x = it.x_dev; q.d0 = it.dims[0]; q.d1 = it.dims[1]; q.d2 = it.dims[2]; q.d3 = it.dims[3];
-        q.clip = it.clip_dev; q.absmax_part = part; q.nparts = nb; q.q = it.q_dev; q.scale = it.scale_dev;
+        q.clip = it.clip_dev; q.absmax_part = it.clip_dev ? nullptr : batch_partials(ws_dev, i); q.nparts = it.clip_dev ? 0 : absmax_blocks(sizes[i]);
+        q.q = it.q_dev; q.scale = it.scale_dev;
         const int8t_kind pk = pass_kind(it.dims, it.kind);
         q.kind = pk == INT8T_ACT ? 0 : pk == INT8T_WGT ? 1 : 2;
         q.stoch = it.mode == INT8T_ROUND_STOCHASTIC;
@@ -416,17 +445,19 @@ int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, vo
         qblocks += (long long)q.gx * q.gy * q.gz;
         if (qblocks > 0x7FFFFFFFll) return INT8T_ERR_SHAPE;
     }
-    if (g_dev) {
-        const DsgcWs dws = dsgc_ws_layout(dsgc_ws_dev);
-        AbsmaxBatchItem& a = ab.it[ab.count++];
-        a.x = g_dev; a.n = g_n; a.part = dws.absmax_part; a.block0 = (int)ablocks; a.nblocks = absmax_blocks(g_n);
-        a.sumsq = dws.partG; a.zero = dws.acc; a.nzero = (int)dsgc_acc_words() + 1;
-        ablocks += a.nblocks;
-    }
-    hipStream_t st = (hipStream_t)stream;
-    if (ab.count && launch_absmax_batch(ab, (int)ablocks, st) != hipSuccess) return INT8T_ERR_RUNTIME;
-    if (launch_quantize_batch(qb, (int)qblocks, st) != hipSuccess) return INT8T_ERR_RUNTIME;
-    return INT8T_OK;
+    return launch_quantize_batch(qb, (int)qblocks, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+}
+
+// int8t_quantize_batch, and with g_dev also the first phase of a clip search on g in the same absmax launch
+int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, void* ws_dev, size_t ws_bytes,
+                                 const float* g_dev, size_t g_n, void* dsgc_ws_dev, size_t dsgc_ws_size, void* stream) {
+    const int8t_status s = quantize_batch_check(count, items, ws_dev, ws_bytes, g_dev, g_n, dsgc_ws_dev, dsgc_ws_size);
+    if (s != INT8T_OK) return s;
+    long long qblocks = 0;
+    for (int i = 0; i < count; ++i) qblocks += quant_blocks(items[i].dims, items[i].kind);
+    if (qblocks > 0x7FFFFFFFll) return INT8T_ERR_SHAPE;
+    if (batch_absmax(count, items, ws_dev, g_dev, g_n, dsgc_ws_dev, (hipStream_t)stream) != hipSuccess) return INT8T_ERR_RUNTIME;
+    return batch_codes(count, items, ws_dev, (hipStream_t)stream);
 }
 }  // namespace
 
@@ -667,6 +698,82 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq
     a.partial = (int32_t*)ws_dev;
     a.xs = (int8_t*)ws_dev + align256((size_t)a.splits * a.K * a.R * a.S * a.Cp * 4);
     return launch_wgrad(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+}
+
+int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, void* stream) {
+    Geo g;
+    int8t_status s = desc_ok(desc, &g);
+    if (s != INT8T_OK) return s;
+    if (!b) return INT8T_ERR_NULL;
+    if (parts <= 0 || parts > INT8T_STEP_ALL) return INT8T_ERR_ARG;
+    const bool absmax = parts & INT8T_STEP_ABSMAX, prepare = parts & INT8T_STEP_PREPARE, search = parts & INT8T_STEP_SEARCH;
+    const bool quant_xw = parts & INT8T_STEP_QUANT_XW, quant_g = parts & INT8T_STEP_QUANT_G;
+    const bool fwd = parts & INT8T_STEP_FWD, bwd_data = parts & INT8T_STEP_BWD_DATA, bwd_weight = parts & INT8T_STEP_BWD_WEIGHT;
+    if (prepare && !absmax) return INT8T_ERR_ARG;
+    const int8t_kind ak = g.depthwise ? INT8T_ACT_PLANAR : INT8T_ACT, wk = g.depthwise ? INT8T_WGT_PLANAR : INT8T_WGT;
+    const size_t n_y = (size_t)desc->N * desc->K * g.P * g.Q;
+    const int ydims[4] = {desc->N, desc->K, g.P, g.Q};
+    // a, W and g_z as a batch; g_z goes with the other two where its codes are wanted at the same time and no deviation is
+    int8t_quantize_item it[3] = {};
+    it[0].x_dev = b->x; it[0].q_dev = b->xq; it[0].scale_dev = b->sx; it[0].kind = ak;
+    it[1].x_dev = b->w; it[1].q_dev = b->wq; it[1].scale_dev = b->sw; it[1].kind = wk;
+    it[2].x_dev = b->dy; it[2].q_dev = b->dyq; it[2].scale_dev = b->sdy; it[2].kind = ak;
+    it[2].clip_dev = b->clip; it[2].mode = INT8T_ROUND_STOCHASTIC; it[2].seed = seed;
+    const int xd[4] = {desc->N, desc->C, desc->H, desc->W}, wd[4] = {desc->K, desc->C / desc->groups, desc->R, desc->S};
+    for (int i = 0; i < 4; ++i) { it[0].dims[i] = xd[i]; it[1].dims[i] = wd[i]; it[2].dims[i] = ydims[i]; }
+    const bool g_in_batch = quant_xw && quant_g && !b->dev_final;
+    // ---- everything that can be wrong, before the first launch
+    if (quant_g && !b->clip) return INT8T_ERR_NULL;
+    if (absmax || quant_xw) {
+        s = quantize_batch_check(g_in_batch ? 3 : 2, it, b->ws_quant, b->ws_quant_bytes, prepare ? b->dy : nullptr, n_y, b->ws_dy, b->ws_dy_bytes);
+        if (s != INT8T_OK) return s;
+        if (prepare && !b->dy) return INT8T_ERR_NULL;
+    }
+    if (search) {
+        if (!b->dy || !b->ratios || !b->clip || !b->dev_search || !b->ws_dy) return INT8T_ERR_NULL;
+        if (b->n_cand < 1 || b->n_cand > INT8T_MAX_CANDIDATES || !aligned16(b->dy) || !aligned16(b->ws_dy)) return INT8T_ERR_ARG;
+        if (b->ws_dy_bytes < dsgc_ws_bytes(n_y)) return INT8T_ERR_WORKSPACE;
+    }
+    if (quant_g && !g_in_batch) {
+        if (!b->dy || !b->dyq || !b->sdy || (b->dev_final && !b->ws_dy)) return INT8T_ERR_NULL;
+        if (!aligned16(b->dy) || !aligned16(b->dyq) || desc->N > 65535) return INT8T_ERR_ARG;
+        if (b->dev_final && b->ws_dy_bytes < int8t_quantize_workspace_bytes(ydims, ak)) return INT8T_ERR_WORKSPACE;
+    }
+    if (((fwd || bwd_weight) && (!b->xq || !b->sx)) || ((fwd || bwd_data) && (!b->wq || !b->sw)) ||
+        ((bwd_data || bwd_weight) && (!b->dyq || !b->sdy)) || (fwd && !b->y) || (bwd_data && !b->dx) ||
+        (bwd_weight && (!b->dw || !b->ws_bwd_weight)))
+        return INT8T_ERR_NULL;
+    if ((fwd && !aligned16(b->y)) || (bwd_data && !aligned16(b->dx)) || (bwd_weight && (!aligned16(b->dw) || !aligned16(b->ws_bwd_weight))) ||
+        !aligned16(b->ws_fwd) || !aligned16(b->ws_bwd_data))
+        return INT8T_ERR_ARG;
+    if (bwd_weight && b->ws_bwd_weight_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
+    // ---- launches
+    hipStream_t st = (hipStream_t)stream;
+    if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
+    if (search) {
+        s = int8t_dsgc_search(b->dy, n_y, b->ratios, b->n_cand, INT8T_ROUND_STOCHASTIC, seed, b->clip, b->dev_search, b->dev_all, b->ws_dy,
+                              b->ws_dy_bytes, stream);
+        if (s != INT8T_OK) return s;
+    }
+    if (quant_xw) {
+        s = batch_codes(g_in_batch ? 3 : 2, it, b->ws_quant, st);
+        if (s != INT8T_OK) return s;
+    }
+    if (quant_g && !g_in_batch) {
+        s = int8t_quantize(b->dy, ydims, ak, b->clip, INT8T_ROUND_STOCHASTIC, seed, b->dyq, b->sdy, b->dev_final, b->ws_dy, b->ws_dy_bytes, stream);
+        if (s != INT8T_OK) return s;
+    }
+    if (fwd) {
+        s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);
+        if (s != INT8T_OK) return s;
+    }
+    if (bwd_data) {
+        s = int8t_conv_bwd_data(desc, b->dyq, b->sdy, b->wq, b->sw, b->dx, b->dx_acc, b->ws_bwd_data, b->ws_bwd_data_bytes, stream);
+        if (s != INT8T_OK) return s;
+    }
+    if (bwd_weight)
+        return int8t_conv_bwd_weight(desc, b->xq, b->sx, b->dyq, b->sdy, b->dw, b->dw_acc, b->ws_bwd_weight, b->ws_bwd_weight_bytes, stream);
+    return INT8T_OK;
 }
 
 double int8t_dclr_scale(double d_c, double alpha, double beta) {

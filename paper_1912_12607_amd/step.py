@@ -164,6 +164,19 @@ class LayerStep:
             B._check(lib.int8t_quantize(*a_qdy, seed, *b_qdy, sp))
 
         self._k_search, self._k_clip, self._k_qdy = k_search, k_clip, k_qdy
+        buf = B.layer_buffers(x=self.x, w=self.w, dy=self.dy, xq=self.xq, wq=self.wq, dyq=self.dyq, sx=self.sx, sw=self.sw, sdy=self.sdy,
+                              ratios=self.ratios, clip=self.clip, dev_search=self.dev_search, dev_all=self.dev_all,
+                              dev_final=self.dev_final if self.requantize_deviation else None, y=self.y, dx=self.dx, dw=self.dw,
+                              y_acc=self.y_acc, dx_acc=self.dx_acc, dw_acc=self.dw_acc, ws_quant=self.ws_xw, ws_dy=self.ws_dy,
+                              ws_fwd=self.ws_fwd, ws_bwd_data=self.ws_bwd_data, ws_bwd_weight=self.ws, n_cand=self.n_cand)
+        step_args, step = (d, C.byref(buf)), lib.int8t_layer_step
+
+        def k_step(parts, seed, sp):
+            status = step(*step_args, parts, seed, sp)
+            if status != B.OK:
+                raise B.Int8tError(status)
+
+        self._k_step, self._layer_buffers = k_step, buf
 
     def upload(self, x: np.ndarray, w: np.ndarray, dy: np.ndarray, ratios: np.ndarray):
         self.x.copy_(torch.from_numpy(np.ascontiguousarray(x)))
@@ -238,27 +251,15 @@ class LayerStep:
             mode = 2
         if not mode:
             sp = B.stream_pointer(stream)
-            if batched:
-                # the clip value is known: a, W and g_z in one batched call (one launch fewer)
-                self._items_xwg[2].seed = seed
-                self._k_xwg(sp)
-            elif self.fused_fwd:
-                self._k_w(sp)
-                if search:
-                    self._k_clip(seed, sp)
-                self._k_qdy(seed, sp)
-            elif search:
-                # max|.| of a, W and g_z (with the sums the search needs) in one launch, then the sweep
-                self._k_xw_prepare(sp)
-                self._k_search(seed, sp)
-                self._k_qdy(seed, sp)
-            else:
-                self._k_xw(sp)
-                self._k_qdy(seed, sp)
-            if self.fused_fwd:
-                self._k_fwd_fused(sp)
-            else:
-                self._k_fwd(sp)
+            if not self.fused_fwd:
+                parts = B.STEP_ALL if search else B.STEP_ALL & ~(B.STEP_PREPARE | B.STEP_SEARCH)
+                self._k_step(parts if self.input_grad else parts & ~B.STEP_BWD_DATA, seed, sp)
+                return
+            self._k_w(sp)
+            if search:
+                self._k_clip(seed, sp)
+            self._k_qdy(seed, sp)
+            self._k_fwd_fused(sp)
             if self.input_grad:
                 self._k_bwd_data(sp)
             self._k_bwd_weight(sp)
@@ -270,38 +271,35 @@ class LayerStep:
         side = self._side
         mp, sp = B.stream_pointer(main), B.stream_pointer(side)
         if mode == 2:
-            if batched:
-                self._items_xwg[2].seed = seed
-                self._k_xwg(mp)
-            else:
-                if search and not self.fused_fwd:
-                    self._k_xw_prepare(mp)
-                    self._k_search(seed, mp)
-                else:
-                    (self._k_w if self.fused_fwd else self._k_xw)(mp)
-                    if search:
-                        self._k_clip(seed, mp)
+            if self.fused_fwd:
+                self._k_w(mp)
+                if search:
+                    self._k_clip(seed, mp)
                 self._k_qdy(seed, mp)
-                if self.fused_fwd:
-                    self._k_fwd_fused(mp)       # writes the codes of a, which backward-weight reads
+                self._k_fwd_fused(mp)       # writes the codes of a, which backward-weight reads
+            else:
+                self._k_step(B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_QUANT_G | (B.STEP_PREPARE | B.STEP_SEARCH if search else 0), seed, mp)
             self._ev_main.record(main)
             side.wait_event(self._ev_main)
             self._k_bwd_weight(sp)
             self._ev_side.record(side)
             if not self.fused_fwd:
-                self._k_fwd(mp)
-            if self.input_grad:
+                self._k_step(B.STEP_FWD | (B.STEP_BWD_DATA if self.input_grad else 0), seed, mp)
+            elif self.input_grad:
                 self._k_bwd_data(mp)
             main.wait_event(self._ev_side)
             return
-        # main stream: clip search, quantize g_z, then backward-data (and backward-weight, unless it is forked).
-        # side stream: quantize a and W, forward convolution (needs nothing from the gradient chain).
-        # It starts behind whatever is queued on the main stream up to the search's first pass (the
+        # main stream: max|.| of a, W and g_z, clip search, quantize g_z, then backward-data (and backward-weight, unless
+        # it is forked).  side stream: quantize a and W, forward convolution (needs nothing from the gradient chain).
+        # It starts behind whatever is queued on the main stream up to the first pass (the
         # previous step's backward passes still read the codes that are about to be overwritten, and
         # that pass is bound by HBM like the side stream's kernels: beside each other they would only
         # slow each other down), i.e. together with the sweep.
-        if search:
-            self._k_prepare(mp)
+        if self.fused_fwd:
+            if search:
+                self._k_prepare(mp)
+        else:
+            self._k_step(B.STEP_ABSMAX | (B.STEP_PREPARE if search else 0), seed, mp)
         self._ev_main.record(main)
         side.wait_event(self._ev_main)
         early = mode >= 3 and not self.fused_fwd
@@ -310,7 +308,7 @@ class LayerStep:
             self._k_fwd_fused(sp)               # writes the codes of a
             self._ev_side.record(side)
         else:
-            self._k_xw(sp)
+            self._k_step(B.STEP_QUANT_XW, seed, sp)
             if early:
                 self._ev_side.record(side)      # the codes of a and W are there
             self._k_fwd(sp)
