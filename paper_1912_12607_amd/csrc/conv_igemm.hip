@@ -443,7 +443,8 @@ __global__ __launch_bounds__(128 * WM, WM == 2 ? (ALLC ? 2 : (BNT == 128 && KG =
     int nr = CLS ? dc.nr : a.R, ns = CLS ? dc.ns : a.S;  // (ALLC: of the class being run)
     int gtot = nr * ns * Cg16;
     int nsteps = (gtot + KG - 1) / KG;
-    const int ctile = (cgroup << 3) + (int)(blockIdx.x & 7);
+    // colrun (igemm_colrun): an XCD takes a run of column tiles instead of every eighth.
+    const int ctile = a.colrun ? (int)(blockIdx.x & 7) * a.colrun + cgroup : (cgroup << 3) + (int)(blockIdx.x & 7);
     if (ctile * BN >= ncols) return;
     const int rowbase = (wg_i % rtiles) * BM;
     const int colbase = ctile * BN;
@@ -627,6 +628,45 @@ __global__ __launch_bounds__(128 * WM, WM == 2 ? (ALLC ? 2 : (BNT == 128 && KG =
 
     // ---- epilogue: Eq.2, straight into N,C,H,W ----------------------------------------------
     const float scale = __fmul_rn(a.sa[0], a.sb[0]);
+    if constexpr (!CLS && WM == 2) {
+        // Image planes of whole 16-byte groups: the tile goes through LDS, 64 rows at a time, so that a store instruction writes
+        // the tile's columns of two to four channels as contiguous 16-byte pieces (512 bytes per channel and 128 columns) and
+        // not 128 bytes each of two channels, which on planes that are no whole cache lines share a line at either end.
+        // 24 -> 144 1x1 at 56 x 56, batch 64: 33.6 -> 26.7 us; 128 -> 512 at 28 x 28: 23.6 -> 20.5 (floor 19.9); 96 -> 576 at
+        // 14 x 14: 12.1 -> 9.6.  Other planes (17 x 17, 7 x 7) keep the stores below: with 4-byte aligned 16-byte stores
+        // and groups split at image borders they lose 3 us.
+        if ((OHW & 3) == 0) {
+            constexpr int PITCH = BN + 8;         // 4 * PITCH mod 64 = 32: the half-waves of a store, 4 rows apart, use different banks
+            static_assert(32 * WM * PITCH * 4 <= NSTAGE * STAGE_SLOTS * 16, "the staged rows fit the ring");
+            int* const stg = reinterpret_cast<int*>(ring);
+            constexpr int QPR = BN / 4, RPI = 128 * WM / QPR;     // 16-byte groups per row, rows per pass of the block
+            const int q = tid % QPR, r0 = tid / QPR;
+            const int col = colbase + 4 * q;
+            const int n = col / OHW, opix = col - n * OHW;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * (BN / 2) + j * 32 + (lane & 31)] = acc[0][i][j][v];
+                __syncthreads();
+                if (col >= ncols) continue;
+#pragma unroll 4
+                for (int r = r0; r < 32 * WM; r += RPI) {
+                    const int row = rowbase + (r >> 5) * 64 + i * 32 + (r & 31);
+                    if (row >= a.rows) continue;
+                    const int4 t = *reinterpret_cast<const int4*>(stg + r * PITCH + 4 * q);
+                    const size_t o = ((size_t)n * a.rows + row) * OHWfull + opix;
+                    *reinterpret_cast<float4*>(a.out + o) = make_float4(__fmul_rn((float)t.x, scale), __fmul_rn((float)t.y, scale),
+                                                                        __fmul_rn((float)t.z, scale), __fmul_rn((float)t.w, scale));
+                    if (a.acc) { a.acc[o] = t.x; a.acc[o + 1] = t.y; a.acc[o + 2] = t.z; a.acc[o + 3] = t.w; }
+                }
+            }
+            return;
+        }
+    }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int col = colbase + wn * (BN / 2) + j * 32 + (lane & 31);
@@ -740,8 +780,20 @@ IgemmShape igemm_shape(const IgemmArgs& a) {
 }
 }  // namespace
 
+// Column tiles an XCD takes in a run (0: every eighth).  Neighbouring column tiles write the two parts of the cache lines at
+// their border; where the rows of the result are no whole lines and a tile's life is mostly its stores, the tiles of an XCD
+// follow each other so that its L2 joins the parts: 256 -> 1024 1x1 backward-data at 14 x 14, batch 128: 40.3 -> 35.0 us
+// (256 reduction bytes per column); 1x1 stride 2, 512 -> 256 at 56 x 56, cells: 73.9 -> 64.2 (512 bytes).  Elsewhere it
+// loses: whole lines (56 x 56 planes) 1 %, longer reductions (512 -> 1024 at 14 x 14: 22.2 -> 23.0; 17 x 17, 1x7 on 768
+// channels: 82 -> 85), few tiles (73 of them at 17 x 17: 11.1 -> 11.9).
+static int igemm_colrun(const IgemmArgs& a, const IgemmShape& g, unsigned ctiles, bool cells) {
+    const bool ragged = (cells ? a.OW : a.OH * a.OW) % 32 != 0;
+    return (ragged && g.gran <= (cells ? 32 : 16) && ctiles >= 96) ? (int)((ctiles + 7) / 8) : 0;
+}
+
 template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS, bool CELL, int BNT = IGD_BN, bool ALLC = false>
-static hipError_t launch_igemm_dma(const IgemmArgs& a, const IgemmShape& g, hipStream_t st, const KernelTimer& kt) {
+static hipError_t launch_igemm_dma(const IgemmArgs& a_in, const IgemmShape& g, hipStream_t st, const KernelTimer& kt) {
+    IgemmArgs a = a_in;
     const size_t lds = (size_t)NSTAGE * (64 * WM + BNT) * KG * 16;
     static std::atomic<unsigned long long> attr_done;
     {
@@ -750,6 +802,7 @@ static hipError_t launch_igemm_dma(const IgemmArgs& a, const IgemmShape& g, hipS
     }
     const unsigned ctiles = (unsigned)((g.ncols + BNT - 1) / BNT), rtiles = (unsigned)((a.rows + 64 * WM - 1) / (64 * WM));
     dim3 grid(((ctiles + 7) / 8) * 8 * rtiles * (unsigned)g.ncls);
+    a.colrun = igemm_colrun(a, g, ctiles, CELL);
     launch_timed(kt, (igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC>), grid, dim3(128 * WM), lds, st, a);
     return hipGetLastError();
 }

@@ -133,6 +133,7 @@ struct IgemmArgs {
     size_t partial_bytes;
     int ksplit;                  // filled by launch_igemm(): blocks per output tile along the reduction
     int variant;                 // ConvVariant: VAR_AUTO, or the kernel the caller selected for this layer
+    int colrun;                  // filled by launch_igemm(): column tiles an XCD takes in a run, 0 = every eighth tile
     // Quantization fused into the forward pass of a 1 x 1, stride-1, unpadded layer (launch_igemm_fused):
     const float* xf;             // fp32 activations N,C,H,W (act is not read)
     const float* xclip;          // clip value of a, or nullptr: max|a| from xabs_part[0..xabs_nparts)

@@ -9,8 +9,10 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
 
+import oracle  # noqa: E402
+from paper_1912_12607_amd import binding as B  # noqa: E402
 from paper_1912_12607_amd import inputs  # noqa: E402
-from test_gpu_parity import RTN, STO, check_dsgc  # noqa: E402
+from test_gpu_parity import DEV, REL_TOL, RTN, STO, check_dsgc, dev, pack_act, pack_wgt  # noqa: E402
 
 
 # The sweep runs blocks of 4 waves up to 1024 wave-iterations of 256 elements and blocks of 16 above, and leaves the clip
@@ -35,3 +37,54 @@ def test_dsgc_block_sizes_and_clip_free_eights(n, kind):
         g = (g / np.abs(g).max() * np.float32(1e-26)).astype(np.float32)
     check_dsgc(g, ratios, STO, seed=n)
     check_dsgc(g, ratios, RTN, seed=n)
+
+
+def conv_pass_elementwise(op, desc, od, xq, wq, dyq, with_acc):
+    """One pass of the library on codes against the oracle: fp32 result (and accumulators)."""
+    s = [dev(np.array([v], np.float32)) for v in (0.013, 0.0021, 3.1e-5)]
+    if op == B.OP_CONV_FWD:
+        want64, call, args, s1, s2 = oracle.conv_fwd(od, xq, wq), B.int8t_conv_fwd, (dev(pack_act(xq)), s[0], dev(pack_wgt(wq)), s[1]), s[0], s[1]
+    elif op == B.OP_CONV_BWD_DATA:
+        want64, call, args, s1, s2 = (oracle.conv_bwd_data(od, dyq, wq), B.int8t_conv_bwd_data,
+                                      (dev(pack_act(dyq)), s[2], dev(pack_wgt(wq)), s[1]), s[2], s[1])
+    else:
+        want64, call, args, s1, s2 = (oracle.conv_bwd_weight(od, xq, dyq), B.int8t_conv_bwd_weight,
+                                      (dev(pack_act(xq)), s[0], dev(pack_act(dyq)), s[2]), s[0], s[2])
+    want, ov = oracle.wrap32(want64)
+    assert ov == 0
+    out = torch.full(want.shape, 7.0, dtype=torch.float32, device=DEV)
+    acc = torch.full(want.shape, 7, dtype=torch.int32, device=DEV) if with_acc else None
+    ws = torch.empty(max(256, B.int8t_workspace_bytes(op, desc)), dtype=torch.uint8, device=DEV)
+    call(desc, *args, out, acc, ws)
+    torch.cuda.synchronize()
+    if with_acc:
+        assert np.array_equal(acc.cpu().numpy(), want)
+    ref = oracle.dequant(want, np.float32(s1.item()), np.float32(s2.item()))
+    assert np.all(np.abs(out.cpu().numpy() - ref) <= REL_TOL * np.abs(ref))
+
+
+def random_layer(shape, seed):
+    N, C, H, W, K, R, S, stride, pad = shape
+    r = np.random.RandomState(seed)
+    desc = B.make_desc(N, C, H, W, K, R, S, (stride, stride), pad)
+    od = oracle.make_desc(N, C, H, W, K, R, S, (stride, stride), pad)
+    P, Q = (H + 2 * pad[0] - R) // stride + 1, (W + 2 * pad[1] - S) // stride + 1
+    codes = [r.randint(-127, 128, size=s).astype(np.int8) for s in ((N, C, H, W), (K, C, R, S), (N, K, P, Q))]
+    return desc, od, codes
+
+
+# Results staged through LDS (planes of whole 16-byte groups), tiles that end inside an image or beyond the last one, ragged
+# rows, and the column tiles of an XCD in a run (rows of no whole lines, short reduction, at least 96 column tiles), forward
+# and backward-data, plain and in 2 x 2 cells.
+@pytest.mark.parametrize("shape", [(3, 40, 6, 6, 150, 1, 1, 1, (0, 0)), (5, 200, 10, 10, 72, 3, 3, 1, (1, 1)), (64, 24, 14, 14, 144, 1, 1, 1, (0, 0)),
+                                   (66, 130, 14, 14, 80, 1, 1, 1, (0, 0)), (33, 70, 20, 20, 96, 1, 1, 2, (0, 0)), (64, 80, 15, 15, 70, 1, 1, 1, (0, 0))])
+@pytest.mark.parametrize("with_acc", [False, True])
+def test_staged_results_and_column_runs(shape, with_acc):
+    desc, od, (xq, wq, dyq) = random_layer(shape, shape[1])
+    for variant in (B.VARIANT_AUTO, B.VARIANT_WIDE_SQ128, B.VARIANT_WIDE_SQ128_DEEP, B.VARIANT_WIDE_128X64, B.VARIANT_WIDE128):
+        for op in (B.OP_CONV_FWD, B.OP_CONV_BWD_DATA):
+            B.int8t_conv_select_variant(op, desc, variant)
+            try:
+                conv_pass_elementwise(op, desc, od, xq, wq, dyq, with_acc)
+            finally:
+                B.int8t_conv_select_variant(op, desc, B.VARIANT_AUTO)
