@@ -391,7 +391,7 @@ typedef enum {
     INT8T_VARIANT_WGRAD_FEWER = 6,
     INT8T_VARIANT_WGRAD_MORE = 7,
     INT8T_VARIANT_WGRAD_IMAGES = 8,  /* backward-weight: operands of 16 images per pixel, transposed in registers */
-    INT8T_VARIANT_WGRAD_LINES = 9,   /* backward-weight, stride 1 with 1, 3 or 7 taps along an axis, 1x1 at any stride without
+    INT8T_VARIANT_WGRAD_LINES = 9,   /* backward-weight, stride 1 with 1, 3, 5 or 7 taps along an axis, 1x1 at any stride without
                                         padding, or 3x3 at stride 2 x 2: operands of 32 image lines per position through
                                         transposing LDS reads, gradient operands in a sliding window */
     INT8T_VARIANT_WIDE_SQ128 = 10,   /* forward / backward-data: 128 x 128 tiles from a 3-stage LDS ring, three blocks per

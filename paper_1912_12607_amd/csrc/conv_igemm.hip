@@ -392,8 +392,10 @@ __global__ __launch_bounds__(256) void igemm_reduce_kernel(const IgemmArgs a, si
 //   block runs the four classes one after the other, each into accumulators of its own, then writes every cell
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class
 //   form writes every other float of a line from four different blocks and pays a block's fixed cost per class.
-template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS = false, bool CELL = false, int BNT = IGD_BN, bool ALLC = false>
+//   STG (plain forms, planes of whole 16-byte groups): the results leave through LDS, see the epilogue.
+template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS = false, bool CELL = false, int BNT = IGD_BN, bool ALLC = false, bool STG = false>
 __global__ __launch_bounds__(128 * WM, WM == 2 ? (ALLC ? 2 : (BNT == 128 && KG == 4) || BNT == 64 ? 3 : 2) : 1) void igemm_dma_kernel(const IgemmArgs a) {
+    static_assert(!STG || (!CLS && WM == 2), "staged results: plain forms of the 128-row tiles");
     static_assert(DGRAD || !CLS, "residue classes exist in the backward-data pass only");
     static_assert(CLS || !CELL, "the cell form is a residue-class form");
     static_assert(!ALLC || (CLS && CELL && BNT == 64), "all classes per block: cell columns, 64 of them");
@@ -628,44 +630,42 @@ __global__ __launch_bounds__(128 * WM, WM == 2 ? (ALLC ? 2 : (BNT == 128 && KG =
 
     // ---- epilogue: Eq.2, straight into N,C,H,W ----------------------------------------------
     const float scale = __fmul_rn(a.sa[0], a.sb[0]);
-    if constexpr (!CLS && WM == 2) {
+    if constexpr (STG) {
         // Image planes of whole 16-byte groups: the tile goes through LDS, 64 rows at a time, so that a store instruction writes
         // the tile's columns of two to four channels as contiguous 16-byte pieces (512 bytes per channel and 128 columns) and
         // not 128 bytes each of two channels, which on planes that are no whole cache lines share a line at either end.
         // 24 -> 144 1x1 at 56 x 56, batch 64: 33.6 -> 26.7 us; 128 -> 512 at 28 x 28: 23.6 -> 20.5 (floor 19.9); 96 -> 576 at
         // 14 x 14: 12.1 -> 9.6.  Other planes (17 x 17, 7 x 7) keep the stores below: with 4-byte aligned 16-byte stores
         // and groups split at image borders they lose 3 us.
-        if ((OHW & 3) == 0) {
-            constexpr int PITCH = BN + 8;         // 4 * PITCH mod 64 = 32: the half-waves of a store, 4 rows apart, use different banks
-            static_assert(32 * WM * PITCH * 4 <= NSTAGE * STAGE_SLOTS * 16, "the staged rows fit the ring");
-            int* const stg = reinterpret_cast<int*>(ring);
-            constexpr int QPR = BN / 4, RPI = 128 * WM / QPR;     // 16-byte groups per row, rows per pass of the block
-            const int q = tid % QPR, r0 = tid / QPR;
-            const int col = colbase + 4 * q;
-            const int n = col / OHW, opix = col - n * OHW;
+        constexpr int PITCH = BN + 8;         // 4 * PITCH mod 64 = 32: the half-waves of a store, 4 rows apart, use different banks
+        static_assert(32 * WM * PITCH * 4 <= NSTAGE * STAGE_SLOTS * 16, "the staged rows fit the ring");
+        int* const stg = reinterpret_cast<int*>(ring);
+        constexpr int QPR = BN / 4, RPI = 128 * WM / QPR;     // 16-byte groups per row, rows per pass of the block
+        const int q = tid % QPR, r0 = tid / QPR;
+        const int col = colbase + 4 * q;
+        const int n = col / OHW, opix = col - n * OHW;
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                __syncthreads();
+        for (int i = 0; i < MI; ++i) {
+            __syncthreads();
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * (BN / 2) + j * 32 + (lane & 31)] = acc[0][i][j][v];
-                __syncthreads();
-                if (col >= ncols) continue;
+                for (int v = 0; v < 16; ++v)
+                    stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * (BN / 2) + j * 32 + (lane & 31)] = acc[0][i][j][v];
+            __syncthreads();
+            if (col >= ncols) continue;
 #pragma unroll 4
-                for (int r = r0; r < 32 * WM; r += RPI) {
-                    const int row = rowbase + (r >> 5) * 64 + i * 32 + (r & 31);
-                    if (row >= a.rows) continue;
-                    const int4 t = *reinterpret_cast<const int4*>(stg + r * PITCH + 4 * q);
-                    const size_t o = ((size_t)n * a.rows + row) * OHWfull + opix;
-                    *reinterpret_cast<float4*>(a.out + o) = make_float4(__fmul_rn((float)t.x, scale), __fmul_rn((float)t.y, scale),
-                                                                        __fmul_rn((float)t.z, scale), __fmul_rn((float)t.w, scale));
-                    if (a.acc) { a.acc[o] = t.x; a.acc[o + 1] = t.y; a.acc[o + 2] = t.z; a.acc[o + 3] = t.w; }
-                }
+            for (int r = r0; r < 32 * WM; r += RPI) {
+                const int row = rowbase + (r >> 5) * 64 + i * 32 + (r & 31);
+                if (row >= a.rows) continue;
+                const int4 t = *reinterpret_cast<const int4*>(stg + r * PITCH + 4 * q);
+                const size_t o = ((size_t)n * a.rows + row) * OHWfull + opix;
+                *reinterpret_cast<float4*>(a.out + o) = make_float4(__fmul_rn((float)t.x, scale), __fmul_rn((float)t.y, scale),
+                                                                    __fmul_rn((float)t.z, scale), __fmul_rn((float)t.w, scale));
+                if (a.acc) { a.acc[o] = t.x; a.acc[o + 1] = t.y; a.acc[o + 2] = t.z; a.acc[o + 3] = t.w; }
             }
-            return;
         }
+        return;
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -791,23 +791,29 @@ static int igemm_colrun(const IgemmArgs& a, const IgemmShape& g, unsigned ctiles
     return (ragged && g.gran <= (cells ? 32 : 16) && ctiles >= 96) ? (int)((ctiles + 7) / 8) : 0;
 }
 
-template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS, bool CELL, int BNT = IGD_BN, bool ALLC = false>
+template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS, bool CELL, int BNT = IGD_BN, bool ALLC = false, bool STG = false>
 static hipError_t launch_igemm_dma(const IgemmArgs& a_in, const IgemmShape& g, hipStream_t st, const KernelTimer& kt) {
     IgemmArgs a = a_in;
     const size_t lds = (size_t)NSTAGE * (64 * WM + BNT) * KG * 16;
     static std::atomic<unsigned long long> attr_done;
     {
-        hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC>), (int)lds, attr_done);
+        hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC, STG>), (int)lds, attr_done);
         if (e != hipSuccess) return e;
     }
     const unsigned ctiles = (unsigned)((g.ncols + BNT - 1) / BNT), rtiles = (unsigned)((a.rows + 64 * WM - 1) / (64 * WM));
     dim3 grid(((ctiles + 7) / 8) * 8 * rtiles * (unsigned)g.ncls);
     a.colrun = igemm_colrun(a, g, ctiles, CELL);
-    launch_timed(kt, (igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC>), grid, dim3(128 * WM), lds, st, a);
+    launch_timed(kt, (igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC, STG>), grid, dim3(128 * WM), lds, st, a);
     return hipGetLastError();
 }
 template <int WM, int KG, int NSTAGE, int BNT = IGD_BN>
 static hipError_t launch_igemm_dma_any(const IgemmArgs& a, const IgemmShape& g, hipStream_t st, const KernelTimer& kt) {
+    if constexpr (WM == 2) {
+        if (!g.cell && !g.cls && ((a.OH * a.OW) & 3) == 0) {
+            if (a.dgrad) return launch_igemm_dma<true, WM, KG, NSTAGE, false, false, BNT, false, true>(a, g, st, kt);
+            return launch_igemm_dma<false, WM, KG, NSTAGE, false, false, BNT, false, true>(a, g, st, kt);
+        }
+    }
     if (!a.dgrad) return launch_igemm_dma<false, WM, KG, NSTAGE, false, false, BNT>(a, g, st, kt);
     if (g.cell) return launch_igemm_dma<true, WM, KG, NSTAGE, true, true, BNT>(a, g, st, kt);
     if (g.cls) return launch_igemm_dma<true, WM, KG, NSTAGE, true, false, BNT>(a, g, st, kt);

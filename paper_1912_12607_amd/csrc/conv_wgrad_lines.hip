@@ -1,4 +1,4 @@
-// Dense backward-weight convolution (Sec.3.4: g_W = g_z^T a) for stride-1 filters with 1, 3 or 7 taps along
+// Dense backward-weight convolution (Sec.3.4: g_W = g_z^T a) for stride-1 filters with 1, 3, 5 or 7 taps along
 // one image axis, strided 1x1 filters and 3x3 filters under stride 2, on int8 MFMA with int32 accumulation.  Same result, partial-tile format and final
 // reduction as conv_wgrad.hip; what differs is how the operands reach the matrix cores.
 //
@@ -336,8 +336,8 @@ bool wgrad_lines_applies(const WgradArgs& a) {
     // strides: 1x1 filters without padding (the pass then runs on every stride-th row and pixel), and 3x3 filters
     // under stride 2 x 2
     if ((a.stride_h != 1 || a.stride_w != 1) && !(one && a.pad_h == 0 && a.pad_w == 0) && !wgrad_lines_s2(a)) return false;
-    const bool along_w = a.S == 3 || a.S == 7;
-    const bool along_h = a.S == 1 && (a.R == 3 || a.R == 7);
+    const bool along_w = a.S == 3 || a.S == 5 || a.S == 7;
+    const bool along_h = a.S == 1 && (a.R == 3 || a.R == 5 || a.R == 7);
     if (!one && !along_w && !along_h) return false;
     // byte offsets into either tensor stay below the value that stands for "nothing to load"
     if ((unsigned long long)a.N * a.H * a.W * a.Cp >= IGD_OOB || (unsigned long long)a.N * a.P * a.Q * a.Kp >= IGD_OOB) return false;
@@ -349,7 +349,7 @@ void wgrad_plan_lines(WgradArgs* a) {
     const int ST = along_w ? a->S : a->R;
     const int WT = ST == 1 ? 2 : 1;              // MFMA tiles per wave and tap in each direction
     const bool s2 = wgrad_lines_s2(*a);
-    const int GP = ST == 1 ? 4 : s2 ? 3 : 8;
+    const int GP = ST == 1 ? 4 : s2 ? 3 : ST == 5 ? 6 : 8;      // a multiple of the window's ST + 1 slots (of 3 under stride 2)
     a->lines = 1;
     a->TB = ST;
     a->CS = WT;
@@ -419,6 +419,7 @@ hipError_t launch_wgrad_lines(const WgradArgs& a, hipStream_t st) {
     } while (0)
     if (a.TB == 3 && wgrad_lines_s2(a)) LAUNCH(3, 1, 3, true);
     else if (a.TB == 3) LAUNCH(3, 1, 8, false);
+    else if (a.TB == 5) LAUNCH(5, 1, 6, false);     // (35 x 35, 5x5, 48 -> 64 channels, batch 32: 23.2 us on wgrad_kernel, 15.9 here)
     else if (a.TB == 7) LAUNCH(7, 1, 8, false);
     else if (a.TB == 1) LAUNCH(1, 2, 4, false);
     else return hipErrorInvalidValue;

@@ -234,7 +234,7 @@ struct WgradArgs {
 size_t wgrad_s2d(WgradArgs* a);
 void wgrad_plan(WgradArgs* a);   // needs the geometry fields above the first comment
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t st);
-// conv_wgrad_lines.hip: the kernel for stride-1 filters with 3 or 7 taps along an image axis
+// conv_wgrad_lines.hip: the kernel for stride-1 filters with 1, 3, 5 or 7 taps along an image axis
 bool wgrad_lines_applies(const WgradArgs& a);    // geometry as wgrad_plan() takes it (after wgrad_s2d())
 // lines are image rows and the taps of a block run along W (else: columns, along H)
 __host__ __device__ inline bool wgrad_lines_along_w(int R, int S) { return S > 1 || R == 1; }

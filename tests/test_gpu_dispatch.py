@@ -88,3 +88,17 @@ def test_staged_results_and_column_runs(shape, with_acc):
                 conv_pass_elementwise(op, desc, od, xq, wq, dyq, with_acc)
             finally:
                 B.int8t_conv_select_variant(op, desc, B.VARIANT_AUTO)
+
+
+# Five taps along a line (a ring stage of 6 positions): lines shorter and longer than a stage, any padding, ragged channel tiles.
+@pytest.mark.parametrize("shape", [(3, 20, 9, 9, 40, 5, 5, 1, (2, 2)), (2, 70, 8, 13, 130, 1, 5, 1, (0, 2)), (5, 33, 12, 7, 70, 5, 1, 1, (1, 0)),
+                                   (40, 16, 5, 5, 24, 5, 5, 1, (0, 0)), (1, 100, 6, 20, 65, 5, 5, 1, (4, 4))])
+def test_backward_weight_five_taps(shape):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 7)
+    assert B.int8t_conv_variant_ok(B.OP_CONV_BWD_WEIGHT, desc, B.VARIANT_WGRAD_LINES)
+    for variant in (B.VARIANT_AUTO, B.VARIANT_WGRAD_LINES, B.VARIANT_WGRAD_MORE):
+        B.int8t_conv_select_variant(B.OP_CONV_BWD_WEIGHT, desc, variant)
+        try:
+            conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
+        finally:
+            B.int8t_conv_select_variant(B.OP_CONV_BWD_WEIGHT, desc, B.VARIANT_AUTO)
