@@ -1,0 +1,101 @@
+// The three convolutions of a training step (forward, backward-data, backward-weight) in one launch.  They depend on the
+// codes of a, W and g_z only, not on one another.
+//
+// Bound: a small layer's passes are bound by the latency of their tiles' load-multiply stages and by launches, not by a rate:
+// 3x3 on 256 channels at 14 x 14, batch 64, has 400 tiles of 128 x 64 per pass for 256 compute units, each about 36 stages
+// of 0.5 us.  Side by side the passes fill the compute units that each of them leaves idle.  The tiles are those of the
+// kernels that run the passes alone (igemm_dma_tile, wgrad_lines_tile); block ranges deal them: backward-weight first, whose
+// blocks live longest.  All forms take 64 KB of LDS at most, so two blocks fit a compute unit.
+#include <algorithm>
+
+#include "conv_igemm_dma.h"
+#include "conv_wgrad_lines.h"
+
+namespace int8t {
+
+namespace {
+struct TrioBlocks {
+    unsigned wgrad, wgrad8, fwd;     // backward-weight's blocks, and rounded up to the 8 XCDs; the forward pass's
+};
+constexpr int trio_wt(int ST) { return ST == 1 ? 2 : 1; }
+constexpr int trio_gp(int ST) { return ST == 1 ? 4 : ST == 5 ? 6 : 8; }
+template <int BN, int ST>
+constexpr size_t trio_lds() {
+    return std::max((size_t)2 * (128 + BN) * 8 * 16, (size_t)WL_NSTAGE * wl_stage_bytes(trio_wt(ST), trio_wt(ST), trio_gp(ST)));
+}
+}  // namespace
+
+// ST taps along backward-weight's lines; STG: results of whole 16-byte groups staged through LDS (igemm_dma_tile).
+template <int BN, int ST, bool STG>
+__global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, const IgemmArgs b, const WgradArgs w, const TrioBlocks n) {
+    const unsigned block = blockIdx.x;
+    if (block < n.wgrad8) {
+        if (block < n.wgrad) wgrad_lines_tile<ST, trio_wt(ST), trio_wt(ST), trio_gp(ST)>(w, block);
+    } else if (block < n.wgrad8 + n.fwd) {
+        igemm_dma_tile<false, 2, 8, 2, false, false, BN, false, STG>(f, block - n.wgrad8);
+    } else {
+        igemm_dma_tile<true, 2, 8, 2, false, false, BN, false, STG>(b, block - n.wgrad8 - n.fwd);
+    }
+}
+
+// Which layers, and with which tile.  Over 200 random stride-1 layers of 1 to 350 MB, us for the three passes one by one, on
+// 128 x 64 tiles together and on 128 x 128 tiles together:
+//   3x3, 256 channels, 14 x 14, batch 64            57.6   50.4   45.7      7 x 7, 512 channels, 3x3, batch 64   78.9  51.3  58.3
+//   5x5, 48 -> 64 channels, 35 x 35, batch 32       52.2   37.5   42.8      1x1, 960 -> 160, 7 x 7, batch 64     29.4  17.2  19.4
+//   1x1, 1024 -> 256, 14 x 14, batch 128            67.9   61.2   53.9      3x3, 16 -> 32, 16 x 16, batch 2      20.6   8.9   9.7
+//   3x3, 64 channels, 56 x 56, batch 64             57.2   92.1   75.6      1x7, 768 channels, 17 x 17, batch 64  267   328   277
+// One by one stay (the last row): passes that the filter-bank-resident kernels run with many tiles (more than 4000 of 64
+// columns over both; the 128-row tiles are half empty there and fetch every pixel once per tap), and passes that fill the chip
+// with 256 x 256 tiles.  The wider tile where the work per block slot (512 of them) exceeds 1.2 times the longest reduction: below,
+// the time is one tile's chain of stages, and the narrow tile's is shorter.  Against the best of the three per layer this
+// rule loses 1.3 % on average, 19 % at most.
+int conv_trio_tile(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w) {
+    if (fwd.variant != VAR_AUTO || bwd.variant != VAR_AUTO || w.variant != VAR_AUTO) return 0;
+    if (fwd.stride_h != 1 || fwd.stride_w != 1 || bwd.stride_h != 1 || bwd.stride_w != 1 || !w.lines) return 0;
+    long long band_tiles = 0, work = 0, longest = 0;
+    for (const IgemmArgs* a : {&fwd, &bwd}) {
+        const int v = igemm_auto_variant(*a);
+        if (v == VAR_WIDE256) return 0;
+        const long long tiles = (((long long)a->N * a->OH * a->OW + 63) / 64) * ((a->rows + 127) / 128);
+        const long long gran = (long long)a->R * a->S * (a->Ca >> 4);
+        if (v == VAR_BAND) band_tiles += tiles;
+        work += tiles * gran;
+        longest = std::max(longest, gran);
+    }
+    if (band_tiles > 4000) return 0;
+    return 5 * work >= 6 * 512 * longest ? 128 : 64;
+}
+
+hipError_t launch_conv_trio(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st) {
+    IgemmArgs f = fwd, b = bwd;
+    TrioBlocks n;
+    n.wgrad = wgrad_lines_grid(w);
+    n.wgrad8 = (n.wgrad + 7) & ~7u;
+    n.fwd = igemm_plain_blocks(&f, bn);
+    const unsigned nb = igemm_plain_blocks(&b, bn);
+    if (!n.fwd || !nb) return hipErrorInvalidValue;
+    const dim3 grid(n.wgrad8 + n.fwd + nb);
+    const bool stg = ((f.OH * f.OW) & 3) == 0 && ((b.OH * b.OW) & 3) == 0;
+    KernelTimer kt(KID_CONV_TRIO, st);
+#define LAUNCH(BNv, STv, STGv)                                                                                                     \
+    do {                                                                                                                           \
+        static std::atomic<unsigned long long> attr_done;                                                                         \
+        const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(conv_trio_kernel<BNv, STv, STGv>), (int)trio_lds<BNv, STv>(), attr_done); \
+        if (e != hipSuccess) return e;                                                                                             \
+        launch_timed(kt, (conv_trio_kernel<BNv, STv, STGv>), grid, dim3(256), trio_lds<BNv, STv>(), st, f, b, w, n);               \
+    } while (0)
+#define LAUNCH_ST(BNv, STv) do { if (stg) LAUNCH(BNv, STv, true); else LAUNCH(BNv, STv, false); } while (0)
+#define LAUNCH_BN(STv) do { if (bn == 64) LAUNCH_ST(64, STv); else LAUNCH_ST(128, STv); } while (0)
+    if (w.TB == 1) LAUNCH_BN(1);
+    else if (w.TB == 3) LAUNCH_BN(3);
+    else if (w.TB == 5) LAUNCH_BN(5);
+    else if (w.TB == 7) LAUNCH_BN(7);
+    else return hipErrorInvalidValue;
+#undef LAUNCH_BN
+#undef LAUNCH_ST
+#undef LAUNCH
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_wgrad_reduce(w, st);
+}
+
+}  // namespace int8t

@@ -597,6 +597,10 @@ hipError_t launch_wgrad(const WgradArgs& a_in, hipStream_t st) {
 #undef LAUNCH
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    return launch_wgrad_reduce(a, st);
+}
+
+hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
     // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (256, 64 or
     // 16) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
     // loads of a small layer are latency, not bandwidth; one tap x 16 channels if nothing does.  A block's

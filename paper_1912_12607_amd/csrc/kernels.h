@@ -168,6 +168,9 @@ int igemm_auto_variant(const IgemmArgs& a, bool allow_split = true);   // allow_
 // rewritten input and filter codes (0: does not apply, the geometry is left alone).
 size_t igemm_s2d(IgemmArgs* a);
 hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st);
+// Blocks of the 128 x bn tiles of igemm_dma_tile over a pass that is not split by pixel classes (0: it is); fills what
+// launch_igemm() would.
+unsigned igemm_plain_blocks(IgemmArgs* a, int bn);
 // forward pass that quantizes fp32 activations in its load path; 1 x 1 filter, stride 1, no padding
 hipError_t launch_igemm_fused(const IgemmArgs& a, hipStream_t st);
 // conv_band.hip: LDS-resident variant for small filter banks; false = shape not covered
@@ -234,12 +237,15 @@ struct WgradArgs {
 size_t wgrad_s2d(WgradArgs* a);
 void wgrad_plan(WgradArgs* a);   // needs the geometry fields above the first comment
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t st);
+hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st);     // its second launch: the shares' partial tiles -> dw
 // conv_wgrad_lines.hip: the kernel for stride-1 filters with 1, 3, 5 or 7 taps along an image axis
 bool wgrad_lines_applies(const WgradArgs& a);    // geometry as wgrad_plan() takes it (after wgrad_s2d())
 // lines are image rows and the taps of a block run along W (else: columns, along H)
 __host__ __device__ inline bool wgrad_lines_along_w(int R, int S) { return S > 1 || R == 1; }
 void wgrad_plan_lines(WgradArgs* a);
 hipError_t launch_wgrad_lines(const WgradArgs& a, hipStream_t st);
+unsigned wgrad_lines_grid(const WgradArgs& a);
+bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filters, stride 2 x 2
 // which kernel VAR_AUTO stands for: true = wgrad_lines_kernel
 bool wgrad_auto_lines(const WgradArgs& a);
 // Share z runs on XCD z mod 8 with all its output tiles (they read the same lines of both tensors, and every XCD fills
@@ -249,6 +255,11 @@ bool wgrad_auto_lines(const WgradArgs& a);
 __host__ __device__ inline bool wgrad_xcd_mapping(int splits) {
     return splits >= 8 && (((splits + 7) & ~7) - splits) * 7 <= splits;
 }
+
+// ---- conv_trio.hip (the three dense passes of a layer in one launch) ---------------------------
+// Column width of the implicit-GEMM tiles with which the passes share a launch, 0: they run one by one.  w: after wgrad_plan().
+int conv_trio_tile(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w);
+hipError_t launch_conv_trio(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st);
 
 // ---- conv_dw.hip (depthwise, planar codes) ----------------------------------------------------
 struct DwArgs {

@@ -32,6 +32,7 @@ enum KernelId : int {
     KID_WGRAD_REDUCE,
     KID_S2D_REPACK,
     KID_S2D_WEIGHTS,
+    KID_CONV_TRIO,
     KID_DW_CONV,
     KID_DW_WGRAD,
     KID_DW_WGRAD_REDUCE,

@@ -12,6 +12,7 @@ if not torch.cuda.is_available():
 import oracle  # noqa: E402
 from paper_1912_12607_amd import binding as B  # noqa: E402
 from paper_1912_12607_amd import inputs  # noqa: E402
+from paper_1912_12607_amd.step import LayerStep  # noqa: E402
 from test_gpu_parity import DEV, REL_TOL, RTN, STO, check_dsgc, dev, pack_act, pack_wgt  # noqa: E402
 
 
@@ -102,3 +103,35 @@ def test_backward_weight_five_taps(shape):
             conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
         finally:
             B.int8t_conv_select_variant(B.OP_CONV_BWD_WEIGHT, desc, B.VARIANT_AUTO)
+
+
+# The three passes of a step in one launch: both tile widths, 1, 3, 5 and 7 taps along either axis, planes of whole 16-byte
+# groups and others, ragged rows and columns, backward-weight grids that are no multiple of the 8 XCDs.  Against the three
+# calls one by one, which the other tests hold against the oracle, bit for bit -- and that the launch is the one under test.
+@pytest.mark.parametrize("shape,together", [((2, 16, 16, 16, 32, 3, 3), True), ((64, 256, 14, 14, 256, 3, 3), True), ((32, 48, 35, 35, 64, 5, 5), True),
+                                            ((3, 130, 17, 17, 200, 1, 7), True), ((5, 70, 9, 11, 129, 7, 1), True), ((1, 300, 1, 1, 65, 1, 1), True),
+                                            ((64, 40, 28, 28, 500, 1, 3), True), ((64, 1000, 14, 14, 260, 1, 1), True), ((16, 64, 56, 56, 64, 3, 3), True),
+                                            ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True)])
+def test_three_passes_in_one_launch(shape, together):
+    N, C, H, W, K, R, S = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    B.int8t_profile_start("conv_trio_kernel")
+    st.run(seed=5, overlap=0)
+    torch.cuda.synchronize()
+    assert bool(B.int8t_profile_stop()) == together
+    outs = (st.y, st.dx, st.dw, st.y_acc, st.dx_acc, st.dw_acc)
+    got = [t.clone() for t in outs]
+    for t in outs:
+        t.fill_(7)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    torch.cuda.synchronize()
+    for a, b in zip(got, outs):
+        assert torch.equal(a, b)
