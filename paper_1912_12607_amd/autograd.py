@@ -54,6 +54,15 @@ class _LayerBuffers:
                      B.int8t_workspace_bytes(B.OP_CONV_BWD_WEIGHT, self.desc),
                      B.int8t_workspace_bytes(B.OP_CONV_BWD_DATA, self.desc))
         self.ws = torch.empty(nbytes, dtype=u8, device=dev)
+        # (one scratch for all calls: they follow each other on one stream, and passes that share a launch use one scratch at most)
+        self._bwd = B.layer_buffers(wq=self.wq, dyq=self.dyq, sw=self.sw, sdy=self.sdy, ws_dy=self.ws, ws_bwd_data=self.ws,
+                                    ws_bwd_weight=self.ws)
+
+    def backward_buffers(self, dy, xq, sx, clip, dev_out) -> "B.LayerBuffers":
+        """The arguments of a backward pass's call, dx and dw still to be set."""
+        b = B.LayerBuffers.from_buffer_copy(self._bwd)
+        b.dy, b.xq, b.sx, b.clip, b.dev_final = B._ptr(dy), B._ptr(xq), B._ptr(sx), B._ptr(clip), B._ptr(dev_out)
+        return b
 
     def take_xq(self):
         if self.xq_pool:
@@ -116,19 +125,24 @@ class _Int8ConvFn(torch.autograd.Function):
         else:
             dev_out = layer.deviation          # Eq.6 of the codes actually produced with the kept clip
         layer.backward_calls += 1
-        B.int8t_quantize(dy, buf.y_shape, buf.act_kind, layer.clip, B.ROUND_STOCHASTIC, seed, buf.dyq, buf.sdy, dev_out, buf.ws)
         if layer.weight._version != ctx.w_version:
             # the weights changed between this layer's forward and backward pass (an optimizer step in
             # between): the codes of W the forward used are gone, quantize the current ones again
             B.int8t_quantize(layer.weight.detach().contiguous().view(buf.w_shape), buf.w_shape, buf.wgt_kind, None, B.ROUND_NEAREST_EVEN, 0,
                              buf.wq, buf.sw, None, buf.ws)
+        # codes of g_z and the passes wanted, in one call (it lets passes that do not fill the chip share a launch)
         dx = dw = None
+        parts = B.STEP_QUANT_G
+        step = buf.backward_buffers(dy, xq, sx, layer.clip, dev_out)
         if ctx.needs_input_grad[0]:
             dx = torch.empty(buf.x_shape, dtype=torch.float32, device=dy.device)
-            B.int8t_conv_bwd_data(buf.desc, buf.dyq, buf.sdy, buf.wq, buf.sw, dx, None, buf.ws)
+            step.dx = B._ptr(dx)
+            parts |= B.STEP_BWD_DATA
         if ctx.needs_input_grad[1]:
             dw = torch.empty(buf.w_shape, dtype=torch.float32, device=dy.device)
-            B.int8t_conv_bwd_weight(buf.desc, xq, sx, buf.dyq, buf.sdy, dw, None, buf.ws)
+            step.dw = B._ptr(dw)
+            parts |= B.STEP_BWD_WEIGHT
+        B.int8t_layer_step(buf.desc, step, parts, seed)
         buf.give_xq((xq, sx))
         ctx.xq = None
         return dx, dw, None, None

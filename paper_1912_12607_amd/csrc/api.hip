@@ -702,13 +702,13 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq
 
 // Whether what the three passes of a step write overlaps nothing that one of them reads or writes, so that they may run
 // side by side (one after the other, a pass may reuse the buffers of the passes before it).
-static bool disjoint_results(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b) {
+static bool disjoint_results(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool fwd) {
     struct Range { const void* p; size_t n; };
     const size_t nx = (size_t)d->N * d->C * d->H * d->W * 4, ny = (size_t)d->N * d->K * g.P * g.Q * 4;
     const size_t nw = (size_t)d->K * d->C * d->R * d->S * 4;
     const int xd[4] = {d->N, d->C, d->H, d->W}, wd[4] = {d->K, d->C, d->R, d->S}, yd[4] = {d->N, d->K, g.P, g.Q};
     // (dw comes from the second launch: it may not overlap a result or an input of the first, which are written or read before)
-    const Range r[] = {{b->y, ny}, {b->y_acc, ny}, {b->dx, nx}, {b->dx_acc, nx}, {b->ws_bwd_weight, b->ws_bwd_weight_bytes},
+    const Range r[] = {{fwd ? b->y : nullptr, ny}, {fwd ? b->y_acc : nullptr, ny}, {b->dx, nx}, {b->dx_acc, nx}, {b->ws_bwd_weight, b->ws_bwd_weight_bytes},
                        {b->dw, nw}, {b->dw_acc, nw},
                        {b->xq, int8t_code_bytes(xd, INT8T_ACT)}, {b->wq, int8t_code_bytes(wd, INT8T_WGT)}, {b->dyq, int8t_code_bytes(yd, INT8T_ACT)},
                        {b->sx, 4}, {b->sw, 4}, {b->sdy, 4}};
@@ -783,8 +783,8 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         s = int8t_quantize(b->dy, ydims, ak, b->clip, INT8T_ROUND_STOCHASTIC, seed, b->dyq, b->sdy, b->dev_final, b->ws_dy, b->ws_dy_bytes, stream);
         if (s != INT8T_OK) return s;
     }
-    if (fwd && bwd_data && bwd_weight && !g.depthwise && aligned16(b->xq) && aligned16(b->wq) && aligned16(b->dyq) && aligned4(b->y_acc) &&
-        aligned4(b->dx_acc) && aligned4(b->dw_acc) && disjoint_results(desc, g, b)) {      // (else the calls below say what is wrong)
+    if (bwd_data && bwd_weight && !g.depthwise && aligned16(b->xq) && aligned16(b->wq) && aligned16(b->dyq) && aligned4(b->y_acc) &&
+        aligned4(b->dx_acc) && aligned4(b->dw_acc) && disjoint_results(desc, g, b, fwd)) {      // (else the calls below say what is wrong)
         IgemmArgs f{}, d{};
         WgradArgs w{};
         fill_igemm_fwd(&f, desc, g);
@@ -800,8 +800,8 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         wgrad_plan(&w);
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
-        const int bn = conv_trio_tile(f, d, w);
-        if (bn) return launch_conv_trio(f, d, w, bn, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+        const int bn = conv_trio_tile(fwd ? &f : nullptr, d, w);
+        if (bn) return launch_conv_trio(fwd ? &f : nullptr, d, w, bn, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     if (fwd) {
         s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);

@@ -1,5 +1,5 @@
-// The three convolutions of a training step (forward, backward-data, backward-weight) in one launch.  They depend on the
-// codes of a, W and g_z only, not on one another.
+// The three convolutions of a training step (forward, backward-data, backward-weight), or the two backward ones, in one
+// launch.  They depend on the codes of a, W and g_z only, not on one another.
 //
 // Bound: a small layer's passes are bound by the latency of their tiles' load-multiply stages and by launches, not by a rate:
 // 3x3 on 256 channels at 14 x 14, batch 64, has 400 tiles of 128 x 64 per pass for 256 compute units, each about 36 stages
@@ -48,12 +48,15 @@ __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, co
 // columns over both; the 128-row tiles are half empty there and fetch every pixel once per tap), and passes that fill the chip
 // with 256 x 256 tiles.  The wider tile where the work per block slot (512 of them) exceeds 1.2 times the longest reduction: below,
 // the time is one tile's chain of stages, and the narrow tile's is shorter.  Against the best of the three per layer this
-// rule loses 1.3 % on average, 19 % at most.
-int conv_trio_tile(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w) {
-    if (fwd.variant != VAR_AUTO || bwd.variant != VAR_AUTO || w.variant != VAR_AUTO) return 0;
-    if (fwd.stride_h != 1 || fwd.stride_w != 1 || bwd.stride_h != 1 || bwd.stride_w != 1 || !w.lines) return 0;
+// rule loses 1.3 % on average, 19 % at most.  The two backward passes alone (a forward pass ran earlier; 104 random layers:
+// 7x1, 76 -> 216 channels, 65 x 65, batch 3: 33.0, 21.7, 22.6): up to 3000 such tiles, the wider tile from twice the longest
+// reduction on; loses 1.9 % on average, 13 % at most.
+int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
+    if (w.variant != VAR_AUTO || !w.lines) return 0;
     long long band_tiles = 0, work = 0, longest = 0;
-    for (const IgemmArgs* a : {&fwd, &bwd}) {
+    for (const IgemmArgs* a : {fwd, &bwd}) {
+        if (!a) continue;
+        if (a->variant != VAR_AUTO || a->stride_h != 1 || a->stride_w != 1) return 0;
         const int v = igemm_auto_variant(*a);
         if (v == VAR_WIDE256) return 0;
         const long long tiles = (((long long)a->N * a->OH * a->OW + 63) / 64) * ((a->rows + 127) / 128);
@@ -62,18 +65,18 @@ int conv_trio_tile(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& 
         work += tiles * gran;
         longest = std::max(longest, gran);
     }
-    if (band_tiles > 4000) return 0;
-    return 5 * work >= 6 * 512 * longest ? 128 : 64;
+    if (band_tiles > (fwd ? 4000 : 3000)) return 0;
+    return 5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64;
 }
 
-hipError_t launch_conv_trio(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st) {
-    IgemmArgs f = fwd, b = bwd;
+hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st) {
+    IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
     TrioBlocks n;
     n.wgrad = wgrad_lines_grid(w);
     n.wgrad8 = (n.wgrad + 7) & ~7u;
-    n.fwd = igemm_plain_blocks(&f, bn);
+    n.fwd = fwd ? igemm_plain_blocks(&f, bn) : 0;
     const unsigned nb = igemm_plain_blocks(&b, bn);
-    if (!n.fwd || !nb) return hipErrorInvalidValue;
+    if ((fwd && !n.fwd) || !nb) return hipErrorInvalidValue;
     const dim3 grid(n.wgrad8 + n.fwd + nb);
     const bool stg = ((f.OH * f.OW) & 3) == 0 && ((b.OH * b.OW) & 3) == 0;
     KernelTimer kt(KID_CONV_TRIO, st);

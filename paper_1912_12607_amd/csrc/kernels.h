@@ -257,9 +257,10 @@ __host__ __device__ inline bool wgrad_xcd_mapping(int splits) {
 }
 
 // ---- conv_trio.hip (the three dense passes of a layer in one launch) ---------------------------
-// Column width of the implicit-GEMM tiles with which the passes share a launch, 0: they run one by one.  w: after wgrad_plan().
-int conv_trio_tile(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w);
-hipError_t launch_conv_trio(const IgemmArgs& fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st);
+// Column width of the implicit-GEMM tiles with which the passes share a launch, 0: they run one by one.  w: after wgrad_plan();
+// fwd: nullptr where only the two backward passes run.
+int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
+hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st);
 
 // ---- conv_dw.hip (depthwise, planar codes) ----------------------------------------------------
 struct DwArgs {

@@ -127,6 +127,13 @@ def test_three_passes_in_one_launch(shape, together):
     assert bool(B.int8t_profile_stop()) == together
     outs = (st.y, st.dx, st.dw, st.y_acc, st.dx_acc, st.dw_acc)
     got = [t.clone() for t in outs]
+    for t in outs[1:]:
+        t.fill_(7)
+    # the two backward passes without the forward one
+    B.int8t_layer_step(st.desc, st._layer_buffers, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT)
+    torch.cuda.synchronize()
+    for i in (1, 2, 4, 5):
+        assert torch.equal(got[i], outs[i])
     for t in outs:
         t.fill_(7)
     st.fwd()
