@@ -25,21 +25,25 @@ def align256(v: int) -> int:
 
 def two_stream_default(L: Layer) -> bool:
     """Whether LayerStep.run(overlap=None) uses the second stream in a step that searches the clip: the
-    search must be long enough to hide the other chain behind (the hand-over between the streams costs
-    about 10 us per step, and the extra calls make a step cost the host about 100 us: over the dense
-    layers of ResNet-50, MobileNetV2 and InceptionV3 at batch 32-64 the second stream gains from about
-    6 M gradient elements on and loses up to 20 us below 5 M; MobileNetV2's depthwise layers gain from
-    7 M elements on: 144 channels at 56 x 56, batch 64, 300 -> 258 us)."""
-    return L.N * L.K * L.P * L.Q >= (6 << 20)
+    search must be long enough to hide the other chain behind.  The hand-over between the streams costs
+    about 10 us per step, and on one stream a, W and g_z share one absmax and one quantize launch and the
+    convolutions of layers that do not fill the chip another.  Over 90 layers (one stream / two, us): 3x3 on 256 channels at
+    14 x 14, batch 64, 3.2 M gradient elements, 78 / 86, batch 128, 6.4 M, 127 / 130; 1x3, 132 -> 271 channels at 12 x 12,
+    10 M, 125 / 116; 3x3 on 64 channels at 56 x 56, 12.8 M, 153 / 142; 1x7 on 768 channels at 17 x 17, 14.2 M, 376 / 340;
+    depthwise 3x3, 144 channels at 56 x 56, 28.9 M, 275 / 248: two streams from 8 M elements on (between 4 M and 8 M either
+    may win by up to 10 %, below they lose up to 25 us, above at most 6 %)."""
+    return L.N * L.K * L.P * L.Q >= (8 << 20)
 
 
 def two_stream_mode(L: Layer) -> int:
     """The schedule (run()'s overlap) of a layer two_stream_default() sends to two streams.  4 lets the backward passes start
     before the forward pass is done: its wide tiles fill a compute unit's LDS and wait for the search to end where the
-    reduction is long (1x7 on 768 channels, 17 x 17, batch 64: 362 us with 1, 349 with 4); a short forward pass is
-    done beside the search, and the backward passes then have the chip to themselves (3x3 on 64 channels, 56 x 56:
-    141.7 with 1, 143.0 with 4)."""
-    return 4 if (L.C // L.groups) * L.R * L.S >= 1024 else 1
+    reduction is long (1x7 on 768 channels, 17 x 17, batch 64: 355 us with 1, 340 with 4; 3x3, 72 -> 274 channels, 26 x 26:
+    243 and 215), and the side stream's passes over an input much larger than the gradient outlast the search (depthwise
+    3x3 under stride 2, 96 channels, 112 x 112: 369 and 350); a short forward pass is done beside the search, and the
+    backward passes then have the chip to themselves (64 -> 256 1x1 at 56 x 56: 307 with 1, 310 with 4)."""
+    long_reduction = (L.C // L.groups) * L.R * L.S >= 512
+    return 4 if long_reduction or L.N * L.C * L.H * L.W >= 2 * L.N * L.K * L.P * L.Q else 1
 
 
 _SIDE_STREAMS: dict = {}
@@ -289,17 +293,16 @@ class LayerStep:
                 self._k_bwd_data(mp)
             main.wait_event(self._ev_side)
             return
-        # main stream: max|.| of a, W and g_z, clip search, quantize g_z, then backward-data (and backward-weight, unless
-        # it is forked).  side stream: quantize a and W, forward convolution (needs nothing from the gradient chain).
+        # main stream: max|g_z|, clip search, quantize g_z, then backward-data (and backward-weight, unless
+        # it is forked).  side stream: max|.| of a and W, their codes, forward convolution (needs nothing from the gradient chain).
         # It starts behind whatever is queued on the main stream up to the first pass (the
         # previous step's backward passes still read the codes that are about to be overwritten, and
         # that pass is bound by HBM like the side stream's kernels: beside each other they would only
-        # slow each other down), i.e. together with the sweep.
-        if self.fused_fwd:
-            if search:
-                self._k_prepare(mp)
-        else:
-            self._k_step(B.STEP_ABSMAX | (B.STEP_PREPARE if search else 0), seed, mp)
+        # slow each other down), i.e. together with the sweep.  (max|.| of a and W in the launch of max|g_z|, as on one
+        # stream, is the longer chain: the sweep is bound by arithmetic and hides it.  3x3 on 64 channels at 56 x 56, batch 64:
+        # 143 -> 137 us; 24 -> 144 1x1 at 56 x 56: 196 -> 191; depthwise 3x3, 144 channels at 56 x 56: 249 -> 246.)
+        if search:
+            self._k_prepare(mp)
         self._ev_main.record(main)
         side.wait_event(self._ev_main)
         early = mode >= 3 and not self.fused_fwd
@@ -308,7 +311,7 @@ class LayerStep:
             self._k_fwd_fused(sp)               # writes the codes of a
             self._ev_side.record(side)
         else:
-            self._k_step(B.STEP_QUANT_XW, seed, sp)
+            self._k_step(B.STEP_ABSMAX | B.STEP_QUANT_XW, seed, sp)
             if early:
                 self._ev_side.record(side)      # the codes of a and W are there
             self._k_fwd(sp)
@@ -325,10 +328,13 @@ class LayerStep:
         if early or mode == 3:
             self._ev_side2.record(side)
         main.wait_event(self._ev_side)
-        if self.input_grad:
-            self._k_bwd_data(mp)
-        if mode != 3:
-            self._k_bwd_weight(mp)
+        if self.fused_fwd or mode == 3 or not self.input_grad:
+            if self.input_grad:
+                self._k_bwd_data(mp)
+            if mode != 3:
+                self._k_bwd_weight(mp)
+        else:
+            self._k_step(B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, seed, mp)
         if early or mode == 3:
             main.wait_event(self._ev_side2)
 
