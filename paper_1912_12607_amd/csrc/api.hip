@@ -102,6 +102,22 @@ void fill_wgrad_geometry(WgradArgs* a, const int8t_conv_desc* d, const Geo& g) {
     a->stride_h = d->stride_h; a->stride_w = d->stride_w; a->pad_h = d->pad_h; a->pad_w = d->pad_w;
 }
 
+// geometry of the depthwise passes (pointers are set by the entry points)
+DwArgs dw_args(const int8t_conv_desc* d, const Geo& g, bool dgrad) {
+    DwArgs a{};
+    a.N = d->N; a.C = d->C; a.R = d->R; a.S = d->S;
+    a.IH = dgrad ? g.P : d->H; a.IW = dgrad ? g.Q : d->W;
+    a.OH = dgrad ? d->H : g.P; a.OW = dgrad ? d->W : g.Q;
+    a.stride_h = d->stride_h; a.stride_w = d->stride_w; a.pad_h = d->pad_h; a.pad_w = d->pad_w;
+    a.dgrad = dgrad;
+    return a;
+}
+DwArgs dw_wgrad_args(const int8t_conv_desc* d, const Geo& g) {
+    DwArgs a = dw_args(d, g, false);
+    dw_wgrad_shape(d->N, d->C, d->H, d->W, g.P, g.Q, d->R, d->S, d->stride_h, d->stride_w, &a.threads, &a.chunks, &a.cg);
+    return a;
+}
+
 // geometry of the implicit GEMMs (pointers are set by the entry points)
 void fill_igemm_fwd(IgemmArgs* a, const int8t_conv_desc* d, const Geo& g) {
     a->N = d->N; a->rows = d->K; a->Ca = pad16(d->C);
@@ -585,11 +601,8 @@ int8t_status int8t_conv_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, c
         return INT8T_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
     if (g.depthwise) {
-        DwArgs a{};
+        DwArgs a = dw_args(desc, g, false);
         a.a = xq_dev; a.b = wq_dev; a.sa = sx_dev; a.sb = sw_dev; a.out = y_dev; a.acc = acc_dev;
-        a.N = desc->N; a.C = desc->C; a.IH = desc->H; a.IW = desc->W; a.OH = g.P; a.OW = g.Q;
-        a.R = desc->R; a.S = desc->S; a.stride_h = desc->stride_h; a.stride_w = desc->stride_w;
-        a.pad_h = desc->pad_h; a.pad_w = desc->pad_w; a.dgrad = 0;
         return launch_dw_conv(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     IgemmArgs a{};
@@ -650,11 +663,8 @@ int8t_status int8t_conv_bwd_data(const int8t_conv_desc* desc, const int8_t* dyq_
         return INT8T_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
     if (g.depthwise) {
-        DwArgs a{};
+        DwArgs a = dw_args(desc, g, true);
         a.a = dyq_dev; a.b = wq_dev; a.sa = sdy_dev; a.sb = sw_dev; a.out = dx_dev; a.acc = acc_dev;
-        a.N = desc->N; a.C = desc->C; a.IH = g.P; a.IW = g.Q; a.OH = desc->H; a.OW = desc->W;
-        a.R = desc->R; a.S = desc->S; a.stride_h = desc->stride_h; a.stride_w = desc->stride_w;
-        a.pad_h = desc->pad_h; a.pad_w = desc->pad_w; a.dgrad = 1;
         return launch_dw_conv(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     IgemmArgs a{};
@@ -680,13 +690,9 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq
     if (ws_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (g.depthwise) {
-        DwArgs a{};
+        DwArgs a = dw_wgrad_args(desc, g);
         a.a = xq_dev; a.b = dyq_dev; a.sa = sx_dev; a.sb = sdy_dev; a.out = dw_dev; a.acc = acc_dev;
         a.partial = (int32_t*)ws_dev;
-        dw_wgrad_shape(desc->N, desc->C, desc->H, desc->W, g.P, g.Q, desc->R, desc->S, desc->stride_h, desc->stride_w, &a.threads, &a.chunks, &a.cg);
-        a.N = desc->N; a.C = desc->C; a.IH = desc->H; a.IW = desc->W; a.OH = g.P; a.OW = g.Q;
-        a.R = desc->R; a.S = desc->S; a.stride_h = desc->stride_h; a.stride_w = desc->stride_w;
-        a.pad_h = desc->pad_h; a.pad_w = desc->pad_w; a.dgrad = 0;
         return launch_dw_wgrad(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     WgradArgs a{};
@@ -705,12 +711,14 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq
 static bool disjoint_results(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool fwd) {
     struct Range { const void* p; size_t n; };
     const size_t nx = (size_t)d->N * d->C * d->H * d->W * 4, ny = (size_t)d->N * d->K * g.P * g.Q * 4;
-    const size_t nw = (size_t)d->K * d->C * d->R * d->S * 4;
-    const int xd[4] = {d->N, d->C, d->H, d->W}, wd[4] = {d->K, d->C, d->R, d->S}, yd[4] = {d->N, d->K, g.P, g.Q};
+    const int Cg = d->C / d->groups;
+    const size_t nw = (size_t)d->K * Cg * d->R * d->S * 4;
+    const int8t_kind ak = g.depthwise ? INT8T_ACT_PLANAR : INT8T_ACT, wk = g.depthwise ? INT8T_WGT_PLANAR : INT8T_WGT;
+    const int xd[4] = {d->N, d->C, d->H, d->W}, wd[4] = {d->K, Cg, d->R, d->S}, yd[4] = {d->N, d->K, g.P, g.Q};
     // (dw comes from the second launch: it may not overlap a result or an input of the first, which are written or read before)
     const Range r[] = {{fwd ? b->y : nullptr, ny}, {fwd ? b->y_acc : nullptr, ny}, {b->dx, nx}, {b->dx_acc, nx}, {b->ws_bwd_weight, b->ws_bwd_weight_bytes},
                        {b->dw, nw}, {b->dw_acc, nw},
-                       {b->xq, int8t_code_bytes(xd, INT8T_ACT)}, {b->wq, int8t_code_bytes(wd, INT8T_WGT)}, {b->dyq, int8t_code_bytes(yd, INT8T_ACT)},
+                       {b->xq, int8t_code_bytes(xd, ak)}, {b->wq, int8t_code_bytes(wd, wk)}, {b->dyq, int8t_code_bytes(yd, ak)},
                        {b->sx, 4}, {b->sw, 4}, {b->sdy, 4}};
     for (int i = 0; i < 7; ++i)
         for (int j = i + 1; j < 13; ++j) {
@@ -783,8 +791,17 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         s = int8t_quantize(b->dy, ydims, ak, b->clip, INT8T_ROUND_STOCHASTIC, seed, b->dyq, b->sdy, b->dev_final, b->ws_dy, b->ws_dy_bytes, stream);
         if (s != INT8T_OK) return s;
     }
-    if (bwd_data && bwd_weight && !g.depthwise && aligned16(b->xq) && aligned16(b->wq) && aligned16(b->dyq) && aligned4(b->y_acc) &&
-        aligned4(b->dx_acc) && aligned4(b->dw_acc) && disjoint_results(desc, g, b, fwd)) {      // (else the calls below say what is wrong)
+    const bool together = bwd_data && bwd_weight && aligned16(b->xq) && aligned16(b->wq) && aligned16(b->dyq) && aligned4(b->y_acc) &&
+        aligned4(b->dx_acc) && aligned4(b->dw_acc) && disjoint_results(desc, g, b, fwd);        // (else the calls below say what is wrong)
+    if (together && g.depthwise) {
+        DwArgs f = dw_args(desc, g, false), d = dw_args(desc, g, true), w = dw_wgrad_args(desc, g);
+        f.a = b->xq; f.b = b->wq; f.sa = b->sx; f.sb = b->sw; f.out = b->y; f.acc = b->y_acc;
+        d.a = b->dyq; d.b = b->wq; d.sa = b->sdy; d.sb = b->sw; d.out = b->dx; d.acc = b->dx_acc;
+        w.a = b->xq; w.b = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.out = b->dw; w.acc = b->dw_acc;
+        w.partial = (int32_t*)b->ws_bwd_weight;
+        hipError_t e = hipSuccess;
+        if (launch_dw_trio(fwd ? &f : nullptr, d, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+    } else if (together && !g.depthwise) {
         IgemmArgs f{}, d{};
         WgradArgs w{};
         fill_igemm_fwd(&f, desc, g);

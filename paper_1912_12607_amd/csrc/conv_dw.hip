@@ -285,12 +285,12 @@ constexpr int DW_MAX_PPB = 32;        // planes per block of the fast path, at m
 // start on a dword of LDS and are written four bytes at a time (see dw_fill_plane); the windows then start OFF bytes
 // further right as well.
 template <bool DGRAD, int SD, int NT, int ST = 1, int OFF = 0>    // SD = dwords of packed weights per filter row (S <= 4*SD)
-__global__ __launch_bounds__(NT) void dw_conv_fast_kernel(const DwArgs a, int pitch, int rows, int ppb) {
+__device__ __forceinline__ void dw_conv_fast_tile(const DwArgs& a, int pitch, int rows, int ppb, const int block_x) {
     raise_wave_priority();
     static_assert(ST == 1 || (ST == 2 && !DGRAD), "the strided form is the forward pass at stride 2");
     extern __shared__ __attribute__((aligned(16))) int8_t plane[];
     __shared__ uint32_t wrow[DW_MAX_PPB][DW_FAST_MAXR][SD];
-    const int nc0 = blockIdx.x * ppb;                            // the block's first plane (n * C + c)
+    const int nc0 = block_x * ppb;                            // the block's first plane (n * C + c)
     const int np = a.N * a.C - nc0 < ppb ? a.N * a.C - nc0 : ppb;
     const int OHW = a.OH * a.OW, RS = a.R * a.S, IHW = a.IH * a.IW;
     const int psize = rows * pitch;
@@ -368,6 +368,10 @@ __global__ __launch_bounds__(NT) void dw_conv_fast_kernel(const DwArgs a, int pi
             }
         }
     }
+}
+template <bool DGRAD, int SD, int NT, int ST = 1, int OFF = 0>
+__global__ __launch_bounds__(NT) void dw_conv_fast_kernel(const DwArgs a, int pitch, int rows, int ppb) {
+    dw_conv_fast_tile<DGRAD, SD, NT, ST, OFF>(a, pitch, rows, ppb, blockIdx.x);
 }
 
 
@@ -574,11 +578,11 @@ __global__ __launch_bounds__(NT) void dw_wgrad_kernel(const DwArgs a) {
 // permute -- three instructions and a dot product per tap and four results, where the generic kernel spends some
 // seven per product on index arithmetic and bounds tests (96 channels at 112 x 112, batch 64: 62 us, compute-bound).
 template <int R, int S, int NT, bool PF, int OFF, int ST = 1>
-__global__ __launch_bounds__(NT) void dw_wgrad_fast_kernel(const DwArgs a, int pitch, int gpitch, int xrows) {
+__device__ __forceinline__ void dw_wgrad_fast_tile(const DwArgs& a, int pitch, int gpitch, int xrows, const int block_x, const int block_y) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     __shared__ int red[(NT / 64) * R * S];
     constexpr int SD = (S + 3) / 4;
-    const int c = blockIdx.x, chunk = blockIdx.y;
+    const int c = block_x, chunk = block_y;
     const int IHW = a.IH * a.IW, OHW = a.OH * a.OW;
     const int n0 = (int)(((long long)a.N * chunk) / a.chunks);
     const int n1 = (int)(((long long)a.N * (chunk + 1)) / a.chunks);
@@ -656,6 +660,10 @@ __global__ __launch_bounds__(NT) void dw_wgrad_fast_kernel(const DwArgs a, int p
         for (int sx = 0; sx < S; ++sx) flat[r * S + sx] = acc[r][sx];
     dw_block_sums_store<NT, R * S>(flat, red, part);
 }
+template <int R, int S, int NT, bool PF, int OFF, int ST = 1>
+__global__ __launch_bounds__(NT) void dw_wgrad_fast_kernel(const DwArgs a, int pitch, int gpitch, int xrows) {
+    dw_wgrad_fast_tile<R, S, NT, PF, OFF, ST>(a, pitch, gpitch, xrows, blockIdx.x, blockIdx.y);
+}
 
 // Stride-1 backward-weight for small planes (14 x 14, 7 x 7): a block takes `cg` consecutive channels -- their planes
 // are one contiguous run of cg * IH * IW bytes per image -- and a share of the images; every thread owns one task (four
@@ -667,11 +675,11 @@ __global__ __launch_bounds__(NT) void dw_wgrad_fast_kernel(const DwArgs a, int p
 // Host (dw_wgrad_shape): OH * ceil(OW / 4) <= slot <= 64, cg * slot <= 256 threads, cg * IH * IW and cg * OH * OW whole
 // 16-byte chunks and at most 512 of them together, cg <= 32 and a divisor of C.
 template <int R, int S>
-__global__ __launch_bounds__(256) void dw_wgrad_group_kernel(const DwArgs a, int pitch, int gpitch, int slot, int ni) {
+__device__ __forceinline__ void dw_wgrad_group_tile(const DwArgs& a, int pitch, int gpitch, int slot, int ni, const int block_x, const int block_y) {
     constexpr int NT = 256, SD = (S + 3) / 4, RS = R * S;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     __shared__ int red[32 * RS];
-    const int cg = a.cg, c0 = blockIdx.x * cg, chunk = blockIdx.y;
+    const int cg = a.cg, c0 = block_x * cg, chunk = block_y;
     const int IHW = a.IH * a.IW, OHW = a.OH * a.OW;
     const int n0 = (int)(((long long)a.N * chunk) / a.chunks);
     const int n1 = (int)(((long long)a.N * (chunk + 1)) / a.chunks);
@@ -762,6 +770,37 @@ __global__ __launch_bounds__(256) void dw_wgrad_group_kernel(const DwArgs a, int
     __syncthreads();
     // [chunk][C][R*S]: the group's channels are consecutive
     for (int i = threadIdx.x; i < cg * RS; i += NT) a.partial[((size_t)chunk * a.C + c0) * RS + i] = red[i];
+}
+template <int R, int S>
+__global__ __launch_bounds__(256) void dw_wgrad_group_kernel(const DwArgs a, int pitch, int gpitch, int slot, int ni) {
+    dw_wgrad_group_tile<R, S>(a, pitch, gpitch, slot, ni, blockIdx.x, blockIdx.y);
+}
+
+// The three passes of a stride-1 3x3 layer in one launch.  Forward and backward-data are bound by writing their results,
+// backward-weight by the vector ALUs, and none of them fills the chip at both ends of its grid.  Backward-weight's blocks, which
+// live longest, come first, with half as many shares of the batch as alone: four blocks of a compute unit's eight, so that
+// the other passes' blocks run beside them from the start.  All three, batch 64, us one by one and together: 144 channels at
+// 56 x 56 97.3 -> 78.2 (60 us at the rate of a large copy), 192 at 28 x 28 46.9 -> 32.0, 576 at 14 x 14 60.5 -> 42.8, 960 at
+// 7 x 7 38.4 -> 28.3; 32 channels at 16 x 16, batch 2, 13.2 -> 7.5.  With all shares 80.9, 34.3, 45.5, 31.6; with a third of
+// them 75.9, 31.9, 42.2, 27.6, but 144 channels at 28 x 28, batch 256, 87.7 against 80.2 (111.1 one by one).
+// OFF: as in dw_conv_fast_tile, of both passes (3: rows of whole dwords); GROUP: backward-weight on groups of channels.
+struct DwTrio {
+    int wgrad, wgrad_x, fwd;            // backward-weight's blocks (wgrad_x per share of the batch), the forward pass's
+    int pitch, rows, ppb;               // forward and backward-data (dw_conv_fast_tile)
+    int wpitch, gpitch, xrows, slot, ni;     // backward-weight
+};
+template <int OFF, bool GROUP>
+__global__ __launch_bounds__(256) void dw_trio_kernel(const DwArgs f, const DwArgs b, const DwArgs w, const DwTrio t) {
+    const int block = blockIdx.x;
+    if (block < t.wgrad) {
+        const int y = block / t.wgrad_x, x = block - y * t.wgrad_x;
+        if constexpr (GROUP) dw_wgrad_group_tile<3, 3>(w, t.wpitch, t.gpitch, t.slot, t.ni, x, y);
+        else dw_wgrad_fast_tile<3, 3, 256, true, OFF, 1>(w, t.wpitch, t.gpitch, t.xrows, x, y);
+    } else if (block < t.wgrad + t.fwd) {
+        dw_conv_fast_tile<false, 1, 256, 1, OFF>(f, t.pitch, t.rows, t.ppb, block - t.wgrad);
+    } else {
+        dw_conv_fast_tile<true, 1, 256, 1, OFF>(b, t.pitch, t.rows, t.ppb, block - t.wgrad - t.fwd);
+    }
 }
 
 // 16 lanes per result: each adds every 16th share, then the lanes are summed (integer sums: any order is exact).
@@ -982,21 +1021,36 @@ int dw_wgrad_threads(int P, int Q, int R, int S, int stride_h, int stride_w) {
     return dw_threads(P, Q, fast);
 }
 
+// LDS of one image's planes of a channel group; images staged per pass: as many as two chunks per thread and 32 KB of LDS
+// hold, at most 8
+static size_t dw_group_lds(const DwArgs& a, int pitch, int gpitch) {
+    return (size_t)a.cg * ((((size_t)(a.OH + a.R - 1) * pitch + 15) & ~(size_t)15) + (((size_t)a.OH * gpitch + 15) & ~(size_t)15));
+}
+static int dw_group_images(const DwArgs& a, size_t ldsg) {
+    const int nch = (a.cg * a.IH * a.IW + a.cg * a.OH * a.OW) >> 4;
+    int ni = 512 / nch;
+    if (ni > 8) ni = 8;
+    while (ni > 1 && (size_t)ni * ldsg > 32 * 1024) --ni;
+    return ni < 1 ? 1 : ni;
+}
+
+static hipError_t launch_dw_wgrad_reduce(const DwArgs& a, hipStream_t st) {
+    const int total = a.C * a.R * a.S;
+    KernelTimer kt(KID_DW_WGRAD_REDUCE, st);
+    launch_timed(kt, dw_wgrad_reduce_kernel, dim3((total * 16 + 255) / 256), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st) {
     {
         KernelTimer kt(KID_DW_WGRAD, st);
         bool fast = false;
         if (a.cg > 1) {
             const int pitch = dw_fast_pitch(a.OW, a.S), gpitch = (a.OW + 3) & ~3;
-            const size_t ldsg = (size_t)a.cg * ((((size_t)(a.OH + a.R - 1) * pitch + 15) & ~(size_t)15) + (((size_t)a.OH * gpitch + 15) & ~(size_t)15));
+            const size_t ldsg = dw_group_lds(a, pitch, gpitch);
             const dim3 grid((unsigned)(a.C / a.cg), (unsigned)a.chunks);
             const int slot = dw_wgrad_slot(a.OH, a.OW);
-            // images staged per pass: as many as two chunks per thread and 32 KB of LDS hold, at most 8
-            const int nch = (a.cg * a.IH * a.IW + a.cg * a.OH * a.OW) >> 4;
-            int ni = 512 / nch;
-            if (ni > 8) ni = 8;
-            while (ni > 1 && (size_t)ni * ldsg > 32 * 1024) --ni;
-            if (ni < 1) ni = 1;
+            const int ni = dw_group_images(a, ldsg);
             if (a.R == 3) launch_timed(kt, (dw_wgrad_group_kernel<3, 3>), grid, dim3(256), ldsg * ni, st, a, pitch, gpitch, slot, ni);
             else launch_timed(kt, (dw_wgrad_group_kernel<5, 5>), grid, dim3(256), ldsg * ni, st, a, pitch, gpitch, slot, ni);
             fast = true;
@@ -1053,9 +1107,57 @@ hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int total = a.C * a.R * a.S;
-    { KernelTimer kt(KID_DW_WGRAD_REDUCE, st); launch_timed(kt, dw_wgrad_reduce_kernel, dim3((total * 16 + 255) / 256), dim3(256), 0, st, a); }
-    return hipGetLastError();
+    return launch_dw_wgrad_reduce(a, st);
+}
+
+// The three passes together (fwd: nullptr where only the backward ones run): 3x3 under stride 1 and "same" padding, planes
+// large enough for blocks of 256 threads and, where backward-weight does not take groups of channels, of whole 16-byte chunks
+// in rows of whole dwords up to 4096 bytes (56 x 56; 112 x 112 planes keep their own launches).  Every layer of this kind
+// measured gains (20 of them, batch 1 to 256, 13 - 49 %).  false: not a layer for it, nothing launched.
+bool launch_dw_trio(const DwArgs* fwd, const DwArgs& b, const DwArgs& w_in, hipStream_t st, hipError_t* err) {
+    DwArgs w = w_in;
+    const DwArgs& f = fwd ? *fwd : b;
+    if (f.R != 3 || f.S != 3 || f.stride_h != 1 || f.stride_w != 1 || f.pad_h != 1 || f.pad_w != 1 || w.threads != 256) return false;
+    DwTrio t{};
+    // forward and backward-data have one geometry under "same" padding
+    t.pitch = dw_fast_pitch(f.OW, 3) + 4;
+    t.rows = f.OH + 2;
+    const size_t lds1 = (size_t)t.rows * t.pitch;
+    if (lds1 > 60 * 1024) return false;
+    t.ppb = dw_fast_ppb(f.N * f.C, f.OH, f.OW, f.IH, f.IW, lds1);
+    if (dw_fast_threads(f.OH, f.OW, t.ppb) != 256) return false;
+    const int planes = (f.N * f.C + t.ppb - 1) / t.ppb;
+    t.fwd = fwd ? planes : 0;
+    const bool al = (f.IW & 3) == 0, group = w.cg > 1;
+    const int ihw = w.IH * w.IW;
+    t.gpitch = (w.OW + 3) & ~3;
+    size_t ldsw;
+    if (group) {
+        t.wpitch = dw_fast_pitch(w.OW, 3);
+        const size_t ldsg = dw_group_lds(w, t.wpitch, t.gpitch);
+        t.slot = dw_wgrad_slot(w.OH, w.OW);
+        t.ni = dw_group_images(w, ldsg);
+        ldsw = ldsg * t.ni;
+    } else {
+        if (!al || (ihw & 15) != 0 || ihw > 4096) return false;
+        t.wpitch = dw_fast_pitch(w.OW, 3) + 4;
+        t.xrows = w.OH + 2;
+        ldsw = (((size_t)t.xrows * t.wpitch + 15) & ~(size_t)15) + (size_t)w.OH * t.gpitch;
+    }
+    w.chunks = (w.chunks + 1) / 2;
+    t.wgrad_x = w.C / w.cg;
+    t.wgrad = t.wgrad_x * w.chunks;
+    const size_t lds = ldsw > lds1 * t.ppb ? ldsw : lds1 * t.ppb;
+    const dim3 grid((unsigned)(t.wgrad + t.fwd + planes));
+    {
+        KernelTimer kt(KID_DW_TRIO, st);
+        if (group && al) launch_timed(kt, (dw_trio_kernel<3, true>), grid, dim3(256), lds, st, f, b, w, t);
+        else if (group) launch_timed(kt, (dw_trio_kernel<0, true>), grid, dim3(256), lds, st, f, b, w, t);
+        else launch_timed(kt, (dw_trio_kernel<3, false>), grid, dim3(256), lds, st, f, b, w, t);
+    }
+    *err = hipGetLastError();
+    if (*err == hipSuccess) *err = launch_dw_wgrad_reduce(w, st);
+    return true;
 }
 
 }  // namespace int8t

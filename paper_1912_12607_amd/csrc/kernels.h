@@ -286,5 +286,8 @@ void dw_wgrad_shape(int N, int C, int IH, int IW, int P, int Q, int R, int S, in
                     int* threads, int* chunks, int* cg);
 hipError_t launch_dw_conv(const DwArgs& a, hipStream_t st);
 hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st);
+// the three passes of a layer (fwd: nullptr where only the two backward ones run) in one launch; false: not a layer for it,
+// nothing launched
+bool launch_dw_trio(const DwArgs* fwd, const DwArgs& bwd, const DwArgs& wgrad, hipStream_t st, hipError_t* err);
 
 }  // namespace int8t

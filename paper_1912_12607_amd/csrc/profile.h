@@ -36,6 +36,7 @@ enum KernelId : int {
     KID_DW_CONV,
     KID_DW_WGRAD,
     KID_DW_WGRAD_REDUCE,
+    KID_DW_TRIO,
     KID_COUNT
 };
 

@@ -111,17 +111,23 @@ def test_backward_weight_five_taps(shape):
 @pytest.mark.parametrize("shape,together", [((2, 16, 16, 16, 32, 3, 3), True), ((64, 256, 14, 14, 256, 3, 3), True), ((32, 48, 35, 35, 64, 5, 5), True),
                                             ((3, 130, 17, 17, 200, 1, 7), True), ((5, 70, 9, 11, 129, 7, 1), True), ((1, 300, 1, 1, 65, 1, 1), True),
                                             ((64, 40, 28, 28, 500, 1, 3), True), ((64, 1000, 14, 14, 260, 1, 1), True), ((16, 64, 56, 56, 64, 3, 3), True),
-                                            ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True)])
+                                            ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True),
+                                            # depthwise: planes alone and several to a block, rows of whole dwords and others, channel
+                                            # groups; planes that backward-weight does not prefetch
+                                            ((3, 5, 56, 56, 5, 3, 3), True), ((2, 6, 40, 64, 6, 3, 3), True), ((5, 32, 28, 28, 32, 3, 3), True),
+                                            ((3, 48, 14, 14, 48, 3, 3), True), ((9, 64, 7, 7, 64, 3, 3), True), ((1, 16, 16, 16, 16, 3, 3), True),
+                                            ((2, 3, 112, 112, 3, 3, 3), False), ((2, 5, 35, 35, 5, 3, 3), False)])
 def test_three_passes_in_one_launch(shape, together):
     N, C, H, W, K, R, S = shape
-    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=1)
+    depthwise = C == K and (R, S) == (3, 3) and (C != 64 or H == 7) and C < 256
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=C if depthwise else 1)
     st = LayerStep(L, keep_acc=True, requantize_deviation=False)
     g = torch.Generator(device=DEV).manual_seed(3)
     for t in (st.x, st.w, st.dy):
         t.normal_(generator=g)
     st.ratios.copy_(dev(inputs.default_ratios(32)))
     st.run(seed=5, overlap=0)
-    B.int8t_profile_start("conv_trio_kernel")
+    B.int8t_profile_start("dw_trio_kernel" if depthwise else "conv_trio_kernel")
     st.run(seed=5, overlap=0)
     torch.cuda.synchronize()
     assert bool(B.int8t_profile_stop()) == together
