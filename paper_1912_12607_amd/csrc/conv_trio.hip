@@ -10,6 +10,7 @@
 
 #include "conv_igemm_dma.h"
 #include "conv_wgrad_lines.h"
+#include "conv_wgrad_tile.h"
 
 namespace int8t {
 
@@ -17,10 +18,12 @@ namespace {
 struct TrioBlocks {
     unsigned wgrad, wgrad8, fwd;     // backward-weight's blocks, and rounded up to the 8 XCDs; the forward pass's
 };
+// ST = 0: backward-weight on image granules, one tap and 64 channels per block (narrow 1x1 layers)
 constexpr int trio_wt(int ST) { return ST == 1 ? 2 : 1; }
 constexpr int trio_gp(int ST) { return ST == 1 ? 4 : ST == 5 ? 6 : 8; }
 template <int BN, int ST>
 constexpr size_t trio_lds() {
+    if (ST == 0) return W2_LDS_BUDGET;
     return std::max((size_t)2 * (128 + BN) * 8 * 16, (size_t)WL_NSTAGE * wl_stage_bytes(trio_wt(ST), trio_wt(ST), trio_gp(ST)));
 }
 }  // namespace
@@ -30,7 +33,9 @@ template <int BN, int ST, bool STG>
 __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, const IgemmArgs b, const WgradArgs w, const TrioBlocks n) {
     const unsigned block = blockIdx.x;
     if (block < n.wgrad8) {
-        if (block < n.wgrad) wgrad_lines_tile<ST, trio_wt(ST), trio_wt(ST), trio_gp(ST)>(w, block);
+        if (block >= n.wgrad) return;
+        if constexpr (ST == 0) wgrad_tile<1, 1>(w, block);
+        else wgrad_lines_tile<ST, trio_wt(ST), trio_wt(ST), trio_gp(ST)>(w, block);
     } else if (block < n.wgrad8 + n.fwd) {
         igemm_dma_tile<false, 2, 8, 2, false, false, BN, false, STG>(f, block - n.wgrad8);
     } else {
@@ -50,9 +55,11 @@ __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, co
 // the time is one tile's chain of stages, and the narrow tile's is shorter.  Against the best of the three per layer this
 // rule loses 1.3 % on average, 19 % at most.  The two backward passes alone (a forward pass ran earlier; 104 random layers:
 // 7x1, 76 -> 216 channels, 65 x 65, batch 3: 33.0, 21.7, 22.6): up to 3000 such tiles, the wider tile from twice the longest
-// reduction on; loses 1.9 % on average, 13 % at most.
+// reduction on; loses 1.9 % on average, 13 % at most.  Layers whose backward-weight works on image granules (narrow 1x1 layers,
+// 3x5 and the like; 100 random ones: 1x1, 64 channels, 56 x 56, batch 2, 18.7, 10.1, 9.9; 96 -> 576 at 14 x 14, batch 64,
+// 32.9, 25.0, 25.5; 24 -> 144 at 56 x 56, 53.9, 71.0, 57.9): up to 3000 tiles as well.
 int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
-    if (w.variant != VAR_AUTO || !w.lines) return 0;
+    if (w.variant != VAR_AUTO || w.s2d || !(w.lines || (w.TB == 1 && w.CS == 1 && !w.pk))) return 0;
     long long band_tiles = 0, work = 0, longest = 0;
     for (const IgemmArgs* a : {fwd, &bwd}) {
         if (!a) continue;
@@ -65,14 +72,14 @@ int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& 
         work += tiles * gran;
         longest = std::max(longest, gran);
     }
-    if (band_tiles > (fwd ? 4000 : 3000)) return 0;
+    if (band_tiles > (fwd && w.lines ? 4000 : 3000)) return 0;
     return 5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64;
 }
 
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st) {
     IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
     TrioBlocks n;
-    n.wgrad = wgrad_lines_grid(w);
+    n.wgrad = w.lines ? wgrad_lines_grid(w) : wgrad_grid(w);
     n.wgrad8 = (n.wgrad + 7) & ~7u;
     n.fwd = fwd ? igemm_plain_blocks(&f, bn) : 0;
     const unsigned nb = igemm_plain_blocks(&b, bn);
@@ -89,7 +96,8 @@ hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const Wg
     } while (0)
 #define LAUNCH_ST(BNv, STv) do { if (stg) LAUNCH(BNv, STv, true); else LAUNCH(BNv, STv, false); } while (0)
 #define LAUNCH_BN(STv) do { if (bn == 64) LAUNCH_ST(64, STv); else LAUNCH_ST(128, STv); } while (0)
-    if (w.TB == 1) LAUNCH_BN(1);
+    if (!w.lines) LAUNCH_BN(0);
+    else if (w.TB == 1) LAUNCH_BN(1);
     else if (w.TB == 3) LAUNCH_BN(3);
     else if (w.TB == 5) LAUNCH_BN(5);
     else if (w.TB == 7) LAUNCH_BN(7);

@@ -244,6 +244,7 @@ bool wgrad_lines_applies(const WgradArgs& a);    // geometry as wgrad_plan() tak
 __host__ __device__ inline bool wgrad_lines_along_w(int R, int S) { return S > 1 || R == 1; }
 void wgrad_plan_lines(WgradArgs* a);
 hipError_t launch_wgrad_lines(const WgradArgs& a, hipStream_t st);
+unsigned wgrad_grid(const WgradArgs& a);         // blocks of wgrad_kernel
 unsigned wgrad_lines_grid(const WgradArgs& a);
 bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filters, stride 2 x 2
 // which kernel VAR_AUTO stands for: true = wgrad_lines_kernel

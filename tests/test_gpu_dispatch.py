@@ -112,6 +112,9 @@ def test_backward_weight_five_taps(shape):
                                             ((3, 130, 17, 17, 200, 1, 7), True), ((5, 70, 9, 11, 129, 7, 1), True), ((1, 300, 1, 1, 65, 1, 1), True),
                                             ((64, 40, 28, 28, 500, 1, 3), True), ((64, 1000, 14, 14, 260, 1, 1), True), ((16, 64, 56, 56, 64, 3, 3), True),
                                             ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True),
+                                            # backward-weight on image granules
+                                            ((64, 96, 14, 14, 576, 1, 1), True), ((3, 50, 9, 11, 30, 1, 1), True), ((5, 33, 12, 8, 40, 5, 3), True),
+                                            ((64, 24, 56, 56, 144, 1, 1), False),
                                             # depthwise: planes alone and several to a block, rows of whole dwords and others, channel
                                             # groups; planes that backward-weight does not prefetch
                                             ((3, 5, 56, 56, 5, 3, 3), True), ((2, 6, 40, 64, 6, 3, 3), True), ((5, 32, 28, 28, 32, 3, 3), True),
