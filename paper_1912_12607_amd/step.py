@@ -31,8 +31,11 @@ def two_stream_default(L: Layer) -> bool:
     14 x 14, batch 64, 3.2 M gradient elements, 78 / 86, batch 128, 6.4 M, 127 / 130; 1x3, 132 -> 271 channels at 12 x 12,
     10 M, 125 / 116; 3x3 on 64 channels at 56 x 56, 12.8 M, 153 / 142; 1x7 on 768 channels at 17 x 17, 14.2 M, 376 / 340;
     depthwise 3x3, 144 channels at 56 x 56, 28.9 M, 275 / 248: two streams from 8 M elements on (between 4 M and 8 M either
-    may win by up to 10 %, below they lose up to 25 us, above at most 6 %)."""
-    return L.N * L.K * L.P * L.Q >= (8 << 20)
+    may win by up to 10 %, below they lose up to 25 us, above at most 6 %), and from 5 M on where the input is at least twice
+    the gradient, whose passes the search then hides (1x7, 108 -> 32 channels at 25 x 25, 5.1 M, 156 / 138; 213 -> 102 1x1 at
+    55 x 55, 7.7 M, 157 / 145; nine such layers: 14 % gained at most, 1 % lost)."""
+    n_x, n_y = L.N * L.C * L.H * L.W, L.N * L.K * L.P * L.Q
+    return n_y >= (8 << 20) or (n_y >= 5_000_000 and n_x >= 2 * n_y)
 
 
 def two_stream_mode(L: Layer) -> int:
