@@ -94,12 +94,13 @@ __device__ __forceinline__ void digit_planes(const uint32_t y[4], uint32_t plane
     plane[2] = t1 | t3;
 }
 
-// 2 v of a positive scale (or of an infinite one: the reciprocal of a very small clip value), on the scalar unit: the
-// exponent plus one.  (0 becomes a tiny number, which only meets elements that are 0 and candidates that do not exist.)
+// 2 v of a scale, on the scalar unit: the exponent plus one, an infinity (the reciprocal of a very small clip value) stays
+// one, and 0 stays 0 -- the scale of an infinite clip value, which has to turn an infinite element into no number and so into
+// code 0, and of candidates that do not exist.
 // Volatile, so that the doubled scales of all candidates are not kept, and spilled, across the loop.
 __device__ __forceinline__ float twice(float v) {
     int b;
-    asm volatile("s_add_u32 %0, %1, 0x800000\n\ts_min_u32 %0, %0, 0x7f800000" : "=&s"(b) : "s"(v) : "scc");
+    asm volatile("s_min_u32 %0, %1, 0x800000\n\ts_add_u32 %0, %0, %1\n\ts_min_u32 %0, %0, 0x7f800000" : "=&s"(b) : "s"(v) : "scc");
     return __int_as_float(b);
 }
 

@@ -13,7 +13,7 @@ import oracle  # noqa: E402
 from paper_1912_12607_amd import binding as B  # noqa: E402
 from paper_1912_12607_amd import inputs  # noqa: E402
 from paper_1912_12607_amd.step import LayerStep  # noqa: E402
-from test_gpu_parity import DEV, REL_TOL, RTN, STO, check_dsgc, dev, pack_act, pack_wgt  # noqa: E402
+from test_gpu_parity import DEV, REL_TOL, RTN, STO, check_dsgc, dev, gpu_dsgc, pack_act, pack_wgt  # noqa: E402
 
 
 # The sweep runs blocks of 4 waves up to 1024 wave-iterations of 256 elements and blocks of 16 above, and leaves the clip
@@ -38,6 +38,22 @@ def test_dsgc_block_sizes_and_clip_free_eights(n, kind):
         g = (g / np.abs(g).max() * np.float32(1e-26)).astype(np.float32)
     check_dsgc(g, ratios, STO, seed=n)
     check_dsgc(g, ratios, RTN, seed=n)
+
+
+# An infinite gradient element makes every clip value infinite and every scale 0: all codes are 0, so the deviation is 1 by
+# definition (a zero vector), whatever else the gradient holds.  The waves that hold the infinity work with clipped candidates,
+# the others without; large finite elements stand beside it, and a NaN, whose code is 0 as well.
+@pytest.mark.parametrize("n_cand", [32, 7])
+@pytest.mark.parametrize("with_nan", [False, True])
+def test_dsgc_infinite_element(n_cand, with_nan):
+    n = 5003
+    g = (np.random.RandomState(4).standard_t(3, size=n) * 1e-3).astype(np.float32)
+    g[3] = np.inf
+    g[5] = -3e38
+    if with_nan:
+        g[[6, 4000]] = np.nan
+    clip, d, da = gpu_dsgc(g, inputs.default_ratios(n_cand), STO, 9)
+    assert np.isinf(clip) and d == 1.0 and np.all(np.asarray(da) == 1.0)
 
 
 def conv_pass_elementwise(op, desc, od, xq, wq, dyq, with_acc):
