@@ -764,7 +764,8 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     }
     if (quant_g && !g_in_batch) {
         if (!b->dy || !b->dyq || !b->sdy || (b->dev_final && !b->ws_dy)) return INT8T_ERR_NULL;
-        if (!aligned16(b->dy) || !aligned16(b->dyq) || desc->N > 65535) return INT8T_ERR_ARG;
+        if (!aligned16(b->dy) || !aligned16(b->dyq)) return INT8T_ERR_ARG;
+        if (ak == INT8T_ACT && desc->N > 65535) return INT8T_ERR_SHAPE;      // grid.z of the channels-last pass, as in int8t_quantize
         if (b->dev_final && b->ws_dy_bytes < int8t_quantize_workspace_bytes(ydims, ak)) return INT8T_ERR_WORKSPACE;
     }
     if (((fwd || bwd_weight) && (!b->xq || !b->sx)) || ((fwd || bwd_data) && (!b->wq || !b->sw)) ||

@@ -218,6 +218,32 @@ def test_dsgc_two_phase_argument_errors(lib):
     assert search(0x1000, 1000, 0x5000, 32, 1, 0, 0x2000, 0x3000, None, 0x4000, need - 1, None) == 4
 
 
+# int8t_layer_step with made-up addresses: every call below has to end in one of the argument checks, before a launch.
+LAYER_STEP_ADDRESSES = {name: 0x100000 + 0x1000 * i for i, name in enumerate(
+    ("x", "w", "dy", "xq", "wq", "dyq", "sx", "sw", "sdy", "ratios", "clip", "dev_search", "dev_all", "dev_final",
+     "y", "dx", "dw", "y_acc", "dx_acc", "dw_acc"))}
+LAYER_STEP_ADDRESSES.update({"ws_quant": 0x10000000, "ws_dy": 0x20000000, "ws_fwd": 0x30000000, "ws_bwd_data": 0x40000000,
+                             "ws_bwd_weight": 0x50000000})
+
+
+def layer_step_status(desc, parts, **fields):
+    from paper_1912_12607_amd import binding as B
+    b = B.LayerBuffers(n_cand=32, **LAYER_STEP_ADDRESSES)
+    for name in ("ws_quant", "ws_dy", "ws_fwd", "ws_bwd_data", "ws_bwd_weight"):
+        setattr(b, name + "_bytes", 1 << 24)
+    for name, v in fields.items():
+        setattr(b, name, v)
+    return B.lib.int8t_layer_step(C.byref(desc), C.byref(b), parts, 0, None)
+
+
+def test_layer_step_batch_limit_of_the_codes():
+    """The channels-last quantizer takes 65535 images; planar codes (depthwise layers) have no such limit."""
+    from paper_1912_12607_amd import binding as B
+    dense, planar = B.make_desc(70000, 8, 5, 5, 8, 3, 3, (1, 1), (1, 1)), B.make_desc(70000, 8, 5, 5, 8, 3, 3, (1, 1), (1, 1), 8)
+    parts = B.STEP_QUANT_G | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    assert layer_step_status(dense, parts) == 2                            # INT8T_ERR_SHAPE, as int8t_quantize says
+    assert layer_step_status(planar, parts, ws_dy_bytes=16) == 4           # past that check: INT8T_ERR_WORKSPACE
+
 
 def test_unpack_codes_matches_the_documented_layouts():
     """int8t_unpack_codes against the layout formulas of include/int8t.h written out with numpy."""

@@ -12,6 +12,7 @@ if not torch.cuda.is_available():
 import oracle  # noqa: E402
 from paper_1912_12607_amd import binding as B  # noqa: E402
 from paper_1912_12607_amd import inputs  # noqa: E402
+from paper_1912_12607_amd.autograd import Int8Conv2d  # noqa: E402
 from paper_1912_12607_amd.step import LayerStep  # noqa: E402
 from test_gpu_parity import DEV, REL_TOL, RTN, STO, check_dsgc, dev, gpu_dsgc, pack_act, pack_wgt  # noqa: E402
 
@@ -166,4 +167,36 @@ def test_three_passes_in_one_launch(shape, together):
     st.bwd_weight()
     torch.cuda.synchronize()
     for a, b in zip(got, outs):
+        assert torch.equal(a, b)
+
+
+# Batches above 65535 images: the limit of the channels-last quantizer, not of planar codes.  Step and module against the calls
+# one by one.
+def test_depthwise_batch_above_65535():
+    L = inputs.Layer("layer", 65537, 2, 5, 5, 2, 3, 3, stride=(1, 1), pad=(1, 1), groups=2)
+    st = LayerStep(L)
+    g = torch.Generator(device=DEV).manual_seed(2)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    got = [t.clone() for t in (st.y, st.dx, st.dw, st.clip, st.dev_final)]
+    layer = Int8Conv2d(2, 2, 3, padding=1, groups=2, seed=4)          # (its first backward pass draws with seed 5)
+    with torch.no_grad():
+        layer.weight.copy_(st.w)
+    x = st.x.clone().requires_grad_()
+    y = layer(x)
+    module = [y.detach()] + list(torch.autograd.grad(y, [x, layer.weight], st.dy)) + [layer.clip]
+    for t in (st.y, st.dx, st.dw, st.clip, st.dev_final):
+        t.fill_(7)
+    st.quantize_xw()
+    st.dsgc(5)
+    st.quantize_dy(5)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    torch.cuda.synchronize()
+    for a, b in zip(got, (st.y, st.dx, st.dw, st.clip, st.dev_final)):
+        assert torch.equal(a, b)
+    for a, b in zip(module, got):
         assert torch.equal(a, b)
