@@ -364,8 +364,9 @@ size_t int8t_quantize_batch_workspace_bytes(int count, const int8t_quantize_item
 namespace {
 DsgcWs dsgc_ws_layout(void* ws_dev);
 
-// Argument checks of a batch of tensors (and of the tensor of a clip search beside them).
-int8t_status quantize_batch_check(int count, const int8t_quantize_item* items, const void* ws_dev, size_t ws_bytes,
+// Argument checks of a batch of tensors (and of the tensor of a clip search beside them); codes: their codes and scales are
+// written, not only their maxima found.
+int8t_status quantize_batch_check(int count, const int8t_quantize_item* items, bool codes, const void* ws_dev, size_t ws_bytes,
                                   const float* g_dev, size_t g_n, const void* dsgc_ws_dev, size_t dsgc_ws_size) {
     if (!items) return INT8T_ERR_NULL;
     if (count < 1 || count > INT8T_MAX_BATCH) return INT8T_ERR_ARG;
@@ -378,7 +379,7 @@ int8t_status quantize_batch_check(int count, const int8t_quantize_item* items, c
     bool any_absmax = false;
     for (int i = 0; i < count; ++i) {
         const int8t_quantize_item& it = items[i];
-        if (!it.x_dev || !it.q_dev || !it.scale_dev) return INT8T_ERR_NULL;
+        if (!it.x_dev || (codes && (!it.q_dev || !it.scale_dev))) return INT8T_ERR_NULL;
         size_t n;
         if (!dims_ok(it.dims, &n)) return INT8T_ERR_SHAPE;
         if (it.kind != INT8T_ACT && it.kind != INT8T_WGT && it.kind != INT8T_ACT_PLANAR && it.kind != INT8T_WGT_PLANAR)
@@ -467,7 +468,7 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
 // int8t_quantize_batch, and with g_dev also the first phase of a clip search on g in the same absmax launch
 int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, void* ws_dev, size_t ws_bytes,
                                  const float* g_dev, size_t g_n, void* dsgc_ws_dev, size_t dsgc_ws_size, void* stream) {
-    const int8t_status s = quantize_batch_check(count, items, ws_dev, ws_bytes, g_dev, g_n, dsgc_ws_dev, dsgc_ws_size);
+    const int8t_status s = quantize_batch_check(count, items, true, ws_dev, ws_bytes, g_dev, g_n, dsgc_ws_dev, dsgc_ws_size);
     if (s != INT8T_OK) return s;
     long long qblocks = 0;
     for (int i = 0; i < count; ++i) qblocks += quant_blocks(items[i].dims, items[i].kind);
@@ -753,7 +754,7 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     // ---- everything that can be wrong, before the first launch
     if (quant_g && !b->clip) return INT8T_ERR_NULL;
     if (absmax || quant_xw) {
-        s = quantize_batch_check(g_in_batch ? 3 : 2, it, b->ws_quant, b->ws_quant_bytes, prepare ? b->dy : nullptr, n_y, b->ws_dy, b->ws_dy_bytes);
+        s = quantize_batch_check(g_in_batch ? 3 : 2, it, quant_xw, b->ws_quant, b->ws_quant_bytes, prepare ? b->dy : nullptr, n_y, b->ws_dy, b->ws_dy_bytes);
         if (s != INT8T_OK) return s;
         if (prepare && !b->dy) return INT8T_ERR_NULL;
     }

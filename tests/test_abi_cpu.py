@@ -244,6 +244,25 @@ def test_layer_step_batch_limit_of_the_codes():
     assert layer_step_status(dense, parts) == 2                            # INT8T_ERR_SHAPE, as int8t_quantize says
     assert layer_step_status(planar, parts, ws_dy_bytes=16) == 4           # past that check: INT8T_ERR_WORKSPACE
 
+def test_layer_step_unused_pointers_may_be_null():
+    """A pointer that no part of the call uses may be NULL; one that a part uses may not."""
+    from paper_1912_12607_amd import binding as B
+    d = B.make_desc(2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1))
+    used = {B.STEP_ABSMAX: {"x", "w", "ws_quant"},
+            B.STEP_ABSMAX | B.STEP_PREPARE: {"x", "w", "dy", "ws_quant", "ws_dy"},
+            B.STEP_SEARCH: {"dy", "ratios", "clip", "dev_search", "ws_dy"},
+            B.STEP_QUANT_XW: {"x", "w", "xq", "wq", "sx", "sw", "ws_quant"},
+            B.STEP_QUANT_G: {"dy", "clip", "dyq", "sdy", "dev_final", "ws_dy"},
+            B.STEP_BWD_WEIGHT: {"xq", "sx", "dyq", "sdy", "dw", "ws_bwd_weight"}}
+    for parts, names in used.items():
+        unused = {n: None for n in LAYER_STEP_ADDRESSES if n not in names}
+        # with scratch too small for every part: the last check before the launches, so all others have passed
+        small = {n + "_bytes": 16 for n in ("ws_quant", "ws_dy", "ws_bwd_weight")}
+        assert layer_step_status(d, parts, **unused, **small) == 4
+        for n in names - {"dev_final"}:
+            assert layer_step_status(d, parts, **{**unused, n: None}) == 1, (parts, n)
+    assert layer_step_status(d, B.STEP_FWD, xq=None) == 1 and layer_step_status(d, B.STEP_BWD_DATA, dx=None) == 1
+
 
 def test_unpack_codes_matches_the_documented_layouts():
     """int8t_unpack_codes against the layout formulas of include/int8t.h written out with numpy."""
