@@ -26,6 +26,7 @@ namespace {
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline int pad16(int v) { return (v + 15) & ~15; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+inline bool aligned8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0; }
 inline bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0; }
 
 constexpr size_t kMaxElems = 0x7FFFFFFFull;   // 32-bit indices inside the kernels
@@ -465,14 +466,19 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
     return launch_quantize_batch(qb, (int)qblocks, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
 }
 
+// the codes' launch has one block index over all tensors of a batch
+bool batch_blocks_ok(int count, const int8t_quantize_item* items) {
+    long long blocks = 0;
+    for (int i = 0; i < count; ++i) blocks += quant_blocks(items[i].dims, items[i].kind);
+    return blocks <= 0x7FFFFFFFll;
+}
+
 // int8t_quantize_batch, and with g_dev also the first phase of a clip search on g in the same absmax launch
 int8t_status quantize_batch_impl(int count, const int8t_quantize_item* items, void* ws_dev, size_t ws_bytes,
                                  const float* g_dev, size_t g_n, void* dsgc_ws_dev, size_t dsgc_ws_size, void* stream) {
     const int8t_status s = quantize_batch_check(count, items, true, ws_dev, ws_bytes, g_dev, g_n, dsgc_ws_dev, dsgc_ws_size);
     if (s != INT8T_OK) return s;
-    long long qblocks = 0;
-    for (int i = 0; i < count; ++i) qblocks += quant_blocks(items[i].dims, items[i].kind);
-    if (qblocks > 0x7FFFFFFFll) return INT8T_ERR_SHAPE;
+    if (!batch_blocks_ok(count, items)) return INT8T_ERR_SHAPE;
     if (batch_absmax(count, items, ws_dev, g_dev, g_n, dsgc_ws_dev, (hipStream_t)stream) != hipSuccess) return INT8T_ERR_RUNTIME;
     return batch_codes(count, items, ws_dev, (hipStream_t)stream);
 }
@@ -526,7 +532,7 @@ int8t_status int8t_dsgc_search(const float* g_dev, size_t n, const float* ratios
     if (n_cand < 1 || n_cand > INT8T_MAX_CANDIDATES) return INT8T_ERR_ARG;
     if (mode != INT8T_ROUND_NEAREST_EVEN && mode != INT8T_ROUND_STOCHASTIC) return INT8T_ERR_ARG;
     if (!aligned16(g_dev) || !aligned16(ws_dev) || !aligned4(ratios_dev) || !aligned4(clip_dev) ||
-        (reinterpret_cast<uintptr_t>(deviation_dev) & 7) || (reinterpret_cast<uintptr_t>(deviation_all_dev) & 7))
+        !aligned8(deviation_dev) || !aligned8(deviation_all_dev))
         return INT8T_ERR_ARG;
     if (ws_bytes < dsgc_ws_bytes(n)) return INT8T_ERR_WORKSPACE;
     const DsgcWs ws = dsgc_ws_layout(ws_dev);
@@ -545,7 +551,7 @@ int8t_status int8t_dsgc_clip(const float* g_dev, size_t n, const float* ratios_d
     if (n_cand < 1 || n_cand > INT8T_MAX_CANDIDATES) return INT8T_ERR_ARG;
     if (mode != INT8T_ROUND_NEAREST_EVEN && mode != INT8T_ROUND_STOCHASTIC) return INT8T_ERR_ARG;
     if (!aligned16(g_dev) || !aligned16(ws_dev) || !aligned4(ratios_dev) || !aligned4(clip_dev) ||
-        (reinterpret_cast<uintptr_t>(deviation_dev) & 7) || (reinterpret_cast<uintptr_t>(deviation_all_dev) & 7))
+        !aligned8(deviation_dev) || !aligned8(deviation_all_dev))
         return INT8T_ERR_ARG;
     if (ws_bytes < dsgc_ws_bytes(n)) return INT8T_ERR_WORKSPACE;
     int8t_status s = int8t_dsgc_prepare(g_dev, n, ws_dev, ws_bytes, stream);
@@ -756,16 +762,19 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     if (absmax || quant_xw) {
         s = quantize_batch_check(g_in_batch ? 3 : 2, it, quant_xw, b->ws_quant, b->ws_quant_bytes, prepare ? b->dy : nullptr, n_y, b->ws_dy, b->ws_dy_bytes);
         if (s != INT8T_OK) return s;
+        if (quant_xw && !batch_blocks_ok(g_in_batch ? 3 : 2, it)) return INT8T_ERR_SHAPE;
         if (prepare && !b->dy) return INT8T_ERR_NULL;
     }
     if (search) {
         if (!b->dy || !b->ratios || !b->clip || !b->dev_search || !b->ws_dy) return INT8T_ERR_NULL;
-        if (b->n_cand < 1 || b->n_cand > INT8T_MAX_CANDIDATES || !aligned16(b->dy) || !aligned16(b->ws_dy)) return INT8T_ERR_ARG;
+        if (b->n_cand < 1 || b->n_cand > INT8T_MAX_CANDIDATES || !aligned16(b->dy) || !aligned16(b->ws_dy) || !aligned4(b->ratios) ||
+            !aligned4(b->clip) || !aligned8(b->dev_search) || !aligned8(b->dev_all))
+            return INT8T_ERR_ARG;
         if (b->ws_dy_bytes < dsgc_ws_bytes(n_y)) return INT8T_ERR_WORKSPACE;
     }
     if (quant_g && !g_in_batch) {
         if (!b->dy || !b->dyq || !b->sdy || (b->dev_final && !b->ws_dy)) return INT8T_ERR_NULL;
-        if (!aligned16(b->dy) || !aligned16(b->dyq)) return INT8T_ERR_ARG;
+        if (!aligned16(b->dy) || !aligned16(b->dyq) || !aligned4(b->sdy) || (b->dev_final && !aligned16(b->ws_dy))) return INT8T_ERR_ARG;
         if (ak == INT8T_ACT && desc->N > 65535) return INT8T_ERR_SHAPE;      // grid.z of the channels-last pass, as in int8t_quantize
         if (b->dev_final && b->ws_dy_bytes < int8t_quantize_workspace_bytes(ydims, ak)) return INT8T_ERR_WORKSPACE;
     }
@@ -773,7 +782,9 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         ((bwd_data || bwd_weight) && (!b->dyq || !b->sdy)) || (fwd && !b->y) || (bwd_data && !b->dx) ||
         (bwd_weight && (!b->dw || !b->ws_bwd_weight)))
         return INT8T_ERR_NULL;
-    if ((fwd && !aligned16(b->y)) || (bwd_data && !aligned16(b->dx)) || (bwd_weight && (!aligned16(b->dw) || !aligned16(b->ws_bwd_weight))) ||
+    if (((fwd || bwd_weight) && !aligned16(b->xq)) || ((fwd || bwd_data) && !aligned16(b->wq)) || ((bwd_data || bwd_weight) && !aligned16(b->dyq)) ||
+        (fwd && (!aligned16(b->y) || !aligned4(b->y_acc))) || (bwd_data && (!aligned16(b->dx) || !aligned4(b->dx_acc))) ||
+        (bwd_weight && (!aligned16(b->dw) || !aligned4(b->dw_acc) || !aligned16(b->ws_bwd_weight))) ||
         !aligned16(b->ws_fwd) || !aligned16(b->ws_bwd_data))
         return INT8T_ERR_ARG;
     if (bwd_weight && b->ws_bwd_weight_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
@@ -793,8 +804,7 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         s = int8t_quantize(b->dy, ydims, ak, b->clip, INT8T_ROUND_STOCHASTIC, seed, b->dyq, b->sdy, b->dev_final, b->ws_dy, b->ws_dy_bytes, stream);
         if (s != INT8T_OK) return s;
     }
-    const bool together = bwd_data && bwd_weight && aligned16(b->xq) && aligned16(b->wq) && aligned16(b->dyq) && aligned4(b->y_acc) &&
-        aligned4(b->dx_acc) && aligned4(b->dw_acc) && disjoint_results(desc, g, b, fwd);        // (else the calls below say what is wrong)
+    const bool together = bwd_data && bwd_weight && disjoint_results(desc, g, b, fwd);
     if (together && g.depthwise) {
         DwArgs f = dw_args(desc, g, false), d = dw_args(desc, g, true), w = dw_wgrad_args(desc, g);
         f.a = b->xq; f.b = b->wq; f.sa = b->sx; f.sb = b->sw; f.out = b->y; f.acc = b->y_acc;

@@ -118,6 +118,25 @@ int main() {
     EXPECT(int8t_conv_bwd_data(&neg, q, f, q, f, f, nullptr, nullptr, 0, nullptr) == INT8T_ERR_SHAPE);
     EXPECT(int8t_conv_bwd_weight(&good, q, f, q, f, f, nullptr, nullptr, 0, nullptr) == INT8T_ERR_NULL);
     EXPECT(int8t_conv_bwd_weight(&good, q, f, q, f, f, nullptr, fake, 16, nullptr) == INT8T_ERR_WORKSPACE);
+    int8t_layer_buffers lb;
+    std::memset(&lb, 0, sizeof(lb));
+    EXPECT(int8t_layer_step(nullptr, &lb, INT8T_STEP_ALL, 0, nullptr) == INT8T_ERR_NULL);
+    EXPECT(int8t_layer_step(&good, nullptr, INT8T_STEP_ALL, 0, nullptr) == INT8T_ERR_NULL);
+    EXPECT(int8t_layer_step(&grp, &lb, INT8T_STEP_ALL, 0, nullptr) == INT8T_ERR_SHAPE);
+    EXPECT(int8t_layer_step(&good, &lb, 0, 0, nullptr) == INT8T_ERR_ARG);
+    EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_PREPARE, 0, nullptr) == INT8T_ERR_ARG);
+    for (int part = 1; part <= 128; part *= 2)
+        if (part != INT8T_STEP_PREPARE) EXPECT(int8t_layer_step(&good, &lb, part, 0, nullptr) == INT8T_ERR_NULL);
+    lb.x = lb.w = lb.dy = lb.ratios = f;
+    lb.xq = lb.wq = lb.dyq = q;
+    lb.sx = lb.sw = lb.sdy = lb.clip = lb.y = lb.dx = lb.dw = f;
+    lb.dev_search = dd;
+    lb.ws_quant = lb.ws_dy = lb.ws_bwd_weight = fake;
+    lb.n_cand = 4;
+    EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_ALL, 0, nullptr) == INT8T_ERR_WORKSPACE);
+    EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_BWD_WEIGHT, 0, nullptr) == INT8T_ERR_WORKSPACE);
+    lb.dyq = q + 1;
+    EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_BWD_DATA, 0, nullptr) == INT8T_ERR_ARG);
     EXPECT(int8t_profile_start("no_such_kernel") == INT8T_ERR_ARG);
     EXPECT(int8t_profile_start_sampled("wgrad_kernel", 0) == INT8T_ERR_ARG);
     EXPECT(int8t_dclr_scale(0.0, 20.0, 0.1) == 1.0 && int8t_dclr_scale(1.0, 20.0, 0.1) == 0.1);

@@ -263,6 +263,26 @@ def test_layer_step_unused_pointers_may_be_null():
             assert layer_step_status(d, parts, **{**unused, n: None}) == 1, (parts, n)
     assert layer_step_status(d, B.STEP_FWD, xq=None) == 1 and layer_step_status(d, B.STEP_BWD_DATA, dx=None) == 1
 
+def test_layer_step_checks_everything_before_the_first_launch():
+    from paper_1912_12607_amd import binding as B
+    d = B.make_desc(2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1))
+    by = {"x": 4, "w": 4, "dy": 4, "xq": 4, "wq": 4, "dyq": 4, "sx": 2, "sw": 2, "sdy": 2, "ratios": 2, "clip": 2, "dev_search": 4, "dev_all": 4,
+          "y": 4, "dx": 4, "dw": 4, "y_acc": 2, "dx_acc": 2, "dw_acc": 2, "ws_quant": 4, "ws_dy": 4, "ws_fwd": 4, "ws_bwd_data": 4,
+          "ws_bwd_weight": 4}
+    for dev_final in (LAYER_STEP_ADDRESSES["dev_final"], None):       # g_z quantized by itself, and in one launch with a and W
+        for n, off in by.items():
+            assert layer_step_status(d, B.STEP_ALL, **{"dev_final": dev_final, n: LAYER_STEP_ADDRESSES[n] + off}) == 3, n
+        for ws, nbytes in (("ws_quant", 4096), ("ws_dy", 4096), ("ws_bwd_weight", 16)):
+            assert layer_step_status(d, B.STEP_ALL, dev_final=dev_final, **{ws + "_bytes": nbytes}) == 4, ws
+    convs = B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    for n in ("xq", "wq", "dyq", "y", "dx", "dw", "y_acc", "dx_acc", "dw_acc"):
+        assert layer_step_status(d, convs, **{n: LAYER_STEP_ADDRESSES[n] + by[n]}) == 3, n
+    assert layer_step_status(d, B.STEP_ALL, n_cand=0) == 3 and layer_step_status(d, B.STEP_ALL, n_cand=65) == 3
+    assert layer_step_status(d, 0) == 3 and layer_step_status(d, 256) == 3 and layer_step_status(d, B.STEP_PREPARE) == 3
+    assert B.lib.int8t_layer_step(C.byref(d), None, B.STEP_ALL, 0, None) == 1
+    grouped = B.make_desc(2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1), 4)
+    assert layer_step_status(grouped, B.STEP_ALL) == 2
+
 
 def test_unpack_codes_matches_the_documented_layouts():
     """int8t_unpack_codes against the layout formulas of include/int8t.h written out with numpy."""
