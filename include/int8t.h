@@ -333,7 +333,9 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc *desc,
  *           this call uses as well.  Read before the call returns.
  *   ws_quant     3 x int8t_quantize_batch_workspace_bytes(1, ..) bytes: the absmax partials of a and W, kept between
  *                INT8T_STEP_ABSMAX and INT8T_STEP_QUANT_XW
- *   ws_dy        max(int8t_workspace_bytes(INT8T_OP_DSGC, ..), int8t_quantize_workspace_bytes(dims of g_z)) bytes
+ *   ws_dy        max(int8t_workspace_bytes(INT8T_OP_DSGC, ..), int8t_quantize_workspace_bytes(dims of g_z)) bytes; between
+ *                INT8T_STEP_ABSMAX and INT8T_STEP_QUANT_XW a search may not run in memory that overlaps ws_quant
+ *                (INT8T_ERR_ARG within one call)
  *   ws_fwd, ws_bwd_data    as for int8t_conv_fwd / int8t_conv_bwd_data (optional);  ws_bwd_weight: required by that part
  * Errors as for the calls; arguments are checked before anything is launched.
  */

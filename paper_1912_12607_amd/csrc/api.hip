@@ -772,6 +772,11 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
             return INT8T_ERR_ARG;
         if (b->ws_dy_bytes < dsgc_ws_bytes(n_y)) return INT8T_ERR_WORKSPACE;
     }
+    // the partials of a and W and the search's scratch are in use at the same time
+    if ((absmax || quant_xw) && (prepare || search)) {
+        const uintptr_t p = (uintptr_t)b->ws_quant, q = (uintptr_t)b->ws_dy;
+        if (p < q + dsgc_ws_bytes(n_y) && q < p + int8t_quantize_batch_workspace_bytes(2, it)) return INT8T_ERR_ARG;
+    }
     if (quant_g && !g_in_batch) {
         if (!b->dy || !b->dyq || !b->sdy || (b->dev_final && !b->ws_dy)) return INT8T_ERR_NULL;
         if (!aligned16(b->dy) || !aligned16(b->dyq) || !aligned4(b->sdy) || (b->dev_final && !aligned16(b->ws_dy))) return INT8T_ERR_ARG;

@@ -283,6 +283,16 @@ def test_layer_step_checks_everything_before_the_first_launch():
     grouped = B.make_desc(2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1), 4)
     assert layer_step_status(grouped, B.STEP_ALL) == 2
 
+def test_layer_step_scratch_of_the_search_and_of_the_maxima_overlap():
+    from paper_1912_12607_amd import binding as B
+    d = B.make_desc(2, 16, 8, 8, 16, 3, 3, (1, 1), (1, 1))
+    need, q = B.int8t_workspace_bytes(B.OP_DSGC, None, 2 * 16 * 64, 32), LAYER_STEP_ADDRESSES["ws_quant"]
+    for parts in (B.STEP_ALL, B.STEP_ABSMAX | B.STEP_PREPARE, B.STEP_ABSMAX | B.STEP_SEARCH, B.STEP_SEARCH | B.STEP_QUANT_XW):
+        for ws_dy in (q, q + 8192 - 16, q - need + 16):
+            assert layer_step_status(d, parts, ws_dy=ws_dy) == 3
+        for ws_dy in (q + 8192, q - need):          # side by side: on to the next check
+            assert layer_step_status(d, parts | B.STEP_BWD_DATA, ws_dy=ws_dy, dx=None) == 1
+
 
 def test_unpack_codes_matches_the_documented_layouts():
     """int8t_unpack_codes against the layout formulas of include/int8t.h written out with numpy."""
