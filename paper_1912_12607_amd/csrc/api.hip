@@ -810,6 +810,7 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         if (s != INT8T_OK) return s;
     }
     const bool together = bwd_data && bwd_weight && disjoint_results(desc, g, b, fwd);
+    bool fwd_left = fwd;
     if (together && g.depthwise) {
         DwArgs f = dw_args(desc, g, false), d = dw_args(desc, g, true), w = dw_wgrad_args(desc, g);
         f.a = b->xq; f.b = b->wq; f.sa = b->sx; f.sb = b->sw; f.out = b->y; f.acc = b->y_acc;
@@ -818,26 +819,33 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         w.partial = (int32_t*)b->ws_bwd_weight;
         hipError_t e = hipSuccess;
         if (launch_dw_trio(fwd ? &f : nullptr, d, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
-    } else if (together && !g.depthwise) {
+    } else if (together && !g.depthwise && desc->stride_h == 1 && desc->stride_w == 1) {
         IgemmArgs f{}, d{};
         WgradArgs w{};
         fill_igemm_fwd(&f, desc, g);
         f.variant = selected_variant(INT8T_OP_CONV_FWD, desc);
         f.act = b->xq; f.wgt = b->wq; f.sa = b->sx; f.sb = b->sw; f.out = b->y; f.acc = b->y_acc;
+        f.partial = (int32_t*)b->ws_fwd; f.partial_bytes = b->ws_fwd ? b->ws_fwd_bytes : 0;
         fill_igemm_bwd_data(&d, desc, g);
         d.variant = selected_variant(INT8T_OP_CONV_BWD_DATA, desc);
         d.act = b->dyq; d.wgt = b->wq + align256((size_t)desc->K * desc->R * desc->S * pad16(desc->C));
         d.sa = b->sdy; d.sb = b->sw; d.out = b->dx; d.acc = b->dx_acc;
+        d.partial = (int32_t*)b->ws_bwd_data; d.partial_bytes = b->ws_bwd_data ? b->ws_bwd_data_bytes : 0;
         fill_wgrad_geometry(&w, desc, g);
         wgrad_s2d(&w);
         w.variant = selected_variant(INT8T_OP_CONV_BWD_WEIGHT, desc);
         wgrad_plan(&w);
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
-        const int bn = conv_trio_tile(fwd ? &f : nullptr, d, w);
-        if (bn) return launch_conv_trio(fwd ? &f : nullptr, d, w, bn, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+        if (fwd && conv_trio_fwd_apart(f, d)) {
+            if (launch_igemm(f, st) != hipSuccess) return INT8T_ERR_RUNTIME;
+            fwd_left = false;
+        }
+        const IgemmArgs* fp = fwd_left ? &f : nullptr;
+        const int bn = conv_trio_tile(fp, d, w);
+        if (bn) return launch_conv_trio(fp, d, w, bn, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
-    if (fwd) {
+    if (fwd_left) {
         s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);
         if (s != INT8T_OK) return s;
     }

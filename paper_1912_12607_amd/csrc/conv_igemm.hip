@@ -529,6 +529,14 @@ hipError_t launch_igemm_fused(const IgemmArgs& a_in, hipStream_t st) {
     return hipGetLastError();
 }
 
+// whether the caller's scratch holds the partial sums of a split reduction
+static bool igemm_split_scratch(const IgemmArgs& a) {
+    return a.partial != nullptr && a.partial_bytes >= (size_t)igemm_ksplit(a) * a.rows * a.N * a.OH * a.OW * 4;
+}
+bool igemm_splits(const IgemmArgs& a) {
+    return a.variant == VAR_AUTO && igemm_auto_variant(a, igemm_split_scratch(a)) == VAR_TILE_SPLIT;
+}
+
 size_t igemm_s2d(IgemmArgs* a) {
     if (a->dgrad || a->C < 1 || a->Ca != 16 || !s2d_applies(a->C, a->stride_h, a->stride_w)) return 0;
     const S2dGeo g = s2d_geometry(a->R, a->S, a->pad_h, a->pad_w);
@@ -564,7 +572,7 @@ hipError_t launch_igemm(const IgemmArgs& a_in, hipStream_t st) {
     }
     int variant = a.variant;
     if (variant == VAR_AUTO || !igemm_variant_ok(a, variant))
-        variant = igemm_auto_variant(a, a.partial != nullptr && a.partial_bytes >= (size_t)igemm_ksplit(a) * a.rows * a.N * a.OH * a.OW * 4);
+        variant = igemm_auto_variant(a, igemm_split_scratch(a));
     if (variant == VAR_BAND) {
         hipError_t berr = hipSuccess;
         if (launch_band(a, st, &berr)) return berr;   // small filter bank: LDS-resident kernel

@@ -58,8 +58,30 @@ __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, co
 // reduction on; loses 1.9 % on average, 13 % at most.  Layers whose backward-weight works on image granules (narrow 1x1 layers,
 // 3x5 and the like; 100 random ones: 1x1, 64 channels, 56 x 56, batch 2, 18.7, 10.1, 9.9; 96 -> 576 at 14 x 14, batch 64,
 // 32.9, 25.0, 25.5; 24 -> 144 at 56 x 56, 53.9, 71.0, 57.9): up to 3000 tiles as well.
+//
+// Passes that alone run as a split reduction (few tiles, long reductions; with the caller's scratch) have one tile's whole chain of
+// stages in here, about 1 us each beside backward-weight's blocks, against 15 - 25 us for the split.  Of 200 random ones, us
+// for the three passes one by one and all in one launch:
+//   5x5, 1024 channels, 10 x 10, batch 1             260    354      3x3, 120 -> 816, 5 x 5, batch 1               32.0   40.5
+//   5x5, 128 -> 1016, 15 x 15, batch 1              85.6    158      5x5, 384 -> 512, 15 x 15, batch 14             164    135
+//   5x5, 1024 -> 96, 8 x 8, batch 4                 67.0    128      5x5, 328 -> 272, 15 x 15, batch 5              159    128
+// The forward pass alone splits: it runs ahead and the two backward ones share the launch (conv_trio_fwd_apart; 59.2 on the third
+// layer of the left column), unless backward-data's chain, which stays whole, is nearly as long (the last layer: 146 that way).
+// Backward-data splits: one by one, unless its chain is fewer than 45 stages longer than that of a forward pass that stays whole;
+// without the forward pass one by one always (0.81 of the shared launch's time on average, 7 % slower at most).  Over the 200 the
+// three passes take 0.93 of the time one by one on average and 1.07 at most, 0.89 and 1.10 of the time all in one launch.
+static long long trio_stages(const IgemmArgs& a) { return ((long long)a.R * a.S * (a.Ca >> 4) + 7) / 8; }
+bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd) {
+    return igemm_splits(fwd) && !igemm_splits(bwd) && 5 * trio_stages(fwd) >= 8 * trio_stages(bwd);
+}
 int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
     if (w.variant != VAR_AUTO || w.s2d || !(w.lines || (w.TB == 1 && w.CS == 1 && !w.pk))) return 0;
+    if (igemm_splits(bwd)) {
+        if (!fwd) return 0;
+        const bool both = igemm_splits(*fwd);
+        const long long f = trio_stages(*fwd), b = trio_stages(bwd);
+        if (both ? std::max(f, b) >= 45 : b >= 45 + f) return 0;
+    }
     long long band_tiles = 0, work = 0, longest = 0;
     for (const IgemmArgs* a : {fwd, &bwd}) {
         if (!a) continue;

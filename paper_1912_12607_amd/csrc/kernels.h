@@ -164,6 +164,7 @@ int igemm_ksplit(const IgemmArgs& a);   // largest split a launch of this layer 
 // whether `variant` can run this layer (VAR_AUTO always can); resolved = the variant VAR_AUTO stands for
 bool igemm_variant_ok(const IgemmArgs& a, int variant);
 int igemm_auto_variant(const IgemmArgs& a, bool allow_split = true);   // allow_split: the caller's scratch holds the partial sums of a split reduction
+bool igemm_splits(const IgemmArgs& a);   // whether launch_igemm() would run the split reduction on its own choice
 // Forward pass of a layer s2d.hip covers: rewrites the geometry and returns the scratch bytes of the
 // rewritten input and filter codes (0: does not apply, the geometry is left alone).
 size_t igemm_s2d(IgemmArgs* a);
@@ -261,6 +262,7 @@ __host__ __device__ inline bool wgrad_xcd_mapping(int splits) {
 // Column width of the implicit-GEMM tiles with which the passes share a launch, 0: they run one by one.  w: after wgrad_plan();
 // fwd: nullptr where only the two backward passes run.
 int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
+bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd);    // the forward pass is better launched ahead, by itself
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st);
 
 // ---- conv_dw.hip (depthwise, planar codes) ----------------------------------------------------

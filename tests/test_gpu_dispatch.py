@@ -200,3 +200,43 @@ def test_depthwise_batch_above_65535():
         assert torch.equal(a, b)
     for a, b in zip(module, got):
         assert torch.equal(a, b)
+
+
+# Passes whose reduction is split when they run alone: the forward pass ahead of a shared launch of the backward ones, all three by
+# themselves, or together in spite of it (5 to 88 stages of 128 bytes per tile); without the scratch of a split always together.
+# Bit for bit the calls one by one.
+@pytest.mark.parametrize("shape,reductions,together,reductions2,together2", [
+    ((4, 1024, 8, 8, 96, 5, 5), 1, True, 0, True),              # forward 200 stages, backward-data 19
+    ((1, 1024, 7, 7, 1024, 3, 3), 2, False, 1, False),          # 72 and 72
+    ((1, 128, 10, 10, 440, 5, 5), 1, False, 1, False),          # 25 and 88
+    ((2, 104, 8, 8, 200, 5, 5), 0, True, 1, False),             # 22 and 41
+    ((1, 992, 10, 10, 832, 1, 7), 0, True, 0, True)])           # 55 and 46, backward-data not split
+def test_split_reductions_and_the_shared_launch(shape, reductions, together, reductions2, together2):
+    N, C, H, W, K, R, S = shape
+    st = LayerStep(inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2)), keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    outs = (st.y, st.dx, st.dw, st.y_acc, st.dx_acc, st.dw_acc)
+    for t in outs:
+        t.fill_(7)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    want = [t.clone() for t in outs]
+    two = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    no_scratch = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+    no_scratch.ws_fwd = no_scratch.ws_bwd_data = None
+    for buffers, parts, n_reduce, shared in ((st._layer_buffers, B.STEP_FWD | two, reductions, together), (st._layer_buffers, two, reductions2, together2),
+                                             (no_scratch, B.STEP_FWD | two, 0, True), (no_scratch, two, 0, True)):
+        for t in outs:
+            t.fill_(7)
+        B.int8t_profile_start(None)
+        B.int8t_layer_step(st.desc, buffers, parts)
+        torch.cuda.synchronize()
+        launches = B.int8t_profile_stop()
+        assert launches.get("igemm_reduce_kernel", (0,))[0] == n_reduce and ("conv_trio_kernel" in launches) == shared
+        for i, t in enumerate(outs):
+            assert torch.equal(t, want[i]) or (parts == two and i in (0, 3))
