@@ -381,7 +381,8 @@ int8t_status int8t_layer_step(const int8t_conv_desc *desc, const int8t_layer_buf
  *                             reduction shares of the cost model's choice); query int8t_workspace_bytes() again
  *                             after selecting any of them
  * Depthwise layers are served by the library's own choice among their kernels only.  A variant that needs scratch (TILE_SPLIT) and is not
- * given enough falls back to TILE.
+ * given enough falls back to TILE.  A pass with a selected variant does not share a launch with others in int8t_layer_step,
+ * nor do they then with it: time the step's passes together before keeping a selection.
  */
 typedef enum {
     INT8T_VARIANT_AUTO = 0,

@@ -8,6 +8,8 @@ memory).  Used by the tests, the smoke check and the benchmark.
 """
 from __future__ import annotations
 
+import functools
+
 import numpy as np
 import torch
 
@@ -372,54 +374,72 @@ class LayerStep:
             self.ws = torch.empty(need, dtype=torch.uint8, device=self.dev)
             self._bind_calls()
 
+    def _time_us(self, call, reps: int) -> float:
+        """Microseconds per call(stream pointer) on the current stream."""
+        import time
+        sp = B.stream_pointer(None)
+        for _ in range(5):
+            call(sp)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(reps):
+            call(sp)
+        torch.cuda.synchronize()
+        return (time.perf_counter() - t0) / reps * 1e6
+
     def tune_kernels(self, reps: int = 30, verbose: bool = False) -> dict:
         """The per-layer choice of the convolution kernels "before training" (Suppl. "INT8 Convolution",
         last paragraph): for each of the three passes, times every kernel variant the library admits for
         this layer on the layer's own buffers and selects the fastest (int8t_conv_select_variant; the
         library keeps the choice per (pass, shape), so every layer of that shape in the process uses it).
+        A selected variant keeps its pass out of the launch that the passes of a step share -- all three on one stream, the
+        two backward ones in a step on two -- so the selection stays only if these are no slower with it
+        (3x3 on 512 channels at 7 x 7, batch 64: one pass 3 % faster by itself made the step 82 -> 111 us).
         All variants write identical results.  The code buffers must hold codes (run() once before).
         Returns {pass: (chosen variant name, {variant name: microseconds})}."""
-        import time
         if self.depthwise:
             return {}
-        out = {}
-        for name, op, call in (("fwd", B.OP_CONV_FWD, "_k_fwd"), ("bwd_data", B.OP_CONV_BWD_DATA, "_k_bwd_data"),
-                               ("bwd_weight", B.OP_CONV_BWD_WEIGHT, "_k_bwd_weight")):
-            if name == "bwd_data" and not self.input_grad:
-                continue
-            times = {}
-            sp = B.stream_pointer(None)
-            for v in range(len(B.VARIANT_NAMES)):
-                if not B.int8t_conv_variant_ok(op, self.desc, v):
-                    continue
-                B.int8t_conv_select_variant(op, self.desc, v)
-                if op == B.OP_CONV_BWD_WEIGHT:
-                    need = B.int8t_workspace_bytes(op, self.desc)      # depends on the variant's split count
-                    if need > self.ws.numel():
-                        self.ws = torch.empty(need, dtype=torch.uint8, device=self.dev)
-                        self._bind_calls()
-                fn = getattr(self, call)
-                for _ in range(5):
-                    fn(sp)
-                torch.cuda.synchronize()
-                t0 = time.perf_counter()
-                for _ in range(reps):
-                    fn(sp)
-                torch.cuda.synchronize()
-                times[v] = (time.perf_counter() - t0) / reps * 1e6
-            # the library's own choice stays unless another variant is at least 2 % faster (timing noise)
-            best = min(times, key=times.get)
-            if times[best] > 0.98 * times[B.VARIANT_AUTO]:
-                best = B.VARIANT_AUTO
-            B.int8t_conv_select_variant(op, self.desc, best)
+        chosen, times = {}, {}
+        ops = (("fwd", B.OP_CONV_FWD, "_k_fwd"), ("bwd_data", B.OP_CONV_BWD_DATA, "_k_bwd_data"),
+               ("bwd_weight", B.OP_CONV_BWD_WEIGHT, "_k_bwd_weight"))
+        ops = [o for o in ops if o[0] != "bwd_data" or self.input_grad]
+
+        def select(op, v):
+            B.int8t_conv_select_variant(op, self.desc, v)
             if op == B.OP_CONV_BWD_WEIGHT:
-                need = B.int8t_workspace_bytes(op, self.desc)
-                if need > self.ws.numel():
-                    self.ws = torch.empty(need, dtype=torch.uint8, device=self.dev)
-                    self._bind_calls()
-            out[name] = (B.VARIANT_NAMES[best], {B.VARIANT_NAMES[v]: round(t, 2) for v, t in times.items()})
-            if verbose:
-                print(self.L.name, name, out[name], flush=True)
+                self.refresh_scratch()          # depends on the variant's split count
+
+        for name, op, call in ops:
+            t = {}
+            for v in range(len(B.VARIANT_NAMES)):
+                if B.int8t_conv_variant_ok(op, self.desc, v):
+                    select(op, v)
+                    t[v] = self._time_us(getattr(self, call), reps)
+            # the library's own choice stays unless another variant is at least 2 % faster (timing noise)
+            best = min(t, key=t.get)
+            if t[best] > 0.98 * t[B.VARIANT_AUTO]:
+                best = B.VARIANT_AUTO
+            select(op, best)
+            chosen[name], times[name] = best, t
+        two = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+        two_streams = self._tuned_overlap if self._tuned_overlap is not None else two_stream_default(self.L)
+        for parts, shared in ((B.STEP_FWD | two, ops), (two, ops[1:])):
+            if not self.input_grad or self.fused_fwd or (parts == two and not two_streams):
+                continue
+            if all(chosen[name] == B.VARIANT_AUTO for name, _, _ in shared):
+                continue
+            call = functools.partial(self._k_step, parts, 0)
+            with_chosen = self._time_us(call, reps)
+            for _, op, _ in shared:
+                select(op, B.VARIANT_AUTO)
+            if with_chosen > self._time_us(call, reps):
+                chosen.update((name, B.VARIANT_AUTO) for name, _, _ in shared)
+            for name, op, _ in shared:
+                select(op, chosen[name])
+        out = {name: (B.VARIANT_NAMES[chosen[name]], {B.VARIANT_NAMES[v]: round(us, 2) for v, us in times[name].items()}) for name, _, _ in ops}
+        if verbose:
+            for name, v in out.items():
+                print(self.L.name, name, v, flush=True)
         return out
 
     # -- host copies of the code tensors in logical order (the library's own unpacking aid) ----------
