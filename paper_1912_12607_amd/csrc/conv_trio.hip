@@ -5,7 +5,7 @@
 // 3x3 on 256 channels at 14 x 14, batch 64, has 400 tiles of 128 x 64 per pass for 256 compute units, each about 36 stages
 // of 0.5 us.  Side by side the passes fill the compute units that each of them leaves idle.  The tiles are those of the
 // kernels that run the passes alone (igemm_dma_tile, wgrad_lines_tile); block ranges deal them: backward-weight first, whose
-// blocks live longest.  All forms take 64 KB of LDS at most, so two blocks fit a compute unit.
+// blocks live longest.  All forms take 72 KB of LDS at most, so two blocks fit a compute unit.
 #include <algorithm>
 
 #include "conv_igemm_dma.h"

@@ -12,7 +12,10 @@ constexpr int kWave = 64;            // CDNA wavefront width
 // Raises the wave's issue priority.  For the kernels that may run on a second stream beside the clip search: they wait for
 // memory most of the time and issue little, the search's waves issue all the time, and at equal priority the older waves
 // -- the search's -- go first (64 -> 256 1x1 layer at 56 x 56, batch 256: step 1233 -> 1124 us; 7x7 stem, batch 64: 365 ->
-// 336).  Without such a neighbour all waves of a compute unit have the same priority and nothing changes.
+// 336).  Alone on the chip all waves of such a kernel have the same priority and nothing changes.  In the shared launches of the
+// convolution passes forward and backward-data raise theirs and backward-weight does not; with none or all three raised
+// the three passes take between 4 % less and 4 % more, now one and now the other (3x3, 256 channels, 14 x 14, batch 64: 48.6 us as
+// it is, 46.8 none, 49.7 all; 5x5, 48 -> 64, 35 x 35, batch 32: 41.2, 42.7, 42.6; depthwise, 576 channels, 14 x 14: 43.2, 44.1, 43.9).
 __device__ __forceinline__ void raise_wave_priority() { __builtin_amdgcn_s_setprio(3); }
 
 // ---------------------------------------------------------------------------

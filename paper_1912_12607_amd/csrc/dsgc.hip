@@ -29,8 +29,10 @@
 // What an instruction costs here (one SIMD, many waves, cycles per wave instruction): 2 - 2.5 for fp32 add / multiply /
 // fused multiply-add, integer add, right shift and the bitwise operations on vector registers, 4 - 4.5 for
 // everything else (conversions, byte permutes, min / max, 24-bit and full integer multiplies, left shifts, and any of the first
-// group with a scalar operand) -- two pipes, of which one does everything.  About 400 instructions per 256 elements at
-// 2.5 cycles each, 16 MFMAs and their operand reads (a fifth of the time) are what the loop now consists of.
+// group with a scalar operand) -- two pipes, of which one does everything.  A wave's 256 elements take 380 vector instructions
+// where one of the four eights of candidates clips: 64 per eight (a multiply-add with its scalar scale and a convert per
+// element and candidate), 16 cheap ones more where it clips, 108 for the draw, the digits and the loop; with 16 MFMAs and
+// their operand reads (a fifth of the time) they are what the loop consists of.
 //
 // One block of 16 waves per compute unit: a compute unit issues from its oldest waves first, so of three equal
 // blocks that share one the first was done in half the time of the last, and the last ran alone (205 M elements: blocks
@@ -355,8 +357,8 @@ __global__ __launch_bounds__(DSGC_MAX_THREADS) void dsgc_sweep_kernel(
     // block's additions have been acknowledged before its ticket is drawn: every thread waits for
     // its outstanding memory operations, then the barrier.  (The memory model's own way to say this,
     // a device-scope release fence per thread in front of the barrier and an acquire fence in the
-    // last block, was measured: each release fence writes the whole L2 of its XCD back, 768 blocks
-    // of them stretch the sweep from 58 to 75 us with the GPU to itself and to 126 us beside another
+    // last block, was measured: each release fence writes the whole L2 of its XCD back; with 768 blocks of
+    // 256 threads they stretched the sweep from 58 to 75 us with the GPU to itself and to 126 us beside another
     // stream's kernels, whose dirty lines they flush.  What the wait below relies on is only that an
     // atomic's vmcnt decrement means it has been performed, which the return path of a device-scope
     // atomic guarantees.)

@@ -1,10 +1,12 @@
 """One conv-layer training step of the INT8 path as a sequence of C-ABI calls.
 
-Pure plumbing: allocates device buffers with torch, uploads the fp32 tensors once, and chains
-    quantize_batch(a, W) -> dsgc_clip(g_z) -> quantize(g_z; clip, stochastic, d_c)
+Pure plumbing: allocates device buffers with torch, uploads the fp32 tensors once, and runs
+    quantize(a, W) -> dsgc_clip(g_z) -> quantize(g_z; clip, stochastic, d_c)
     -> conv_fwd -> conv_bwd_data -> conv_bwd_weight
-on one stream with no host synchronisation in between (scales, clip and deviation stay in device
-memory).  Used by the tests, the smoke check and the benchmark.
+as one int8t_layer_step on one stream, or its parts on two, with no host synchronisation in between (scales, clip and
+deviation stay in device memory).  Used by the tests, the smoke check and the benchmark.  Here all of a layer's tensors are
+at hand at once, as in the benchmark's definition of a step; in a training program g_z comes after the forward passes
+of the layers behind, so a forward pass shares no launch with the backward ones there (see autograd.py).
 """
 from __future__ import annotations
 
@@ -140,17 +142,12 @@ class LayerStep:
         p, nb, lib, L = B._ptr, B._nbytes, B.lib, self.L
         n_y = self.dy.numel()
         self._items_xw = B._items(self.xw_items)
-        self._items_xwg = B._items(self.xw_items + [(self.dy, L.y_shape, self.act_kind, self.clip, self.dyq, self.sdy,
-                                                     B.ROUND_STOCHASTIC, 0)])
         self._k_xw = B.bind(lib.int8t_quantize_batch, 2, self._items_xw, p(self.ws_xw), nb(self.ws_xw))
-        self._k_xwg = B.bind(lib.int8t_quantize_batch, 3, self._items_xwg, p(self.ws_xw), nb(self.ws_xw))
         self._k_w = B.bind(lib.int8t_quantize, p(self.w), B._dims(L.w_shape), self.wgt_kind, None, B.ROUND_NEAREST_EVEN, 0,
                            p(self.wq), p(self.sw), None, p(self.ws_w), nb(self.ws_w))
         self._k_fwd_fused = B.bind(lib.int8t_conv_fwd_fused, C.byref(self.desc), p(self.x), None, p(self.wq), p(self.sw), p(self.y),
                                    p(self.y_acc), p(self.xq), p(self.sx), p(self.ws_x), nb(self.ws_x))
         self._k_prepare = B.bind(lib.int8t_dsgc_prepare, p(self.dy), n_y, p(self.ws_dy), nb(self.ws_dy))
-        self._k_xw_prepare = B.bind(lib.int8t_quantize_batch_prepare, 2, self._items_xw, p(self.ws_xw), nb(self.ws_xw),
-                                    p(self.dy), n_y, p(self.ws_dy), nb(self.ws_dy))
         d = C.byref(self.desc)
         self._k_fwd = B.bind(lib.int8t_conv_fwd, d, p(self.xq), p(self.sx), p(self.wq), p(self.sw), p(self.y), p(self.y_acc),
                              p(self.ws_fwd), nb(self.ws_fwd))
