@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, co
 // rule loses 1.3 % on average, 19 % at most.  The two backward passes alone (a forward pass ran earlier; 104 random layers:
 // 7x1, 76 -> 216 channels, 65 x 65, batch 3: 33.0, 21.7, 22.6): up to 3000 such tiles, the wider tile from twice the longest
 // reduction on; loses 1.9 % on average, 13 % at most.  Layers whose backward-weight works on image granules (narrow 1x1 layers,
-// 3x5 and the like; 100 random ones: 1x1, 64 channels, 56 x 56, batch 2, 18.7, 10.1, 9.9; 96 -> 576 at 14 x 14, batch 64,
+// 2x2 and the like; 100 random ones: 1x1, 64 channels, 56 x 56, batch 2, 18.7, 10.1, 9.9; 96 -> 576 at 14 x 14, batch 64,
 // 32.9, 25.0, 25.5; 24 -> 144 at 56 x 56, 53.9, 71.0, 57.9): up to 3000 tiles as well.
 //
 // Passes that alone run as a split reduction (few tiles, long reductions; with the caller's scratch) have one tile's whole chain of

@@ -125,21 +125,23 @@ def test_backward_weight_five_taps(shape):
 # The three passes of a step in one launch: both tile widths, 1, 3, 5 and 7 taps along either axis, planes of whole 16-byte
 # groups and others, ragged rows and columns, backward-weight grids that are no multiple of the 8 XCDs.  Against the three
 # calls one by one, which the other tests hold against the oracle, bit for bit -- and that the launch is the one under test.
-@pytest.mark.parametrize("shape,together", [((2, 16, 16, 16, 32, 3, 3), True), ((64, 256, 14, 14, 256, 3, 3), True), ((32, 48, 35, 35, 64, 5, 5), True),
-                                            ((3, 130, 17, 17, 200, 1, 7), True), ((5, 70, 9, 11, 129, 7, 1), True), ((1, 300, 1, 1, 65, 1, 1), True),
-                                            ((64, 40, 28, 28, 500, 1, 3), True), ((64, 1000, 14, 14, 260, 1, 1), True), ((16, 64, 56, 56, 64, 3, 3), True),
-                                            ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True),
-                                            # backward-weight on image granules
-                                            ((64, 96, 14, 14, 576, 1, 1), True), ((3, 50, 9, 11, 30, 1, 1), True), ((5, 33, 12, 8, 40, 5, 3), True),
-                                            ((64, 24, 56, 56, 144, 1, 1), False),
-                                            # depthwise: planes alone and several to a block, rows of whole dwords and others, channel
-                                            # groups; planes that backward-weight does not prefetch
-                                            ((3, 5, 56, 56, 5, 3, 3), True), ((2, 6, 40, 64, 6, 3, 3), True), ((5, 32, 28, 28, 32, 3, 3), True),
-                                            ((3, 48, 14, 14, 48, 3, 3), True), ((9, 64, 7, 7, 64, 3, 3), True), ((1, 16, 16, 16, 16, 3, 3), True),
-                                            ((2, 3, 112, 112, 3, 3, 3), False), ((2, 5, 35, 35, 5, 3, 3), False)])
-def test_three_passes_in_one_launch(shape, together):
+TOGETHER_DENSE = [((2, 16, 16, 16, 32, 3, 3), True), ((64, 256, 14, 14, 256, 3, 3), True), ((32, 48, 35, 35, 64, 5, 5), True),
+                  ((3, 130, 17, 17, 200, 1, 7), True), ((5, 70, 9, 11, 129, 7, 1), True), ((1, 300, 1, 1, 65, 1, 1), True),
+                  ((64, 40, 28, 28, 500, 1, 3), True), ((64, 1000, 14, 14, 260, 1, 1), True), ((16, 64, 56, 56, 64, 3, 3), True),
+                  ((48, 64, 56, 56, 64, 3, 3), False), ((64, 768, 17, 17, 768, 1, 7), False), ((2, 64, 9, 9, 64, 3, 5), True),
+                  ((64, 96, 14, 14, 576, 1, 1), True), ((3, 50, 9, 11, 30, 1, 1), True), ((5, 33, 12, 8, 40, 5, 3), True),
+                  ((64, 24, 56, 56, 144, 1, 1), False),
+                  # backward-weight on image granules, one of several taps per block (and the narrow 1x1 layers above)
+                  ((5, 33, 12, 8, 40, 4, 4), True), ((3, 40, 9, 11, 50, 2, 2), True), ((2, 24, 10, 19, 72, 1, 9), True)]
+# planes alone and several to a block, rows of whole dwords and others, channel groups; planes that backward-weight does not prefetch
+TOGETHER_DEPTHWISE = [((3, 5, 56, 56, 5, 3, 3), True), ((2, 6, 40, 64, 6, 3, 3), True), ((5, 32, 28, 28, 32, 3, 3), True),
+                      ((3, 48, 14, 14, 48, 3, 3), True), ((9, 64, 7, 7, 64, 3, 3), True), ((1, 16, 16, 16, 16, 3, 3), True),
+                      ((2, 3, 112, 112, 3, 3, 3), False), ((2, 5, 35, 35, 5, 3, 3), False)]
+
+
+@pytest.mark.parametrize("shape,together,depthwise", [(*c, False) for c in TOGETHER_DENSE] + [(*c, True) for c in TOGETHER_DEPTHWISE])
+def test_three_passes_in_one_launch(shape, together, depthwise):
     N, C, H, W, K, R, S = shape
-    depthwise = C == K and (R, S) == (3, 3) and (C != 64 or H == 7) and C < 256
     L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=C if depthwise else 1)
     st = LayerStep(L, keep_acc=True, requantize_deviation=False)
     g = torch.Generator(device=DEV).manual_seed(3)
@@ -240,3 +242,64 @@ def test_split_reductions_and_the_shared_launch(shape, reductions, together, red
         assert launches.get("igemm_reduce_kernel", (0,))[0] == n_reduce and ("conv_trio_kernel" in launches) == shared
         for i, t in enumerate(outs):
             assert torch.equal(t, want[i]) or (parts == two and i in (0, 3))
+
+
+def small_step(depthwise, requantize_deviation=False):
+    L = inputs.Layer("layer", 3, 32, 14, 14, 32, 3, 3, stride=(1, 1), pad=(1, 1), groups=32 if depthwise else 1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=requantize_deviation)
+    g = torch.Generator(device=DEV).manual_seed(6)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    torch.cuda.synchronize()
+    return st
+
+
+# A step dealt out over several calls, each with the pointers of its part alone: the tensors of the step in one call.
+@pytest.mark.parametrize("requantize_deviation", [False, True])
+@pytest.mark.parametrize("depthwise", [False, True])
+def test_layer_step_parts_one_by_one(depthwise, requantize_deviation):
+    st = small_step(depthwise, requantize_deviation)
+    outs = ["xq", "wq", "dyq", "sx", "sw", "sdy", "clip", "dev_search", "dev_all", "y", "dx", "dw", "y_acc", "dx_acc", "dw_acc"]
+    outs += ["dev_final"] if requantize_deviation else []
+    want = [getattr(st, n).clone() for n in outs]
+    for n in outs:
+        getattr(st, n).fill_(7)
+    parts = [(B.STEP_ABSMAX | B.STEP_PREPARE, "x w dy ws_quant ws_dy"), (B.STEP_SEARCH, "dy ratios clip dev_search dev_all ws_dy"),
+             (B.STEP_QUANT_XW, "x w xq wq sx sw ws_quant"),
+             (B.STEP_QUANT_G, "dy clip dyq sdy" + (" dev_final ws_dy" if requantize_deviation else "")),
+             (B.STEP_FWD, "xq wq sx sw y y_acc"), (B.STEP_BWD_DATA, "dyq wq sdy sw dx dx_acc"),
+             (B.STEP_BWD_WEIGHT, "xq dyq sx sdy dw dw_acc ws_bwd_weight")]
+    tensors = {"ws_quant": st.ws_xw, "ws_bwd_weight": st.ws}
+    for part, names in parts:
+        buf = B.layer_buffers(n_cand=st.n_cand, **{n: tensors.get(n, getattr(st, n, None)) for n in names.split()})
+        B.int8t_layer_step(st.desc, buf, part, 5)
+    torch.cuda.synchronize()
+    for n, w in zip(outs, want):
+        assert torch.equal(getattr(st, n), w), n
+
+
+# Results that overlap what another pass of the step writes: legal one after the other, so the passes do not share a launch.
+@pytest.mark.parametrize("depthwise", [False, True])
+@pytest.mark.parametrize("alias", ["dx over y", "dw over y", "scratch over y"])
+def test_overlapping_results_run_one_by_one(depthwise, alias):
+    st = small_step(depthwise)
+    want = [st.dx.clone(), st.dw.clone()]
+    st.y.fill_(7)
+    buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+    dx, dw = st.dx, st.dw
+    if alias == "dx over y":
+        buf.dx, dx = buf.y, st.y
+    elif alias == "dw over y":
+        buf.dw, dw = buf.y, st.y.view(-1)[:st.dw.numel()].view_as(st.dw)
+    else:
+        st.y_acc = torch.zeros(max(st.y_acc.numel(), st.ws.numel() // 4 + 4), dtype=torch.int32, device=DEV)
+        buf.y_acc = buf.ws_bwd_weight = st.y_acc.data_ptr()
+    for t in (st.dx, st.dw):
+        t.fill_(7)
+    B.int8t_profile_start("dw_trio_kernel" if depthwise else "conv_trio_kernel")
+    B.int8t_layer_step(st.desc, buf, B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT)
+    torch.cuda.synchronize()
+    assert not B.int8t_profile_stop()
+    assert torch.equal(dx, want[0]) and torch.equal(dw, want[1])
