@@ -39,7 +39,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 INT8_MFMA_PEAK_TOPS = 5000.0
-# plain (unpacked) vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one operation per lane per issue
+# plain (unpacked) vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, a 64-lane instruction every four cycles (an add,
+# multiply-add, right shift or bitwise operation on vector registers alone takes two: half an operation)
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 # STORED figures, not measured by this run: HBM bytes per launch from rocprofv3 counter runs
@@ -76,10 +77,11 @@ def pass_algorithmic(L, n_cand):
         "absmax_xw": (4 * (n_x + n_w), 0, None),                 # one read of a and W
         "quantize_xw": (5 * n_x + 6 * n_w, 0, None),             # fp32 read + code write (W: two layouts)
         "absmax_gz": (4 * n_y, 0, None),                         # max|g_z| and sum g_z^2, one read
-        # One read of g_z.  Vector-ALU work of the sweep: 2.5 operations per element and candidate (round-down
-        # fused multiply-add, convert-and-pack, a shift and a mask per four) + 31 per element and 32-candidate
-        # chunk (draw, fixed point, digit planes, LDS traffic); the products and sums themselves run on the matrix cores.
-        "dsgc_search": (4 * n_y, (2.5 * n_cand + 31 * ((n_cand + 31) // 32)) * n_y, "valu"),
+        # One read of g_z.  Vector-ALU work of the sweep: 2 operations per element and candidate (multiply-add with a scalar
+        # scale, convert-and-pack) and per element and 32-candidate chunk 2 where one of the four eights of candidates clips
+        # (the default grid nearly always) and 20 for draw, fixed point, digit planes and the loop; the products and sums
+        # themselves run on the matrix cores.
+        "dsgc_search": (4 * n_y, (2 * n_cand + 22 * ((n_cand + 31) // 32)) * n_y, "valu"),
         "quantize_gz": (5 * n_y, 0, None),
         "fwd": (n_x + n_w + 4 * n_y, 2 * macs, "mfma"),
         "bwd_data": (n_y + n_w + 4 * n_x, 2 * macs, "mfma"),
@@ -311,6 +313,12 @@ def main():
     t_step, dom_us = timed_steps(sets, args.steps, 20, dom, every)
     tops = 6 * L.macs / t_step / 1e12
 
+    two_streams = overlap is None and period == 1 and two_stream_default(L)
+    if dom in ("conv_trio_kernel", "dw_trio_kernel"):
+        # one launch for the passes of a step, the backward ones in the two-stream step (pass_table() runs each by itself)
+        alg = pass_algorithmic(L, n_cand)
+        shared = [alg[p] for p in ("bwd_data", "bwd_weight") + (() if two_streams else ("fwd",))]
+        kernel_alg[dom] = [sum(a[0] for a in shared), sum(a[1] for a in shared), "mfma", 1]
     nbytes, ops, kind, launches = kernel_alg.get(dom, [0, 0, None, per_kernel[dom][0]])
     launches = launches or per_kernel[dom][0]
     # per launch, as the duration is: the kernel's algorithmic work of the step / its launches per step
@@ -323,8 +331,7 @@ def main():
     roof["us_per_launch"] = dom_us
     roof["algorithmic_bytes_per_launch"] = nbytes / launches
     roof["algorithmic_ops_per_launch"] = ops / launches
-    two_streams = overlap is None and period == 1 and two_stream_default(L)
-    if two_streams:
+    if two_streams and not dom.endswith("trio_kernel"):
         # In the timed region the kernel may share the compute units with the second stream's kernels;
         # what it does with the machine to itself comes from the untimed one-stream pass.
         roof["us_per_launch_one_stream"] = per_kernel[dom][1]
