@@ -735,6 +735,31 @@ static bool disjoint_results(const int8t_conv_desc* d, const Geo& g, const int8t
     return true;
 }
 
+// The same for quantization and passes side by side: what they write overlaps nothing that they read or write.  x: codes of a and
+// W and the forward pass, dy: codes of g_z and the backward passes.
+static bool disjoint_step(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool x, bool dy) {
+    struct Range { const void* p; size_t n; bool written; };
+    const size_t nx = (size_t)d->N * d->C * d->H * d->W * 4, ny = (size_t)d->N * d->K * g.P * g.Q * 4;
+    const int Cg = d->C / d->groups;
+    const size_t nw = (size_t)d->K * Cg * d->R * d->S * 4;
+    const int8t_kind ak = g.depthwise ? INT8T_ACT_PLANAR : INT8T_ACT, wk = g.depthwise ? INT8T_WGT_PLANAR : INT8T_WGT;
+    const int xd[4] = {d->N, d->C, d->H, d->W}, wd[4] = {d->K, Cg, d->R, d->S}, yd[4] = {d->N, d->K, g.P, g.Q};
+    const Range r[] = {{x ? b->x : nullptr, nx, false}, {x ? b->w : nullptr, nw, false}, {x ? b->ws_quant : nullptr, b->ws_quant_bytes, false},
+                       {dy ? b->dy : nullptr, ny, false}, {dy ? b->clip : nullptr, 4, false},
+                       {b->xq, int8t_code_bytes(xd, ak), x}, {b->wq, int8t_code_bytes(wd, wk), x}, {b->sx, 4, x}, {b->sw, 4, x},
+                       {x ? b->y : nullptr, ny, true}, {x ? b->y_acc : nullptr, ny, true},
+                       {dy ? b->dyq : nullptr, int8t_code_bytes(yd, ak), true}, {dy ? b->sdy : nullptr, 4, true},
+                       {dy ? b->dx : nullptr, nx, true}, {dy ? b->dx_acc : nullptr, nx, true}, {dy ? b->dw : nullptr, nw, true},
+                       {dy ? b->dw_acc : nullptr, nw, true}, {dy ? b->ws_bwd_weight : nullptr, b->ws_bwd_weight_bytes, true}};
+    constexpr int count = sizeof(r) / sizeof(r[0]);
+    for (int i = 0; i < count; ++i)
+        for (int j = i + 1; j < count; ++j) {
+            const uintptr_t p = (uintptr_t)r[i].p, q = (uintptr_t)r[j].p;
+            if ((r[i].written || r[j].written) && p && q && p < q + r[j].n && q < p + r[i].n) return false;
+        }
+    return true;
+}
+
 int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, void* stream) {
     Geo g;
     int8t_status s = desc_ok(desc, &g);
@@ -793,6 +818,12 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         !aligned16(b->ws_fwd) || !aligned16(b->ws_bwd_data))
         return INT8T_ERR_ARG;
     if (bwd_weight && b->ws_bwd_weight_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
+    // Depthwise layers whose codes are formed in this call: quantization and passes in one launch (conv_dw_fused.hip), where nothing
+    // overlaps what another part of the call reads or writes.
+    const bool dw_x = quant_xw && fwd, dw_g = quant_g && !b->dev_final && bwd_data && bwd_weight;
+    const bool dw_fused = g.depthwise && desc->R == 3 && desc->S == 3 && desc->stride_h == 1 && desc->stride_w == 1 && desc->pad_h == 1 &&
+                          desc->pad_w == 1 && (dw_x || dw_g) && dw_x == (quant_xw || fwd) && dw_g == (quant_g || bwd_data || bwd_weight) &&
+                          disjoint_step(desc, g, b, dw_x, dw_g);
     // ---- launches
     hipStream_t st = (hipStream_t)stream;
     if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
@@ -800,6 +831,29 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
         s = int8t_dsgc_search(b->dy, n_y, b->ratios, b->n_cand, INT8T_ROUND_STOCHASTIC, seed, b->clip, b->dev_search, b->dev_all, b->ws_dy,
                               b->ws_dy_bytes, stream);
         if (s != INT8T_OK) return s;
+    }
+    if (dw_fused) {
+        DwFused f{};
+        f.N = desc->N; f.C = desc->C; f.H = desc->H; f.W = desc->W;
+        f.xq = b->xq; f.wq = b->wq; f.gq = b->dyq;
+        f.sx = b->sx; f.sw = b->sw; f.sg = b->sdy;
+        if (dw_x) {
+            size_t nx = 0, nw = 0;
+            (void)dims_ok(xd, &nx);
+            (void)dims_ok(wd, &nw);
+            f.x = b->x; f.w = b->w; f.y = b->y; f.y_acc = b->y_acc;
+            f.part_x = batch_partials(b->ws_quant, 0); f.np_x = absmax_blocks(nx);
+            f.part_w = batch_partials(b->ws_quant, 1); f.np_w = absmax_blocks(nw);
+        }
+        DwArgs w = dw_wgrad_args(desc, g);
+        if (dw_g) {
+            f.g = b->dy; f.clip = b->clip; f.dx = b->dx; f.dx_acc = b->dx_acc;
+            f.key_x = seed_key_x(seed); f.key_a = seed_key_a(seed);
+            f.partial = w.partial = (int32_t*)b->ws_bwd_weight;
+            w.sa = b->sx; w.sb = b->sdy; w.out = b->dw; w.acc = b->dw_acc;
+        }
+        hipError_t e = hipSuccess;
+        if (launch_dw_fused(f, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     if (quant_xw) {
         s = batch_codes(g_in_batch ? 3 : 2, it, b->ws_quant, st);

@@ -1034,7 +1034,7 @@ static int dw_group_images(const DwArgs& a, size_t ldsg) {
     return ni < 1 ? 1 : ni;
 }
 
-static hipError_t launch_dw_wgrad_reduce(const DwArgs& a, hipStream_t st) {
+hipError_t launch_dw_wgrad_reduce(const DwArgs& a, hipStream_t st) {
     const int total = a.C * a.R * a.S;
     KernelTimer kt(KID_DW_WGRAD_REDUCE, st);
     launch_timed(kt, dw_wgrad_reduce_kernel, dim3((total * 16 + 255) / 256), dim3(256), 0, st, a);

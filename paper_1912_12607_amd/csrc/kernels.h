@@ -281,6 +281,22 @@ struct DwArgs {
     int stride_h, stride_w, pad_h, pad_w;
     int dgrad;
 };
+// conv_dw_fused.hip: quantization and convolutions of a 3x3 depthwise layer, from the fp32 tensors (x: codes of a and W and the
+// forward pass; g: codes of g_z and the backward passes; either may be nullptr, the codes are inputs then)
+struct DwFused {
+    const float *x, *w, *g;
+    int8_t *xq, *wq, *gq;
+    const float *part_x, *part_w;    // absmax partials of a and W
+    int np_x, np_w;
+    const float* clip;               // of g_z
+    uint32_t key_x, key_a;
+    float *sx, *sw, *sg;
+    float *y, *dx;
+    int32_t *y_acc, *dx_acc;         // nullable
+    int32_t* partial;                // [shares][C][9]
+    int N, C, H, W;
+    int cg, slot, shares, pitch;     // launch shape, launch_dw_fused()
+};
 int dw_threads(int OH, int OW, bool quads);       // block size by plane size (quads: four results per task)
 int dw_wgrad_threads(int P, int Q, int R, int S, int stride_h, int stride_w);
 int dw_wgrad_chunks(int N, int C, int threads);
@@ -289,6 +305,9 @@ void dw_wgrad_shape(int N, int C, int IH, int IW, int P, int Q, int R, int S, in
                     int* threads, int* chunks, int* cg);
 hipError_t launch_dw_conv(const DwArgs& a, hipStream_t st);
 hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st);
+hipError_t launch_dw_wgrad_reduce(const DwArgs& a, hipStream_t st);
+// false: not a layer for it, nothing launched
+bool launch_dw_fused(const DwFused& a, const DwArgs& wgrad, hipStream_t st, hipError_t* err);
 // the three passes of a layer (fwd: nullptr where only the two backward ones run) in one launch; false: not a layer for it,
 // nothing launched
 bool launch_dw_trio(const DwArgs* fwd, const DwArgs& bwd, const DwArgs& wgrad, hipStream_t st, hipError_t* err);

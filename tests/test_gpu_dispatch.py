@@ -303,3 +303,48 @@ def test_overlapping_results_run_one_by_one(depthwise, alias):
     torch.cuda.synchronize()
     assert not B.int8t_profile_stop()
     assert torch.equal(dx, want[0]) and torch.equal(dw, want[1])
+
+
+# Depthwise layers that form their codes in the launch of the passes, whole and in halves (a and W with the forward pass, g_z with
+# the backward ones), against the calls one by one, bit for bit: one, two and four chunks of a plane per thread, channel groups with
+# rows of whole dwords and others, elements that are no number.  What may not overlap in one launch does in the last form:
+# the input gradient over the output gradient, which is legal one after the other.
+@pytest.mark.parametrize("form", ["whole", "halves", "dx over dy"])
+@pytest.mark.parametrize("shape", [(3, 5, 28, 28), (2, 3, 32, 32), (5, 2, 36, 32), (3, 4, 56, 56), (9, 2, 64, 64), (9, 64, 7, 7), (5, 32, 14, 14),
+                                   (3, 16, 5, 7), (4, 32, 6, 4), (7, 8, 10, 6), (70, 16, 8, 8)])
+def test_depthwise_codes_and_passes_in_one_launch(shape, form):
+    N, C, H, W = shape
+    L = inputs.Layer("layer", N, C, H, W, C, 3, 3, stride=(1, 1), pad=(1, 1), groups=C)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(8)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.x.view(-1)[5] = st.dy.view(-1)[7] = float("nan")
+    dy = st.dy.clone()
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    front = B.STEP_ABSMAX | B.STEP_PREPARE | B.STEP_SEARCH
+    fwd, bwd = B.STEP_QUANT_XW | B.STEP_FWD, B.STEP_QUANT_G | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    outs = ["xq", "wq", "dyq", "sx", "sw", "sdy", "clip", "y", "dx", "dw", "y_acc", "dx_acc", "dw_acc"]
+
+    def result(calls, buf):
+        for n in outs:
+            getattr(st, n).fill_(7)
+        st.dy.copy_(dy)
+        for parts in calls:
+            B.int8t_layer_step(st.desc, buf, parts, 5)
+        torch.cuda.synchronize()
+        return [getattr(st, n).clone() for n in outs]
+
+    want = result([front] + [1 << i for i in range(3, 8)], st._layer_buffers)
+    buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+    if form == "dx over dy":
+        buf.dx = buf.dy
+    B.int8t_profile_start("dw_trio_kernel")
+    got = result([front | fwd, bwd] if form == "halves" else [front | fwd | bwd], buf)
+    launches = B.int8t_profile_stop()
+    if form == "dx over dy":
+        got[outs.index("dx")] = st.dy.clone()
+    else:
+        assert launches["dw_trio_kernel"][0] == (2 if form == "halves" else 1)
+    for n, a, b in zip(outs, got, want):
+        assert torch.equal(a, b), n
