@@ -181,8 +181,85 @@ __host__ __device__ inline int quant_act_nsub(int HW) {
     if ((HW * 4) % 128 == 0 || HW > 4 * QA_PIX) return 1;
     return (HW + QA_PIX - 1) / QA_PIX;
 }
+// 1 x 1 images whose channels need padding (the output gradient of a fully connected layer): the tensor is a matrix of N rows, and
+// a thread takes four channels of a row, padding included, up to QA_ROW_LOADS times.  As tiles
+// of 64 pixels the 256 x 1000 gradient of a classifier was 4096 blocks of 64 elements, 17.1 us; now 4.0.
+constexpr int QA_ROW_LOADS = 2;
+__host__ __device__ inline bool quant_act_rows(int HW) { return HW == 1; }
 __host__ __device__ inline int quant_act_gx(int Cp, int HW) {
     return Cp == 16 ? (HW + QA_NARROW_PIX - 1) / QA_NARROW_PIX : (HW + QA_PIX * quant_act_nsub(HW) - 1) / (QA_PIX * quant_act_nsub(HW));
+}
+// grid of the pass over a tensor of N images
+static void quant_act_grid(int N, int Cp, int HW, int* gx, int* gy, int* gz) {
+    if (quant_act_rows(HW)) {
+        const long long quads = (long long)N * (Cp / 4);
+        // several quads per thread from 512 blocks on
+        const int per = 256 * (quads >= 512ll * 256 * QA_ROW_LOADS ? QA_ROW_LOADS : 1);
+        *gx = (int)((quads + per - 1) / per); *gy = 1; *gz = 1;
+    } else {
+        *gx = quant_act_gx(Cp, HW); *gy = (Cp + QA_CH - 1) / QA_CH; *gz = N;
+    }
+}
+
+template <bool STOCH, bool DEV>
+__device__ __forceinline__ void quantize_rows_body(
+    const float* __restrict__ x, int N, int C, int Cp, const float* __restrict__ clip, const float* __restrict__ absmax_part, int nparts,
+    uint32_t seed_lo, uint32_t seed_hi_mul, int8_t* __restrict__ q, float* __restrict__ scale_out, DevPartial* __restrict__ devpart,
+    const int bx, const int gx, float* lds4) {
+    const float clip_in = clip ? *clip : 0.0f;
+    if (!clip) absmax_partials_begin(absmax_part, nparts, lds4);      // dealt with ahead of the elements
+    const uint32_t per_row = (uint32_t)Cp >> 2, quads = (uint32_t)N * per_row, stride = (uint32_t)gx * 256u;
+    uint32_t t0 = (uint32_t)bx * 256u + threadIdx.x;
+    float v[QA_ROW_LOADS][4];
+    uint32_t first[QA_ROW_LOADS];         // logical index of the first channel
+    int left[QA_ROW_LOADS];               // channels of the row from there on
+    auto fetch = [&]() {                  // (unconditional loads; what is not there is zeroed below)
+#pragma unroll
+        for (int u = 0; u < QA_ROW_LOADS; ++u) {
+            const uint32_t t = t0 + u * stride, row = t / per_row, c = (t - row * per_row) * 4u;
+            left[u] = t < quads ? C - (int)c : 0;
+            first[u] = row * (uint32_t)C + c;
+            if ((C & 3) == 0) {           // (uniform) rows start on 16 bytes
+                const float4 f = *reinterpret_cast<const float4*>(x + (left[u] > 0 ? first[u] : 0u));
+                v[u][0] = f.x; v[u][1] = f.y; v[u][2] = f.z; v[u][3] = f.w;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[u][k] = x[k < left[u] ? first[u] + k : 0u];
+            }
+        }
+    };
+    fetch();
+    float cval = clip_in;
+    if (!clip) cval = absmax_partials_end(lds4);
+    float inv = inv_scale_of(cval), sc = scale_of(cval);
+    if (STOCH) {
+        inv = __fmul_rn(inv, kTwo24);        // the scaled value carries 24 fraction bits
+        fp32_round_down_mode(inv, sc);
+    }
+    if (bx == 0 && threadIdx.x == 0) *scale_out = sc;
+    double A = 0.0, G = 0.0;
+    unsigned long long B = 0;
+    while (t0 < quads) {
+#pragma unroll
+        for (int u = 0; u < QA_ROW_LOADS; ++u) {
+            int code[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float g32 = k < left[u] ? v[u][k] : 0.0f;
+                code[k] = quantize_one<STOCH>(g32, inv, seed_lo, seed_hi_mul, first[u] + k);
+                if (DEV) {
+                    const double g = (double)g32;
+                    A = fma(g, (double)code[k], A);
+                    G = fma(g, g, G);
+                    B += (unsigned)(code[k] * code[k]);
+                }
+            }
+            if (t0 + u * stride < quads) reinterpret_cast<uint32_t*>(q)[t0 + u * stride] = pack4(code[0], code[1], code[2], code[3]);
+        }
+        t0 += QA_ROW_LOADS * stride;
+        if (t0 < quads) fetch();
+    }
+    if (DEV) block_store_devpartial(A, G, B, devpart + bx);
 }
 
 // VEC: H*W is a multiple of 4, so a thread can fetch four consecutive pixels of a channel with one
@@ -190,12 +267,16 @@ __host__ __device__ inline int quant_act_gx(int Cp, int HW) {
 // writes one dword (4 channels) per pixel to the LDS tile.  Otherwise one pixel per lane, 4-byte loads.
 template <bool STOCH, bool DEV, bool VEC>
 __device__ __forceinline__ void quantize_act_body(
-    const float* __restrict__ x, int C, int Cp, int HW, const float* __restrict__ clip,
+    const float* __restrict__ x, int N, int C, int Cp, int HW, const float* __restrict__ clip,
     const float* __restrict__ absmax_part, int nparts, uint32_t seed_lo, uint32_t seed_hi_mul,
     int8_t* __restrict__ q, float* __restrict__ scale_out, DevPartial* __restrict__ devpart, const VBlock vb,
     float* lds4, uint32_t (*tile)[QA_CH / 4 + 1]) {
     // lds4: 4 floats, tile: [QA_PIX][QA_CH / 4 + 1] dwords of LDS supplied by the kernel
     const int n = vb.z;
+    if (!VEC && quant_act_rows(HW)) {
+        quantize_rows_body<STOCH, DEV>(x, N, C, Cp, clip, absmax_part, nparts, seed_lo, seed_hi_mul, q, scale_out, devpart, vb.x, vb.gx, lds4);
+        return;
+    }
     if (Cp == 16) {
         const int p = vb.x * QA_NARROW_PIX + (int)threadIdx.x;
         const bool pv = p < HW;
@@ -370,32 +451,36 @@ __device__ __forceinline__ void quantize_act_body(
 
 template <bool STOCH, bool DEV, bool VEC>
 __global__ __launch_bounds__(256) void quantize_act_kernel(
-    const float* __restrict__ x, int C, int Cp, int HW, const float* __restrict__ clip,
+    const float* __restrict__ x, int N, int C, int Cp, int HW, const float* __restrict__ clip,
     const float* __restrict__ absmax_part, int nparts, uint32_t seed_lo, uint32_t seed_hi_mul,
     int8_t* __restrict__ q, float* __restrict__ scale_out, DevPartial* __restrict__ devpart) {
     __shared__ float lds4[4];
     __shared__ uint32_t tile[QA_PIX][QA_CH / 4 + 1];
     const VBlock vb = {(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
-    quantize_act_body<STOCH, DEV, VEC>(x, C, Cp, HW, clip, absmax_part, nparts, seed_lo, seed_hi_mul, q, scale_out,
+    quantize_act_body<STOCH, DEV, VEC>(x, N, C, Cp, HW, clip, absmax_part, nparts, seed_lo, seed_hi_mul, q, scale_out,
                                        devpart, vb, lds4, tile);
 }
 
 int quant_blocks_act(int N, int Cp, int HW) {
-    return quant_act_gx(Cp, HW) * ((Cp + QA_CH - 1) / QA_CH) * N;
+    int gx, gy, gz;
+    quant_act_grid(N, Cp, HW, &gx, &gy, &gz);
+    return gx * gy * gz;
 }
 
 hipError_t launch_quantize_act(const QuantArgs& a, hipStream_t st) {
     const int N = a.d0, C = a.d1, HW = a.d2 * a.d3, Cp = (C + 15) & ~15;
-    dim3 grid(quant_act_gx(Cp, HW), (Cp + QA_CH - 1) / QA_CH, N);
+    int gx, gy, gz;
+    quant_act_grid(N, Cp, HW, &gx, &gy, &gz);
+    const dim3 grid(gx, gy, gz);
     const uint32_t slo = seed_key_x(a.seed), shi = seed_key_a(a.seed);
     KernelTimer kt(KID_QUANTIZE_ACT, st);
 #define LAUNCH(ST, DV)                                                                                      \
     do {                                                                                                    \
         if ((HW & 3) == 0)                                                                                  \
-            launch_timed(kt, (quantize_act_kernel<ST, DV, true>), grid, dim3(256), 0, st, a.x, C, Cp, HW, \
+            launch_timed(kt, (quantize_act_kernel<ST, DV, true>), grid, dim3(256), 0, st, a.x, N, C, Cp, HW, \
                                a.clip, a.absmax_part, a.nparts, slo, shi, a.q, a.scale, a.devpart);         \
         else                                                                                                \
-            launch_timed(kt, (quantize_act_kernel<ST, DV, false>), grid, dim3(256), 0, st, a.x, C, Cp, HW, \
+            launch_timed(kt, (quantize_act_kernel<ST, DV, false>), grid, dim3(256), 0, st, a.x, N, C, Cp, HW, \
                                a.clip, a.absmax_part, a.nparts, slo, shi, a.q, a.scale, a.devpart);         \
     } while (0)
     if (a.stochastic) {
@@ -663,9 +748,13 @@ __global__ __launch_bounds__(256) void quantize_wgt_kernel(
 // serves the tensor whose block range holds it and runs that tensor's ordinary pass.
 // ---------------------------------------------------------------------------------------------
 // ANYSTOCH: some item rounds stochastically (Eq.3).  The round-to-nearest launch of a layer's a and
-// W is a kernel of its own, so that it keeps its register count beside the clip search.
-template <bool ANYSTOCH>
-__global__ __launch_bounds__(256) void quantize_batch_kernel(const QuantBatch b) {
+// W is a kernel of its own, so that it keeps its register count beside the clip search.  RAGGED: some activation tensor has
+// planes of no whole 16-byte groups; those passes need more registers, which the launch without them does not pay for (77 and 79
+// against 40 and 43).  Four blocks per compute unit are enough where nothing runs beside the kernel: with seven, 14 x 14 planes
+// of 1024 channels, batch 128, take 34.1 us instead of 33.0 (beside the clip search they would take 21 instead of 13 us at
+// 12.8 M elements, so the launch of a and W alone keeps its occupancy).
+template <bool ANYSTOCH, bool RAGGED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH && !RAGGED ? 4 : 8))) void quantize_batch_kernel(const QuantBatch b) {
     raise_wave_priority();
     // one LDS area for whichever pass this block runs, sized by the host for the tensors of this launch
     // (a 3x3 weight tensor needs 2.3 KB of tile, not the 16 KB of the largest case: the kernel then fits
@@ -684,11 +773,11 @@ __global__ __launch_bounds__(256) void quantize_batch_kernel(const QuantBatch b)
     const bool st = ANYSTOCH && t.stoch;          // block-uniform
     if (t.kind == 0) {          // activations, N,C,H,W -> N,H,W,Cp
         const int HW = t.d2 * t.d3, Cp = (t.d1 + 15) & ~15;
-#define ACT(STv, VECv) quantize_act_body<STv, false, VECv>(t.x, t.d1, Cp, HW, t.clip, t.absmax_part, t.nparts, t.seed_lo, t.seed_hi, t.q, t.scale, nullptr, vb, lds4, atile)
+#define ACT(STv, VECv) quantize_act_body<STv, false, VECv>(t.x, t.d0, t.d1, Cp, HW, t.clip, t.absmax_part, t.nparts, t.seed_lo, t.seed_hi, t.q, t.scale, nullptr, vb, lds4, atile)
         if (ANYSTOCH && st) {
-            if ((HW & 3) == 0) ACT(ANYSTOCH, true); else ACT(ANYSTOCH, false);
+            if (!RAGGED || (HW & 3) == 0) ACT(ANYSTOCH, true); else ACT(ANYSTOCH, !RAGGED);
         } else {
-            if ((HW & 3) == 0) ACT(false, true); else ACT(false, false);
+            if (!RAGGED || (HW & 3) == 0) ACT(false, true); else ACT(false, !RAGGED);
         }
 #undef ACT
     } else if (t.kind == 1) {   // weights, two views
@@ -713,7 +802,7 @@ __global__ __launch_bounds__(256) void quantize_batch_kernel(const QuantBatch b)
 void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz) {
     if (kind == 0) {
         const int HW = d[2] * d[3], Cp = (d[1] + 15) & ~15;
-        *gx = quant_act_gx(Cp, HW); *gy = (Cp + QA_CH - 1) / QA_CH; *gz = d[0];
+        quant_act_grid(d[0], Cp, HW, gx, gy, gz);
     } else if (kind == 1) {
         *gx = quant_wgt_gx(d[0], d[1], d[2], d[3]); *gy = (d[0] + QW_T - 1) / QW_T; *gz = quant_wgt_zsplit(d[0], d[1], d[2], d[3]);
     } else {
@@ -736,10 +825,15 @@ hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStrea
     }
     lds = (lds + 15) & ~(size_t)15;
     KernelTimer kt(KID_QUANTIZE_BATCH, st);
-    bool any_stoch = false;
-    for (int i = 0; i < b.count; ++i) any_stoch = any_stoch || b.it[i].stoch;
-    if (any_stoch) launch_timed(kt, quantize_batch_kernel<true>, dim3(total_blocks), dim3(256), lds, st, b);
-    else launch_timed(kt, quantize_batch_kernel<false>, dim3(total_blocks), dim3(256), lds, st, b);
+    bool any_stoch = false, ragged = false;
+    for (int i = 0; i < b.count; ++i) {
+        any_stoch = any_stoch || b.it[i].stoch;
+        ragged = ragged || (b.it[i].kind == 0 && ((b.it[i].d2 * b.it[i].d3) & 3) != 0);
+    }
+#define LAUNCH(ST, RG) launch_timed(kt, (quantize_batch_kernel<ST, RG>), dim3(total_blocks), dim3(256), lds, st, b)
+    if (any_stoch) { if (ragged) LAUNCH(true, true); else LAUNCH(true, false); }
+    else { if (ragged) LAUNCH(false, true); else LAUNCH(false, false); }
+#undef LAUNCH
     return hipGetLastError();
 }
 

@@ -348,3 +348,37 @@ def test_depthwise_codes_and_passes_in_one_launch(shape, form):
         assert launches["dw_trio_kernel"][0] == (2 if form == "halves" else 1)
     for n, a, b in zip(outs, got, want):
         assert torch.equal(a, b), n
+
+
+# Codes of 1 x 1 images whose channels need padding: rows of whole 16 bytes and others, one to four and many quads per thread, a
+# single granule; both roundings, with and without a clip value and Eq.6, alone and in a batch.
+@pytest.mark.parametrize("N,C", [(1, 1), (3, 7), (5, 18), (256, 1000), (17, 1001), (2, 4092), (300, 1785), (2100, 996)])
+def test_codes_of_rows(N, C):
+    r = np.random.RandomState(C)
+    x = (r.standard_t(3, size=(N, C, 1, 1)) * 1e-3).astype(np.float32)
+    x.reshape(-1)[0] = np.nan if C > 1 else 1.0
+    xd, q, s = dev(x), torch.full((N * ((C + 15) // 16 * 16),), 7, dtype=torch.int8, device=DEV), torch.zeros(1, device=DEV)
+    ws = torch.empty(B.int8t_quantize_workspace_bytes((N, C, 1, 1), B.ACT), dtype=torch.uint8, device=DEV)
+    d = torch.zeros(1, dtype=torch.float64, device=DEV)
+    finite = np.nan_to_num(x)
+    for mode, om in ((RTN, oracle.ROUND_NEAREST_EVEN), (STO, oracle.ROUND_STOCHASTIC)):
+        for clip in (None, np.float32(4e-3)):
+            want, sc = oracle.quantize(finite, c=clip, mode=om, seed=11)
+            cd = None if clip is None else dev(np.array([clip], np.float32))
+            for batch in (False, True):
+                q.fill_(7)
+                if batch:
+                    B.int8t_quantize_batch([(xd, (N, C, 1, 1), B.ACT, cd, q, s, mode, 11)], ws=torch.empty(1 << 14, dtype=torch.uint8, device=DEV))
+                else:
+                    B.int8t_quantize(xd, (N, C, 1, 1), B.ACT, cd, mode, 11, q, s, None if C > 1 else d, ws)
+                torch.cuda.synchronize()
+                got, pad = B.int8t_unpack_codes(q.cpu().numpy(), (N, C, 1, 1), B.ACT)
+                assert np.array_equal(got, want) and pad == 0 and s.item() == sc
+            if C > 1:
+                xd0 = dev(finite)
+                B.int8t_quantize(xd0, (N, C, 1, 1), B.ACT, cd, mode, 11, q, s, d, ws)
+                torch.cuda.synchronize()
+                ref = want.astype(np.float64).reshape(-1)
+                g64 = finite.astype(np.float64).reshape(-1)
+                dw = 1.0 - (g64 @ ref) / (np.sqrt(g64 @ g64) * np.sqrt(ref @ ref)) if ref.any() else 1.0
+                assert abs(d.item() - dw) < 1e-9
