@@ -368,6 +368,16 @@ int8t_status int8t_layer_step(const int8t_conv_desc *desc, const int8t_layer_buf
                               void *stream);
 
 /*
+ * The backward half of a step in one call, for callers whose forward pass ran earlier (a layer inside a network): as
+ * int8t_layer_step with any of INT8T_STEP_PREPARE together with INT8T_STEP_SEARCH (here without INT8T_STEP_ABSMAX),
+ * INT8T_STEP_QUANT_G, INT8T_STEP_BWD_DATA and INT8T_STEP_BWD_WEIGHT; other parts: INT8T_ERR_ARG.
+ *   db_dev   NULL, or K floats: out, the sum of dy over the batch (the gradient of a bias; summed in fp64), for layers with one
+ *            output pixel (P = Q = 1; INT8T_ERR_ARG for others).  It may not overlap what the call reads or writes otherwise.
+ */
+int8t_status int8t_layer_backward(const int8t_conv_desc *desc, const int8t_layer_buffers *b, int parts, uint64_t seed,
+                                  float *db_dev, void *stream);
+
+/*
  * Choice of the kernel per layer by measurement "before training" (Suppl. "INT8 Convolution", last
  * paragraph: the paper picks between its two convolution algorithms per layer; here the choice is
  * among this library's kernels for a pass).  Every variant computes the same integer sums, so the

@@ -29,7 +29,7 @@ EXPORTS = ["int8t_status_string", "int8t_code_bytes", "int8t_unpack_codes", "int
            "int8t_quantize_workspace_bytes", "int8t_quantize", "int8t_quantize_batch_workspace_bytes",
            "int8t_quantize_batch", "int8t_quantize_batch_prepare", "int8t_dsgc_clip", "int8t_dsgc_clip_static", "int8t_dsgc_prepare", "int8t_dsgc_search", "int8t_conv_fwd", "int8t_conv_fwd_fused",
            "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_dclr_scale",
-           "int8t_layer_step", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
+           "int8t_layer_step", "int8t_layer_backward", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
            "int8t_profile_start", "int8t_profile_start_sampled", "int8t_profile_stop", "int8t_profile_mfma_ceiling"]
 
 
@@ -107,6 +107,8 @@ def _load():
     L.int8t_conv_fwd_fused.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.int8t_layer_step.restype = i32
     L.int8t_layer_step.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp]
+    L.int8t_layer_backward.restype = i32
+    L.int8t_layer_backward.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp, vp]
     L.int8t_conv_variant_ok.restype = i32
     L.int8t_conv_variant_ok.argtypes = [i32, dp, i32]
     L.int8t_conv_select_variant.restype = i32
@@ -303,6 +305,10 @@ def layer_buffers(**fields) -> LayerBuffers:
 
 def int8t_layer_step(desc, buffers: LayerBuffers, parts: int = STEP_ALL, seed: int = 0, stream=None):
     _check(lib.int8t_layer_step(C.byref(desc), C.byref(buffers), parts, seed, _stream(stream)))
+
+
+def int8t_layer_backward(desc, buffers: LayerBuffers, parts: int, seed: int = 0, db=None, stream=None):
+    _check(lib.int8t_layer_backward(C.byref(desc), C.byref(buffers), parts, seed, _ptr(db), _stream(stream)))
 
 
 def int8t_conv_variant_ok(op: int, desc: ConvDesc, variant: int) -> bool:

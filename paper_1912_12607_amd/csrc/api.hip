@@ -414,12 +414,18 @@ float* batch_partials(void* ws_dev, int i) { return (float*)((char*)ws_dev + (si
 
 // First launch of a batch: the absmax partials of the items without a clip value and, with g_dev, the first phase of a
 // clip search on g.  (checked arguments)
+// sums: the column sums of `sums_of` (g_n elements) as a matrix of `cols` columns, in the same launch.
 hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_dev, const float* g_dev, size_t g_n, void* dsgc_ws_dev,
-                        hipStream_t st) {
+                        hipStream_t st, float* sums = nullptr, const float* sums_of = nullptr, int cols = 0) {
     AbsmaxBatch ab{};
     long long ablocks = 0;
     int order[INT8T_MAX_BATCH];
     size_t sizes[INT8T_MAX_BATCH];
+    if (sums) {
+        AbsmaxBatchItem& a = ab.it[ab.count++];
+        a.x = sums_of; a.n = g_n; a.part = sums; a.cols = cols; a.nblocks = absmax_colsum_blocks(cols);
+        ablocks += a.nblocks;
+    }
     batch_order(count, items, order, sizes);
     for (int oi = 0; oi < count; ++oi) {
         const int i = order[oi];
@@ -760,7 +766,10 @@ static bool disjoint_step(const int8t_conv_desc* d, const Geo& g, const int8t_la
     return true;
 }
 
-int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, void* stream) {
+// int8t_layer_step (backward: false) and int8t_layer_backward (true: the first phase of the search without max|a| and max|W|, and
+// the column sums db of g_z).
+static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, bool backward, float* db,
+                               void* stream) {
     Geo g;
     int8t_status s = desc_ok(desc, &g);
     if (s != INT8T_OK) return s;
@@ -769,7 +778,9 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     const bool absmax = parts & INT8T_STEP_ABSMAX, prepare = parts & INT8T_STEP_PREPARE, search = parts & INT8T_STEP_SEARCH;
     const bool quant_xw = parts & INT8T_STEP_QUANT_XW, quant_g = parts & INT8T_STEP_QUANT_G;
     const bool fwd = parts & INT8T_STEP_FWD, bwd_data = parts & INT8T_STEP_BWD_DATA, bwd_weight = parts & INT8T_STEP_BWD_WEIGHT;
-    if (prepare && !absmax) return INT8T_ERR_ARG;
+    if (backward ? absmax || quant_xw || fwd || prepare != search || (db && g.P * g.Q != 1) : prepare && !absmax) return INT8T_ERR_ARG;
+    if (db && !b->dy) return INT8T_ERR_NULL;
+    if (db && (!aligned4(db) || !aligned4(b->dy))) return INT8T_ERR_ARG;
     const int8t_kind ak = g.depthwise ? INT8T_ACT_PLANAR : INT8T_ACT, wk = g.depthwise ? INT8T_WGT_PLANAR : INT8T_WGT;
     const size_t n_y = (size_t)desc->N * desc->K * g.P * g.Q;
     const int ydims[4] = {desc->N, desc->K, g.P, g.Q};
@@ -827,6 +838,8 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     // ---- launches
     hipStream_t st = (hipStream_t)stream;
     if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
+    if (backward && (prepare || db) && batch_absmax(0, nullptr, nullptr, prepare ? b->dy : nullptr, n_y, b->ws_dy, st, db, b->dy, desc->K) != hipSuccess)
+        return INT8T_ERR_RUNTIME;
     if (search) {
         s = int8t_dsgc_search(b->dy, n_y, b->ratios, b->n_cand, INT8T_ROUND_STOCHASTIC, seed, b->clip, b->dev_search, b->dev_all, b->ws_dy,
                               b->ws_dy_bytes, stream);
@@ -910,6 +923,15 @@ int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buf
     if (bwd_weight)
         return int8t_conv_bwd_weight(desc, b->xq, b->sx, b->dyq, b->sdy, b->dw, b->dw_acc, b->ws_bwd_weight, b->ws_bwd_weight_bytes, stream);
     return INT8T_OK;
+}
+
+int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, void* stream) {
+    return layer_step(desc, b, parts, seed, false, nullptr, stream);
+}
+
+int8t_status int8t_layer_backward(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, float* db_dev,
+                                  void* stream) {
+    return layer_step(desc, b, parts, seed, true, db_dev, stream);
 }
 
 double int8t_dclr_scale(double d_c, double alpha, double beta) {

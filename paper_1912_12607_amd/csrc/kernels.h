@@ -65,6 +65,8 @@ struct AbsmaxBatchItem {
     double* sumsq;
     unsigned long long* zero;
     int nzero;
+    // > 0: not a maximum but column sums: x is a matrix of n / cols rows, part receives its `cols` sums (absmax_colsum_blocks() blocks)
+    int cols;
 };
 struct AbsmaxBatch {
     int count;
@@ -88,6 +90,7 @@ struct QuantBatch {
     QuantBatchItem it[kMaxBatch];
 };
 int absmax_blocks(size_t n);
+int absmax_colsum_blocks(int cols);
 void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz);
 hipError_t launch_absmax_batch(const AbsmaxBatch& b, int total_blocks, hipStream_t st);
 hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStream_t st);

@@ -326,3 +326,17 @@ def test_unpack_codes_matches_the_documented_layouts():
     assert np.array_equal(out, w)
     with pytest.raises(B.Int8tError):
         B.int8t_unpack_codes(buf, (K, Cg, R, S), B.ACT_PLANAR, 1)
+
+
+def test_layer_backward_arguments():
+    from paper_1912_12607_amd import binding as B
+    d, b = B.make_desc(2, 16, 8, 8, 32, 3, 3, (1, 1), (1, 1)), B.LayerBuffers()
+
+    def call(parts, db=None):
+        return B.lib.int8t_layer_backward(C.byref(d), C.byref(b), parts, 0, db, None)
+
+    null, bad = 1, 3                               # INT8T_ERR_NULL, INT8T_ERR_ARG
+    for parts in (0, 256, B.STEP_ABSMAX, B.STEP_QUANT_XW | B.STEP_QUANT_G, B.STEP_FWD, B.STEP_PREPARE, B.STEP_SEARCH, B.STEP_ALL):
+        assert call(parts) == bad
+    assert call(B.STEP_BWD_DATA, 4096) == bad      # a bias gradient of a layer with more than one output pixel
+    assert call(B.STEP_PREPARE | B.STEP_SEARCH) == null and call(B.STEP_QUANT_G) == null and call(B.STEP_BWD_WEIGHT) == null

@@ -247,3 +247,52 @@ def test_replace_modules_swaps_conv_and_linear_and_trains_without_new_buffers():
     with torch.no_grad():                          # inference: the activation codes go straight back to the pool
         model(x)
     assert all(len(next(iter(m._buffers.values())).xq_pool) == 1 for m in int8)
+
+
+def _with_bias(linear, *shape):
+    from paper_1912_12607_amd.autograd import Int8Conv2d, Int8Linear
+    torch.manual_seed(5)
+    m = Int8Linear(*shape, seed=100) if linear else Int8Conv2d(*shape, bias=True, seed=100)
+    with torch.no_grad():
+        m.bias.copy_(torch.randn(m.out_channels, device="cuda"))
+    return m
+
+
+# The bias inside the layer's node: column sums of one row to several per wave, ragged column blocks, inputs with any leading
+# shape; against the layer without one, an addition and a sum in 64 bits (fp32 result of an fp64 sum: half a unit in the last place).
+@pytest.mark.parametrize("lead,C,K", [((1,), 16, 1), ((3,), 20, 63), ((2, 5), 48, 65), ((), 32, 10), ((700,), 64, 1000), ((4, 3, 30), 17, 130)])
+def test_bias_of_a_fully_connected_layer(lead, C, K):
+    m = _with_bias(True, C, K)
+    x = torch.randn(*lead, C, device="cuda", requires_grad=True)
+    g = torch.randn(*lead, K, device="cuda") * 1e-3
+    y = m(x)
+    assert y.shape == g.shape
+    grads = torch.autograd.grad(y, [x, m.weight, m.bias], g)
+    bias, m.bias, m._seed, m.backward_calls = m.bias, None, 100, 0
+    y0 = m(x)
+    assert torch.equal(y, y0 + bias)
+    want = torch.autograd.grad(y0, [x, m.weight], g)
+    assert torch.equal(grads[0], want[0]) and torch.equal(grads[1], want[1])
+    s = g.reshape(-1, K).double().sum(0)
+    assert grads[2].shape == (K,) and torch.all((grads[2].double() - s).abs() <= 2.0 ** -24 * 1.01 * s.abs() + 1e-44)
+
+
+def test_bias_of_a_frozen_layer_and_of_a_convolution():
+    for m, x in ((_with_bias(True, 24, 40), torch.randn(6, 24, device="cuda")), (_with_bias(False, 8, 12, 3), torch.randn(2, 8, 9, 9, device="cuda"))):
+        dims = (0,) if x.dim() == 2 else (0, 2, 3)
+        y = m(x)
+        g = torch.randn_like(y)
+        y.backward(g)
+        assert torch.allclose(m.bias.grad, g.sum(dims), rtol=1e-5, atol=1e-6) and m.backward_calls == 1 and m.weight.grad is not None
+        m.weight.requires_grad_(False)
+        m.bias.grad = None
+        m(x).backward(g)                  # neither the input nor the weights want a gradient: no codes, no search
+        assert torch.allclose(m.bias.grad, g.sum(dims), rtol=1e-5, atol=1e-6) and m.backward_calls == 1
+        # a forward-mode tangent of the bias passes as it does through an addition
+        with torch.autograd.forward_ad.dual_level(), torch.no_grad():
+            t = torch.randn_like(m.bias)
+            bias = m.bias
+            del m.bias
+            m.bias = torch.autograd.forward_ad.make_dual(bias.detach(), t)
+            out = torch.autograd.forward_ad.unpack_dual(m(x)).tangent
+            assert torch.equal(out, t.view(1, -1, *[1] * (x.dim() - 2)).expand_as(out))
