@@ -2,6 +2,7 @@
 // No device memory is allocated here and nothing synchronises with the host.
 #include <math.h>
 
+#include <algorithm>
 #include <array>
 #include <map>
 #include <mutex>
@@ -418,10 +419,12 @@ float* batch_partials(void* ws_dev, int i) { return (float*)((char*)ws_dev + (si
 hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_dev, const float* g_dev, size_t g_n, void* dsgc_ws_dev,
                         hipStream_t st, float* sums = nullptr, const float* sums_of = nullptr, int cols = 0) {
     AbsmaxBatch ab{};
+    std::fill(std::begin(ab.block0), std::end(ab.block0), 0x7fffffff);
     long long ablocks = 0;
     int order[INT8T_MAX_BATCH];
     size_t sizes[INT8T_MAX_BATCH];
     if (sums) {
+        ab.block0[ab.count] = (int)ablocks;
         AbsmaxBatchItem& a = ab.it[ab.count++];
         a.x = sums_of; a.n = g_n; a.part = sums; a.cols = cols; a.nblocks = absmax_colsum_blocks(cols);
         ablocks += a.nblocks;
@@ -430,14 +433,16 @@ hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_de
     for (int oi = 0; oi < count; ++oi) {
         const int i = order[oi];
         if (items[i].clip_dev) continue;
+        ab.block0[ab.count] = (int)ablocks;
         AbsmaxBatchItem& a = ab.it[ab.count++];
-        a.x = items[i].x_dev; a.n = sizes[i]; a.part = batch_partials(ws_dev, i); a.block0 = (int)ablocks; a.nblocks = absmax_blocks(sizes[i]);
+        a.x = items[i].x_dev; a.n = sizes[i]; a.part = batch_partials(ws_dev, i); a.nblocks = absmax_blocks(sizes[i]);
         ablocks += a.nblocks;
     }
     if (g_dev) {
         const DsgcWs dws = dsgc_ws_layout(dsgc_ws_dev);
+        ab.block0[ab.count] = (int)ablocks;
         AbsmaxBatchItem& a = ab.it[ab.count++];
-        a.x = g_dev; a.n = g_n; a.part = dws.absmax_part; a.block0 = (int)ablocks; a.nblocks = absmax_blocks(g_n);
+        a.x = g_dev; a.n = g_n; a.part = dws.absmax_part; a.nblocks = absmax_blocks(g_n);
         a.sumsq = dws.partG; a.zero = dws.acc; a.nzero = (int)dsgc_acc_words() + 1;
         ablocks += a.nblocks;
     }
@@ -448,6 +453,7 @@ hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_de
 int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_dev, hipStream_t st) {
     QuantBatch qb{};
     qb.count = count;
+    std::fill(std::begin(qb.block0), std::end(qb.block0), 0x7fffffff);
     long long qblocks = 0;
     int order[INT8T_MAX_BATCH];
     size_t sizes[INT8T_MAX_BATCH];
@@ -465,7 +471,7 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
         q.seed_lo = seed_key_x(it.seed);
         q.seed_hi = seed_key_a(it.seed);
         quant_grid(q.kind, it.dims, &q.gx, &q.gy, &q.gz);
-        q.block0 = (int)qblocks;
+        qb.block0[oi] = (int)qblocks;
         qblocks += (long long)q.gx * q.gy * q.gz;
         if (qblocks > 0x7FFFFFFFll) return INT8T_ERR_SHAPE;
     }

@@ -59,7 +59,7 @@ struct AbsmaxBatchItem {
     const float* x;
     size_t n;
     float* part;                 // this tensor's partials
-    int block0, nblocks;         // its block range inside the launch (nblocks = 0: clip supplied)
+    int nblocks;                 // its blocks inside the launch
     // the tensor of a clip search (at most one, the last item): its blocks also leave the sums of squares and clear
     // the search's accumulators, as absmax_kernel<true> does
     double* sumsq;
@@ -68,7 +68,17 @@ struct AbsmaxBatchItem {
     // > 0: not a maximum but column sums: x is a matrix of n / cols rows, part receives its `cols` sums (absmax_colsum_blocks() blocks)
     int cols;
 };
+// The item that holds a block of a batched launch.  The first blocks of all items stand side by side at the front of the kernel's
+// arguments (0x7fffffff where there is no item): one load, where walking the items is a chain of them, each a round trip to memory.
+template <int COUNT>
+__device__ __forceinline__ int batch_item(const int (&block0)[COUNT], int block) {
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < COUNT; ++k) i += block >= block0[k] ? 1 : 0;
+    return i;
+}
 struct AbsmaxBatch {
+    int block0[kMaxBatch + 1];   // first block of every item: batch_item()
     int count;
     AbsmaxBatchItem it[kMaxBatch + 1];
 };
@@ -81,11 +91,12 @@ struct QuantBatchItem {
     int8_t* q;
     float* scale;
     int kind;                    // 0 activations, 1 weights, 2 planar
-    int block0, gx, gy, gz;      // its block range and virtual grid inside the launch
+    int gx, gy, gz;              // its virtual grid inside the launch
     int stoch;                   // Eq.3 instead of Eq.1
     uint32_t seed_lo, seed_hi;   // seed_key_x(seed), seed_key_a(seed): the draw's two keys
 };
 struct QuantBatch {
+    int block0[kMaxBatch];       // as in AbsmaxBatch
     int count;
     QuantBatchItem it[kMaxBatch];
 };

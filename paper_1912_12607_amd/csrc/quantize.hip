@@ -130,12 +130,11 @@ int absmax_colsum_blocks(int cols) { return (cols + kWave - 1) / kWave; }
 template <bool SUMS>
 __global__ __launch_bounds__(AM_THREADS) void absmax_batch_kernel(const AbsmaxBatch b) {
     raise_wave_priority();
-    int i = 0;
-    while (i + 1 < b.count && (int)blockIdx.x >= b.it[i].block0 + b.it[i].nblocks) ++i;
+    const int i = batch_item(b.block0, (int)blockIdx.x), block = (int)blockIdx.x - b.block0[i];
     const AbsmaxBatchItem& t = b.it[i];
-    if (SUMS && t.cols) colsum_body(t.x, t.n, t.cols, t.part, (int)blockIdx.x - t.block0);
-    else if (t.sumsq) absmax_body<true>(t.x, t.n, t.part, t.sumsq, t.zero, t.nzero, (int)blockIdx.x - t.block0, t.nblocks);
-    else absmax_body<false>(t.x, t.n, t.part, nullptr, nullptr, 0, (int)blockIdx.x - t.block0, t.nblocks);
+    if (SUMS && t.cols) colsum_body(t.x, t.n, t.cols, t.part, block);
+    else if (t.sumsq) absmax_body<true>(t.x, t.n, t.part, t.sumsq, t.zero, t.nzero, block, t.nblocks);
+    else absmax_body<false>(t.x, t.n, t.part, nullptr, nullptr, 0, block, t.nblocks);
 }
 
 int absmax_blocks(size_t n) {
@@ -799,10 +798,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH
     __shared__ float lds4[4];
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     uint32_t (*const atile)[QA_CH / 4 + 1] = reinterpret_cast<uint32_t (*)[QA_CH / 4 + 1]>(smem);
-    int i = 0;
-    while (i + 1 < b.count && (int)blockIdx.x >= b.it[i].block0 + b.it[i].gx * b.it[i].gy * b.it[i].gz) ++i;
+    const int i = batch_item(b.block0, (int)blockIdx.x);
     const QuantBatchItem& t = b.it[i];
-    const int local = (int)blockIdx.x - t.block0;
+    const int local = (int)blockIdx.x - b.block0[i];
     const int gxy = t.gx * t.gy;
     const int z = local / gxy, rem = local - z * gxy;
     const int y = rem / t.gx;
