@@ -380,6 +380,9 @@ __global__ __launch_bounds__(DSGC_MAX_THREADS) void dsgc_sweep_kernel(
     {
         const int j = threadIdx.x & 63, part = threadIdx.x >> 6;
         if (part < 4) {
+        // G: the absmax pass's per-block sums of squares, at most one per thread (asked for ahead of the sets)
+        static_assert(kAbsmaxPartials <= 256, "one partial sum of squares per thread");
+        double gs = (int)threadIdx.x < nparts ? partG[threadIdx.x] : 0.0;
         long long t[3] = {0, 0, 0};
         if (j < n_cand) {
             long long v[DSGC_GROUPS / 4][3];
@@ -396,9 +399,6 @@ __global__ __launch_bounds__(DSGC_MAX_THREADS) void dsgc_sweep_kernel(
         }
 #pragma unroll
         for (int q = 0; q < 3; ++q) f_part[part][j][q] = t[q];
-        // G: the absmax pass's per-block sums of squares
-        double gs = 0.0;
-        for (int i = threadIdx.x; i < nparts; i += 256) gs += partG[i];
         gs = wave_sum(gs);
         if (j == 0) f_g[part] = gs;
         }
@@ -426,14 +426,20 @@ __global__ __launch_bounds__(DSGC_MAX_THREADS) void dsgc_sweep_kernel(
         const double inf = __builtin_huge_val();
         double bd = (j < n_cand && d == d) ? d : (j == 0 ? -inf : inf);
         int bj = j;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double od = __shfl_xor(bd, o, kWave);
-            const int oj = __shfl_xor(bj, o, kWave);
+        auto better = [&](double od, int oj) {
             if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
-        }
+        };
+        better(dpp_of<kDppSwap1>(bd), dpp_word<kDppSwap1>(bj));
+        better(dpp_of<kDppSwap2>(bd), dpp_word<kDppSwap2>(bj));
+        better(dpp_of<kDppRor4>(bd), dpp_word<kDppRor4>(bj));
+        better(dpp_of<kDppRor8>(bd), dpp_word<kDppRor8>(bj));
+        const double rd[4] = {lane_of(bd, 0), lane_of(bd, 16), lane_of(bd, 32), lane_of(bd, 48)};
+        const int rj[4] = {__builtin_amdgcn_readlane(bj, 0), __builtin_amdgcn_readlane(bj, 16), __builtin_amdgcn_readlane(bj, 32),
+                           __builtin_amdgcn_readlane(bj, 48)};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) better(rd[r], rj[r]);
         const int best = (Mn == 0.0f) ? 0 : bj;
-        const double dbest = __shfl(d, best, kWave);
+        const double dbest = lane_of(d, best);
         if (j == 0) {
             *clip_out = __fmul_rn(Mn, ratios[best]);
             *dev_out = dbest;
