@@ -915,8 +915,8 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
             fwd_left = false;
         }
         const IgemmArgs* fp = fwd_left ? &f : nullptr;
-        const int bn = conv_trio_tile(fp, d, w);
-        if (bn) return launch_conv_trio(fp, d, w, bn, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+        const TrioTile tile = conv_trio_tile(fp, d, w);
+        if (tile.bn) return launch_conv_trio(fp, d, w, tile, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     if (fwd_left) {
         s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);

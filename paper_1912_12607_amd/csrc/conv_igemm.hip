@@ -438,13 +438,13 @@ static bool igemm_cells_ok(const IgemmArgs& a) {
     return a.dgrad && a.stride_h == 2 && a.stride_w == 2 && a.R >= 2 && a.S >= 2;
 }
 
-unsigned igemm_plain_blocks(IgemmArgs* a, int bn) {
+unsigned igemm_plain_blocks(IgemmArgs* a, int bm, int bn) {
     const IgemmShape g = igemm_shape(*a);
     if (g.cls || g.cell) return 0;
     a->cls_h = a->cls_w = 1;
     a->cell = 0;
     a->ksplit = 1;
-    const unsigned ctiles = (unsigned)((g.ncols + bn - 1) / bn), rtiles = (unsigned)((a->rows + 127) / 128);
+    const unsigned ctiles = (unsigned)((g.ncols + bn - 1) / bn), rtiles = (unsigned)((a->rows + bm - 1) / bm);
     a->colrun = igemm_colrun(*a, g, ctiles, false);
     return ((ctiles + 7) / 8) * 8 * rtiles;
 }

@@ -81,20 +81,21 @@ __device__ __forceinline__ void store_cell(T* __restrict__ dst, size_t o, int OW
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class
 //   form writes every other float of a line from four different blocks and pays a block's fixed cost per class.
 //   STG (plain forms, planes of whole 16-byte groups): the results leave through LDS, see the epilogue.
-template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS = false, bool CELL = false, int BNT = IGD_BN, bool ALLC = false, bool STG = false>
+//   NWN: waves along the columns.  4 with WM = 1 (and 256 columns): 64-row tiles for passes of at most 64 rows.
+template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS = false, bool CELL = false, int BNT = IGD_BN, bool ALLC = false, bool STG = false, int NWN = 2>
 __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigned block) {
-    static_assert(!STG || (!CLS && WM == 2), "staged results: plain forms of the 128-row tiles");
+    static_assert(!STG || (!CLS && WM * NWN == 4), "staged results: plain forms of the tiles of four waves");
     static_assert(DGRAD || !CLS, "residue classes exist in the backward-data pass only");
     static_assert(CLS || !CELL, "the cell form is a residue-class form");
     static_assert(!ALLC || (CLS && CELL && BNT == 64), "all classes per block: cell columns, 64 of them");
-    constexpr int BM = 64 * WM, BN = BNT, MI = 2, NJ = BN / 64, NW = 2 * WM;
+    constexpr int BM = 64 * WM, BN = BNT, CW = BN / NWN, MI = 2, NJ = CW / 32, NW = NWN * WM;      // CW: columns of a wave
     constexpr int NC = ALLC ? 4 : 1;                    // classes a block runs
     constexpr int STAGE_SLOTS = (BM + BN) * KG;         // 16-byte slots per stage: A tile, then B tile
     constexpr int RPL = 64 / KG;                        // tile rows covered by one wave-wide load
     constexpr int NLA = BM * KG / 64 / NW;              // A loads per wave and stage
     constexpr int NLB = BN * KG / 64 / NW;              // B loads per wave and stage
     constexpr int NL = NLA + NLB;
-    static_assert(NSTAGE == 2 || NL == 6 || NL == 4, "vmcnt waits below are written for these");
+    static_assert(NSTAGE == 2 || NL == 6 || NL == 5 || NL == 4, "vmcnt waits below are written for these");
     extern __shared__ __attribute__((aligned(16))) uint4 ring[];   // [NSTAGE][STAGE_SLOTS]
     raise_wave_priority();
 
@@ -303,7 +304,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
             }
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                const uint4 t = sB[igd_slot<KG>(wn * (BN / 2) + j * 32 + (lane & 31), g)];
+                const uint4 t = sB[igd_slot<KG>(wn * CW + j * 32 + (lane & 31), g)];
                 fb[j] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
             }
 #pragma unroll
@@ -328,7 +329,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         constexpr int PITCH = BN + 8;         // 4 * PITCH mod 64 = 32: the half-waves of a store, 4 rows apart, use different banks
         static_assert(32 * WM * PITCH * 4 <= NSTAGE * STAGE_SLOTS * 16, "the staged rows fit the ring");
         int* const stg = reinterpret_cast<int*>(ring);
-        constexpr int QPR = BN / 4, RPI = 128 * WM / QPR;     // 16-byte groups per row, rows per pass of the block
+        constexpr int QPR = BN / 4, RPI = 64 * NW / QPR;     // 16-byte groups per row, rows per pass of the block
         const int q = tid % QPR, r0 = tid / QPR;
         const int col = colbase + 4 * q;
         const int n = col / OHW, opix = col - n * OHW;
@@ -339,7 +340,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
-                    stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * (BN / 2) + j * 32 + (lane & 31)] = acc[0][i][j][v];
+                    stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * CW + j * 32 + (lane & 31)] = acc[0][i][j][v];
             __syncthreads();
             if (col >= ncols) continue;
 #pragma unroll 4
@@ -357,7 +358,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        const int col = colbase + wn * (BN / 2) + j * 32 + (lane & 31);
+        const int col = colbase + wn * CW + j * 32 + (lane & 31);
         if (col >= ncols) continue;
         const int n = col / OHW;
         int opix = col - n * OHW;

@@ -17,7 +17,13 @@ namespace int8t {
 namespace {
 struct TrioBlocks {
     unsigned wgrad, wgrad8, fwd;     // backward-weight's blocks, and rounded up to the 8 XCDs; the forward pass's
+    bool fwd64, bwd64;               // 64 x 128 tiles (conv_trio_tile)
 };
+template <bool DGRAD, int BN, bool STG>
+__device__ __forceinline__ void trio_pass(const IgemmArgs& a, bool rows64, unsigned block) {
+    if (rows64) igemm_dma_tile<DGRAD, 1, 8, 2, false, false, 128, false, STG, 4>(a, block);
+    else igemm_dma_tile<DGRAD, 2, 8, 2, false, false, BN, false, STG>(a, block);
+}
 // ST = 0: backward-weight on image granules, one tap and 64 channels per block (narrow 1x1 layers)
 constexpr int trio_wt(int ST) { return ST == 1 ? 2 : 1; }
 constexpr int trio_gp(int ST) { return ST == 1 ? 4 : ST == 5 ? 6 : 8; }
@@ -37,9 +43,9 @@ __global__ __launch_bounds__(256, 2) void conv_trio_kernel(const IgemmArgs f, co
         if constexpr (ST == 0) wgrad_tile<1, 1>(w, block);
         else wgrad_lines_tile<ST, trio_wt(ST), trio_wt(ST), trio_gp(ST)>(w, block);
     } else if (block < n.wgrad8 + n.fwd) {
-        igemm_dma_tile<false, 2, 8, 2, false, false, BN, false, STG>(f, block - n.wgrad8);
+        trio_pass<false, BN, STG>(f, n.fwd64, block - n.wgrad8);
     } else {
-        igemm_dma_tile<true, 2, 8, 2, false, false, BN, false, STG>(b, block - n.wgrad8 - n.fwd);
+        trio_pass<true, BN, STG>(b, n.bwd64, block - n.wgrad8 - n.fwd);
     }
 }
 
@@ -74,37 +80,60 @@ static long long trio_stages(const IgemmArgs& a) { return ((long long)a.R * a.S 
 bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd) {
     return igemm_splits(fwd) && !igemm_splits(bwd) && 5 * trio_stages(fwd) >= 8 * trio_stages(bwd);
 }
-int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
-    if (w.variant != VAR_AUTO || w.s2d || !(w.lines || (w.TB == 1 && w.CS == 1 && !w.pk))) return 0;
+// Passes of at most 64 rows leave half of every 128-row tile empty: they take 64 x 128 tiles (four waves of 64 x 32) instead, where the
+// work per block slot, counted with these, makes up for the chain of stages of one tile, which is 5 - 10 % longer than that
+// of a 128 x 64 tile: from 0.4 times the longest reduction on where all passes are that narrow, on the launch whose blocks fit
+// a compute unit three times; from 0.55 times on beside a wider pass, with the wider tile for that one; the two backward passes
+// alone from 0.45 on.  Over 290 random such layers, the three passes, us before and now:
+//   5x5, 48 -> 64, 35 x 35, batch 32    41.7   35.6      3x3, 64 channels, 28 x 28, batch 64     26.6   23.1
+//   5x5, 32 -> 64, 28 x 28, batch 32    27.0   21.5      3x3, 32 -> 29, 21 x 21, batch 256       42.1   33.5
+//   3x3, 40 -> 186, 28 x 28, batch 256  144.7  128.8     3x3, 408 -> 8, 9 x 9, batch 256         42.6   36.5
+// all narrow 0.86 of the time before on average, mixed 0.97, the two backward ones 0.95, none slower.  64 x 256 tiles gained
+// nothing (5x5, 48 -> 64: 40.5).
+TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
+    const TrioTile apart{0, false};
+    if (w.variant != VAR_AUTO || w.s2d || !(w.lines || (w.TB == 1 && w.CS == 1 && !w.pk))) return apart;
     if (igemm_splits(bwd)) {
-        if (!fwd) return 0;
+        if (!fwd) return apart;
         const bool both = igemm_splits(*fwd);
         const long long f = trio_stages(*fwd), b = trio_stages(bwd);
-        if (both ? std::max(f, b) >= 45 : b >= 45 + f) return 0;
+        if (both ? std::max(f, b) >= 45 : b >= 45 + f) return apart;
     }
     long long band_tiles = 0, work = 0, longest = 0;
+    long long work64 = 0;                 // in half units: a pass of at most 64 rows on 64 x 128 tiles
+    int narrow = 0, passes = 0;
     for (const IgemmArgs* a : {fwd, &bwd}) {
         if (!a) continue;
-        if (a->variant != VAR_AUTO || a->stride_h != 1 || a->stride_w != 1) return 0;
+        if (a->variant != VAR_AUTO || a->stride_h != 1 || a->stride_w != 1) return apart;
         const int v = igemm_auto_variant(*a);
-        if (v == VAR_WIDE256) return 0;
+        if (v == VAR_WIDE256) return apart;
         const long long tiles = (((long long)a->N * a->OH * a->OW + 63) / 64) * ((a->rows + 127) / 128);
         const long long gran = (long long)a->R * a->S * (a->Ca >> 4);
         if (v == VAR_BAND) band_tiles += tiles;
         work += tiles * gran;
+        work64 += (a->rows <= 64 ? 1 : 2) * tiles * gran;
+        narrow += a->rows <= 64;
+        ++passes;
         longest = std::max(longest, gran);
     }
-    if (band_tiles > (fwd && w.lines ? 4000 : 3000)) return 0;
-    return 5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64;
+    // in hundredths of (512 block slots x the longest reduction), against twice the work64 units
+    const long long least = !fwd ? 45 : narrow == passes ? 40 : 55;
+    const bool rows64 = narrow > 0 && 100 * work64 >= 2 * least * 512 * longest;
+    if (band_tiles > (fwd && w.lines ? 4000 : 3000)) return apart;
+    if (rows64) return TrioTile{narrow == passes ? 64 : 128, true};
+    return TrioTile{5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64, false};
 }
 
-hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st) {
+hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st) {
+    const int bn = tile.bn;
     IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
     TrioBlocks n;
     n.wgrad = w.lines ? wgrad_lines_grid(w) : wgrad_grid(w);
     n.wgrad8 = (n.wgrad + 7) & ~7u;
-    n.fwd = fwd ? igemm_plain_blocks(&f, bn) : 0;
-    const unsigned nb = igemm_plain_blocks(&b, bn);
+    n.fwd64 = tile.rows64 && f.rows <= 64;
+    n.bwd64 = tile.rows64 && b.rows <= 64;
+    n.fwd = fwd ? igemm_plain_blocks(&f, n.fwd64 ? 64 : 128, n.fwd64 ? 128 : bn) : 0;
+    const unsigned nb = igemm_plain_blocks(&b, n.bwd64 ? 64 : 128, n.bwd64 ? 128 : bn);
     if ((fwd && !n.fwd) || !nb) return hipErrorInvalidValue;
     const dim3 grid(n.wgrad8 + n.fwd + nb);
     const bool stg = ((f.OH * f.OW) & 3) == 0 && ((b.OH * b.OW) & 3) == 0;

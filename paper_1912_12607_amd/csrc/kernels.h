@@ -185,7 +185,7 @@ size_t igemm_s2d(IgemmArgs* a);
 hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st);
 // Blocks of the 128 x bn tiles of igemm_dma_tile over a pass that is not split by pixel classes (0: it is); fills what
 // launch_igemm() would.
-unsigned igemm_plain_blocks(IgemmArgs* a, int bn);
+unsigned igemm_plain_blocks(IgemmArgs* a, int bm, int bn);
 // forward pass that quantizes fp32 activations in its load path; 1 x 1 filter, stride 1, no padding
 hipError_t launch_igemm_fused(const IgemmArgs& a, hipStream_t st);
 // conv_band.hip: LDS-resident variant for small filter banks; false = shape not covered
@@ -275,9 +275,13 @@ __host__ __device__ inline bool wgrad_xcd_mapping(int splits) {
 // ---- conv_trio.hip (the three dense passes of a layer in one launch) ---------------------------
 // Column width of the implicit-GEMM tiles with which the passes share a launch, 0: they run one by one.  w: after wgrad_plan();
 // fwd: nullptr where only the two backward passes run.
-int conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
+struct TrioTile {
+    int bn;          // columns of the 128-row tiles, 0: the passes run one by one
+    bool rows64;     // 64 x 128 tiles for the passes of at most 64 rows
+};
+TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
 bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd);    // the forward pass is better launched ahead, by itself
-hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, int bn, hipStream_t st);
+hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st);
 
 // ---- conv_dw.hip (depthwise, planar codes) ----------------------------------------------------
 struct DwArgs {

@@ -382,3 +382,37 @@ def test_codes_of_rows(N, C):
                 g64 = finite.astype(np.float64).reshape(-1)
                 dw = 1.0 - (g64 @ ref) / (np.sqrt(g64 @ g64) * np.sqrt(ref @ ref)) if ref.any() else 1.0
                 assert abs(d.item() - dw) < 1e-9
+
+
+# Passes of at most 64 rows on 64 x 128 tiles in the shared launch: all of them, the forward or the backward-data pass beside a wider
+# one, rows that end inside a fragment, planes of whole 16-byte groups and others, the last column tile ragged; and layers just
+# below the rule's bound, which stay on 128-row tiles.  The calls one by one are the other kernels.
+@pytest.mark.parametrize("shape", [(20, 40, 30, 30, 24, 3, 3), (25, 33, 27, 27, 64, 3, 3), (20, 5, 30, 31, 64, 5, 5), (26, 64, 23, 29, 7, 1, 7), (32, 200, 28, 28, 20, 3, 3),
+                                   (32, 20, 28, 28, 200, 3, 3), (33, 48, 27, 27, 130, 3, 1), (15, 40, 30, 30, 24, 3, 3), (27, 200, 28, 28, 20, 3, 3),
+                                   (64, 40, 31, 31, 130, 1, 1)])
+@pytest.mark.parametrize("passes", [B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT])
+def test_narrow_passes_in_one_launch(shape, passes):
+    N, C, H, W, K, R, S = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(13)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    outs = [st.dx, st.dw, st.dx_acc, st.dw_acc] + ([st.y, st.y_acc] if passes & B.STEP_FWD else [])
+    for t in outs:
+        t.fill_(7)
+    B.int8t_profile_start("conv_trio_kernel")
+    B.int8t_layer_step(st.desc, st._layer_buffers, passes)
+    torch.cuda.synchronize()
+    assert B.int8t_profile_stop()
+    got = [t.clone() for t in outs]
+    for t in outs:
+        t.fill_(7)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    torch.cuda.synchronize()
+    for a, b in zip(got, outs):
+        assert torch.equal(a, b)
