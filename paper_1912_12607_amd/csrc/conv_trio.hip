@@ -119,7 +119,9 @@ TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradA
     // in hundredths of (512 block slots x the longest reduction), against twice the work64 units
     const long long least = !fwd ? 45 : narrow == passes ? 40 : 55;
     const bool rows64 = narrow > 0 && 100 * work64 >= 2 * least * 512 * longest;
-    if (band_tiles > (fwd && w.lines ? 4000 : 3000)) return apart;
+    // (narrow 1x1 layers also where backward-weight works on lines: 24 -> 144 at 56 x 56, batch 64, 3136 tiles: 54 either way)
+    const bool narrow1 = w.R * w.S == 1 && !(w.Cp >= 128 && w.Kp >= 128) && !(w.Cp >= 256 && w.Kp >= 64);
+    if (band_tiles > (fwd && w.lines && !narrow1 ? 4000 : 3000)) return apart;
     if (rows64) return TrioTile{narrow == passes ? 64 : 128, true};
     return TrioTile{5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64, false};
 }

@@ -90,12 +90,19 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a) {
 }
 
 // The kernel VAR_AUTO runs: wgrad_lines_kernel wherever it applies (measured on the benchmark's 1x7, 7x1
-// and 3x3 layers it needs 0.6 - 0.85 of wgrad_kernel's time), except for 1x1 filters on few channels: its
-// 128 x 128 tile is mostly padding there (24 or 144 channels: 18 - 19 us against 17.5); with 256 or more input
-// channels 64 filters are enough (56 x 56, 256 -> 64: 19.9 us against 27.5).
+// and 3x3 layers it needs 0.6 - 0.85 of wgrad_kernel's time), for 1x1 filters with fewer than 128 channels on one side where
+//  - there are 256 input channels (the other kernel's 256-channel tile reads the gradient 16 images at a time and is slower at
+//    every size: 21 random layers, 0.79 of its time alone and 0.56 in the shared launch of the three passes), or
+//  - the 32-line chunks are at least as many as the positions of a line (a batch of 32, on square images).  A chunk is walked position
+//    by position: with fewer, long ones most compute units have nothing to do (16 -> 24, 73 x 73, batch 16: 9.3 against 16.9 us).
+//    Over 100 random layers 0.95 alone, 0.92 in the shared launch (40 -> 700, 20 x 20, batch 256: 36.6 and 23.5; 96 -> 512 at
+//    28 x 28, batch 64: 21.2, 18.1; 64 -> 256 at 56 x 56, batch 256: 56.2, 52.9) -- but not for less than a hundred channels in all on
+//    large images, where its 128 x 128 tile is mostly padding (24 -> 16, 70 x 70, batch 256: 29.1 against 37.5; 16 -> 40, 62 x 62,
+//    batch 40: 11.2, 15.8).
 bool wgrad_auto_lines(const WgradArgs& a) {
     if (!wgrad_lines_applies(a)) return false;
-    return !(a.R == 1 && a.S == 1) || (a.Cp >= 128 && a.Kp >= 128) || (a.Cp >= 256 && a.Kp >= 64);
+    if (!(a.R == 1 && a.S == 1) || (a.Cp >= 128 && a.Kp >= 128) || a.Cp >= 256) return true;
+    return (long long)a.N * a.P >= 32ll * a.Q && !(a.Cp + a.Kp <= 96 && a.P * a.Q >= 1024);
 }
 
 size_t wgrad_s2d(WgradArgs* a) {

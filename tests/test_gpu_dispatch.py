@@ -416,3 +416,13 @@ def test_narrow_passes_in_one_launch(shape, passes):
     torch.cuda.synchronize()
     for a, b in zip(got, outs):
         assert torch.equal(a, b)
+
+
+# Backward-weight of 1x1 filters with few channels on one side, either side of the bounds between its two kernels: 256 input
+# channels, a batch of 32 on square and other images and under a stride, less than a hundred channels in all on large images.
+@pytest.mark.parametrize("shape", [(2, 256, 5, 7, 8, 1, 1, 1, (0, 0)), (2, 240, 5, 7, 8, 1, 1, 1, (0, 0)), (31, 40, 6, 6, 20, 1, 1, 1, (0, 0)),
+                                   (32, 40, 6, 6, 20, 1, 1, 1, (0, 0)), (9, 24, 28, 7, 130, 1, 1, 1, (0, 0)), (33, 3, 9, 9, 250, 1, 1, 2, (0, 0)),
+                                   (32, 48, 32, 32, 33, 1, 1, 1, (0, 0)), (32, 64, 32, 32, 33, 1, 1, 1, (0, 0)), (64, 100, 1, 1, 70, 1, 1, 1, (0, 0))])
+def test_backward_weight_narrow_1x1(shape):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 3)
+    conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
