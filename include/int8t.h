@@ -322,6 +322,18 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc *desc,
                                    void *ws_dev, size_t ws_bytes, void *stream);
 
 /*
+ * The same with the scratch that an int8t_conv_fwd on this layer and these codes xq was given, its contents unchanged since (and that
+ * call ordered before this one): where both passes of a layer rewrite the codes of a first (stride 2 on at most 4 channels),
+ * the forward pass's are used.  fwd_ws_dev NULL, or of fewer bytes than int8t_workspace_bytes(INT8T_OP_CONV_FWD, ..): as int8t_conv_bwd_weight.
+ */
+int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc *desc,
+                                       const int8_t *xq_dev, const float *sx_dev,
+                                       const int8_t *dyq_dev, const float *sdy_dev,
+                                       float *dw_dev, int32_t *acc_dev,
+                                       void *ws_dev, size_t ws_bytes,
+                                       const void *fwd_ws_dev, size_t fwd_ws_bytes, void *stream);
+
+/*
  * The calls of one layer's training step (Sec.3.4) in one: what int8t_quantize_batch_prepare, int8t_dsgc_search,
  * int8t_quantize of g_z and the three convolutions write, bit for bit, in fewer launches -- calls that do not depend on
  * one another share a launch, and a step of a small layer is a chain of launches before it is anything else.
@@ -434,7 +446,7 @@ int8t_variant int8t_conv_selected_variant(int8t_op op, const int8t_conv_desc *de
  *            "absmax_batch_kernel", "quantize_batch_kernel", "quantize_act_kernel", "quantize_planar_kernel", "quantize_wgt_kernel",
  *            "deviation_finish_kernel", "igemm_kernel", "igemm_dma_kernel", "igemm_fused_kernel", "igemm_reduce_kernel",
  *            "band_kernel", "band_reg_kernel", "wgrad_kernel", "wgrad_lines_kernel", "wgrad_reduce_kernel", "s2d_repack_kernel",
- *            "s2d_weights_kernel", "conv_trio_kernel", "dw_conv_kernel" (every depthwise forward / backward-data variant),
+ *            "s2d_weights_kernel" (now part of the former; never launched), "conv_trio_kernel", "dw_conv_kernel" (every depthwise forward / backward-data variant),
  *            "dw_wgrad_kernel" (every depthwise backward-weight variant), "dw_wgrad_reduce_kernel", "dw_trio_kernel");
  *            NULL or "" selects every kernel.
  *            An unknown name returns INT8T_ERR_ARG and leaves timing off.

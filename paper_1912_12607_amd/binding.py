@@ -28,7 +28,7 @@ MAX_BATCH = 8
 EXPORTS = ["int8t_status_string", "int8t_code_bytes", "int8t_unpack_codes", "int8t_workspace_bytes",
            "int8t_quantize_workspace_bytes", "int8t_quantize", "int8t_quantize_batch_workspace_bytes",
            "int8t_quantize_batch", "int8t_quantize_batch_prepare", "int8t_dsgc_clip", "int8t_dsgc_clip_static", "int8t_dsgc_prepare", "int8t_dsgc_search", "int8t_conv_fwd", "int8t_conv_fwd_fused",
-           "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_dclr_scale",
+           "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_conv_bwd_weight_fwd", "int8t_dclr_scale",
            "int8t_layer_step", "int8t_layer_backward", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
            "int8t_profile_start", "int8t_profile_start_sampled", "int8t_profile_stop", "int8t_profile_mfma_ceiling"]
 
@@ -103,6 +103,8 @@ def _load():
         f = getattr(L, name)
         f.restype = i32
         f.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+    L.int8t_conv_bwd_weight_fwd.restype = i32
+    L.int8t_conv_bwd_weight_fwd.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp, sz, vp]
     L.int8t_conv_fwd_fused.restype = i32
     L.int8t_conv_fwd_fused.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.int8t_layer_step.restype = i32
@@ -288,6 +290,11 @@ def int8t_conv_bwd_data(desc, dyq, sdy, wq, sw, dx, acc=None, ws=None, stream=No
 def int8t_conv_bwd_weight(desc, xq, sx, dyq, sdy, dw, acc=None, ws=None, stream=None):
     _check(lib.int8t_conv_bwd_weight(C.byref(desc), _ptr(xq), _ptr(sx), _ptr(dyq), _ptr(sdy), _ptr(dw),
                                      _ptr(acc), _ptr(ws), _nbytes(ws), _stream(stream)))
+
+
+def int8t_conv_bwd_weight_fwd(desc, xq, sx, dyq, sdy, dw, acc=None, ws=None, fwd_ws=None, stream=None):
+    _check(lib.int8t_conv_bwd_weight_fwd(C.byref(desc), _ptr(xq), _ptr(sx), _ptr(dyq), _ptr(sdy), _ptr(dw), _ptr(acc),
+                                         _ptr(ws), _nbytes(ws), _ptr(fwd_ws), _nbytes(fwd_ws), _stream(stream)))
 
 
 def layer_buffers(**fields) -> LayerBuffers:

@@ -120,6 +120,8 @@ DwArgs dw_wgrad_args(const int8t_conv_desc* d, const Geo& g) {
     return a;
 }
 
+size_t fwd_s2d_bytes(const int8t_conv_desc* d, const Geo& g);
+
 // geometry of the implicit GEMMs (pointers are set by the entry points)
 void fill_igemm_fwd(IgemmArgs* a, const int8t_conv_desc* d, const Geo& g) {
     a->N = d->N; a->rows = d->K; a->Ca = pad16(d->C);
@@ -139,6 +141,14 @@ void fill_igemm_bwd_data(IgemmArgs* a, const int8t_conv_desc* d, const Geo& g) {
 // library's own choice.  Process-wide, guarded by a mutex (a lookup per convolution call).
 std::mutex g_variant_mutex;
 std::map<std::array<int, 13>, int> g_variant_table;
+
+// What the forward pass of a layer that runs in space-to-depth form puts at the front of its scratch, 0: another layer
+size_t fwd_s2d_bytes(const int8t_conv_desc* d, const Geo& g) {
+    if (g.depthwise) return 0;
+    IgemmArgs a{};
+    fill_igemm_fwd(&a, d, g);
+    return igemm_s2d(&a);
+}
 
 std::array<int, 13> variant_key(int8t_op op, const int8t_conv_desc* d) {
     return {(int)op, d->N, d->C, d->H, d->W, d->K, d->R, d->S, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->groups};
@@ -700,11 +710,17 @@ int8t_status int8t_conv_bwd_data(const int8t_conv_desc* desc, const int8_t* dyq_
 int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq_dev, const float* sx_dev,
                                    const int8_t* dyq_dev, const float* sdy_dev, float* dw_dev, int32_t* acc_dev,
                                    void* ws_dev, size_t ws_bytes, void* stream) {
+    return int8t_conv_bwd_weight_fwd(desc, xq_dev, sx_dev, dyq_dev, sdy_dev, dw_dev, acc_dev, ws_dev, ws_bytes, nullptr, 0, stream);
+}
+
+int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, const float* sx_dev,
+                                       const int8_t* dyq_dev, const float* sdy_dev, float* dw_dev, int32_t* acc_dev,
+                                       void* ws_dev, size_t ws_bytes, const void* fwd_ws_dev, size_t fwd_ws_bytes, void* stream) {
     Geo g;
     int8t_status s = desc_ok(desc, &g);
     if (s != INT8T_OK) return s;
     if (!xq_dev || !sx_dev || !dyq_dev || !sdy_dev || !dw_dev || !ws_dev) return INT8T_ERR_NULL;
-    if (!aligned16(xq_dev) || !aligned16(dyq_dev) || !aligned16(dw_dev) || !aligned4(acc_dev) || !aligned16(ws_dev))
+    if (!aligned16(xq_dev) || !aligned16(dyq_dev) || !aligned16(dw_dev) || !aligned4(acc_dev) || !aligned16(ws_dev) || !aligned16(fwd_ws_dev))
         return INT8T_ERR_ARG;
     if (ws_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
@@ -722,7 +738,28 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc* desc, const int8_t* xq
     a.x = xq_dev; a.dy = dyq_dev; a.sa = sx_dev; a.sb = sdy_dev; a.dw = dw_dev; a.acc = acc_dev;
     a.partial = (int32_t*)ws_dev;
     a.xs = (int8_t*)ws_dev + align256((size_t)a.splits * a.K * a.R * a.S * a.Cp * 4);
+    if (fwd_ws_dev && fwd_s2d_bytes(desc, g) && fwd_ws_bytes >= fwd_s2d_bytes(desc, g)) {
+        a.xs = (int8_t*)const_cast<void*>(fwd_ws_dev);      // (read only)
+        a.xs_ready = 1;
+    }
     return launch_wgrad(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+}
+
+// Whether the codes of a that the forward pass of a step leaves in its scratch (int8t_conv_bwd_weight_fwd) are still there when
+// backward-weight runs: nothing that is written from then on overlaps them.
+static bool fwd_scratch_kept(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool bwd_data) {
+    const size_t bytes = fwd_s2d_bytes(d, g);
+    if (!b->ws_fwd || !bytes || b->ws_fwd_bytes < bytes) return false;
+    struct Range { const void* p; size_t n; };
+    const size_t nx = (size_t)d->N * d->C * d->H * d->W * 4, ny = (size_t)d->N * d->K * g.P * g.Q * 4, nw = (size_t)d->K * d->C * d->R * d->S * 4;
+    const Range r[] = {{b->y, ny}, {b->y_acc, ny}, {bwd_data ? b->dx : nullptr, nx}, {bwd_data ? b->dx_acc : nullptr, nx},
+                       {bwd_data ? b->ws_bwd_data : nullptr, b->ws_bwd_data_bytes}, {b->ws_bwd_weight, b->ws_bwd_weight_bytes}, {b->dw, nw}, {b->dw_acc, nw}};
+    const uintptr_t q = (uintptr_t)b->ws_fwd;
+    for (const Range& t : r) {
+        const uintptr_t p = (uintptr_t)t.p;
+        if (p && p < q + bytes && q < p + t.n) return false;
+    }
+    return true;
 }
 
 // Whether what the three passes of a step write overlaps nothing that one of them reads or writes, so that they may run
@@ -926,8 +963,11 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         s = int8t_conv_bwd_data(desc, b->dyq, b->sdy, b->wq, b->sw, b->dx, b->dx_acc, b->ws_bwd_data, b->ws_bwd_data_bytes, stream);
         if (s != INT8T_OK) return s;
     }
-    if (bwd_weight)
-        return int8t_conv_bwd_weight(desc, b->xq, b->sx, b->dyq, b->sdy, b->dw, b->dw_acc, b->ws_bwd_weight, b->ws_bwd_weight_bytes, stream);
+    if (bwd_weight) {
+        const bool kept = fwd && fwd_scratch_kept(desc, g, b, bwd_data);
+        return int8t_conv_bwd_weight_fwd(desc, b->xq, b->sx, b->dyq, b->sdy, b->dw, b->dw_acc, b->ws_bwd_weight, b->ws_bwd_weight_bytes,
+                                         kept ? b->ws_fwd : nullptr, kept ? b->ws_fwd_bytes : 0, stream);
+    }
     return INT8T_OK;
 }
 

@@ -267,8 +267,10 @@ unsigned wgrad_grid(const WgradArgs& a) {
 hipError_t launch_wgrad(const WgradArgs& a_in, hipStream_t st) {
     WgradArgs a = a_in;
     if (a.s2d) {
-        hipError_t e = launch_s2d_repack(a.x, a.xs, a.N, a.oH, a.oW, a.oC, st);
-        if (e != hipSuccess) return e;
+        if (!a.xs_ready) {
+            const hipError_t e = launch_s2d_repack(a.x, a.xs, a.N, a.oH, a.oW, a.oC, nullptr, nullptr, 0, 0, 0, S2dGeo{}, st);
+            if (e != hipSuccess) return e;
+        }
         a.x = a.xs;
     }
     const dim3 grid(wgrad_grid(a));

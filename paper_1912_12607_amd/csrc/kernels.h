@@ -215,10 +215,9 @@ inline S2dGeo s2d_geometry(int R, int S, int pad_h, int pad_w) {
     g.S2 = (S + g.ew + 1) / 2;
     return g;
 }
-// input codes [N][H][W][16] -> [N][ceil(H/2)][ceil(W/2)][16]
-hipError_t launch_s2d_repack(const int8_t* x, int8_t* xs, int N, int H, int W, int C, hipStream_t st);
-// filter codes [K][R][S][16] -> [K][R2][S2][16]
-hipError_t launch_s2d_weights(const int8_t* w, int8_t* ws, int K, int R, int S, int C, const S2dGeo& g, hipStream_t st);
+// input codes [N][H][W][16] -> [N][ceil(H/2)][ceil(W/2)][16] and, unless w is nullptr, filter codes [K][R][S][16] -> [K][R2][S2][16]
+hipError_t launch_s2d_repack(const int8_t* x, int8_t* xs, int N, int H, int W, int C, const int8_t* w, int8_t* ws, int K, int R, int S,
+                             const S2dGeo& g, hipStream_t st);
 
 // ---- conv_wgrad.hip (dense backward-weight) ---------------------------------------------------
 struct WgradArgs {
@@ -243,6 +242,7 @@ struct WgradArgs {
     int s2d;                     // 1: C, Cp, H, W, R, S, strides and pads describe the rewritten problem
     int oC, oR, oS, oH, oW, eh, ew;   // the layer's own channels, filter and image; tap r = 2 r' + dy - eh, s = 2 s' + dx - ew
     int8_t* xs;                  // scratch: the input codes in space-to-depth form, [N][H][W][16]
+    int xs_ready;                // they are there already (the forward pass made them)
     int variant;                 // VAR_AUTO or a VAR_WGRAD_*: set before wgrad_plan()
     int lines;                   // filled by wgrad_plan(): 1 = wgrad_lines_kernel runs (TB = taps along the line)
     int xgk, xgc;                // ... and its patches of output tiles per XCD: xgk x xgc = 8, or 0 0: tiles dealt by share

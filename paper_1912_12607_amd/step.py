@@ -155,6 +155,8 @@ class LayerStep:
                                   p(self.dx_acc), p(self.ws_bwd_data), nb(self.ws_bwd_data))
         self._k_bwd_weight = B.bind(lib.int8t_conv_bwd_weight, d, p(self.xq), p(self.sx), p(self.dyq), p(self.sdy), p(self.dw),
                                     p(self.dw_acc), p(self.ws), nb(self.ws))
+        self._k_bwd_weight_fwd = B.bind(lib.int8t_conv_bwd_weight_fwd, d, p(self.xq), p(self.sx), p(self.dyq), p(self.sdy), p(self.dw),
+                                        p(self.dw_acc), p(self.ws), nb(self.ws), p(self.ws_fwd), nb(self.ws_fwd))
         a_search = (p(self.dy), n_y, p(self.ratios), self.n_cand, B.ROUND_STOCHASTIC)
         b_search = (p(self.clip), p(self.dev_search), p(self.dev_all), p(self.ws_dy), nb(self.ws_dy))
         a_qdy = (p(self.dy), B._dims(L.y_shape), self.act_kind, p(self.clip), B.ROUND_STOCHASTIC)
@@ -345,7 +347,8 @@ class LayerStep:
             if self.input_grad:
                 self._k_bwd_data(mp)
             if mode != 3:
-                self._k_bwd_weight(mp)
+                # (mode 1: this step's forward pass is done, what it made of the codes of a lies in its scratch)
+                (self._k_bwd_weight_fwd if mode == 1 and not self.fused_fwd else self._k_bwd_weight)(mp)
         else:
             self._k_step(B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, seed, mp)
         if early or mode == 3:

@@ -426,3 +426,46 @@ def test_narrow_passes_in_one_launch(shape, passes):
 def test_backward_weight_narrow_1x1(shape):
     desc, od, (xq, wq, dyq) = random_layer(shape, 3)
     conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
+
+
+# Layers that run in space-to-depth form: backward-weight on what the forward pass made of the codes, in one call, in calls of their
+# own and on two streams, against the pass that makes it itself; not where something may be written over it in between: one
+# scratch for both passes, whose partial results then lie on the codes, and the schedule whose backward pass does not wait for the forward one.
+@pytest.mark.parametrize("shape", [(3, 3, 33, 30, 24, 7, 7, 3), (2, 4, 16, 16, 40, 3, 3, 1), (5, 1, 11, 17, 130, 5, 5, 2)])
+def test_backward_weight_on_the_forward_passes_codes(shape):
+    N, C, H, W, K, R, S, pad = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(2, 2), pad=(pad, pad), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False, input_grad=False)
+    g = torch.Generator(device=DEV).manual_seed(14)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    st.dw.fill_(7)
+    st.bwd_weight()
+    torch.cuda.synchronize()
+    want = [st.dw.clone(), st.dw_acc.clone()]
+
+    def check(run, repacks):
+        st.dw.fill_(7)
+        st.dw_acc.fill_(7)
+        B.int8t_profile_start("s2d_repack_kernel")
+        run()
+        torch.cuda.synchronize()
+        assert B.int8t_profile_stop()["s2d_repack_kernel"][0] == repacks
+        assert torch.equal(st.dw, want[0]) and torch.equal(st.dw_acc, want[1])
+
+    def apart():
+        st.fwd()
+        B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, st.ws, st.ws_fwd)
+
+    check(lambda: st.run(seed=5, overlap=0), 1)
+    check(lambda: st.run(seed=5, overlap=1), 1)
+    check(lambda: st.run(seed=5, overlap=4), 2)
+    check(apart, 1)
+    check(lambda: (st.fwd(), B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, st.ws, None)), 2)
+    both = B.STEP_FWD | B.STEP_BWD_WEIGHT
+    buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+    shared = torch.empty(max(st.ws.numel(), st.ws_fwd.numel()), dtype=torch.uint8, device=DEV)
+    buf.ws_fwd = buf.ws_bwd_weight = shared.data_ptr()
+    check(lambda: B.int8t_layer_step(st.desc, buf, both), 2)
