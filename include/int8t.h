@@ -390,6 +390,13 @@ int8t_status int8t_layer_backward(const int8t_conv_desc *desc, const int8t_layer
                                   float *db_dev, void *stream);
 
 /*
+ * The forward pass of a layer nobody wants the codes of (a network in use): y as int8t_layer_step with INT8T_STEP_ABSMAX,
+ * INT8T_STEP_QUANT_XW and INT8T_STEP_FWD writes it, bit for bit; the same buffers are required, but what is in xq, wq, sx and sw
+ * afterwards is undefined (a 1x1 layer with few filters quantizes inside the convolution).
+ */
+int8t_status int8t_layer_infer(const int8t_conv_desc *desc, const int8t_layer_buffers *b, void *stream);
+
+/*
  * Choice of the kernel per layer by measurement "before training" (Suppl. "INT8 Convolution", last
  * paragraph: the paper picks between its two convolution algorithms per layer; here the choice is
  * among this library's kernels for a pass).  Every variant computes the same integer sums, so the
@@ -447,7 +454,7 @@ int8t_variant int8t_conv_selected_variant(int8t_op op, const int8t_conv_desc *de
  *            "deviation_finish_kernel", "igemm_kernel", "igemm_dma_kernel", "igemm_fused_kernel", "igemm_reduce_kernel",
  *            "band_kernel", "band_reg_kernel", "wgrad_kernel", "wgrad_lines_kernel", "wgrad_reduce_kernel", "s2d_repack_kernel",
  *            "s2d_weights_kernel" (now part of the former; never launched), "conv_trio_kernel", "dw_conv_kernel" (every depthwise forward / backward-data variant),
- *            "dw_wgrad_kernel" (every depthwise backward-weight variant), "dw_wgrad_reduce_kernel", "dw_trio_kernel");
+ *            "dw_wgrad_kernel" (every depthwise backward-weight variant), "dw_wgrad_reduce_kernel", "dw_trio_kernel", "infer_1x1_kernel");
  *            NULL or "" selects every kernel.
  *            An unknown name returns INT8T_ERR_ARG and leaves timing off.
  * int8t_profile_stop waits for the recorded events, writes one entry per kernel that was

@@ -93,10 +93,14 @@ class _Int8ConvFn(torch.autograd.Function):
             raise RuntimeError(f"weight of {w.numel()} elements in a layer of {buf.w_numel}")
         xq, sx = buf.take_xq()
         y = torch.empty(x_shape[:-1] + (buf.y_shape[1],) if linear else buf.y_shape, dtype=torch.float32, device=x.device)
-        # codes of the activations and the weights (one absmax launch, one quantize launch) and the convolution
+        # codes of the activations and the weights (one absmax launch, one quantize launch) and the convolution; where no backward
+        # pass will come for the codes, the library may do without them
         b = B.LayerBuffers.from_buffer_copy(buf._fwd)
         b.x, b.w, b.xq, b.sx, b.y = _device(x), _device(w), xq.data_ptr(), sx.data_ptr(), y.data_ptr()
-        B.int8t_layer_step(buf.desc, b, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_FWD)
+        if keep:
+            B.int8t_layer_step(buf.desc, b, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_FWD)
+        else:
+            B.int8t_layer_infer(buf.desc, b)
         if bias is not None:
             y.add_(bias if linear else bias.view(1, -1, 1, 1))
         if keep:      # a backward pass will come for the codes

@@ -29,7 +29,7 @@ EXPORTS = ["int8t_status_string", "int8t_code_bytes", "int8t_unpack_codes", "int
            "int8t_quantize_workspace_bytes", "int8t_quantize", "int8t_quantize_batch_workspace_bytes",
            "int8t_quantize_batch", "int8t_quantize_batch_prepare", "int8t_dsgc_clip", "int8t_dsgc_clip_static", "int8t_dsgc_prepare", "int8t_dsgc_search", "int8t_conv_fwd", "int8t_conv_fwd_fused",
            "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_conv_bwd_weight_fwd", "int8t_dclr_scale",
-           "int8t_layer_step", "int8t_layer_backward", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
+           "int8t_layer_step", "int8t_layer_backward", "int8t_layer_infer", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
            "int8t_profile_start", "int8t_profile_start_sampled", "int8t_profile_stop", "int8t_profile_mfma_ceiling"]
 
 
@@ -109,6 +109,8 @@ def _load():
     L.int8t_conv_fwd_fused.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.int8t_layer_step.restype = i32
     L.int8t_layer_step.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp]
+    L.int8t_layer_infer.restype = i32
+    L.int8t_layer_infer.argtypes = [dp, C.POINTER(LayerBuffers), vp]
     L.int8t_layer_backward.restype = i32
     L.int8t_layer_backward.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp, vp]
     L.int8t_conv_variant_ok.restype = i32
@@ -316,6 +318,10 @@ def int8t_layer_step(desc, buffers: LayerBuffers, parts: int = STEP_ALL, seed: i
 
 def int8t_layer_backward(desc, buffers: LayerBuffers, parts: int, seed: int = 0, db=None, stream=None):
     _check(lib.int8t_layer_backward(C.byref(desc), C.byref(buffers), parts, seed, _ptr(db), _stream(stream)))
+
+
+def int8t_layer_infer(desc, buffers: LayerBuffers, stream=None):
+    _check(lib.int8t_layer_infer(C.byref(desc), C.byref(buffers), _stream(stream)))
 
 
 def int8t_conv_variant_ok(op: int, desc: ConvDesc, variant: int) -> bool:

@@ -809,10 +809,12 @@ static bool disjoint_step(const int8t_conv_desc* d, const Geo& g, const int8t_la
     return true;
 }
 
-// int8t_layer_step (backward: false) and int8t_layer_backward (true: the first phase of the search without max|a| and max|W|, and
-// the column sums db of g_z).
-static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, bool backward, float* db,
+// int8t_layer_step, int8t_layer_backward (the first phase of the search without max|a| and max|W|, and the column sums db of g_z)
+// and int8t_layer_infer (codes and scales may be left out).
+enum class StepForm { kStep, kBackward, kInfer };
+static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, StepForm form, float* db,
                                void* stream) {
+    const bool backward = form == StepForm::kBackward;
     Geo g;
     int8t_status s = desc_ok(desc, &g);
     if (s != INT8T_OK) return s;
@@ -883,6 +885,21 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
     if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
     if (backward && (prepare || db) && batch_absmax(0, nullptr, nullptr, prepare ? b->dy : nullptr, n_y, b->ws_dy, st, db, b->dy, desc->K) != hipSuccess)
         return INT8T_ERR_RUNTIME;
+    if (form == StepForm::kInfer && !g.depthwise && desc->R == 1 && desc->S == 1 && desc->stride_h == 1 && desc->stride_w == 1 && desc->pad_h == 0 &&
+        desc->pad_w == 0 && !b->y_acc && selected_variant(INT8T_OP_CONV_FWD, desc) == VAR_AUTO) {
+        size_t nx = 0, nw = 0;
+        (void)dims_ok(xd, &nx);
+        (void)dims_ok(wd, &nw);
+        InferArgs a{};
+        a.x = b->x; a.w = b->w; a.y = b->y;
+        a.N = desc->N; a.C = desc->C; a.K = desc->K; a.HW = desc->H * desc->W;
+        a.part_x = batch_partials(b->ws_quant, 0); a.np_x = absmax_blocks(nx);
+        a.part_w = batch_partials(b->ws_quant, 1); a.np_w = absmax_blocks(nw);
+        const uintptr_t y = (uintptr_t)b->y, ye = y + n_y * 4;      // the results are written while the tensors are read
+        const bool apart = (ye <= (uintptr_t)b->x || (uintptr_t)b->x + nx * 4 <= y) && (ye <= (uintptr_t)b->w || (uintptr_t)b->w + nw * 4 <= y) &&
+                           (ye <= (uintptr_t)b->ws_quant || (uintptr_t)b->ws_quant + b->ws_quant_bytes <= y);
+        if (apart && infer_1x1_applies(a)) return launch_infer_1x1(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+    }
     if (search) {
         s = int8t_dsgc_search(b->dy, n_y, b->ratios, b->n_cand, INT8T_ROUND_STOCHASTIC, seed, b->clip, b->dev_search, b->dev_all, b->ws_dy,
                               b->ws_dy_bytes, stream);
@@ -972,12 +989,16 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
 }
 
 int8t_status int8t_layer_step(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, void* stream) {
-    return layer_step(desc, b, parts, seed, false, nullptr, stream);
+    return layer_step(desc, b, parts, seed, StepForm::kStep, nullptr, stream);
 }
 
 int8t_status int8t_layer_backward(const int8t_conv_desc* desc, const int8t_layer_buffers* b, int parts, uint64_t seed, float* db_dev,
                                   void* stream) {
-    return layer_step(desc, b, parts, seed, true, db_dev, stream);
+    return layer_step(desc, b, parts, seed, StepForm::kBackward, db_dev, stream);
+}
+
+int8t_status int8t_layer_infer(const int8t_conv_desc* desc, const int8t_layer_buffers* b, void* stream) {
+    return layer_step(desc, b, INT8T_STEP_ABSMAX | INT8T_STEP_QUANT_XW | INT8T_STEP_FWD, 0, StepForm::kInfer, nullptr, stream);
 }
 
 double int8t_dclr_scale(double d_c, double alpha, double beta) {

@@ -16,20 +16,6 @@
 
 namespace int8t {
 
-// max of the partials of an absmax pass, by one wave
-__device__ __forceinline__ float dwf_wave_partials(const float* __restrict__ part, int nparts, int lane) {
-    float v[kAbsmaxPartials / kWave];
-#pragma unroll
-    for (int u = 0; u < kAbsmaxPartials / kWave; ++u) {
-        const int i = lane + kWave * u;
-        v[u] = part[i < nparts ? i : 0];
-    }
-    float m = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kAbsmaxPartials / kWave; ++u) m = fmaxf(m, v[u]);
-    return wave_max(m);
-}
-
 // Blocks per compute unit (by registers): what a grid is dealt for, so that no block waits for a second round.
 constexpr int dwf_blocks(int U, bool XQ, bool GQ) { return !GQ ? 7 : U > 1 ? 4 : XQ ? 5 : 6; }
 
@@ -53,7 +39,7 @@ __global__ __launch_bounds__(256, dwf_blocks(U, XQ, GQ)) void dw_fused_kernel(co
 
     if (XQ && tid < 2 * kWave) {
         const bool second = tid >= kWave;
-        const float m = dwf_wave_partials(second ? a.part_w : a.part_x, second ? a.np_w : a.np_x, tid & (kWave - 1));
+        const float m = absmax_partials_wave(second ? a.part_w : a.part_x, second ? a.np_w : a.np_x, tid & (kWave - 1));
         if ((tid & (kWave - 1)) == 0) s_max[second] = m;
     }
     // this thread's chunks: place in the run, and in LDS (`brk` bytes at off, the others at off2 behind the end of the row)

@@ -73,20 +73,23 @@ __device__ __forceinline__ float block_max_256(float v, float* lds4) {
 // and leaves the result in LDS -- all blocks of the consuming pass read the same few cache lines, one wave
 // each is enough -- while the other waves go straight on to their loads; everybody picks the value up after
 // a barrier.
+__device__ __forceinline__ float absmax_partials_wave(const float* __restrict__ part, int nparts, int lane) {
+    // (straight-line loads: after a load inside a loop the compiler waits for ALL outstanding loads at
+    // the next register it cannot account for, which serialised the tile loads that follow)
+    float v[kAbsmaxPartials / kWave];
+#pragma unroll
+    for (int u = 0; u < kAbsmaxPartials / kWave; ++u) {
+        const int i = lane + kWave * u;
+        v[u] = part[i < nparts ? i : 0];      // (unconditional: a repeated partial does not change the max)
+    }
+    float m = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kAbsmaxPartials / kWave; ++u) m = fmaxf(m, v[u]);
+    return wave_max(m);
+}
 __device__ __forceinline__ void absmax_partials_begin(const float* __restrict__ part, int nparts, float* lds4) {
     if (threadIdx.x < kWave) {
-        // (straight-line loads: after a load inside a loop the compiler waits for ALL outstanding loads at
-        // the next register it cannot account for, which serialised the tile loads that follow)
-        float v[kAbsmaxPartials / kWave];
-#pragma unroll
-        for (int u = 0; u < kAbsmaxPartials / kWave; ++u) {
-            const int i = (int)threadIdx.x + kWave * u;
-            v[u] = part[i < nparts ? i : 0];      // (unconditional: a repeated partial does not change the max)
-        }
-        float m = 0.0f;
-#pragma unroll
-        for (int u = 0; u < kAbsmaxPartials / kWave; ++u) m = fmaxf(m, v[u]);
-        m = wave_max(m);
+        const float m = absmax_partials_wave(part, nparts, (int)threadIdx.x);
         if (threadIdx.x == 0) lds4[0] = m;
     }
 }

@@ -283,6 +283,18 @@ TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradA
 bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd);    // the forward pass is better launched ahead, by itself
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st);
 
+// ---- conv_infer.hip (1x1 forward pass from the fp32 tensors, no codes written) -----------------
+struct InferArgs {
+    const float *x, *w;
+    const float *part_x, *part_w;    // absmax partials of a and W
+    int np_x, np_w;
+    float* y;
+    int N, C, K, HW;
+    int tiles_img, tiles;            // tiles of 128 pixels, launch_infer_1x1()
+};
+bool infer_1x1_applies(const InferArgs& a);
+hipError_t launch_infer_1x1(const InferArgs& a, hipStream_t st);
+
 // ---- conv_dw.hip (depthwise, planar codes) ----------------------------------------------------
 struct DwArgs {
     const int8_t* a;             // planar codes, input of the gather ([N][C][IH][IW])

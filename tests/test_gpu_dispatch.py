@@ -469,3 +469,34 @@ def test_backward_weight_on_the_forward_passes_codes(shape):
     shared = torch.empty(max(st.ws.numel(), st.ws_fwd.numel()), dtype=torch.uint8, device=DEV)
     buf.ws_fwd = buf.ws_bwd_weight = shared.data_ptr()
     check(lambda: B.int8t_layer_step(st.desc, buf, both), 2)
+
+
+# The forward pass without codes: one and two row tiles of filters, planes of whole 16-byte groups and others, ragged pixel tiles,
+# more tiles than resident blocks, channels that end inside 64, elements that are no number; layers just outside the rule, and
+# results over the input, which the calls one after the other allow.  Against the step's forward pass, bit for bit.
+@pytest.mark.parametrize("shape,fused", [((3, 144, 20, 20, 24), True), ((2, 64, 9, 9, 32), True), ((5, 3, 16, 14, 33), True), ((1, 200, 8, 8, 40), True),
+                                         ((31, 20, 57, 57, 7), True), ((40, 70, 48, 48, 40), True), ((2, 256, 10, 10, 32), True), ((260, 256, 16, 16, 64), True),
+                                         ((2, 64, 7, 9, 24), False), ((2, 64, 10, 10, 65), False), ((2, 257, 10, 10, 24), False),
+                                         ((2, 256, 10, 10, 33), False), ((2, 65, 9, 9, 8), False), ((2, 16, 9, 9, 33), False), ((42, 16, 57, 57, 8), False)])
+def test_forward_without_codes(shape, fused):
+    N, C, H, W, K = shape
+    L = inputs.Layer("layer", N, C, H, W, K, 1, 1, stride=(1, 1), pad=(0, 0), groups=1)
+    st = LayerStep(L, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(15)
+    for t in (st.x, st.w):
+        t.normal_(generator=g)
+    st.x.view(-1)[11] = float("nan")
+    B.int8t_layer_step(st.desc, st._layer_buffers, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_FWD)
+    torch.cuda.synchronize()
+    want = st.y.clone()
+    st.y.fill_(7)
+    B.int8t_profile_start("infer_1x1_kernel")
+    B.int8t_layer_infer(st.desc, st._layer_buffers)
+    torch.cuda.synchronize()
+    assert bool(B.int8t_profile_stop()) == fused and torch.equal(st.y, want)
+    if K <= C:
+        buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+        buf.y = buf.x
+        B.int8t_layer_infer(st.desc, buf)
+        torch.cuda.synchronize()
+        assert torch.equal(st.x.view(-1)[:want.numel()], want.view(-1))
