@@ -946,7 +946,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         w.partial = (int32_t*)b->ws_bwd_weight;
         hipError_t e = hipSuccess;
         if (launch_dw_trio(fwd ? &f : nullptr, d, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
-    } else if (together && !g.depthwise && desc->stride_h == 1 && desc->stride_w == 1) {
+    } else if (together && !g.depthwise) {
         IgemmArgs f{}, d{};
         WgradArgs w{};
         fill_igemm_fwd(&f, desc, g);
@@ -964,13 +964,18 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         wgrad_plan(&w);
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
-        if (fwd && conv_trio_fwd_apart(f, d)) {
-            if (launch_igemm(f, st) != hipSuccess) return INT8T_ERR_RUNTIME;
-            fwd_left = false;
+        if (desc->stride_h != 1 || desc->stride_w != 1) {
+            if (conv_trio_strided(fwd ? &f : nullptr, d, w))
+                return launch_conv_trio_strided(fwd ? &f : nullptr, d, w, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+        } else {
+            if (fwd && conv_trio_fwd_apart(f, d)) {
+                if (launch_igemm(f, st) != hipSuccess) return INT8T_ERR_RUNTIME;
+                fwd_left = false;
+            }
+            const IgemmArgs* fp = fwd_left ? &f : nullptr;
+            const TrioTile tile = conv_trio_tile(fp, d, w);
+            if (tile.bn) return launch_conv_trio(fp, d, w, tile, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
         }
-        const IgemmArgs* fp = fwd_left ? &f : nullptr;
-        const TrioTile tile = conv_trio_tile(fp, d, w);
-        if (tile.bn) return launch_conv_trio(fp, d, w, tile, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     if (fwd_left) {
         s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);

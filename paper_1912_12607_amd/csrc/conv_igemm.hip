@@ -449,6 +449,27 @@ unsigned igemm_plain_blocks(IgemmArgs* a, int bm, int bn) {
     return ((ctiles + 7) / 8) * 8 * rtiles;
 }
 
+unsigned igemm_strided_blocks(IgemmArgs* a, int* form) {
+    IgemmShape g = igemm_shape(*a);
+    if (igemm_auto_variant(*a) == VAR_WIDE_CELLS) {
+        *form = STRIDED_CELLS;
+        g.cls = true;
+        g.cell = 0;
+        g.cls_h = g.cls_w = 2;
+        g.ncls = 1;
+        g.ncols = (long long)a->N * ((a->OH + 1) / 2) * ((a->OW + 1) / 2);
+    } else {
+        *form = g.cell ? STRIDED_CELL : g.cls ? STRIDED_CLASSES : STRIDED_PLAIN;
+    }
+    a->cls_h = g.cls_h;
+    a->cls_w = g.cls_w;
+    a->cell = g.cell;
+    a->ksplit = 1;
+    const unsigned ctiles = (unsigned)((g.ncols + 63) / 64), rtiles = (unsigned)((a->rows + 127) / 128);
+    a->colrun = igemm_colrun(*a, g, ctiles, *form == STRIDED_CELL || *form == STRIDED_CELLS);
+    return ((ctiles + 7) / 8) * 8 * rtiles * (unsigned)g.ncls;
+}
+
 // The variant the library picks on its own (rules from measurements over the layers of ResNet-50,
 // MobileNetV2 and InceptionV3); a caller may overrule it per layer (include/int8t.h).
 int igemm_auto_variant(const IgemmArgs& a, bool allow_split) {

@@ -162,4 +162,74 @@ hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const Wg
     return e != hipSuccess ? e : launch_wgrad_reduce(w, st);
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same for strided layers whose backward-weight works on image lines (3x3 under stride 2 x 2, 1x1 without padding).  The tiles are
+// the 128 x 64 ones; backward-data in the form it takes by itself: the pixel classes of a cell one after the other in a
+// block, cells with one class of taps, a class per tile, or plain.
+// Over 100 random such layers, us for the three passes one by one and in one launch (0.70 on average), and for the two backward ones (0.77):
+//   3x3, 128 channels, 56 x 56, batch 64       79.0   73.0     60.6   53.8     1x1, 1024 -> 2048, 14 x 14, batch 64   70.5  60.4  50.6  49.7
+//   3x3, 256 channels, 28 x 28, batch 64       72.3   62.0     53.4   48.5     1x1, 544 -> 164, 9 x 9, batch 30       25.1  14.1  19.1  13.3
+//   3x3, 192 -> 320, 17 x 17, pad 0, batch 64  51.2   34.7     39.0   30.2     3x3, 16 -> 32, 16 x 16, batch 2        16.8   8.8  12.9   8.8
+// Apart stay 1x1 layers of many tiles, which are bound by writing results that the wider tiles alone write through LDS
+// (8 -> 360, 31 x 31, batch 216, 5800 tiles: 53.6 against 62.9), passes on 256 x 256 tiles and split reductions.
+// ---------------------------------------------------------------------------------------------
+template <int FORM, bool S2>
+__global__ __launch_bounds__(256, 2) void conv_trio_strided_kernel(const IgemmArgs f, const IgemmArgs b, const WgradArgs w, const TrioBlocks n) {
+    const unsigned block = blockIdx.x;
+    if (block < n.wgrad8) {
+        if (block >= n.wgrad) return;
+        if constexpr (S2) wgrad_lines_tile<3, 1, 1, 3, true>(w, block);
+        else wgrad_lines_tile<1, 2, 2, 4>(w, block);
+    } else if (block < n.wgrad8 + n.fwd) {
+        igemm_dma_tile<false, 2, 8, 2, false, false, 64>(f, block - n.wgrad8);
+    } else {
+        constexpr bool CLS = FORM != STRIDED_PLAIN, CELL = FORM == STRIDED_CELL || FORM == STRIDED_CELLS;
+        igemm_dma_tile<true, 2, 8, 2, CLS, CELL, 64, FORM == STRIDED_CELLS>(b, block - n.wgrad8 - n.fwd);
+    }
+}
+
+bool conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
+    if (w.variant != VAR_AUTO || w.s2d || !w.lines || !(w.TB == 1 || wgrad_lines_s2(w))) return false;
+    long long tiles = 0;
+    for (const IgemmArgs* a : {fwd, &bwd}) {
+        if (!a) continue;
+        if (a->variant != VAR_AUTO || igemm_splits(*a) || igemm_auto_variant(*a) == VAR_WIDE256) return false;
+        const long long pixels = (long long)a->N * a->OH * a->OW;
+        tiles += (pixels + 63) / 64 * ((a->rows + 127) / 128);
+    }
+    return w.TB == 3 || tiles <= 4500;
+}
+
+hipError_t launch_conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, hipStream_t st) {
+    IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
+    TrioBlocks n{};
+    n.wgrad = wgrad_lines_grid(w);
+    n.wgrad8 = (n.wgrad + 7) & ~7u;
+    n.fwd = fwd ? igemm_plain_blocks(&f, 128, 64) : 0;
+    int form = STRIDED_PLAIN;
+    const unsigned nb = igemm_strided_blocks(&b, &form);
+    if ((fwd && !n.fwd) || !nb) return hipErrorInvalidValue;
+    const bool s2 = w.TB == 3;
+    const dim3 grid(n.wgrad8 + n.fwd + nb);
+    const size_t lds = std::max((size_t)2 * (128 + 64) * 8 * 16, w.lds_bytes);
+    KernelTimer kt(KID_CONV_TRIO, st);
+#define LAUNCH(Fv, S2v)                                                                                                            \
+    do {                                                                                                                           \
+        static std::atomic<unsigned long long> attr_done;                                                                         \
+        const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(conv_trio_strided_kernel<Fv, S2v>), 72 * 1024, attr_done); \
+        if (e != hipSuccess) return e;                                                                                             \
+        launch_timed(kt, (conv_trio_strided_kernel<Fv, S2v>), grid, dim3(256), lds, st, f, b, w, n);                               \
+    } while (0)
+    // (3x3 filters have four classes of taps, 1x1 filters one)
+    if (s2 && form == STRIDED_CELLS) LAUNCH(STRIDED_CELLS, true);
+    else if (s2 && form == STRIDED_CLASSES) LAUNCH(STRIDED_CLASSES, true);
+    else if (s2 && form == STRIDED_PLAIN) LAUNCH(STRIDED_PLAIN, true);
+    else if (!s2 && form == STRIDED_CELL) LAUNCH(STRIDED_CELL, false);
+    else if (!s2 && form == STRIDED_PLAIN) LAUNCH(STRIDED_PLAIN, false);
+    else return hipErrorInvalidValue;
+#undef LAUNCH
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_wgrad_reduce(w, st);
+}
+
 }  // namespace int8t

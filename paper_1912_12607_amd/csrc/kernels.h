@@ -186,6 +186,9 @@ hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st);
 // Blocks of the 128 x bn tiles of igemm_dma_tile over a pass that is not split by pixel classes (0: it is); fills what
 // launch_igemm() would.
 unsigned igemm_plain_blocks(IgemmArgs* a, int bm, int bn);
+// Forms of a strided backward-data pass on 128 x 64 tiles, and the one the pass takes by itself; fills the geometry, returns the blocks
+enum StridedForm { STRIDED_PLAIN, STRIDED_CLASSES, STRIDED_CELL, STRIDED_CELLS };
+unsigned igemm_strided_blocks(IgemmArgs* a, int* form);
 // forward pass that quantizes fp32 activations in its load path; 1 x 1 filter, stride 1, no padding
 hipError_t launch_igemm_fused(const IgemmArgs& a, hipStream_t st);
 // conv_band.hip: LDS-resident variant for small filter banks; false = shape not covered
@@ -282,6 +285,9 @@ struct TrioTile {
 TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
 bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd);    // the forward pass is better launched ahead, by itself
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st);
+
+bool conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);      // whether the passes of a strided layer share one
+hipError_t launch_conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, hipStream_t st);
 
 // ---- conv_infer.hip (1x1 forward pass from the fp32 tensors, no codes written) -----------------
 struct InferArgs {

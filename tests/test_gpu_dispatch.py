@@ -500,3 +500,37 @@ def test_forward_without_codes(shape, fused):
         B.int8t_layer_infer(st.desc, buf)
         torch.cuda.synchronize()
         assert torch.equal(st.x.view(-1)[:want.numel()], want.view(-1))
+
+
+# The passes of a strided layer in one launch: 3x3 filters with the four pixel classes of a cell in a block, a class per tile, and plain
+# (short runs of pixels); 1x1 filters in cells of even images, odd images, other strides; paddings, ragged rows and columns, results on
+# planes of no whole 16-byte groups.  Against the calls one by one, bit for bit.
+@pytest.mark.parametrize("shape", [(3, 130, 28, 28, 40, 3, 2, 2, 1), (2, 150, 30, 32, 200, 3, 2, 2, 0), (5, 40, 24, 25, 70, 3, 2, 2, 1), (2, 257, 33, 27, 30, 3, 2, 2, 2),
+                                   (9, 16, 11, 11, 33, 3, 2, 2, 1), (34, 70, 14, 14, 50, 1, 2, 2, 0), (3, 300, 15, 13, 140, 1, 2, 2, 0), (3, 300, 14, 10, 20, 1, 3, 1, 0),
+                                   (2, 260, 9, 12, 33, 1, 1, 2, 0)])
+@pytest.mark.parametrize("passes", [B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT])
+def test_strided_passes_in_one_launch(shape, passes):
+    N, C, H, W, K, R, sh, sw, pad = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, R, stride=(sh, sw), pad=(pad, pad), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(16)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    outs = [st.dx, st.dw, st.dx_acc, st.dw_acc] + ([st.y, st.y_acc] if passes & B.STEP_FWD else [])
+    for t in outs:
+        t.fill_(7)
+    B.int8t_profile_start("conv_trio_kernel")
+    B.int8t_layer_step(st.desc, st._layer_buffers, passes)
+    torch.cuda.synchronize()
+    assert B.int8t_profile_stop()
+    got = [t.clone() for t in outs]
+    for t in outs:
+        t.fill_(7)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    torch.cuda.synchronize()
+    for a, b in zip(got, outs):
+        assert torch.equal(a, b)
