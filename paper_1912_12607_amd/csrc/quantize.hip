@@ -5,6 +5,8 @@
 // written.  The layout change fp32 N,C,H,W -> int8 N,H,W,C (reduction dimension innermost, the
 // analogue of the paper's NC4HW transposition) happens inside the quantize pass through an LDS
 // tile, so it costs no extra HBM traffic.
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -784,13 +786,16 @@ __global__ __launch_bounds__(256) void quantize_wgt_kernel(
 // serves the tensor whose block range holds it and runs that tensor's ordinary pass.
 // ---------------------------------------------------------------------------------------------
 // ANYSTOCH: some item rounds stochastically (Eq.3).  The round-to-nearest launch of a layer's a and
-// W is a kernel of its own, so that it keeps its register count beside the clip search.  RAGGED: some activation tensor has
-// planes of no whole 16-byte groups; those passes need more registers, which the launch without them does not pay for (77 and 79
-// against 40 and 43).  Four blocks per compute unit are enough where nothing runs beside the kernel: with seven, 14 x 14 planes
-// of 1024 channels, batch 128, take 34.1 us instead of 33.0 (beside the clip search they would take 21 instead of 13 us at
-// 12.8 M elements, so the launch of a and W alone keeps its occupancy).
-template <bool ANYSTOCH, bool RAGGED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH && !RAGGED ? 4 : 8))) void quantize_batch_kernel(const QuantBatch b) {
+// W is a kernel of its own, so that it keeps its register count beside the clip search.  ACTS: ACTS_RAGGED, some tensor of
+// N,H,W,Cp codes has planes of no whole 16-byte groups; those passes need more registers, which the launch without them does not
+// pay for (77 and 79 against 40 and 43).  ACTS_EVEN: four blocks per compute unit are enough where nothing runs beside the kernel:
+// with seven, 14 x 14 planes of 1024 channels, batch 128, take 34.1 us instead of 33.0 (beside the clip search they would take 21
+// instead of 13 us at 12.8 M elements, so the launch of a and W alone keeps its occupancy).  ACTS_NONE, planar codes only: they want
+// all the blocks that fit (13 channels at 43 x 43, batch 256, a and g_z: 14.5 us; with four blocks 15.7).
+enum { ACTS_NONE, ACTS_EVEN, ACTS_RAGGED };
+template <bool ANYSTOCH, int ACTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH && ACTS == ACTS_EVEN ? 4 : 8))) void quantize_batch_kernel(const QuantBatch b) {
+    constexpr bool RAGGED = ACTS == ACTS_RAGGED;
     raise_wave_priority();
     // one LDS area for whichever pass this block runs, sized by the host for the tensors of this launch
     // (a 3x3 weight tensor needs 2.3 KB of tile, not the 16 KB of the largest case: the kernel then fits
@@ -806,7 +811,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH
     const int y = rem / t.gx;
     const VBlock vb = {rem - y * t.gx, y, z, t.gx, t.gy, t.gz};
     const bool st = ANYSTOCH && t.stoch;          // block-uniform
-    if (t.kind == 0) {          // activations, N,C,H,W -> N,H,W,Cp
+    if (ACTS != ACTS_NONE && t.kind == 0) {          // activations, N,C,H,W -> N,H,W,Cp
         const int HW = t.d2 * t.d3, Cp = (t.d1 + 15) & ~15;
 #define ACT(STv, VECv) quantize_act_body<STv, false, VECv>(t.x, t.d0, t.d1, Cp, HW, t.clip, t.absmax_part, t.nparts, t.seed_lo, t.seed_hi, t.q, t.scale, nullptr, vb, lds4, atile)
         if (ANYSTOCH && st) {
@@ -860,14 +865,22 @@ hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStrea
     }
     lds = (lds + 15) & ~(size_t)15;
     KernelTimer kt(KID_QUANTIZE_BATCH, st);
-    bool any_stoch = false, ragged = false;
+    bool any_stoch = false;
+    int acts = ACTS_NONE;
     for (int i = 0; i < b.count; ++i) {
         any_stoch = any_stoch || b.it[i].stoch;
-        ragged = ragged || (b.it[i].kind == 0 && ((b.it[i].d2 * b.it[i].d3) & 3) != 0);
+        if (b.it[i].kind == 0) acts = std::max(acts, ((b.it[i].d2 * b.it[i].d3) & 3) != 0 ? (int)ACTS_RAGGED : (int)ACTS_EVEN);
     }
-#define LAUNCH(ST, RG) launch_timed(kt, (quantize_batch_kernel<ST, RG>), dim3(total_blocks), dim3(256), lds, st, b)
-    if (any_stoch) { if (ragged) LAUNCH(true, true); else LAUNCH(true, false); }
-    else { if (ragged) LAUNCH(false, true); else LAUNCH(false, false); }
+#define LAUNCH(ST, ACTSv) launch_timed(kt, (quantize_batch_kernel<ST, ACTSv>), dim3(total_blocks), dim3(256), lds, st, b)
+#define LAUNCH_ACTS(ST)                                             \
+    do {                                                            \
+        if (acts == ACTS_NONE) LAUNCH(ST, ACTS_NONE);               \
+        else if (acts == ACTS_EVEN) LAUNCH(ST, ACTS_EVEN);          \
+        else LAUNCH(ST, ACTS_RAGGED);                               \
+    } while (0)
+    if (any_stoch) LAUNCH_ACTS(true);
+    else LAUNCH_ACTS(false);
+#undef LAUNCH_ACTS
 #undef LAUNCH
     return hipGetLastError();
 }
