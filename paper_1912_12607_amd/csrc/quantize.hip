@@ -227,7 +227,16 @@ __host__ __device__ inline bool quant_act_rows(int HW) { return HW == 1; }
 __host__ __device__ inline int quant_act_gx(int Cp, int HW) {
     return Cp == 16 ? (HW + QA_NARROW_PIX - 1) / QA_NARROW_PIX : (HW + QA_PIX * quant_act_nsub(HW) - 1) / (QA_PIX * quant_act_nsub(HW));
 }
-// grid of the pass over a tensor of N images
+// Blocks are dealt to the 8 XCDs one by one: where planes are not whole 128-byte lines, eight images are walked side by side, one per
+// XCD, so that neighbouring tiles of a plane meet the line they share in one L2 (nearest / stochastic, us: 288 channels, 35 x 35,
+// batch 64: 27.6 / 27.7 -> 22.8 / 25.7; 768, 17 x 17: 17.0 / 17.8 -> 15.1 / 17.4; 64, 147 x 147: 88.3 / 89.0 -> 79.9 / 80.5).
+// Not where the 64-byte runs of codes of neighbouring channel groups are then written too far apart to meet in a line of L2: more
+// than 64 channels on large planes (160, 75 x 75: 54.7 / 59.2 against 66.2 / 67.4; 192, 71 x 71: 61.2 against 63.6).  Nor where the
+// last eight images leave more than a sixteenth of the XCDs' time unused (10 images, 149 x 149: 16.2 against 19.2).
+__host__ __device__ inline bool quant_act_side_by_side(int N, int HW, int gx, int gy) {
+    return (HW & 31) != 0 && gx > 1 && (gy == 1 || HW <= 2048) && (-N & 7) * 16 <= N;
+}
+// grid of the pass over a tensor of N images: tiles of a plane, channel groups, images
 static void quant_act_grid(int N, int Cp, int HW, int* gx, int* gy, int* gz) {
     if (quant_act_rows(HW)) {
         const long long quads = (long long)N * (Cp / 4);
@@ -300,9 +309,13 @@ __device__ __forceinline__ void quantize_rows_body(
     if (DEV) block_store_devpartial(A, G, B, devpart + bx);
 }
 
-// VEC: H*W is a multiple of 4, so a thread can fetch four consecutive pixels of a channel with one
-// 16-byte load; it then owns a 4-channel x 4-pixel block, transposes its codes in registers and
-// writes one dword (4 channels) per pixel to the LDS tile.  Otherwise one pixel per lane, 4-byte loads.
+// A thread fetches four consecutive pixels of a channel with one 16-byte load, of four channels; it then owns a 4-channel x
+// 4-pixel block, transposes its codes in registers and writes one dword (4 channels) per pixel to the LDS tile.  VEC: H*W is a multiple
+// of 4 and the loads start on 16 bytes; otherwise on 4 (global memory takes that), and a plane's last quad reaches into the next plane.
+// (It was one pixel per lane, 4-byte loads there; 160 channels, 78 x 75, batch 78: nearest 81.4 -> 83.1, stochastic 85.2 -> 80.8 us;
+// 64 at 149 x 149, batch 10: 16.4 / 18.9 -> 16.2 / 16.7; 24 at 111 x 111, batch 32: 16.6 / 24.1 -> 14.6 / 21.2.)
+struct QuadF32 { float v[4]; };
+
 template <bool STOCH, bool DEV, bool VEC>
 __device__ __forceinline__ void quantize_act_body(
     const float* __restrict__ x, int N, int C, int Cp, int HW, const float* __restrict__ clip,
@@ -363,53 +376,43 @@ __device__ __forceinline__ void quantize_act_body(
     const float clip_in = clip ? *clip : 0.0f;
     if (!clip) absmax_partials_begin(absmax_part, nparts, lds4);
     const int nsub = quant_act_nsub(HW);
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int pq = threadIdx.x & 15, cgp = threadIdx.x >> 4;      // VEC: pixel quad, 4-channel group
+    const int pq = threadIdx.x & 15, cgp = threadIdx.x >> 4;      // pixel quad, 4-channel group
+    const size_t last4 = (size_t)N * C * HW - 4;                  // (more than 16 channels here)
     float inv = 0.0f, sc = 0.0f;
     double A = 0.0, G = 0.0;
     unsigned long long B = 0;
     for (int sub = 0; sub < nsub; ++sub) {
         const int p0 = (vb.x * nsub + sub) * QA_PIX;
         if (p0 >= HW) break;                                      // (uniform over the block)
-        const int p = p0 + lane;
-        const bool pv = p < HW;
-
-        // issue every global load of this thread before anything depends on them
-        float v[4][4];
-        if (VEC) {
-            // unconditional loads (lanes outside the tensor re-read its first floats and are zeroed afterwards):
-            // with a branch around each load the compiler has been seen to wait for one load before issuing the next
-            float4 f[4];
-            bool ok[4];
+        // issue every global load of this thread before anything depends on them; unconditional loads (lanes outside the tensor
+        // re-read its first floats and are zeroed afterwards): with a branch around each load the compiler has been seen to wait
+        // for one load before issuing the next
+        QuadF32 f[4];
+        float v[4][4];                                            // [channel][pixel]
+        const int pleft = HW - p0 - 4 * pq;                       // pixels of the plane from this quad on
+        const bool whole = p0 + QA_PIX <= HW && c0 + QA_CH <= C;  // (uniform) nothing to zero in this tile
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = c0 + 4 * cgp + j;
-                ok[j] = p0 + 4 * pq < HW && c < C;
-                f[j] = *reinterpret_cast<const float4*>(x + (ok[j] ? ((size_t)n * C + c) * HW + p0 + 4 * pq : (size_t)0));
-            }
-            const bool whole = p0 + QA_PIX <= HW && c0 + QA_CH <= C;      // (uniform) nothing to zero in this tile
+        for (int j = 0; j < 4; ++j) {
+            const int c = c0 + 4 * cgp + j;
+            const size_t at = pleft > 0 && c < C ? ((size_t)n * C + c) * HW + p0 + 4 * pq : (size_t)0;
+            if (VEC) f[j] = *reinterpret_cast<const QuadF32*>(__builtin_assume_aligned(x + at, 16));
+            else f[j] = *reinterpret_cast<const QuadF32*>(x + (at < last4 ? at : last4));
+        }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (!whole && !ok[j]) f[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                v[j][0] = f[j].x; v[j][1] = f[j].y; v[j][2] = f[j].z; v[j][3] = f[j].w;     // v[channel][pixel]
-            }
-        } else {
-            const bool whole = p0 + QA_PIX <= HW && c0 + QA_CH <= C;      // (uniform) nothing to zero in this tile
+        for (int j = 0; j < 4; ++j) {
+            const int c = c0 + 4 * cgp + j;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c = c0 + 4 * (wv + 4 * i) + j;
-                    v[i][j] = x[(pv && c < C) ? ((size_t)n * C + c) * HW + p : (size_t)0];      // unconditional, as above
-                }
-            }
+            for (int k = 0; k < 4; ++k) v[j][k] = f[j].v[k];
             if (!whole) {
+                if (!VEC && c == C - 1 && n == N - 1 && pleft > 0 && pleft < 4) {
+                    // the tensor's last quad: loaded 4 - pleft floats ahead of its place
+                    v[j][0] = pleft == 1 ? f[j].v[3] : pleft == 2 ? f[j].v[2] : f[j].v[1];
+                    v[j][1] = pleft == 2 ? f[j].v[3] : f[j].v[2];
+                    v[j][2] = f[j].v[3];
+                }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (!(pv && c0 + 4 * (wv + 4 * i) + j < C)) v[i][j] = 0.0f;
+                for (int k = 0; k < 4; ++k)
+                    if (c >= C || k >= pleft) v[j][k] = 0.0f;
             }
         }
 
@@ -427,47 +430,27 @@ __device__ __forceinline__ void quantize_act_body(
             __syncthreads();                         // the previous tile's codes have left LDS
         }
 
-        if (VEC) {
-            uint32_t d[4], o[4];
+        uint32_t d[4], o[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = c0 + 4 * cgp + j;
-                int code[4];
+        for (int j = 0; j < 4; ++j) {
+            const int c = c0 + 4 * cgp + j;
+            int code[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t idx = (uint32_t)(((size_t)n * C + c) * HW + p0 + 4 * pq + k);
-                    code[k] = quantize_one<STOCH>(v[j][k], inv, seed_lo, seed_hi_mul, idx);
-                    if (DEV) {
-                        const double g = (double)v[j][k];
-                        A = fma(g, (double)code[k], A);
-                        G = fma(g, g, G);
-                        B += (unsigned)(code[k] * code[k]);
-                    }
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t idx = (uint32_t)(((size_t)n * C + c) * HW + p0 + 4 * pq + k);
+                code[k] = quantize_one<STOCH>(v[j][k], inv, seed_lo, seed_hi_mul, idx);
+                if (DEV) {
+                    const double g = (double)v[j][k];
+                    A = fma(g, (double)code[k], A);
+                    G = fma(g, g, G);
+                    B += (unsigned)(code[k] * code[k]);
                 }
-                d[j] = pack4(code[0], code[1], code[2], code[3]);
             }
-            transpose4x4_bytes(d, o);     // d[channel] = 4 pixels -> o[pixel] = 4 channels
-#pragma unroll
-            for (int k = 0; k < 4; ++k) tile[4 * pq + k][cgp] = o[k];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int code[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c = c0 + 4 * (wv + 4 * i) + j;
-                    const uint32_t idx = (uint32_t)(((size_t)n * C + c) * HW + p);
-                    code[j] = quantize_one<STOCH>(v[i][j], inv, seed_lo, seed_hi_mul, idx);
-                    if (DEV) {
-                        const double g = (double)v[i][j];
-                        A = fma(g, (double)code[j], A);
-                        G = fma(g, g, G);
-                        B += (unsigned)(code[j] * code[j]);
-                    }
-                }
-                tile[lane][wv + 4 * i] = pack4(code[0], code[1], code[2], code[3]);
-            }
+            d[j] = pack4(code[0], code[1], code[2], code[3]);
         }
+        transpose4x4_bytes(d, o);     // d[channel] = 4 pixels -> o[pixel] = 4 channels
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tile[4 * pq + k][cgp] = o[k];
         __syncthreads();
 
         const int pl = threadIdx.x >> 2;
@@ -489,12 +472,18 @@ __device__ __forceinline__ void quantize_act_body(
 
 template <bool STOCH, bool DEV, bool VEC>
 __global__ __launch_bounds__(256) void quantize_act_kernel(
-    const float* __restrict__ x, int N, int C, int Cp, int HW, const float* __restrict__ clip,
+    const float* __restrict__ x, int side, int N, int C, int Cp, int HW, const float* __restrict__ clip,
     const float* __restrict__ absmax_part, int nparts, uint32_t seed_lo, uint32_t seed_hi_mul,
     int8_t* __restrict__ q, float* __restrict__ scale_out, DevPartial* __restrict__ devpart) {
     __shared__ float lds4[4];
     __shared__ uint32_t tile[QA_PIX][QA_CH / 4 + 1];
-    const VBlock vb = {(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
+    VBlock vb = {(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
+    if (side) {                  // eight images side by side
+        vb.z = 8 * vb.z + (vb.x & 7);
+        vb.x >>= 3;
+        vb.gx >>= 3;
+        if (vb.z >= N) return;
+    }
     quantize_act_body<STOCH, DEV, VEC>(x, N, C, Cp, HW, clip, absmax_part, nparts, seed_lo, seed_hi_mul, q, scale_out,
                                        devpart, vb, lds4, tile);
 }
@@ -509,16 +498,17 @@ hipError_t launch_quantize_act(const QuantArgs& a, hipStream_t st) {
     const int N = a.d0, C = a.d1, HW = a.d2 * a.d3, Cp = (C + 15) & ~15;
     int gx, gy, gz;
     quant_act_grid(N, Cp, HW, &gx, &gy, &gz);
-    const dim3 grid(gx, gy, gz);
+    const bool side = quant_act_side_by_side(N, HW, gx, gy);
+    const dim3 grid(side ? 8 * gx : gx, gy, side ? (gz + 7) / 8 : gz);
     const uint32_t slo = seed_key_x(a.seed), shi = seed_key_a(a.seed);
     KernelTimer kt(KID_QUANTIZE_ACT, st);
 #define LAUNCH(ST, DV)                                                                                      \
     do {                                                                                                    \
         if ((HW & 3) == 0)                                                                                  \
-            launch_timed(kt, (quantize_act_kernel<ST, DV, true>), grid, dim3(256), 0, st, a.x, N, C, Cp, HW, \
+            launch_timed(kt, (quantize_act_kernel<ST, DV, true>), grid, dim3(256), 0, st, a.x, (int)side, N, C, Cp, HW, \
                                a.clip, a.absmax_part, a.nparts, slo, shi, a.q, a.scale, a.devpart);         \
         else                                                                                                \
-            launch_timed(kt, (quantize_act_kernel<ST, DV, false>), grid, dim3(256), 0, st, a.x, N, C, Cp, HW, \
+            launch_timed(kt, (quantize_act_kernel<ST, DV, false>), grid, dim3(256), 0, st, a.x, (int)side, N, C, Cp, HW, \
                                a.clip, a.absmax_part, a.nparts, slo, shi, a.q, a.scale, a.devpart);         \
     } while (0)
     if (a.stochastic) {
@@ -787,8 +777,7 @@ __global__ __launch_bounds__(256) void quantize_wgt_kernel(
 // ---------------------------------------------------------------------------------------------
 // ANYSTOCH: some item rounds stochastically (Eq.3).  The round-to-nearest launch of a layer's a and
 // W is a kernel of its own, so that it keeps its register count beside the clip search.  ACTS: ACTS_RAGGED, some tensor of
-// N,H,W,Cp codes has planes of no whole 16-byte groups; those passes need more registers, which the launch without them does not
-// pay for (77 and 79 against 40 and 43).  ACTS_EVEN: four blocks per compute unit are enough where nothing runs beside the kernel:
+// N,H,W,Cp codes has planes of no whole 16-byte groups (and the rows of 1 x 1 images).  ACTS_EVEN: four blocks per compute unit are enough where nothing runs beside the kernel:
 // with seven, 14 x 14 planes of 1024 channels, batch 128, take 34.1 us instead of 33.0 (beside the clip search they would take 21
 // instead of 13 us at 12.8 M elements, so the launch of a and W alone keeps its occupancy).  ACTS_NONE, planar codes only: they want
 // all the blocks that fit (13 channels at 43 x 43, batch 256, a and g_z: 14.5 us; with four blocks 15.7).
@@ -806,10 +795,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH
     const int i = batch_item(b.block0, (int)blockIdx.x);
     const QuantBatchItem& t = b.it[i];
     const int local = (int)blockIdx.x - b.block0[i];
-    const int gxy = t.gx * t.gy;
-    const int z = local / gxy, rem = local - z * gxy;
+    const bool side = ACTS != ACTS_NONE && t.kind == 0 && quant_act_side_by_side(t.d0, t.d2 * t.d3, t.gx, t.gy);
+    const int gxy = t.gx * t.gy, at = side ? local >> 3 : local;
+    const int z = at / gxy, rem = at - z * gxy;
     const int y = rem / t.gx;
-    const VBlock vb = {rem - y * t.gx, y, z, t.gx, t.gy, t.gz};
+    const VBlock vb = {rem - y * t.gx, y, side ? 8 * z + (local & 7) : z, t.gx, t.gy, t.gz};
+    if (side && vb.z >= t.d0) return;
     const bool st = ANYSTOCH && t.stoch;          // block-uniform
     if (ACTS != ACTS_NONE && t.kind == 0) {          // activations, N,C,H,W -> N,H,W,Cp
         const int HW = t.d2 * t.d3, Cp = (t.d1 + 15) & ~15;
@@ -843,6 +834,7 @@ void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz) {
     if (kind == 0) {
         const int HW = d[2] * d[3], Cp = (d[1] + 15) & ~15;
         quant_act_grid(d[0], Cp, HW, gx, gy, gz);
+        if (quant_act_side_by_side(d[0], HW, *gx, *gy)) *gz = (*gz + 7) & ~7;
     } else if (kind == 1) {
         *gx = quant_wgt_gx(d[0], d[1], d[2], d[3]); *gy = (d[0] + QW_T - 1) / QW_T; *gz = quant_wgt_zsplit(d[0], d[1], d[2], d[3]);
     } else {

@@ -534,3 +534,41 @@ def test_strided_passes_in_one_launch(shape, passes):
     torch.cuda.synchronize()
     for a, b in zip(got, outs):
         assert torch.equal(a, b)
+
+
+# Codes of planes of no whole 16-byte groups (a plane's last quad of one, two and three pixels, planes of two and three pixels, the
+# tensor's end), and tiles dealt image by image or eight images side by side (with and without images beyond the batch, one and
+# several channel groups, whole groups too); both roundings, with Eq.6 and in a batch with another tensor behind it.
+@pytest.mark.parametrize("N,C,H,W", [(1, 17, 1, 2), (3, 20, 3, 1), (2, 100, 7, 7), (8, 33, 9, 9), (8, 65, 17, 17), (16, 20, 17, 18), (15, 18, 17, 19),
+                                     (31, 24, 17, 17), (8, 130, 47, 45), (8, 40, 47, 45), (8, 70, 18, 18), (1, 18, 5, 13)])
+def test_codes_of_ragged_planes(N, C, H, W):
+    r = np.random.RandomState(C + W)
+    x = (r.standard_t(3, size=(N, C, H, W)) * 1e-3).astype(np.float32)
+    x2 = r.standard_normal((3, 24, 5, 5)).astype(np.float32)
+    xd, x2d = dev(x), dev(x2)
+    pad16 = lambda c: (c + 15) // 16 * 16
+    q, s = torch.empty(N * H * W * pad16(C), dtype=torch.int8, device=DEV), torch.zeros(1, device=DEV)
+    q2, s2 = torch.empty(3 * 25 * 32, dtype=torch.int8, device=DEV), torch.zeros(1, device=DEV)
+    ws = torch.empty(B.int8t_quantize_workspace_bytes(x.shape, B.ACT), dtype=torch.uint8, device=DEV)
+    d = torch.zeros(1, dtype=torch.float64, device=DEV)
+    want2, _ = oracle.quantize(x2, c=None, mode=oracle.ROUND_NEAREST_EVEN, seed=0)
+    for mode, om in ((RTN, oracle.ROUND_NEAREST_EVEN), (STO, oracle.ROUND_STOCHASTIC)):
+        want, sc = oracle.quantize(x, c=None, mode=om, seed=11)
+        ref, g64 = want.astype(np.float64).reshape(-1), x.astype(np.float64).reshape(-1)
+        for form in ("plain", "eq6", "batch"):
+            q.fill_(7)
+            q2.fill_(7)
+            if form == "batch":
+                B.int8t_quantize_batch([(xd, x.shape, B.ACT, None, q, s, mode, 11), (x2d, x2.shape, B.ACT, None, q2, s2)],
+                                       ws=torch.empty(1 << 14, dtype=torch.uint8, device=DEV))
+            else:
+                B.int8t_quantize(xd, x.shape, B.ACT, None, mode, 11, q, s, d if form == "eq6" else None, ws)
+            torch.cuda.synchronize()
+            got, pad = B.int8t_unpack_codes(q.cpu().numpy(), x.shape, B.ACT)
+            assert np.array_equal(got, want) and pad == 0 and s.item() == sc, form
+            if form == "batch":
+                got2, pad2 = B.int8t_unpack_codes(q2.cpu().numpy(), x2.shape, B.ACT)
+                assert np.array_equal(got2, want2) and pad2 == 0
+            if form == "eq6":
+                # sums of up to 1e6 fp64 products in another order: relative error below 1e6 * 2^-53 = 1.1e-10
+                assert abs(d.item() - (1.0 - (g64 @ ref) / (np.sqrt(g64 @ g64) * np.sqrt(ref @ ref)))) < 1e-9
