@@ -319,6 +319,10 @@ def main():
         alg = pass_algorithmic(L, n_cand)
         shared = [alg[p] for p in ("bwd_data", "bwd_weight") + (() if two_streams else ("fwd",))]
         kernel_alg[dom] = [sum(a[0] for a in shared), sum(a[1] for a in shared), "mfma", 1]
+        if dom == "dw_trio_kernel" and not {"quantize_batch_kernel", "quantize_planar_kernel"} & set(per_kernel):
+            # ... and the codes of a, W and g_z, which are not read back
+            kernel_alg[dom][0] = alg["quantize_xw"][0] + alg["quantize_gz"][0] + 4 * sum(sizes(L))
+            kernel_alg[dom][1], kernel_alg[dom][3] = 6 * L.macs, per_kernel[dom][0]
     nbytes, ops, kind, launches = kernel_alg.get(dom, [0, 0, None, per_kernel[dom][0]])
     launches = launches or per_kernel[dom][0]
     # per launch, as the duration is: the kernel's algorithmic work of the step / its launches per step
