@@ -322,7 +322,8 @@ def main():
         if dom == "dw_trio_kernel" and not {"quantize_batch_kernel", "quantize_planar_kernel"} & set(per_kernel):
             # ... and the codes of a, W and g_z, which are not read back
             kernel_alg[dom][0] = alg["quantize_xw"][0] + alg["quantize_gz"][0] + 4 * sum(sizes(L))
-            kernel_alg[dom][1], kernel_alg[dom][3] = 6 * L.macs, per_kernel[dom][0]
+            # (two launches on two streams: the forward pass with the codes of a and W, the backward ones with those of g_z)
+            kernel_alg[dom][1], kernel_alg[dom][3] = 6 * L.macs, 2 if two_streams else 1
     nbytes, ops, kind, launches = kernel_alg.get(dom, [0, 0, None, per_kernel[dom][0]])
     launches = launches or per_kernel[dom][0]
     # per launch, as the duration is: the kernel's algorithmic work of the step / its launches per step
@@ -331,7 +332,7 @@ def main():
     roof["traffic"] = tr[0] if tr else None
     roof["traffic_source"] = ("stored figure, not measured by this run: " + tr[1]) if tr else None
     roof["kernel"] = dom
-    roof["launches_per_step"] = per_kernel[dom][0]
+    roof["launches_per_step"] = launches if dom == "dw_trio_kernel" else per_kernel[dom][0]
     roof["us_per_launch"] = dom_us
     roof["algorithmic_bytes_per_launch"] = nbytes / launches
     roof["algorithmic_ops_per_launch"] = ops / launches
