@@ -30,6 +30,8 @@ class _LayerBuffers:
     def __init__(self, layer, x_shape, dev):
         N, C, H, W = x_shape
         K, Cg, R, S = layer.weight_shape
+        if C != Cg * layer.groups:      # (the library takes the filters' channel count from the descriptor)
+            raise RuntimeError(f"input of {C} channels in a layer of {Cg * layer.groups}")
         self.desc = B.make_desc(N, C, H, W, K, R, S, layer.stride, layer.padding, layer.groups)
         depthwise = layer.groups != 1
         self.act_kind = B.ACT_PLANAR if depthwise else B.ACT
