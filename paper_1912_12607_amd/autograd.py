@@ -73,8 +73,8 @@ class _LayerBuffers:
 
 
 def _device(t):
-    """Address of a tensor that is contiguous already."""
-    assert t.is_cuda, "device-resident contiguous tensors only"
+    """Address of a tensor for the library."""
+    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
     return t.data_ptr()
 
 
@@ -131,7 +131,7 @@ class _Int8ConvFn(torch.autograd.Function):
         parts = B.STEP_QUANT_G
         step = B.LayerBuffers.from_buffer_copy(buf._bwd)
         step.dy, step.xq, step.sx = _device(dy), xq.data_ptr(), sx.data_ptr()
-        step.clip = layer.clip.data_ptr()
+        step.clip = _device(layer.clip)
         # Periodic Update (Sec.3.4): the clip value is searched every `dsgc_period` backward passes
         if layer.backward_calls % layer.dsgc_period == 0:
             J = layer.ratios.numel()
@@ -141,7 +141,7 @@ class _Int8ConvFn(torch.autograd.Function):
             else:
                 parts |= B.STEP_PREPARE | B.STEP_SEARCH       # with the passes, below
                 step.ratios, step.n_cand = _device(layer.ratios), J
-                step.dev_search = layer.deviation.data_ptr()
+                step.dev_search = _device(layer.deviation)
             # Refinement of the clip value (Sec.3.4 learns c by descending d_c; no step size is given): further
             # sweeps over J candidates spaced geometrically around the last winner, the window shrinking by the
             # factor J / 2 each time.  The winner itself is candidate J / 2, so d_c never rises.  The ratios are
@@ -155,7 +155,7 @@ class _Int8ConvFn(torch.autograd.Function):
                 width = 2.0 * width / J
             layer.last_ratios = ratios          # the candidates of the last sweep (the grid itself without refinement)
         else:
-            step.dev_final = layer.deviation.data_ptr()          # Eq.6 of the codes actually produced with the kept clip
+            step.dev_final = _device(layer.deviation)          # Eq.6 of the codes actually produced with the kept clip
         layer.backward_calls += 1
         if layer.weight._version != ctx.w_version:
             # the weights changed between this layer's forward and backward pass (an optimizer step in

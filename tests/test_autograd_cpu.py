@@ -1,9 +1,35 @@
-"""Host logic of the autograd modules that needs no GPU: what is refused before the library is called."""
+"""Host logic of the autograd modules that needs no GPU: what is refused before the library is called, and what the library is
+asked for (its calls recorded, on host tensors)."""
+import types
+
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from paper_1912_12607_amd import autograd as A  # noqa: E402
+from paper_1912_12607_amd import binding as B  # noqa: E402
 from paper_1912_12607_amd.autograd import Int8Conv2d  # noqa: E402
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    """The library's calls, recorded as (name, arguments); results keep what their memory held."""
+    seen = []
+
+    def record(name):
+        monkeypatch.setattr(B, name, lambda *args: seen.append((name, args)))
+
+    for name in ("int8t_layer_step", "int8t_layer_infer", "int8t_layer_backward", "int8t_dsgc_clip", "int8t_quantize"):
+        record(name)
+
+    device = A._device
+
+    def address(t):         # (a host tensor marked `foreign` stands for one the GPU cannot reach)
+        return device(types.SimpleNamespace(is_cuda=not getattr(t, "foreign", False), is_contiguous=t.is_contiguous, data_ptr=t.data_ptr))
+
+    monkeypatch.setattr(A, "_device", address)
+    monkeypatch.setattr(B, "_ptr", lambda t: None if t is None else address(t))
+    return seen
 
 
 # The library takes the filters' channel count from the input's: one that is not the weights' would read and write past their end.
@@ -15,3 +41,21 @@ def test_input_of_another_channel_count_is_refused(C, K, kernel, groups, grad):
         for c in (C - 4, C + 4, 1, 2 * C):
             with pytest.raises(RuntimeError, match=f"{c} channels.*{C}"):
                 m(torch.zeros(2, c, 9, 9))
+
+
+# Tensors that a program may replace (a clip value out of a checkpoint, candidates of its own) are checked as the others are.
+@pytest.mark.parametrize("name,period,strided", [("clip", 1, False), ("clip", 2, False), ("deviation", 1, False), ("deviation", 2, False),
+                                                 ("ratios", 1, False), ("ratios", 1, True)])
+def test_addresses_of_replaced_tensors_are_checked(calls, name, period, strided):
+    m = Int8Conv2d(8, 8, 3, padding=1, dsgc_period=period, device="cpu")
+    x = torch.zeros(2, 8, 5, 5, requires_grad=True)
+    m(x).sum().backward()
+    assert [c[0] for c in calls] == ["int8t_layer_step", "int8t_layer_backward"]
+    t = getattr(m, name)
+    t = t[::2] if strided else t.clone()
+    t.foreign = not strided
+    setattr(m, name, t)
+    y = m(x)
+    with pytest.raises(AssertionError, match="device-resident"):
+        y.sum().backward()
+    assert len(calls) == 3
