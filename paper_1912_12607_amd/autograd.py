@@ -254,7 +254,7 @@ class Int8Conv2d(torch.nn.Module):
         w, bias = self.weight, self.bias
         keep = torch.is_grad_enabled() and (x.requires_grad or w.requires_grad)
         if (_plain_eager() and (x.dim() >= 1 and x.shape[-1] == self.in_channels if linear else x.dim() == 4)
-                and (bias is None or (bias.dim() == 1 and bias.shape[0] == self.out_channels and bias.is_cuda))):
+                and (bias is None or (bias.dim() == 1 and bias.shape[0] == self.out_channels and bias.is_cuda and bias.dtype is torch.float32))):
             return _Int8ConvFn.apply(x, w, self, keep, bias, linear)
         # the same as single operations
         lead = x.shape[:-1]

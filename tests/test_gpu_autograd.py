@@ -296,3 +296,20 @@ def test_bias_of_a_frozen_layer_and_of_a_convolution():
             m.bias = torch.autograd.forward_ad.make_dual(bias.detach(), t)
             out = torch.autograd.forward_ad.unpack_dual(m(x)).tangent
             assert torch.equal(out, t.view(1, -1, *[1] * (x.dim() - 2)).expand_as(out))
+
+
+# A bias of another type gives the sum's type, and gets a gradient of its own.
+@pytest.mark.parametrize("dtype,result", [(torch.float64, torch.float64), (torch.float16, torch.float32)])
+@pytest.mark.parametrize("linear", [True, False])
+def test_bias_of_another_type(linear, dtype, result):
+    m = _with_bias(linear, *((24, 40) if linear else (8, 12, 3)))
+    m.bias = torch.nn.Parameter(m.bias.detach().to(dtype) + 2.0 ** -40)
+    x = torch.randn(*((6, 24) if linear else (2, 8, 9, 9)), device="cuda", requires_grad=True)
+    y = m(x)
+    assert y.dtype == result
+    g = torch.randn_like(y)
+    y.backward(g)
+    assert m.bias.grad.dtype == dtype
+    bias, m.bias = m.bias, None
+    y0 = m(x)
+    assert y0.dtype == torch.float32 and torch.equal(y, y0 + (bias if linear else bias.view(1, -1, 1, 1)))
