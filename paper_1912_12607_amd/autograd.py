@@ -189,7 +189,7 @@ _functorch_active = getattr(torch._C, "_are_functorch_transforms_active", lambda
 
 def _plain_eager() -> bool:
     """No transformation looks at the single operations of the layer: no functorch level, forward-mode level or tracer."""
-    return (torch.autograd.forward_ad._current_level < 0 and not _functorch_active()
+    return (getattr(torch.autograd.forward_ad, "_current_level", -1) < 0 and not _functorch_active()
             and not torch.jit.is_tracing() and not torch.compiler.is_compiling())
 
 

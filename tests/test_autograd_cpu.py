@@ -59,3 +59,11 @@ def test_addresses_of_replaced_tensors_are_checked(calls, name, period, strided)
     with pytest.raises(AssertionError, match="device-resident"):
         y.sum().backward()
     assert len(calls) == 3
+
+
+# Whether a forward-mode level is open is asked of a private name of torch, which another release need not have.
+def test_without_torchs_forward_mode_level(calls, monkeypatch):
+    assert A._plain_eager()
+    monkeypatch.delattr(torch.autograd.forward_ad, "_current_level")
+    assert A._plain_eager()
+    assert Int8Conv2d(8, 8, 3, device="cpu")(torch.zeros(1, 8, 5, 5)).shape == (1, 8, 3, 3)
