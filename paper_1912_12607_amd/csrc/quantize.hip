@@ -221,7 +221,7 @@ __host__ __device__ inline int quant_act_nsub(int HW) {
 }
 // 1 x 1 images whose channels need padding (the output gradient of a fully connected layer): the tensor is a matrix of N rows, and
 // a thread takes four channels of a row, padding included, up to QA_ROW_LOADS times.  As tiles
-// of 64 pixels the 256 x 1000 gradient of a classifier was 4096 blocks of 64 elements, 17.1 us; now 4.0.
+// of 64 pixels the 256 x 1000 gradient of a classifier was 4096 blocks of 64 elements, 17.1 us; now 4.0 (8192 x 1000: 416, 10.6).
 constexpr int QA_ROW_LOADS = 2;
 __host__ __device__ inline bool quant_act_rows(int HW) { return HW == 1; }
 __host__ __device__ inline int quant_act_gx(int Cp, int HW) {
@@ -232,9 +232,10 @@ __host__ __device__ inline int quant_act_gx(int Cp, int HW) {
 // batch 64: 27.6 / 27.7 -> 22.8 / 25.7; 768, 17 x 17: 17.0 / 17.8 -> 15.1 / 17.4; 64, 147 x 147: 88.3 / 89.0 -> 79.9 / 80.5).
 // Not where the 64-byte runs of codes of neighbouring channel groups are then written too far apart to meet in a line of L2: more
 // than 64 channels on large planes (160, 75 x 75: 54.7 / 59.2 against 66.2 / 67.4; 192, 71 x 71: 61.2 against 63.6).  Nor where the
-// last eight images leave more than a sixteenth of the XCDs' time unused (10 images, 149 x 149: 16.2 against 19.2).
+// last eight images leave more than a sixteenth of the XCDs' time unused (10 images, 149 x 149: 16.2 against 19.2).  Rows of 1 x 1
+// images are one grid over all of them (quant_act_grid): dealt so, every block would run eight times.
 __host__ __device__ inline bool quant_act_side_by_side(int N, int HW, int gx, int gy) {
-    return (HW & 31) != 0 && gx > 1 && (gy == 1 || HW <= 2048) && (-N & 7) * 16 <= N;
+    return !quant_act_rows(HW) && (HW & 31) != 0 && gx > 1 && (gy == 1 || HW <= 2048) && (-N & 7) * 16 <= N;
 }
 // grid of the pass over a tensor of N images: tiles of a plane, channel groups, images
 static void quant_act_grid(int N, int Cp, int HW, int* gx, int* gy, int* gz) {

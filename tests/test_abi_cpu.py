@@ -340,3 +340,18 @@ def test_layer_backward_arguments():
         assert call(parts) == bad
     assert call(B.STEP_BWD_DATA, 4096) == bad      # a bias gradient of a layer with more than one output pixel
     assert call(B.STEP_PREPARE | B.STEP_SEARCH) == null and call(B.STEP_QUANT_G) == null and call(B.STEP_BWD_WEIGHT) == null
+
+
+# The grid of the quantizer of N,H,W,Cp codes (internal functions of the library): every tile once.  Images beyond the batch may fill up
+# the last eight that are walked side by side; the rows of 1 x 1 images are one grid over the whole batch.
+@pytest.mark.parametrize("N,Cc,H,W", [(256, 1000, 1, 1), (64, 1000, 1, 1), (8192, 1000, 1, 1), (2100, 996, 1, 1), (128, 20, 1, 1), (16, 3, 1, 1),
+                                     (8, 24, 17, 17), (31, 24, 17, 17), (15, 18, 17, 19), (64, 288, 35, 35), (8, 3, 33, 31), (64, 64, 56, 56)])
+def test_quantizer_grid_runs_every_tile_once(lib, N, Cc, H, W):
+    grid, count = getattr(lib, "_ZN5int8t10quant_gridEiPKiPiS2_S2_"), getattr(lib, "_ZN5int8t16quant_blocks_actEiii")
+    g = [C.c_int() for _ in range(3)]
+    grid(0, dims(N, Cc, H, W), *[C.byref(v) for v in g])
+    gx, gy, gz = (v.value for v in g)
+    tiles = count(N, (Cc + 15) // 16 * 16, H * W)
+    assert tiles <= gx * gy * gz < tiles + (1 if H * W == 1 else 8 * gx * gy)
+    if H * W > 1:
+        assert tiles == gx * gy * N and gz in (N, (N + 7) // 8 * 8)
