@@ -459,6 +459,11 @@ hipError_t batch_absmax(int count, const int8t_quantize_item* items, void* ws_de
     return ab.count ? launch_absmax_batch(ab, (int)ablocks, st) : hipSuccess;
 }
 
+int batch_kind(const int8t_quantize_item& it) {
+    const int8t_kind pk = pass_kind(it.dims, it.kind);
+    return pk == INT8T_ACT ? 0 : pk == INT8T_WGT ? 1 : 2;
+}
+
 // Second launch: the codes and scales, from the clip values and the partials of the first.  (checked arguments)
 int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_dev, hipStream_t st) {
     QuantBatch qb{};
@@ -475,15 +480,13 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
         q.x = it.x_dev; q.d0 = it.dims[0]; q.d1 = it.dims[1]; q.d2 = it.dims[2]; q.d3 = it.dims[3];
         q.clip = it.clip_dev; q.absmax_part = it.clip_dev ? nullptr : batch_partials(ws_dev, i); q.nparts = it.clip_dev ? 0 : absmax_blocks(sizes[i]);
         q.q = it.q_dev; q.scale = it.scale_dev;
-        const int8t_kind pk = pass_kind(it.dims, it.kind);
-        q.kind = pk == INT8T_ACT ? 0 : pk == INT8T_WGT ? 1 : 2;
+        q.kind = batch_kind(it);
         q.stoch = it.mode == INT8T_ROUND_STOCHASTIC;
         q.seed_lo = seed_key_x(it.seed);
         q.seed_hi = seed_key_a(it.seed);
         quant_grid(q.kind, it.dims, &q.gx, &q.gy, &q.gz);
         qb.block0[oi] = (int)qblocks;
-        qblocks += (long long)q.gx * q.gy * q.gz;
-        if (qblocks > 0x7FFFFFFFll) return INT8T_ERR_SHAPE;
+        qblocks += (long long)q.gx * q.gy * q.gz;      // (batch_blocks_ok)
     }
     return launch_quantize_batch(qb, (int)qblocks, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
 }
@@ -491,7 +494,11 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
 // the codes' launch has one block index over all tensors of a batch
 bool batch_blocks_ok(int count, const int8t_quantize_item* items) {
     long long blocks = 0;
-    for (int i = 0; i < count; ++i) blocks += quant_blocks(items[i].dims, items[i].kind);
+    for (int i = 0; i < count; ++i) {
+        int gx, gy, gz;
+        quant_grid(batch_kind(items[i]), items[i].dims, &gx, &gy, &gz);
+        blocks += (long long)gx * gy * gz;
+    }
     return blocks <= 0x7FFFFFFFll;
 }
 
