@@ -385,6 +385,7 @@ int8t_status int8t_layer_step(const int8t_conv_desc *desc, const int8t_layer_buf
  * INT8T_STEP_QUANT_G, INT8T_STEP_BWD_DATA and INT8T_STEP_BWD_WEIGHT; other parts: INT8T_ERR_ARG.
  *   db_dev   NULL, or K floats: out, the sum of dy over the batch (the gradient of a bias; summed in fp64), for layers with one
  *            output pixel (P = Q = 1; INT8T_ERR_ARG for others).  It may not overlap what the call reads or writes otherwise.
+ *            64 columns are one block, which walks all rows of the batch: meant for up to a thousand rows or two.
  */
 int8t_status int8t_layer_backward(const int8t_conv_desc *desc, const int8t_layer_buffers *b, int parts, uint64_t seed,
                                   float *db_dev, void *stream);

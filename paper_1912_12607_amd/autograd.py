@@ -60,7 +60,12 @@ class _LayerBuffers:
         self._fwd = B.layer_buffers(wq=self.wq, sw=self.sw, ws_quant=self.ws, ws_fwd=self.ws)
         self._bwd = B.layer_buffers(wq=self.wq, dyq=self.dyq, sw=self.sw, sdy=self.sdy, ws_dy=self.ws, ws_bwd_data=self.ws,
                                     ws_bwd_weight=self.ws)
-        self.w_numel, self.pixels = K * Cg * R * S, P * Q
+        self.w_numel = K * Cg * R * S
+        # Sums over the rows of g_z in the call of the backward passes.  64 columns are one block there, whatever the rows: us with
+        # the sums inside / behind it (torch.sum), search included, 1000 columns: 256 rows 33.6, 41.8; 1024: 45.4, 52.3; 2048: 58.7,
+        # 60.1; 4096: 91.8, 85.7; 65535: 1131, 615; 64 columns: 1024 rows 31.4, 36.6; 2048: 38.3, 39.2; 8192: 94.9, 52.8.
+        # (without the search 1000 columns: 1024 rows 32.5, 34.1; 2048: 43.4, 41.2)
+        self.sums = P * Q == 1 and N <= 1024
 
     def take_xq(self):
         if self.xq_pool:
@@ -162,9 +167,10 @@ class _Int8ConvFn(torch.autograd.Function):
             # between): the codes of W the forward used are gone, quantize the current ones again
             B.int8t_quantize(layer.weight.detach().contiguous().view(buf.w_shape), buf.w_shape, buf.wgt_kind, None, B.ROUND_NEAREST_EVEN, 0,
                              buf.wq, buf.sw, None, buf.ws)
-        # the bias gradient: sums over the rows in the same call, where nobody wants to differentiate them again
+        # the bias gradient: sums over the rows in the same call, where nobody wants to differentiate them again and a block can walk
+        # the rows of its columns (_LayerBuffers.sums)
         db = sums = None
-        if want_b and buf.pixels == 1 and not torch.is_grad_enabled():
+        if want_b and buf.sums and not torch.is_grad_enabled():
             db = sums = torch.empty(buf.y_shape[1], dtype=torch.float32, device=dy.device)
         elif want_b:
             db = dy.sum(batch_dims) if batch_dims else dy

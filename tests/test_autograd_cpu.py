@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 
 from paper_1912_12607_amd import autograd as A  # noqa: E402
 from paper_1912_12607_amd import binding as B  # noqa: E402
-from paper_1912_12607_amd.autograd import Int8Conv2d  # noqa: E402
+from paper_1912_12607_amd.autograd import Int8Conv2d, Int8Linear  # noqa: E402
 
 
 @pytest.fixture
@@ -67,3 +67,18 @@ def test_without_torchs_forward_mode_level(calls, monkeypatch):
     monkeypatch.delattr(torch.autograd.forward_ad, "_current_level")
     assert A._plain_eager()
     assert Int8Conv2d(8, 8, 3, device="cpu")(torch.zeros(1, 8, 5, 5)).shape == (1, 8, 3, 3)
+
+
+# Sums over the rows in the library's call are one block per 64 columns: many rows (a batch of tokens) are summed by torch.
+@pytest.mark.parametrize("rows,inside", [(1, True), (1024, True), (1025, False), (4096, False)])
+def test_bias_gradient_of_many_rows(calls, rows, inside):
+    m = Int8Linear(8, 6, device="cpu")
+    x, g = torch.zeros(rows, 8, requires_grad=True), torch.randn(rows, 6)
+    y = A._Int8ConvFn.apply(x, m.weight, m, True, m.bias, True)
+    db = torch.autograd.grad(y, [m.bias, x], g)[0]
+    name, args = calls[-1]
+    assert name == "int8t_layer_backward" and db.shape == (6,)
+    if inside:
+        assert args[4].data_ptr() == db.data_ptr()
+    else:
+        assert args[4] is None and torch.equal(db, g.sum(0))
