@@ -380,6 +380,26 @@ int8t_status int8t_layer_step(const int8t_conv_desc *desc, const int8t_layer_buf
                               void *stream);
 
 /*
+ * The launch that passes of a step share: what int8t_layer_step does with these parts where no two buffers overlap, the scratch is as
+ * int8t_workspace_bytes() says and dev_final is NULL.  (INT8T_FORM_APART also for arguments that it refuses.)
+ */
+typedef enum {
+    INT8T_FORM_APART = 0,                /* a launch per pass */
+    INT8T_FORM_128X128 = 1,              /* dense, stride 1: the passes on tiles of 128 rows x 128 columns, */
+    INT8T_FORM_128X64 = 2,               /* 128 x 64, */
+    INT8T_FORM_64X128 = 3,               /* 64 x 128 (all have at most 64 rows), */
+    INT8T_FORM_64X128_AND_128X128 = 4,   /* or by their rows */
+    INT8T_FORM_STRIDED = 5,              /* dense, strided: backward-data pixel by pixel, */
+    INT8T_FORM_STRIDED_CLASSES = 6,      /* a class of pixels per tile, */
+    INT8T_FORM_STRIDED_CELL = 7,         /* cells of pixels of which one has taps, */
+    INT8T_FORM_STRIDED_CELLS = 8,        /* the classes of a cell one after the other */
+    INT8T_FORM_DW_PASSES = 9,            /* depthwise: the passes, */
+    INT8T_FORM_DW_CODES = 10,            /* and the codes as well */
+    INT8T_FORM_MAX_ENUM = 0x7fffffff
+} int8t_form;
+int8t_form int8t_layer_step_form(const int8t_conv_desc *desc, int parts);
+
+/*
  * The backward half of a step in one call, for callers whose forward pass ran earlier (a layer inside a network): as
  * int8t_layer_step with any of INT8T_STEP_PREPARE together with INT8T_STEP_SEARCH (here without INT8T_STEP_ABSMAX),
  * INT8T_STEP_QUANT_G, INT8T_STEP_BWD_DATA and INT8T_STEP_BWD_WEIGHT; other parts: INT8T_ERR_ARG.

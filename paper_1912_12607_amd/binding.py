@@ -29,7 +29,7 @@ EXPORTS = ["int8t_status_string", "int8t_code_bytes", "int8t_unpack_codes", "int
            "int8t_quantize_workspace_bytes", "int8t_quantize", "int8t_quantize_batch_workspace_bytes",
            "int8t_quantize_batch", "int8t_quantize_batch_prepare", "int8t_dsgc_clip", "int8t_dsgc_clip_static", "int8t_dsgc_prepare", "int8t_dsgc_search", "int8t_conv_fwd", "int8t_conv_fwd_fused",
            "int8t_conv_bwd_data", "int8t_conv_bwd_weight", "int8t_conv_bwd_weight_fwd", "int8t_dclr_scale",
-           "int8t_layer_step", "int8t_layer_backward", "int8t_layer_infer", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
+           "int8t_layer_step", "int8t_layer_step_form", "int8t_layer_backward", "int8t_layer_infer", "int8t_conv_variant_ok", "int8t_conv_select_variant", "int8t_conv_selected_variant",
            "int8t_profile_start", "int8t_profile_start_sampled", "int8t_profile_stop", "int8t_profile_mfma_ceiling"]
 
 
@@ -45,6 +45,8 @@ class QuantizeItem(C.Structure):
 (STEP_ABSMAX, STEP_PREPARE, STEP_SEARCH, STEP_QUANT_XW, STEP_QUANT_G, STEP_FWD, STEP_BWD_DATA,
  STEP_BWD_WEIGHT) = (1 << k for k in range(8))
 STEP_ALL = 255
+(FORM_APART, FORM_128X128, FORM_128X64, FORM_64X128, FORM_64X128_AND_128X128, FORM_STRIDED, FORM_STRIDED_CLASSES, FORM_STRIDED_CELL,
+ FORM_STRIDED_CELLS, FORM_DW_PASSES, FORM_DW_CODES) = range(11)
 
 
 class LayerBuffers(C.Structure):
@@ -109,6 +111,8 @@ def _load():
     L.int8t_conv_fwd_fused.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     L.int8t_layer_step.restype = i32
     L.int8t_layer_step.argtypes = [dp, C.POINTER(LayerBuffers), i32, u64, vp]
+    L.int8t_layer_step_form.restype = i32
+    L.int8t_layer_step_form.argtypes = [dp, i32]
     L.int8t_layer_infer.restype = i32
     L.int8t_layer_infer.argtypes = [dp, C.POINTER(LayerBuffers), vp]
     L.int8t_layer_backward.restype = i32
@@ -314,6 +318,10 @@ def layer_buffers(**fields) -> LayerBuffers:
 
 def int8t_layer_step(desc, buffers: LayerBuffers, parts: int = STEP_ALL, seed: int = 0, stream=None):
     _check(lib.int8t_layer_step(C.byref(desc), C.byref(buffers), parts, seed, _stream(stream)))
+
+
+def int8t_layer_step_form(desc, parts: int) -> int:
+    return int(lib.int8t_layer_step_form(C.byref(desc), parts))
 
 
 def int8t_layer_backward(desc, buffers: LayerBuffers, parts: int, seed: int = 0, db=None, stream=None):

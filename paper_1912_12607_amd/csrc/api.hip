@@ -816,6 +816,66 @@ static bool disjoint_step(const int8t_conv_desc* d, const Geo& g, const int8t_la
     return true;
 }
 
+// Depthwise layers whose codes are formed in the launch of the passes (conv_dw_fused.hip): the parts that belong together
+// are all asked for, codes of a and W with the forward pass (x), codes of g_z with the two backward ones (dy).
+static bool dw_fused_parts(const int8t_conv_desc* d, const Geo& g, int parts, bool* x, bool* dy) {
+    constexpr int kX = INT8T_STEP_QUANT_XW | INT8T_STEP_FWD, kDy = INT8T_STEP_QUANT_G | INT8T_STEP_BWD_DATA | INT8T_STEP_BWD_WEIGHT;
+    *x = (parts & kX) == kX;
+    *dy = (parts & kDy) == kDy;
+    return g.depthwise && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 && d->pad_w == 1 &&
+           (*x || *dy) && *x == ((parts & kX) != 0) && *dy == ((parts & kDy) != 0);
+}
+
+// The passes of a dense layer as their launches plan them: geometry, selected variants, backward-weight's plan, and the scratch that
+// a split reduction would take.  (all other pointers are set by the caller)
+struct DensePasses {
+    IgemmArgs f{}, d{};
+    WgradArgs w{};
+};
+static void dense_passes(DensePasses* p, const int8t_conv_desc* desc, const Geo& g, void* ws_fwd, size_t ws_fwd_bytes, void* ws_bwd_data,
+                         size_t ws_bwd_data_bytes) {
+    fill_igemm_fwd(&p->f, desc, g);
+    p->f.variant = selected_variant(INT8T_OP_CONV_FWD, desc);
+    p->f.partial = (int32_t*)ws_fwd; p->f.partial_bytes = ws_fwd_bytes;
+    fill_igemm_bwd_data(&p->d, desc, g);
+    p->d.variant = selected_variant(INT8T_OP_CONV_BWD_DATA, desc);
+    p->d.partial = (int32_t*)ws_bwd_data; p->d.partial_bytes = ws_bwd_data_bytes;
+    fill_wgrad_geometry(&p->w, desc, g);
+    wgrad_s2d(&p->w);
+    p->w.variant = selected_variant(INT8T_OP_CONV_BWD_WEIGHT, desc);
+    wgrad_plan(&p->w);
+}
+
+int8t_form int8t_layer_step_form(const int8t_conv_desc* desc, int parts) {
+    Geo g;
+    if (desc_ok(desc, &g) != INT8T_OK || parts <= 0 || parts > INT8T_STEP_ALL) return INT8T_FORM_APART;
+    const bool fwd = parts & INT8T_STEP_FWD, both = (parts & INT8T_STEP_BWD_DATA) && (parts & INT8T_STEP_BWD_WEIGHT);
+    if (g.depthwise) {
+        const DwArgs w = dw_wgrad_args(desc, g);
+        bool x, dy;
+        if (dw_fused_parts(desc, g, parts, &x, &dy) && dw_fused_applies(desc->H, desc->W, w)) return INT8T_FORM_DW_CODES;
+        return both && dw_trio_applies(dw_args(desc, g, true), w) ? INT8T_FORM_DW_PASSES : INT8T_FORM_APART;
+    }
+    if (!both) return INT8T_FORM_APART;
+    DensePasses p;
+    int scratch;      // (its address is only looked at)
+    dense_passes(&p, desc, g, &scratch, int8t_workspace_bytes(INT8T_OP_CONV_FWD, desc, 0, 0), &scratch,
+                 int8t_workspace_bytes(INT8T_OP_CONV_BWD_DATA, desc, 0, 0));
+    if (desc->stride_h != 1 || desc->stride_w != 1) {
+        if (!conv_trio_strided(fwd ? &p.f : nullptr, p.d, p.w)) return INT8T_FORM_APART;
+        int form = STRIDED_PLAIN;
+        (void)igemm_strided_blocks(&p.d, &form);
+        return form == STRIDED_PLAIN     ? INT8T_FORM_STRIDED
+               : form == STRIDED_CLASSES ? INT8T_FORM_STRIDED_CLASSES
+               : form == STRIDED_CELL    ? INT8T_FORM_STRIDED_CELL
+                                         : INT8T_FORM_STRIDED_CELLS;
+    }
+    const TrioTile tile = conv_trio_tile(fwd && !conv_trio_fwd_apart(p.f, p.d) ? &p.f : nullptr, p.d, p.w);
+    if (!tile.bn) return INT8T_FORM_APART;
+    if (tile.rows64) return tile.bn == 64 ? INT8T_FORM_64X128 : INT8T_FORM_64X128_AND_128X128;
+    return tile.bn == 64 ? INT8T_FORM_128X64 : INT8T_FORM_128X128;
+}
+
 // int8t_layer_step, int8t_layer_backward (the first phase of the search without max|a| and max|W|, and the column sums db of g_z)
 // and int8t_layer_infer (codes and scales may be left out).
 enum class StepForm { kStep, kBackward, kInfer };
@@ -883,10 +943,8 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
     if (bwd_weight && b->ws_bwd_weight_bytes < int8t_workspace_bytes(INT8T_OP_CONV_BWD_WEIGHT, desc, 0, 0)) return INT8T_ERR_WORKSPACE;
     // Depthwise layers whose codes are formed in this call: quantization and passes in one launch (conv_dw_fused.hip), where nothing
     // overlaps what another part of the call reads or writes.
-    const bool dw_x = quant_xw && fwd, dw_g = quant_g && !b->dev_final && bwd_data && bwd_weight;
-    const bool dw_fused = g.depthwise && desc->R == 3 && desc->S == 3 && desc->stride_h == 1 && desc->stride_w == 1 && desc->pad_h == 1 &&
-                          desc->pad_w == 1 && (dw_x || dw_g) && dw_x == (quant_xw || fwd) && dw_g == (quant_g || bwd_data || bwd_weight) &&
-                          disjoint_step(desc, g, b, dw_x, dw_g);
+    bool dw_x = false, dw_g = false;
+    const bool dw_fused = dw_fused_parts(desc, g, parts, &dw_x, &dw_g) && !(quant_g && b->dev_final) && disjoint_step(desc, g, b, dw_x, dw_g);
     // ---- launches
     hipStream_t st = (hipStream_t)stream;
     if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
@@ -954,21 +1012,13 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         hipError_t e = hipSuccess;
         if (launch_dw_trio(fwd ? &f : nullptr, d, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     } else if (together && !g.depthwise) {
-        IgemmArgs f{}, d{};
-        WgradArgs w{};
-        fill_igemm_fwd(&f, desc, g);
-        f.variant = selected_variant(INT8T_OP_CONV_FWD, desc);
+        DensePasses p;
+        dense_passes(&p, desc, g, b->ws_fwd, b->ws_fwd ? b->ws_fwd_bytes : 0, b->ws_bwd_data, b->ws_bwd_data ? b->ws_bwd_data_bytes : 0);
+        IgemmArgs &f = p.f, &d = p.d;
+        WgradArgs& w = p.w;
         f.act = b->xq; f.wgt = b->wq; f.sa = b->sx; f.sb = b->sw; f.out = b->y; f.acc = b->y_acc;
-        f.partial = (int32_t*)b->ws_fwd; f.partial_bytes = b->ws_fwd ? b->ws_fwd_bytes : 0;
-        fill_igemm_bwd_data(&d, desc, g);
-        d.variant = selected_variant(INT8T_OP_CONV_BWD_DATA, desc);
         d.act = b->dyq; d.wgt = b->wq + align256((size_t)desc->K * desc->R * desc->S * pad16(desc->C));
         d.sa = b->sdy; d.sb = b->sw; d.out = b->dx; d.acc = b->dx_acc;
-        d.partial = (int32_t*)b->ws_bwd_data; d.partial_bytes = b->ws_bwd_data ? b->ws_bwd_data_bytes : 0;
-        fill_wgrad_geometry(&w, desc, g);
-        wgrad_s2d(&w);
-        w.variant = selected_variant(INT8T_OP_CONV_BWD_WEIGHT, desc);
-        wgrad_plan(&w);
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
         if (desc->stride_h != 1 || desc->stride_w != 1) {

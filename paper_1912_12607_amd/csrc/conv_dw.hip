@@ -1114,11 +1114,9 @@ hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st) {
 // large enough for blocks of 256 threads and, where backward-weight does not take groups of channels, of whole 16-byte chunks
 // in rows of whole dwords up to 4096 bytes (56 x 56; 112 x 112 planes keep their own launches).  Every layer of this kind
 // measured gains (20 of them, batch 1 to 256, 13 - 49 %).  false: not a layer for it, nothing launched.
-bool launch_dw_trio(const DwArgs* fwd, const DwArgs& b, const DwArgs& w_in, hipStream_t st, hipError_t* err) {
-    DwArgs w = w_in;
-    const DwArgs& f = fwd ? *fwd : b;
+static bool dw_trio_plan(const DwArgs& f, const DwArgs& w, DwTrio* tp, size_t* lds) {
     if (f.R != 3 || f.S != 3 || f.stride_h != 1 || f.stride_w != 1 || f.pad_h != 1 || f.pad_w != 1 || w.threads != 256) return false;
-    DwTrio t{};
+    DwTrio& t = *tp;
     // forward and backward-data have one geometry under "same" padding
     t.pitch = dw_fast_pitch(f.OW, 3) + 4;
     t.rows = f.OH + 2;
@@ -1126,28 +1124,41 @@ bool launch_dw_trio(const DwArgs* fwd, const DwArgs& b, const DwArgs& w_in, hipS
     if (lds1 > 60 * 1024) return false;
     t.ppb = dw_fast_ppb(f.N * f.C, f.OH, f.OW, f.IH, f.IW, lds1);
     if (dw_fast_threads(f.OH, f.OW, t.ppb) != 256) return false;
-    const int planes = (f.N * f.C + t.ppb - 1) / t.ppb;
-    t.fwd = fwd ? planes : 0;
-    const bool al = (f.IW & 3) == 0, group = w.cg > 1;
     const int ihw = w.IH * w.IW;
     t.gpitch = (w.OW + 3) & ~3;
     size_t ldsw;
-    if (group) {
+    if (w.cg > 1) {
         t.wpitch = dw_fast_pitch(w.OW, 3);
         const size_t ldsg = dw_group_lds(w, t.wpitch, t.gpitch);
         t.slot = dw_wgrad_slot(w.OH, w.OW);
         t.ni = dw_group_images(w, ldsg);
         ldsw = ldsg * t.ni;
     } else {
-        if (!al || (ihw & 15) != 0 || ihw > 4096) return false;
+        if ((f.IW & 3) != 0 || (ihw & 15) != 0 || ihw > 4096) return false;
         t.wpitch = dw_fast_pitch(w.OW, 3) + 4;
         t.xrows = w.OH + 2;
         ldsw = (((size_t)t.xrows * t.wpitch + 15) & ~(size_t)15) + (size_t)w.OH * t.gpitch;
     }
+    *lds = ldsw > lds1 * t.ppb ? ldsw : lds1 * t.ppb;
+    return true;
+}
+bool dw_trio_applies(const DwArgs& pass, const DwArgs& wgrad) {
+    DwTrio t{};
+    size_t lds;
+    return dw_trio_plan(pass, wgrad, &t, &lds);
+}
+bool launch_dw_trio(const DwArgs* fwd, const DwArgs& b, const DwArgs& w_in, hipStream_t st, hipError_t* err) {
+    DwArgs w = w_in;
+    const DwArgs& f = fwd ? *fwd : b;
+    DwTrio t{};
+    size_t lds = 0;
+    if (!dw_trio_plan(f, w, &t, &lds)) return false;
+    const int planes = (f.N * f.C + t.ppb - 1) / t.ppb;
+    t.fwd = fwd ? planes : 0;
+    const bool al = (f.IW & 3) == 0, group = w.cg > 1;
     w.chunks = (w.chunks + 1) / 2;
     t.wgrad_x = w.C / w.cg;
     t.wgrad = t.wgrad_x * w.chunks;
-    const size_t lds = ldsw > lds1 * t.ppb ? ldsw : lds1 * t.ppb;
     const dim3 grid((unsigned)(t.wgrad + t.fwd + planes));
     {
         KernelTimer kt(KID_DW_TRIO, st);

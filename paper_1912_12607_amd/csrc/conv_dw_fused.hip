@@ -262,24 +262,34 @@ __global__ __launch_bounds__(256, dwf_blocks(U, XQ, GQ)) void dw_fused_kernel(co
 // step that keeps the clip value (max|.|, codes and passes; in two launches and the reduction's / here): 144 channels at 56 x 56
 // 154 / 127 (the launch itself 102 us for 520 MB, 5.1 TB/s), 192 at 28 x 28 56 / 41, 576 at 14 x 14 63 / 38, 960 at 7 x 7 40 / 23;
 // 32 channels at 16 x 16, batch 2, 14.2 / 11.1; the halves at 144 channels, 56 x 56: 70 / 61 with the forward pass, 73 / 61 with
-// the backward ones.  `shares` of the batch: one round of resident blocks,
-// at most as many as backward-weight's scratch holds.
+// the backward ones.  Fills the launch shape.
+static bool dw_fused_plan(DwFused* a, const DwArgs& wgrad) {
+    const int HW = a->H * a->W, QW = (a->W + 3) / 4;
+    if (a->W < 4 || wgrad.threads != 256) return false;
+    if (wgrad.cg > 1) {
+        a->cg = wgrad.cg;
+        a->slot = 4;
+        while (a->slot < a->H * QW) a->slot *= 2;
+        if ((a->cg * HW & 15) != 0 || a->cg * HW > 1024 || a->slot > kWave || a->cg * a->slot > 256 || a->cg > 32) return false;
+    } else {
+        a->cg = 1;
+        if ((a->W & 3) != 0 || (HW & 15) != 0 || HW > 4096) return false;
+    }
+    a->pitch = ((a->W + 3) & ~3) + 8;                        // four bytes on either side: windows end inside the last dword
+    return true;
+}
+bool dw_fused_applies(int H, int W, const DwArgs& wgrad) {
+    DwFused a{};
+    a.H = H; a.W = W;
+    return dw_fused_plan(&a, wgrad);
+}
+
+// `shares` of the batch: one round of resident blocks, at most as many as backward-weight's scratch holds.
 bool launch_dw_fused(const DwFused& in, const DwArgs& wgrad, hipStream_t st, hipError_t* err) {
     DwFused a = in;
-    const bool xq = a.x != nullptr, gq = a.g != nullptr;
-    const int HW = a.H * a.W, QW = (a.W + 3) / 4;
-    const bool group = wgrad.cg > 1;
-    if (a.W < 4 || wgrad.threads != 256) return false;
-    if (group) {
-        a.cg = wgrad.cg;
-        a.slot = 4;
-        while (a.slot < a.H * QW) a.slot *= 2;
-        if ((a.cg * HW & 15) != 0 || a.cg * HW > 1024 || a.slot > kWave || a.cg * a.slot > 256 || a.cg > 32) return false;
-    } else {
-        a.cg = 1;
-        if ((a.W & 3) != 0 || (HW & 15) != 0 || HW > 4096) return false;
-    }
-    a.pitch = ((a.W + 3) & ~3) + 8;                          // four bytes on either side: windows end inside the last dword
+    if (!dw_fused_plan(&a, wgrad)) return false;
+    const bool xq = a.x != nullptr, gq = a.g != nullptr, group = wgrad.cg > 1;
+    const int HW = a.H * a.W;
     const size_t lds = (size_t)(gq ? 2 : 1) * a.cg * (a.H + 2) * a.pitch;
     const int groups = a.C / a.cg;
     const int u = group || HW <= 1024 ? 1 : HW <= 2048 ? 2 : 4;

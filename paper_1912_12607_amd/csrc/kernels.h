@@ -342,10 +342,12 @@ void dw_wgrad_shape(int N, int C, int IH, int IW, int P, int Q, int R, int S, in
 hipError_t launch_dw_conv(const DwArgs& a, hipStream_t st);
 hipError_t launch_dw_wgrad(const DwArgs& a, hipStream_t st);
 hipError_t launch_dw_wgrad_reduce(const DwArgs& a, hipStream_t st);
-// false: not a layer for it, nothing launched
+// whether a 3x3 layer under stride 1 and "same" padding is one for it; launch: false, nothing launched, where it is not
+bool dw_fused_applies(int H, int W, const DwArgs& wgrad);
 bool launch_dw_fused(const DwFused& a, const DwArgs& wgrad, hipStream_t st, hipError_t* err);
 // the three passes of a layer (fwd: nullptr where only the two backward ones run) in one launch; false: not a layer for it,
 // nothing launched
+bool dw_trio_applies(const DwArgs& pass, const DwArgs& wgrad);
 bool launch_dw_trio(const DwArgs* fwd, const DwArgs& bwd, const DwArgs& wgrad, hipStream_t st, hipError_t* err);
 
 }  // namespace int8t

@@ -185,6 +185,12 @@ class LayerStep:
                 raise B.Int8tError(status)
 
         self._k_step, self._layer_buffers = k_step, buf
+        # depthwise layers that form their codes in the launch of the passes, in two halves for two streams: 144 channels at 56 x 56,
+        # batch 64, 240 -> 215 us, batch 256 946 -> 801; others quantize g_z beside the forward pass (57 x 57, 96 channels: 232 and
+        # 241 in that order)
+        self._one_pass = (self.depthwise and not self.requantize_deviation and not self.fused_fwd
+                          and all(B.int8t_layer_step_form(self.desc, parts) == B.FORM_DW_CODES
+                                  for parts in (B.STEP_QUANT_XW | B.STEP_FWD, B.STEP_QUANT_G | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT)))
 
     def upload(self, x: np.ndarray, w: np.ndarray, dy: np.ndarray, ratios: np.ndarray):
         self.x.copy_(torch.from_numpy(np.ascontiguousarray(x)))
@@ -310,10 +316,7 @@ class LayerStep:
         self._ev_main.record(main)
         side.wait_event(self._ev_main)
         early = mode >= 3 and not self.fused_fwd
-        # depthwise layers that form their codes in the launch of the passes (int8t_layer_step), in two halves: 144 channels at
-        # 56 x 56, batch 64, 240 -> 215 us, batch 256 946 -> 801
-        one_pass = (mode == 1 and self.depthwise and self.input_grad and not self.requantize_deviation and not self.fused_fwd
-                    and (self.L.R, self.L.S, self.L.stride, self.L.pad) == (3, 3, (1, 1), (1, 1)) and self.L.H * self.L.W <= 4096)
+        one_pass = mode == 1 and self._one_pass and self.input_grad
         if self.fused_fwd:
             self._k_w(sp)
             self._k_fwd_fused(sp)               # writes the codes of a

@@ -51,3 +51,40 @@ def test_tune_kernels_against_the_shared_launch(monkeypatch, overlap, faster, t_
     finally:
         for op in OPS.values():
             B.int8t_conv_select_variant(op, st.desc, B.VARIANT_AUTO)
+
+
+# The two-stream step of a depthwise layer: in two halves, the second behind the first, only where the library takes the codes into the
+# launch of the passes; elsewhere g_z is quantized beside the forward pass, before the main stream waits for it.
+@pytest.mark.parametrize("shape,halves", [((2, 5, 56, 56), True), ((2, 5, 32, 36), True), ((2, 64, 7, 7), True), ((4, 32, 14, 14), True),
+                                          ((2, 5, 57, 57), False), ((2, 5, 43, 43), False), ((2, 5, 55, 55), False), ((2, 5, 45, 45), False),
+                                          ((2, 32, 65, 63), False), ((4, 16, 8, 3), False)])
+def test_two_stream_order_of_depthwise_layers(monkeypatch, shape, halves):
+    N, C_, H, W = shape
+    monkeypatch.setattr(B, "_ptr", lambda t: None if t is None else C.c_void_p(t.data_ptr()))
+    st = LayerStep(Layer("layer", N, C_, H, W, C_, 3, 3, stride=(1, 1), pad=(1, 1), groups=C_), device="cpu", requantize_deviation=False)
+    seen = []
+
+    class Stream:
+        def __init__(self, name):
+            self.name = name
+
+        def wait_event(self, event):
+            seen.append((self.name, "waits"))
+
+    class Event:
+        def record(self, stream):
+            pass
+
+    main = Stream("main")
+    monkeypatch.setattr("paper_1912_12607_amd.step.side_stream", lambda dev: Stream("side"))
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(B, "stream_pointer", lambda s: s.name)
+    for name in ("prepare", "search", "qdy", "fwd"):
+        monkeypatch.setattr(st, "_k_" + name, lambda *a, name=name: seen.append((a[-1], name)))
+    monkeypatch.setattr(st, "_k_step", lambda parts, seed, sp: seen.append((sp, parts)))
+    st.run(seed=1, stream=main, search=True, overlap=1)
+    on_main = [what for name, what in seen if name == "main"]
+    bwd = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    assert on_main == ["prepare", "search"] + (["waits", B.STEP_QUANT_G | bwd] if halves else ["qdy", "waits", bwd])
+    assert [what for name, what in seen if name == "side"][1:] == (
+        [B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_FWD] if halves else [B.STEP_ABSMAX | B.STEP_QUANT_XW, "fwd"])
