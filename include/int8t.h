@@ -324,7 +324,8 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc *desc,
 /*
  * The same with the scratch that an int8t_conv_fwd on this layer and these codes xq was given, its contents unchanged since (and that
  * call ordered before this one): where both passes of a layer rewrite the codes of a first (stride 2 on at most 4 channels),
- * the forward pass's are used.  fwd_ws_dev NULL, or of fewer bytes than int8t_workspace_bytes(INT8T_OP_CONV_FWD, ..): as int8t_conv_bwd_weight.
+ * the forward pass's are used.  fwd_ws_bytes is what that call was given.  fwd_ws_dev NULL, or of too few bytes for the rewritten codes
+ * (the forward pass then did without): as int8t_conv_bwd_weight.
  */
 int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc *desc,
                                        const int8_t *xq_dev, const float *sx_dev,
@@ -412,8 +413,9 @@ int8t_status int8t_layer_backward(const int8t_conv_desc *desc, const int8t_layer
 
 /*
  * The forward pass of a layer nobody wants the codes of (a network in use): y as int8t_layer_step with INT8T_STEP_ABSMAX,
- * INT8T_STEP_QUANT_XW and INT8T_STEP_FWD writes it, bit for bit; the same buffers are required, but what is in xq, wq, sx and sw
- * afterwards is undefined (a 1x1 layer with few filters quantizes inside the convolution).
+ * INT8T_STEP_QUANT_XW and INT8T_STEP_FWD writes it, bit for bit; the same buffers are required.  xq, wq, sx and sw then either
+ * hold what those parts write or are as they were (a 1x1 layer with few filters quantizes inside the convolution): codes of W that an
+ * earlier call left there are still those of the same W.
  */
 int8t_status int8t_layer_infer(const int8t_conv_desc *desc, const int8t_layer_buffers *b, void *stream);
 

@@ -313,3 +313,26 @@ def test_bias_of_another_type(linear, dtype, result):
     bias, m.bias = m.bias, None
     y0 = m(x)
     assert y0.dtype == torch.float32 and torch.equal(y, y0 + (bias if linear else bias.view(1, -1, 1, 1)))
+
+
+# A forward pass without gradients between a layer's forward and backward pass leaves the codes of the weights that the backward pass
+# reads: where it quantizes inside the convolution (64 -> 24, 9 x 9), where it writes the same codes, and with new weights since.
+@pytest.mark.parametrize("C,K,kernel", [(64, 24, 1), (64, 80, 1), (16, 16, 3)])
+@pytest.mark.parametrize("update", [False, True])
+def test_inference_between_forward_and_backward(C, K, kernel, update):
+    def run(between):
+        m = _layer(C, K, kernel, 1, kernel // 2, 1, seed=3)
+        g = torch.Generator(device="cuda").manual_seed(9)
+        x = torch.randn(2, C, 9, 9, generator=g, device="cuda", requires_grad=True)
+        dy = torch.randn(2, K, 9, 9, generator=g, device="cuda")
+        other = torch.randn(2, C, 9, 9, generator=g, device="cuda") * 3.0
+        y = m(x)
+        with torch.no_grad():
+            if update:
+                m.weight.mul_(-0.5)
+            if between:
+                m(other)
+        return [y.detach()] + list(torch.autograd.grad(y, [x, m.weight], dy))
+
+    for a, b in zip(run(True), run(False)):
+        assert torch.equal(a, b)
