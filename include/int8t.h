@@ -476,7 +476,7 @@ int8t_variant int8t_conv_selected_variant(int8t_op op, const int8t_conv_desc *de
  *            "absmax_batch_kernel", "quantize_batch_kernel", "quantize_act_kernel", "quantize_planar_kernel", "quantize_wgt_kernel",
  *            "deviation_finish_kernel", "igemm_kernel", "igemm_dma_kernel", "igemm_fused_kernel", "igemm_reduce_kernel",
  *            "band_kernel", "band_reg_kernel", "wgrad_kernel", "wgrad_lines_kernel", "wgrad_reduce_kernel", "s2d_repack_kernel",
- *            "s2d_weights_kernel" (now part of the former; never launched), "conv_trio_kernel", "dw_conv_kernel" (every depthwise forward / backward-data variant),
+ *            "conv_trio_kernel", "dw_conv_kernel" (every depthwise forward / backward-data variant),
  *            "dw_wgrad_kernel" (every depthwise backward-weight variant), "dw_wgrad_reduce_kernel", "dw_trio_kernel", "infer_1x1_kernel");
  *            "conv_trio_kernel" and "dw_trio_kernel" are all the launches that several passes share: strided layers' and the one that
  *            quantizes depthwise tensors too;

@@ -120,8 +120,6 @@ DwArgs dw_wgrad_args(const int8t_conv_desc* d, const Geo& g) {
     return a;
 }
 
-size_t fwd_s2d_bytes(const int8t_conv_desc* d, const Geo& g);
-
 // geometry of the implicit GEMMs (pointers are set by the entry points)
 void fill_igemm_fwd(IgemmArgs* a, const int8t_conv_desc* d, const Geo& g) {
     a->N = d->N; a->rows = d->K; a->Ca = pad16(d->C);

@@ -81,7 +81,7 @@ __device__ __forceinline__ void store_cell(T* __restrict__ dst, size_t o, int OW
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class
 //   form writes every other float of a line from four different blocks and pays a block's fixed cost per class.
 //   STG (plain forms, planes of whole 16-byte groups): the results leave through LDS, see the epilogue.
-//   NWN: waves along the columns.  4 with WM = 1 (and 256 columns): 64-row tiles for passes of at most 64 rows.
+//   NWN: waves along the columns.  4 with WM = 1: 64 x 128 tiles for passes of at most 64 rows.
 template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS = false, bool CELL = false, int BNT = IGD_BN, bool ALLC = false, bool STG = false, int NWN = 2>
 __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigned block) {
     static_assert(!STG || (!CLS && WM * NWN == 4), "staged results: plain forms of the tiles of four waves");
@@ -95,7 +95,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     constexpr int NLA = BM * KG / 64 / NW;              // A loads per wave and stage
     constexpr int NLB = BN * KG / 64 / NW;              // B loads per wave and stage
     constexpr int NL = NLA + NLB;
-    static_assert(NSTAGE == 2 || NL == 6 || NL == 5 || NL == 4, "vmcnt waits below are written for these");
+    static_assert(NSTAGE == 2 || NL == 6 || NL == 4, "vmcnt waits below are written for these");
     extern __shared__ __attribute__((aligned(16))) uint4 ring[];   // [NSTAGE][STAGE_SLOTS]
     raise_wave_priority();
 

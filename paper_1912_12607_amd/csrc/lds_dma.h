@@ -33,12 +33,11 @@ __device__ __forceinline__ int igd_slot(int row, int g) {
 }
 template <int N>
 __device__ __forceinline__ void igd_wait_vmcnt() {
-    static_assert(N == 0 || N == 1 || N == 2 || N == 4 || N == 5 || N == 6 || N == 8 || N == 12, "outstanding loads allowed while waiting");
+    static_assert(N == 0 || N == 1 || N == 2 || N == 4 || N == 6 || N == 8 || N == 12, "outstanding loads allowed while waiting");
     if (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (N == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
     else if (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
     else if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else if (N == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else if (N == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
     else if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");

@@ -31,7 +31,6 @@ enum KernelId : int {
     KID_WGRAD_LINES,
     KID_WGRAD_REDUCE,
     KID_S2D_REPACK,
-    KID_S2D_WEIGHTS,
     KID_CONV_TRIO,
     KID_DW_CONV,
     KID_DW_WGRAD,
