@@ -339,13 +339,16 @@ def test_depthwise_codes_and_passes_in_one_launch(shape, form):
     buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
     if form == "dx over dy":
         buf.dx = buf.dy
-    B.int8t_profile_start("dw_trio_kernel")
+    B.int8t_profile_start(None)
     got = result([front | fwd, bwd] if form == "halves" else [front | fwd | bwd], buf)
     launches = B.int8t_profile_stop()
+    quantized = any(k.startswith("quantize") for k in launches)        # (a launch of its own for codes)
     if form == "dx over dy":
         got[outs.index("dx")] = st.dy.clone()
+        assert quantized
     else:
-        assert launches["dw_trio_kernel"][0] == (2 if form == "halves" else 1)
+        assert launches["dw_trio_kernel"][0] == (2 if form == "halves" else 1) and not quantized
+        assert all(B.int8t_layer_step_form(st.desc, parts) == B.FORM_DW_CODES for parts in (front | fwd | bwd, fwd, bwd))
     for n, a, b in zip(outs, got, want):
         assert torch.equal(a, b), n
 
@@ -385,16 +388,22 @@ def test_codes_of_rows(N, C):
 
 
 # Passes of at most 64 rows on 64 x 128 tiles in the shared launch: all of them, the forward or the backward-data pass beside a wider
-# one, rows that end inside a fragment, planes of whole 16-byte groups and others, the last column tile ragged; and layers just
-# below the rule's bound, which stay on 128-row tiles.  The calls one by one are the other kernels.
-@pytest.mark.parametrize("shape", [(20, 40, 30, 30, 24, 3, 3), (25, 33, 27, 27, 64, 3, 3), (20, 5, 30, 31, 64, 5, 5), (26, 64, 23, 29, 7, 1, 7), (32, 200, 28, 28, 20, 3, 3),
-                                   (32, 20, 28, 28, 200, 3, 3), (33, 48, 27, 27, 130, 3, 1), (15, 40, 30, 30, 24, 3, 3), (27, 200, 28, 28, 20, 3, 3),
-                                   (64, 40, 31, 31, 130, 1, 1)])
+# one, the two backward passes alone, rows that end inside a fragment, planes of whole 16-byte groups and others, the last column tile
+# ragged; and layers just below the rule's bounds, which stay on 128-row tiles.  The calls one by one are the other kernels.
+@pytest.mark.parametrize("shape,three,two", [
+    ((20, 40, 30, 30, 24, 3, 3), B.FORM_64X128, B.FORM_128X64), ((33, 40, 30, 30, 24, 3, 3), B.FORM_64X128, B.FORM_64X128),
+    ((25, 33, 27, 27, 64, 3, 3), B.FORM_64X128, B.FORM_128X64), ((41, 33, 27, 27, 64, 3, 3), B.FORM_64X128, B.FORM_64X128),
+    ((32, 5, 30, 31, 64, 5, 5), B.FORM_64X128, B.FORM_64X128), ((45, 64, 23, 29, 7, 1, 7), B.FORM_64X128, B.FORM_64X128),
+    ((32, 200, 28, 28, 20, 3, 3), B.FORM_64X128_AND_128X128, B.FORM_128X64), ((42, 200, 28, 28, 20, 3, 3), B.FORM_64X128_AND_128X128, B.FORM_128X128),
+    ((32, 20, 28, 28, 200, 3, 3), B.FORM_64X128_AND_128X128, B.FORM_128X64), ((33, 48, 27, 27, 130, 3, 1), B.FORM_64X128_AND_128X128, B.FORM_128X64),
+    ((17, 40, 30, 30, 24, 3, 3), B.FORM_128X64, B.FORM_128X64), ((28, 200, 28, 28, 20, 3, 3), B.FORM_128X64, B.FORM_128X64),
+    ((64, 40, 31, 31, 130, 1, 1), B.FORM_64X128_AND_128X128, B.FORM_64X128)])
 @pytest.mark.parametrize("passes", [B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT])
-def test_narrow_passes_in_one_launch(shape, passes):
+def test_narrow_passes_in_one_launch(shape, three, two, passes):
     N, C, H, W, K, R, S = shape
     L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2), groups=1)
     st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    assert B.int8t_layer_step_form(st.desc, passes) == (three if passes & B.STEP_FWD else two)
     g = torch.Generator(device=DEV).manual_seed(13)
     for t in (st.x, st.w, st.dy):
         t.normal_(generator=g)
@@ -420,12 +429,16 @@ def test_narrow_passes_in_one_launch(shape, passes):
 
 # Backward-weight of 1x1 filters with few channels on one side, either side of the bounds between its two kernels: 256 input
 # channels, a batch of 32 on square and other images and under a stride, less than a hundred channels in all on large images.
-@pytest.mark.parametrize("shape", [(2, 256, 5, 7, 8, 1, 1, 1, (0, 0)), (2, 240, 5, 7, 8, 1, 1, 1, (0, 0)), (31, 40, 6, 6, 20, 1, 1, 1, (0, 0)),
-                                   (32, 40, 6, 6, 20, 1, 1, 1, (0, 0)), (9, 24, 28, 7, 130, 1, 1, 1, (0, 0)), (33, 3, 9, 9, 250, 1, 1, 2, (0, 0)),
-                                   (32, 48, 32, 32, 33, 1, 1, 1, (0, 0)), (32, 64, 32, 32, 33, 1, 1, 1, (0, 0)), (64, 100, 1, 1, 70, 1, 1, 1, (0, 0))])
-def test_backward_weight_narrow_1x1(shape):
+@pytest.mark.parametrize("shape,lines", [
+    ((2, 256, 5, 7, 8, 1, 1, 1, (0, 0)), True), ((2, 240, 5, 7, 8, 1, 1, 1, (0, 0)), False), ((31, 40, 6, 6, 20, 1, 1, 1, (0, 0)), False),
+    ((32, 40, 6, 6, 20, 1, 1, 1, (0, 0)), True), ((9, 24, 28, 7, 130, 1, 1, 1, (0, 0)), True), ((33, 5, 9, 9, 250, 1, 1, 2, (0, 0)), True),
+    ((32, 48, 32, 32, 33, 1, 1, 1, (0, 0)), False), ((32, 64, 32, 32, 33, 1, 1, 1, (0, 0)), True), ((64, 100, 1, 1, 70, 1, 1, 1, (0, 0)), True)])
+def test_backward_weight_narrow_1x1(shape, lines):
     desc, od, (xq, wq, dyq) = random_layer(shape, 3)
+    B.int8t_profile_start(None)
     conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
+    launches = B.int8t_profile_stop()
+    assert ("wgrad_lines_kernel" in launches, "wgrad_kernel" in launches) == (lines, not lines)
 
 
 # Layers that run in space-to-depth form: backward-weight on what the forward pass made of the codes, in one call, in calls of their
@@ -505,14 +518,17 @@ def test_forward_without_codes(shape, fused):
 # The passes of a strided layer in one launch: 3x3 filters with the four pixel classes of a cell in a block, a class per tile, and plain
 # (short runs of pixels); 1x1 filters in cells of even images, odd images, other strides; paddings, ragged rows and columns, results on
 # planes of no whole 16-byte groups.  Against the calls one by one, bit for bit.
-@pytest.mark.parametrize("shape", [(3, 130, 28, 28, 40, 3, 2, 2, 1), (2, 150, 30, 32, 200, 3, 2, 2, 0), (5, 40, 24, 25, 70, 3, 2, 2, 1), (2, 257, 33, 27, 30, 3, 2, 2, 2),
-                                   (9, 16, 11, 11, 33, 3, 2, 2, 1), (34, 70, 14, 14, 50, 1, 2, 2, 0), (3, 300, 15, 13, 140, 1, 2, 2, 0), (3, 300, 14, 10, 20, 1, 3, 1, 0),
-                                   (2, 260, 9, 12, 33, 1, 1, 2, 0)])
+@pytest.mark.parametrize("shape,form", [
+    ((3, 130, 28, 28, 40, 3, 2, 2, 1), B.FORM_STRIDED_CELLS), ((2, 150, 30, 32, 200, 3, 2, 2, 0), B.FORM_STRIDED_CELLS),
+    ((5, 40, 24, 25, 70, 3, 2, 2, 1), B.FORM_STRIDED_CLASSES), ((2, 257, 33, 27, 30, 3, 2, 2, 2), B.FORM_STRIDED_CLASSES),
+    ((9, 16, 11, 11, 33, 3, 2, 2, 1), B.FORM_STRIDED), ((34, 70, 14, 14, 50, 1, 2, 2, 0), B.FORM_STRIDED_CELL),
+    ((3, 300, 15, 13, 140, 1, 2, 2, 0), B.FORM_STRIDED), ((3, 300, 14, 10, 20, 1, 3, 1, 0), B.FORM_STRIDED), ((2, 260, 9, 12, 33, 1, 1, 2, 0), B.FORM_STRIDED)])
 @pytest.mark.parametrize("passes", [B.STEP_FWD | B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT])
-def test_strided_passes_in_one_launch(shape, passes):
+def test_strided_passes_in_one_launch(shape, form, passes):
     N, C, H, W, K, R, sh, sw, pad = shape
     L = inputs.Layer("layer", N, C, H, W, K, R, R, stride=(sh, sw), pad=(pad, pad), groups=1)
     st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    assert B.int8t_layer_step_form(st.desc, passes) == form
     g = torch.Generator(device=DEV).manual_seed(16)
     for t in (st.x, st.w, st.dy):
         t.normal_(generator=g)
@@ -538,9 +554,10 @@ def test_strided_passes_in_one_launch(shape, passes):
 
 # Codes of planes of no whole 16-byte groups (a plane's last quad of one, two and three pixels, planes of two and three pixels, the
 # tensor's end), and tiles dealt image by image or eight images side by side (with and without images beyond the batch, one and
-# several channel groups, whole groups too); both roundings, with Eq.6 and in a batch with another tensor behind it.
+# several channel groups, whole groups too; at most 16 channels, a pixel per thread); both roundings, with Eq.6 and in a batch with another tensor behind it.
 @pytest.mark.parametrize("N,C,H,W", [(1, 17, 1, 2), (3, 20, 3, 1), (2, 100, 7, 7), (8, 33, 9, 9), (8, 65, 17, 17), (16, 20, 17, 18), (15, 18, 17, 19),
-                                     (31, 24, 17, 17), (8, 130, 47, 45), (8, 40, 47, 45), (8, 70, 18, 18), (1, 18, 5, 13)])
+                                     (31, 24, 17, 17), (8, 130, 47, 45), (8, 40, 47, 45), (8, 70, 18, 18), (1, 18, 5, 13),
+                                     (8, 3, 17, 17), (16, 16, 33, 31), (31, 9, 17, 17), (15, 3, 19, 17)])
 def test_codes_of_ragged_planes(N, C, H, W):
     r = np.random.RandomState(C + W)
     x = (r.standard_t(3, size=(N, C, H, W)) * 1e-3).astype(np.float32)
