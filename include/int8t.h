@@ -324,8 +324,8 @@ int8t_status int8t_conv_bwd_weight(const int8t_conv_desc *desc,
 /*
  * The same with the scratch that an int8t_conv_fwd on this layer and these codes xq was given, its contents unchanged since (and that
  * call ordered before this one): where both passes of a layer rewrite the codes of a first (stride 2 on at most 4 channels),
- * the forward pass's are used.  fwd_ws_bytes is what that call was given.  fwd_ws_dev NULL, or of too few bytes for the rewritten codes
- * (the forward pass then did without): as int8t_conv_bwd_weight.
+ * the forward pass's are used.  fwd_ws_bytes is what that call was given.  fwd_ws_dev NULL, of too few bytes for the rewritten codes
+ * (the forward pass then did without), or within ws_dev, which this call writes: as int8t_conv_bwd_weight.
  */
 int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc *desc,
                                        const int8_t *xq_dev, const float *sx_dev,

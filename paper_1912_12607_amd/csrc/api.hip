@@ -743,7 +743,9 @@ int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc* desc, const int8_t
     a.x = xq_dev; a.dy = dyq_dev; a.sa = sx_dev; a.sb = sdy_dev; a.dw = dw_dev; a.acc = acc_dev;
     a.partial = (int32_t*)ws_dev;
     a.xs = (int8_t*)ws_dev + align256((size_t)a.splits * a.K * a.R * a.S * a.Cp * 4);
-    if (fwd_ws_dev && fwd_s2d_bytes(desc, g) && fwd_ws_bytes >= fwd_s2d_bytes(desc, g)) {
+    const size_t fwd_bytes = fwd_s2d_bytes(desc, g);
+    const bool apart = (uintptr_t)fwd_ws_dev + fwd_bytes <= (uintptr_t)ws_dev || (uintptr_t)ws_dev + ws_bytes <= (uintptr_t)fwd_ws_dev;
+    if (fwd_ws_dev && fwd_bytes && fwd_ws_bytes >= fwd_bytes && apart) {
         a.xs = (int8_t*)const_cast<void*>(fwd_ws_dev);      // (read only)
         a.xs_ready = 1;
     }

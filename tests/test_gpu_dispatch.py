@@ -482,6 +482,8 @@ def test_backward_weight_on_the_forward_passes_codes(shape):
     shared = torch.empty(max(st.ws.numel(), st.ws_fwd.numel()), dtype=torch.uint8, device=DEV)
     buf.ws_fwd = buf.ws_bwd_weight = shared.data_ptr()
     check(lambda: B.int8t_layer_step(st.desc, buf, both), 2)
+    B.int8t_conv_fwd(st.desc, st.xq, st.sx, st.wq, st.sw, st.y, None, shared)
+    check(lambda: B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, shared, shared), 1)
 
 
 # The forward pass without codes: one and two row tiles of filters, planes of whole 16-byte groups and others, ragged pixel tiles,
