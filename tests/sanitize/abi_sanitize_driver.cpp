@@ -137,6 +137,16 @@ int main() {
     EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_BWD_WEIGHT, 0, nullptr) == INT8T_ERR_WORKSPACE);
     lb.dyq = q + 1;
     EXPECT(int8t_layer_step(&good, &lb, INT8T_STEP_BWD_DATA, 0, nullptr) == INT8T_ERR_ARG);
+    EXPECT(int8t_layer_step_form(nullptr, INT8T_STEP_ALL) == INT8T_FORM_APART && int8t_layer_step_form(&grp, INT8T_STEP_ALL) == INT8T_FORM_APART);
+    for (int parts = -1; parts <= INT8T_STEP_ALL + 1; ++parts) {
+        const int8t_conv_desc plain = good, stem = {2, 3, 17, 17, 24, 7, 7, 2, 2, 3, 3, 1}, strided = {2, 40, 17, 16, 70, 3, 3, 2, 2, 1, 1, 1},
+                              dw = {3, 24, 14, 14, 24, 3, 3, 1, 1, 1, 1, 24};
+        for (const int8t_conv_desc* d : {&plain, &stem, &strided, &dw}) {
+            const int8t_form form = int8t_layer_step_form(d, parts);
+            EXPECT(form >= INT8T_FORM_APART && form <= INT8T_FORM_DW_CODES);
+            if (parts <= 0 || parts > INT8T_STEP_ALL || d == &stem) EXPECT(form == INT8T_FORM_APART);
+        }
+    }
     EXPECT(int8t_profile_start("no_such_kernel") == INT8T_ERR_ARG);
     EXPECT(int8t_profile_start_sampled("wgrad_kernel", 0) == INT8T_ERR_ARG);
     EXPECT(int8t_dclr_scale(0.0, 20.0, 0.1) == 1.0 && int8t_dclr_scale(1.0, 20.0, 0.1) == 0.1);
