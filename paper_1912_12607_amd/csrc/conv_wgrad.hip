@@ -10,6 +10,71 @@ __global__ __launch_bounds__(256, 2) void wgrad_kernel(const WgradArgs a) {
     wgrad_tile<TB, CS, PK>(a, blockIdx.x);
 }
 
+// Where a sum of filter k, tap rs, channel c of the pass's own geometry goes.
+__device__ __forceinline__ void wgrad_result(const WgradArgs& a, int k, int rs, int c, int sum, float scale) {
+    if (c >= a.C) return;
+    size_t o = ((size_t)k * a.C + c) * (a.R * a.S) + rs;
+    if (a.s2d) {
+        // back from the space-to-depth form: channel (2 dy + dx) * oC + c0 of tap (r', s') is channel c0
+        // of tap (2 r' + dy - eh, 2 s' + dx - ew); taps outside the layer's own filter are dropped
+        const int blk = c / a.oC, c0 = c - blk * a.oC;
+        const int rr = rs / a.S;
+        const int r = 2 * rr + (blk >> 1) - a.eh, s = 2 * (rs - rr * a.S) + (blk & 1) - a.ew;
+        if (r < 0 || r >= a.oR || s < 0 || s >= a.oS) return;
+        o = (((size_t)k * a.oC + c0) * a.oR + r) * a.oS + s;
+    }
+    a.dw[o] = __fmul_rn((float)sum, scale);
+    if (a.acc) a.acc[o] = sum;
+}
+
+// Few weights under many shares (a share's partial tile set is a few hundred KB at most): a block owns Q quads of four
+// channels, side by side in the partial's own order whatever taps and filters they belong to, its threads are (quads) x (split
+// lanes); every thread has up to 8 shares' 16 bytes in flight at once, the lanes of a wave are combined by lane
+// exchanges, the four waves through LDS.
+// Bound: one round trip to memory and the launch.  Before, 4 or 16 quads x one tap with the shares one after the other and the lanes summed
+// in LDS, and now, us: 3x3, 64 channels at 56 x 56, batch 64 (112 shares) 7.2, 4.7; 1x1, 64 -> 256 at 56 x 56, batch 256 (224) 7.2, 4.6;
+// 1x1, 1024 -> 256 at 14 x 14, batch 128 (19) 6.8, 5.5; 5x5, 48 -> 64 at 35 x 35, batch 32 (35) 5.4, 4.5.
+template <int Q>
+__global__ __launch_bounds__(256) void wgrad_reduce_flat_kernel(const WgradArgs a) {
+    constexpr int ZL = 256 / Q, ZU = 8;
+    __shared__ int4 part[4][Q];
+    const unsigned quads = (unsigned)a.K * (unsigned)(a.R * a.S) * (unsigned)(a.Cp >> 2);
+    const unsigned q0 = blockIdx.x * Q;
+    const int zl = threadIdx.x / Q;
+    const unsigned qi = q0 + threadIdx.x % Q;
+    const int4* __restrict__ p = reinterpret_cast<const int4*>(a.partial) + (qi < quads ? qi : 0u);
+    int4 sum = make_int4(0, 0, 0, 0);
+    for (int z0 = zl; z0 < a.splits; z0 += ZU * ZL) {
+        int4 v[ZU];
+#pragma unroll
+        for (int u = 0; u < ZU; ++u) {           // (unconditional: past the end the last share again, not added)
+            const int z = z0 + u * ZL;
+            v[u] = p[(size_t)(z < a.splits ? z : a.splits - 1) * quads];
+        }
+#pragma unroll
+        for (int u = 0; u < ZU; ++u) {
+            const int keep = z0 + u * ZL < a.splits ? -1 : 0;
+            sum.x += v[u].x & keep; sum.y += v[u].y & keep; sum.z += v[u].z & keep; sum.w += v[u].w & keep;
+        }
+    }
+#pragma unroll
+    for (int o = Q; o < kWave; o <<= 1) {
+        sum.x += __shfl_xor(sum.x, o, kWave); sum.y += __shfl_xor(sum.y, o, kWave);
+        sum.z += __shfl_xor(sum.z, o, kWave); sum.w += __shfl_xor(sum.w, o, kWave);
+    }
+    if ((int)(threadIdx.x & (kWave - 1)) < Q) part[threadIdx.x / kWave][threadIdx.x % Q] = sum;
+    __syncthreads();
+    if (threadIdx.x >= 4 * Q) return;
+    const unsigned e = 4 * q0 + threadIdx.x;     // element of the partial
+    if (e >= 4 * quads) return;
+    const int* const t = reinterpret_cast<const int*>(&part[0][0]) + threadIdx.x;
+    const int v = (t[0] + t[4 * Q]) + (t[8 * Q] + t[12 * Q]);
+    const unsigned kt = e / (unsigned)a.Cp;      // filter and tap
+    const int c = (int)(e - kt * (unsigned)a.Cp), RS = a.R * a.S;
+    const int k = (int)(kt / (unsigned)RS), rs = (int)(kt - (unsigned)k * (unsigned)RS);
+    wgrad_result(a, k, rs, c, v, __fmul_rn(a.sa[0], a.sb[0]));
+}
+
 // Sum the split partials, apply Eq.2 and scatter [k][(r,s,c)] -> K,C,R,S.  A block owns, for one filter k,
 // 4*QN channels x RSC taps; its 256 threads are 256/QN split lanes x QN channel quads.  Every thread adds up the
 // splits z = lane, lane + 256/QN, ... of its quad at each tap (independent 16-byte loads, RSC of them in flight
@@ -72,20 +137,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a) {
         const int cl = t / RSC;
         int sum = 0;
         for (int z = 0; z < nz; ++z) sum += sred[z * PITCH + t + (cl >> 2)];
-        const int c = ct * CB + cl, rs = rg * RSC + (t - cl * RSC);
-        if (c >= a.C) continue;
-        size_t o = ((size_t)k * a.C + c) * RS + rs;
-        if (a.s2d) {
-            // back from the space-to-depth form: channel (2 dy + dx) * oC + c0 of tap (r', s') is channel c0
-            // of tap (2 r' + dy - eh, 2 s' + dx - ew); taps outside the layer's own filter are dropped
-            const int blk = c / a.oC, c0 = c - blk * a.oC;
-            const int rr = rs / a.S;
-            const int r = 2 * rr + (blk >> 1) - a.eh, s = 2 * (rs - rr * a.S) + (blk & 1) - a.ew;
-            if (r < 0 || r >= a.oR || s < 0 || s >= a.oS) continue;
-            o = (((size_t)k * a.oC + c0) * a.oR + r) * a.oS + s;
-        }
-        a.dw[o] = __fmul_rn((float)sum, scale);
-        if (a.acc) a.acc[o] = sum;
+        wgrad_result(a, k, rg * RSC + (t - cl * RSC), ct * CB + cl, sum, scale);
     }
 }
 
@@ -301,13 +353,23 @@ hipError_t launch_wgrad(const WgradArgs& a_in, hipStream_t st) {
     return launch_wgrad_reduce(a, st);
 }
 
+// A block's quads in the flat reduction.  Longer runs read better, but a thread should have all its shares in flight at once (8 loads,
+// 256 / Q lanes) and the chip two blocks per compute unit.
+static int wgrad_flat_quads(unsigned quads, int splits) {
+    int q = 64;
+    while (q > 8 && (quads / q < 512 || (long long)splits * q > 8 * 256)) q /= 2;
+    return q;
+}
+
 hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
+    if (a.lines && a.splits == 1) return hipSuccess;       // (wgrad_lines_tile wrote the result)
     // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (256, 64 or
     // 16) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
-    // loads of a small layer are latency, not bandwidth; one tap x 16 channels if nothing does.  A block's
+    // loads of a small layer are latency, not bandwidth; the flat kernel if nothing does.  A block's
     // threads are (channels / 4) x (split lanes): 256 channels leave 4 split lanes, which is what few splits
     // can keep busy.
     const int RS = a.R * a.S;
+    const size_t elems = (size_t)a.K * RS * a.Cp;
     int rsc = 1, qn = 4;
     {
         const int cand[3] = {9, 7, 3};
@@ -323,21 +385,29 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
             }
         }
     }
-    const unsigned rblocks = (unsigned)(a.K * (a.Cp / (4 * qn)) * (RS / rsc));
-    {
-        KernelTimer kt(KID_WGRAD_REDUCE, st);
+    KernelTimer kt(KID_WGRAD_REDUCE, st);
+    if (rsc == 1 && elems < ((size_t)1 << 31)) {
+        const unsigned quads = (unsigned)(elems >> 2);
+        const int q = wgrad_flat_quads(quads, a.splits);
+        const dim3 blocks((quads + q - 1) / q);
+        if (q == 64) launch_timed(kt, (wgrad_reduce_flat_kernel<64>), blocks, dim3(256), 0, st, a);
+        else if (q == 32) launch_timed(kt, (wgrad_reduce_flat_kernel<32>), blocks, dim3(256), 0, st, a);
+        else if (q == 16) launch_timed(kt, (wgrad_reduce_flat_kernel<16>), blocks, dim3(256), 0, st, a);
+        else launch_timed(kt, (wgrad_reduce_flat_kernel<8>), blocks, dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    const dim3 blocks((unsigned)(a.K * (a.Cp / (4 * qn)) * (RS / rsc)));
 #define REDUCE(RSCv)                                                                                         \
     do {                                                                                                     \
-        if (qn == 64) launch_timed(kt, (wgrad_reduce_kernel<64, RSCv>), dim3(rblocks), dim3(256), 0, st, a); \
-        else if (qn == 16) launch_timed(kt, (wgrad_reduce_kernel<16, RSCv>), dim3(rblocks), dim3(256), 0, st, a); \
-        else launch_timed(kt, (wgrad_reduce_kernel<4, RSCv>), dim3(rblocks), dim3(256), 0, st, a);          \
+        if (qn == 64) launch_timed(kt, (wgrad_reduce_kernel<64, RSCv>), blocks, dim3(256), 0, st, a);      \
+        else if (qn == 16) launch_timed(kt, (wgrad_reduce_kernel<16, RSCv>), blocks, dim3(256), 0, st, a); \
+        else launch_timed(kt, (wgrad_reduce_kernel<4, RSCv>), blocks, dim3(256), 0, st, a);                \
     } while (0)
-        if (rsc == 9) REDUCE(9);
-        else if (rsc == 7) REDUCE(7);
-        else if (rsc == 3) REDUCE(3);
-        else REDUCE(1);
+    if (rsc == 9) REDUCE(9);
+    else if (rsc == 7) REDUCE(7);
+    else if (rsc == 3) REDUCE(3);
+    else launch_timed(kt, (wgrad_reduce_kernel<4, 1>), blocks, dim3(256), 0, st, a);
 #undef REDUCE
-    }
     return hipGetLastError();
 }
 

@@ -591,3 +591,18 @@ def test_codes_of_ragged_planes(N, C, H, W):
             if form == "eq6":
                 # sums of up to 1e6 fp64 products in another order: relative error below 1e6 * 2^-53 = 1.1e-10
                 assert abs(d.item() - (1.0 - (g64 @ ref) / (np.sqrt(g64 @ g64) * np.sqrt(ref @ ref)))) < 1e-9
+
+
+# Backward-weight's partial tiles: one share, whose tile is the result (no reduction launched), and the flat reduction with 64, 32, 16
+# and 8 quads to a block, more shares than a thread has in flight, a last block that is not full, the space-to-depth stem.
+@pytest.mark.parametrize("shape,one_share", [
+    ((2, 16, 16, 16, 32, 3, 3, 1, (1, 1)), True), ((1, 300, 1, 1, 65, 1, 1, 1, (0, 0)), True), ((2, 70, 4, 9, 130, 7, 1, 1, (3, 0)), True),
+    ((3, 33, 9, 9, 40, 3, 3, 2, (1, 1)), True), ((2, 130, 8, 8, 129, 1, 1, 2, (0, 0)), True), ((1, 40, 6, 7, 33, 5, 5, 1, (2, 2)), True),
+    ((64, 500, 7, 7, 300, 1, 1, 1, (0, 0)), False), ((32, 250, 14, 14, 280, 1, 1, 1, (0, 0)), False), ((64, 64, 14, 14, 63, 3, 3, 1, (1, 1)), False),
+    ((32, 33, 35, 35, 17, 3, 3, 1, (1, 1)), False), ((256, 60, 40, 40, 50, 1, 1, 1, (0, 0)), False), ((20, 3, 32, 32, 17, 7, 7, 2, (3, 3)), False)])
+@pytest.mark.parametrize("with_acc", [False, True])
+def test_backward_weight_shares(shape, one_share, with_acc):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 11)
+    B.int8t_profile_start("wgrad_reduce_kernel")
+    conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, with_acc)
+    assert bool(B.int8t_profile_stop()) != one_share
