@@ -30,6 +30,11 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 inline bool aligned8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0; }
 inline bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0; }
 
+// whether two ranges of bytes share one
+inline bool overlap(const void* p, size_t np, const void* q, size_t nq) {
+    return (uintptr_t)p < (uintptr_t)q + nq && (uintptr_t)q < (uintptr_t)p + np;
+}
+
 constexpr size_t kMaxElems = 0x7FFFFFFFull;   // 32-bit indices inside the kernels
 
 bool dims_ok(const int d[4], size_t* n) {
@@ -749,6 +754,14 @@ int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc* desc, const int8_t
         a.xs = (int8_t*)const_cast<void*>(fwd_ws_dev);      // (read only)
         a.xs_ready = 1;
     }
+    // (the result of a reduction may go where the codes lay, that of a tile may not)
+    const int xd[4] = {desc->N, desc->C, desc->H, desc->W}, yd[4] = {desc->N, desc->K, g.P, g.Q};
+    const size_t nw = (size_t)desc->K * desc->C * desc->R * desc->S * 4;
+    a.direct = a.lines && a.splits == 1;
+    for (const void* out : {(const void*)dw_dev, (const void*)acc_dev})
+        if (out && (overlap(out, nw, xq_dev, int8t_code_bytes(xd, INT8T_ACT)) || overlap(out, nw, dyq_dev, int8t_code_bytes(yd, INT8T_ACT)) ||
+                    overlap(out, nw, sx_dev, 4) || overlap(out, nw, sdy_dev, 4)))
+            a.direct = 0;
     return launch_wgrad(a, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
 }
 
@@ -1021,6 +1034,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         d.sa = b->sdy; d.sb = b->sw; d.out = b->dx; d.acc = b->dx_acc;
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
+        w.direct = w.lines && w.splits == 1;        // (disjoint_results)
         if (desc->stride_h != 1 || desc->stride_w != 1) {
             if (conv_trio_strided(fwd ? &f : nullptr, d, w))
                 return launch_conv_trio_strided(fwd ? &f : nullptr, d, w, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;

@@ -305,7 +305,7 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
         if (++g == GC) g = 0;
     }
 
-    if (a.splits == 1) {
+    if (a.direct) {
         // one share: nothing to sum, the tile is the result, and launch_wgrad_reduce() has nothing to launch (us per step before and now:
         // 3x3, 16 -> 32 at 16 x 16, batch 2: 24.3, 22.0; fully connected 164 -> 1616, batch 256: 37.2, 28.7)
         const float scale = __fmul_rn(a.sa[0], a.sb[0]);

@@ -241,6 +241,8 @@ struct WgradArgs {
     int ktiles, ctiles, tapgroups;
     int xt_slots;                // 16-byte granules of the staged input window
     size_t lds_bytes;
+    // set by the caller, who knows the buffers: one share on image lines, whose tiles are written as the result (dw and acc overlap nothing the pass reads)
+    int direct;
     // filled by wgrad_s2d() when it rewrites the geometry above into the space-to-depth form:
     int s2d;                     // 1: C, Cp, H, W, R, S, strides and pads describe the rewritten problem
     int oC, oR, oS, oH, oW, eh, ew;   // the layer's own channels, filter and image; tap r = 2 r' + dy - eh, s = 2 s' + dx - ew

@@ -606,3 +606,22 @@ def test_backward_weight_shares(shape, one_share, with_acc):
     B.int8t_profile_start("wgrad_reduce_kernel")
     conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, with_acc)
     assert bool(B.int8t_profile_stop()) != one_share
+
+
+# The weight gradient over the codes it comes from: legal, the reduction runs after they have been read.
+def test_backward_weight_over_its_codes():
+    desc, od, (xq, wq, dyq) = random_layer((2, 70, 4, 9, 130, 7, 1, 1, (3, 0)), 12)
+    want, _ = oracle.wrap32(oracle.conv_bwd_weight(od, xq, dyq))
+    ws = torch.empty(B.int8t_workspace_bytes(B.OP_CONV_BWD_WEIGHT, desc), dtype=torch.uint8, device=DEV)
+    one = torch.ones(1, device=DEV)
+    for over_x in (True, False):
+        codes = [dev(pack_act(xq)), dev(pack_act(dyq))]
+        buf = torch.zeros(max(4 * want.size, codes[0].numel(), codes[1].numel()), dtype=torch.int8, device=DEV)
+        i = 0 if over_x else 1
+        buf[:codes[i].numel()].copy_(codes[i].view(-1))
+        codes[i] = buf[:codes[i].numel()]
+        dw = buf[:4 * want.size].view(torch.float32)
+        B.int8t_profile_start("wgrad_reduce_kernel")
+        B.int8t_conv_bwd_weight(desc, codes[0], one, codes[1], one, dw, None, ws)
+        torch.cuda.synchronize()
+        assert B.int8t_profile_stop() and np.array_equal(dw.cpu().numpy().reshape(want.shape), want.astype(np.float32))
