@@ -396,6 +396,7 @@ typedef enum {
     INT8T_FORM_STRIDED_CELLS = 8,        /* the classes of a cell one after the other */
     INT8T_FORM_DW_PASSES = 9,            /* depthwise: the passes, */
     INT8T_FORM_DW_CODES = 10,            /* and the codes as well */
+    INT8T_FORM_BANDS = 11,               /* dense, stride 1: bands of rows, the filter bank on chip; the forward pass ahead where its form is another */
     INT8T_FORM_MAX_ENUM = 0x7fffffff
 } int8t_form;
 int8t_form int8t_layer_step_form(const int8t_conv_desc *desc, int parts);

@@ -46,7 +46,7 @@ class QuantizeItem(C.Structure):
  STEP_BWD_WEIGHT) = (1 << k for k in range(8))
 STEP_ALL = 255
 (FORM_APART, FORM_128X128, FORM_128X64, FORM_64X128, FORM_64X128_AND_128X128, FORM_STRIDED, FORM_STRIDED_CLASSES, FORM_STRIDED_CELL,
- FORM_STRIDED_CELLS, FORM_DW_PASSES, FORM_DW_CODES) = range(11)
+ FORM_STRIDED_CELLS, FORM_DW_PASSES, FORM_DW_CODES, FORM_BANDS) = range(12)
 
 
 class LayerBuffers(C.Structure):

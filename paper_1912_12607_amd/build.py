@@ -13,8 +13,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(CSRC, "libint8t.so")
-SOURCES = ["api.hip", "quantize.hip", "dsgc.hip", "conv_igemm.hip", "conv_band.hip", "conv_wgrad.hip", "conv_wgrad_lines.hip", "conv_trio.hip", "s2d.hip", "conv_dw.hip", "conv_dw_fused.hip", "conv_infer.hip", "profile.hip"]
-HEADERS = ["device_common.h", "kernels.h", "profile.h", "lds_dma.h", "conv_igemm_dma.h", "conv_wgrad_lines.h", "conv_wgrad_tile.h", os.path.join("..", "..", "include", "int8t.h")]
+SOURCES = ["api.hip", "quantize.hip", "dsgc.hip", "conv_igemm.hip", "conv_band.hip", "conv_wgrad.hip", "conv_wgrad_lines.hip", "conv_trio.hip", "conv_band_trio.hip", "s2d.hip", "conv_dw.hip", "conv_dw_fused.hip", "conv_infer.hip", "profile.hip"]
+HEADERS = ["device_common.h", "kernels.h", "profile.h", "lds_dma.h", "conv_igemm_dma.h", "conv_wgrad_lines.h", "conv_wgrad_tile.h", "conv_band.h", os.path.join("..", "..", "include", "int8t.h")]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-fno-fast-math", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -884,7 +884,7 @@ int8t_form int8t_layer_step_form(const int8t_conv_desc* desc, int parts) {
                                          : INT8T_FORM_STRIDED_CELLS;
     }
     const TrioTile tile = conv_trio_tile(fwd && !conv_trio_fwd_apart(p.f, p.d) ? &p.f : nullptr, p.d, p.w);
-    if (!tile.bn) return INT8T_FORM_APART;
+    if (!tile.bn) return conv_band_trio(nullptr, p.d, p.w) ? INT8T_FORM_BANDS : INT8T_FORM_APART;
     if (tile.rows64) return tile.bn == 64 ? INT8T_FORM_64X128 : INT8T_FORM_64X128_AND_128X128;
     return tile.bn == 64 ? INT8T_FORM_128X64 : INT8T_FORM_128X128;
 }
@@ -1046,6 +1046,13 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
             const IgemmArgs* fp = fwd_left ? &f : nullptr;
             const TrioTile tile = conv_trio_tile(fp, d, w);
             if (tile.bn) return launch_conv_trio(fp, d, w, tile, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+            if (const int passes = conv_band_trio(fp, d, w)) {
+                if (fp && passes == 2) {
+                    if (launch_igemm(f, st) != hipSuccess) return INT8T_ERR_RUNTIME;
+                    fp = nullptr;
+                }
+                return launch_conv_band_trio(fp, d, w, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+            }
         }
     }
     if (fwd_left) {

@@ -288,6 +288,12 @@ TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradA
 bool conv_trio_fwd_apart(const IgemmArgs& fwd, const IgemmArgs& bwd);    // the forward pass is better launched ahead, by itself
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st);
 
+// The same for passes whose filter bank stays on chip (conv_band_trio.hip): 0: they run one by one; 2: the two backward passes
+// share a launch, the forward pass (if any) runs ahead; 3: all three
+int conv_band_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);
+hipError_t launch_conv_band_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, hipStream_t st);
+constexpr int kBandTrioKernels = 16;
+
 bool conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w);      // whether the passes of a strided layer share one
 hipError_t launch_conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, hipStream_t st);
 

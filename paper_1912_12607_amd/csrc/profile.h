@@ -37,6 +37,7 @@ enum KernelId : int {
     KID_DW_WGRAD_REDUCE,
     KID_DW_TRIO,
     KID_INFER,
+    KID_CONV_BAND_TRIO,
     KID_COUNT
 };
 

@@ -27,7 +27,7 @@ const char* const kNames[KID_COUNT] = {
     "quantize_batch_kernel",
     "deviation_finish_kernel", "dsgc_sweep_kernel",   "igemm_kernel", "igemm_dma_kernel", "igemm_fused_kernel", "igemm_reduce_kernel",
     "band_kernel",         "band_reg_kernel",     "wgrad_kernel",        "wgrad_lines_kernel", "wgrad_reduce_kernel",    "s2d_repack_kernel", "conv_trio_kernel", "dw_conv_kernel",
-    "dw_wgrad_kernel",     "dw_wgrad_reduce_kernel", "dw_trio_kernel", "infer_1x1_kernel"};
+    "dw_wgrad_kernel",     "dw_wgrad_reduce_kernel", "dw_trio_kernel", "infer_1x1_kernel", "conv_band_trio_kernel"};
 
 void drop_all() {
     for (Rec& r : g_recs) {

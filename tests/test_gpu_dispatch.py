@@ -625,3 +625,41 @@ def test_backward_weight_over_its_codes():
         B.int8t_conv_bwd_weight(desc, codes[0], one, codes[1], one, dw, None, ws)
         torch.cuda.synchronize()
         assert B.int8t_profile_stop() and np.array_equal(dw.cpu().numpy().reshape(want.shape), want.astype(np.float32))
+
+
+# Passes with the filter bank on chip in one launch with backward-weight: every body (weights in registers, in LDS with one and two
+# row tiles) with every form of backward-weight (image granules; 1, 3, 5, 7 taps along a line), all three passes or the
+# forward pass ahead, bands that end below the image, planes of odd sizes.  Bit for bit the calls one by one.
+@pytest.mark.parametrize("shape,ahead", [
+    ((65, 24, 57, 55, 64, 1, 1), True), ((65, 64, 56, 56, 64, 1, 1), False), ((40, 16, 50, 100, 128, 1, 1), True), ((65, 16, 56, 56, 128, 1, 1), True),
+    ((58, 32, 59, 60, 32, 3, 3), False), ((65, 64, 56, 56, 64, 3, 3), False), ((65, 24, 56, 56, 24, 1, 1), False), ((65, 16, 56, 56, 256, 1, 1), True),
+    ((65, 16, 56, 57, 16, 3, 3), False), ((65, 8, 56, 56, 16, 5, 5), False), ((65, 24, 56, 56, 16, 1, 7), False), ((65, 40, 56, 56, 24, 1, 1), True),
+    ((65, 56, 56, 56, 256, 1, 1), True), ((65, 40, 56, 56, 16, 3, 3), True), ((65, 48, 56, 56, 16, 1, 5), True), ((65, 56, 55, 56, 40, 7, 1), False)])
+def test_bands_and_backward_weight_in_one_launch(shape, ahead):
+    N, C, H, W, K, R, S = shape
+    st = LayerStep(inputs.Layer("layer", N, C, H, W, K, R, S, stride=(1, 1), pad=(R // 2, S // 2)), keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.ratios.copy_(dev(inputs.default_ratios(32)))
+    st.run(seed=5, overlap=0)
+    outs = (st.y, st.dx, st.dw, st.y_acc, st.dx_acc, st.dw_acc)
+    for t in outs:
+        t.fill_(7)
+    st.fwd()
+    st.bwd_data()
+    st.bwd_weight()
+    want = [t.clone() for t in outs]
+    two = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    for parts in (two, B.STEP_FWD | two):
+        assert B.int8t_layer_step_form(st.desc, parts) == B.FORM_BANDS
+        for t in outs:
+            t.fill_(7)
+        B.int8t_profile_start(None)
+        B.int8t_layer_step(st.desc, st._layer_buffers, parts)
+        torch.cuda.synchronize()
+        launches = B.int8t_profile_stop()
+        assert launches.pop("conv_band_trio_kernel")[0] == 1 and launches.pop("wgrad_reduce_kernel")[0] == 1
+        assert bool(launches) == (ahead and parts != two)
+        for i, t in enumerate(outs):
+            assert torch.equal(t, want[i]) or (parts == two and i in (0, 3))
