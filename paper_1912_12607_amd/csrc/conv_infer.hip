@@ -8,7 +8,11 @@
 // A block keeps the filter bank's codes in LDS (quantized there, from the partial maxima) and walks tiles of 128 pixels, 64 channels at
 // a time: a thread loads 2 x 4 channels x 4 pixels, quantizes, turns them round in registers as the quantizer does, and leaves
 // four channels per pixel in an LDS tile ([pixel][80 bytes]: an odd number of 16-byte granules, conflict-free operand
-// reads); the next 64 channels are on their way meanwhile, two tiles alternate, one barrier per 64 channels.
+// reads); the next two rounds of 64 channels are on their way meanwhile, two tiles alternate, one barrier per 64 channels.  (With one round
+// ahead, zeroed where it was loaded -- which waited for it on the spot -- and addresses of 64 bits, us per call: 144 -> 24 at 56 x 56, batch 64:
+// 53.3, now 49.8; 32 -> 16 at 112 x 112: 55.8, 48.1; 16 -> 34 at 96 x 96, batch 43: 33.6, 26.8.  Five blocks per compute unit: no gain.)
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -37,40 +41,52 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
     unsigned char* const xt = lds;                       // two tiles of codes
     unsigned char* const wt = lds + 2 * INF_TILE;        // [RT * 32][wpitch]
 
-    float4 f[2][4];                                      // [half][channel]: four pixels
-    auto fetch = [&](int tile, int cc) {
+    float4 f0[2][4], f1[2][4];                           // [half][channel]: four pixels, of this round of 64 channels and the next
+    // Loads and stores go through a descriptor that spans one image: channels and filters beyond it, and lanes given an offset beyond
+    // it, read zeros and write nothing.  No branches, past the last tile neither (an empty descriptor): the compiler then knows what is
+    // outstanding and waits for one round only.
+    constexpr uint32_t kOut = 0x80000000u;
+    const uint32_t plane = 4u * (uint32_t)a.HW, x_bytes = (uint32_t)a.C * plane, y_bytes = (uint32_t)a.K * plane;
+    auto fetch = [&](float4 (&f)[2][4], int tile, int cc) {
         const int n = tile / a.tiles_img, p0 = (tile - n * a.tiles_img) * INF_PIX;
+        const __amdgpu_buffer_rsrc_t img = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(a.x) + (tile < a.tiles ? (size_t)n * a.C * a.HW : (size_t)0), 0, tile < a.tiles ? x_bytes : 0u, 0x00020000);
+        const uint32_t row = (uint32_t)(cc * INF_CH + 4 * cgp) * plane;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int p = p0 + 64 * h + 4 * pq;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int c = cc * INF_CH + 4 * cgp + j;
-                const size_t at = ((size_t)n * a.C + c) * a.HW + p;
-                // (unconditional loads: what is not there re-reads the first floats and is zeroed)
+                const uint32_t at = row + (uint32_t)j * plane + 4u * (uint32_t)p;
                 if (VEC) {
-                    const bool ok = c < a.C && p < a.HW;
-                    f[h][j] = *reinterpret_cast<const float4*>(a.x + (ok ? at : (size_t)0));
-                    if (!ok) f[h][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(img, p < a.HW ? at : kOut, 0, 0);
+                    f[h][j] = make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
                 } else {
                     float v[4];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool ok = c < a.C && p + k < a.HW;
-                        v[k] = a.x[ok ? at + k : (size_t)0];
-                        if (!ok) v[k] = 0.0f;
-                    }
+                    for (int k = 0; k < 4; ++k) v[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(img, p + k < a.HW ? at + 4u * k : kOut, 0, 0));
                     f[h][j] = make_float4(v[0], v[1], v[2], v[3]);
                 }
             }
         }
     };
-    int tile = blockIdx.x, cc = 0;
     if (tid < 2 * kWave) {
         const float m = absmax_partials_wave(wave ? a.part_w : a.part_x, wave ? a.np_w : a.np_x, lane);
         if (lane == 0) s_max[wave] = m;
     }
-    if (tile < a.tiles) fetch(tile, 0);
+    // the rounds of a block, 64 channels of a tile each: the one at work, the next one and the one after it
+    int tile = blockIdx.x, cc = 0;
+    auto after = [&](int& t, int& c) {
+        if (++c == nch) {
+            c = 0;
+            t += (int)gridDim.x;
+        }
+    };
+    int tile1 = tile, cc1 = 0;
+    after(tile1, cc1);
+    int tile2 = tile1, cc2 = cc1;
+    fetch(f0, tile, 0);
+    fetch(f1, tile1, cc1);
     __syncthreads();
     const float inv_x = inv_scale_of(s_max[0]), inv_w = inv_scale_of(s_max[1]);
     const float scale = __fmul_rn(scale_of(s_max[0]), scale_of(s_max[1]));
@@ -98,8 +114,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
         for (int v = 0; v < 16; ++v) acc[r][v] = 0;
     const unsigned char* const rx = xt + (wave * 32 + (lane & 31)) * INF_PITCH + 16 * (lane >> 5);
     const unsigned char* const rw = wt + (lane & 31) * wpitch + 16 * (lane >> 5);
-    int buf = 0;
-    while (tile < a.tiles) {                             // (uniform over the block)
+    auto round = [&](float4 (&f)[2][4], unsigned char* const xb, const unsigned char* const rb) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             uint32_t d[4], o[4];
@@ -110,35 +125,43 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
             transpose4x4_bytes(d, o);                    // d[channel] = 4 pixels -> o[pixel] = 4 channels
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                *reinterpret_cast<uint32_t*>(xt + buf * INF_TILE + (64 * h + 4 * pq + k) * INF_PITCH + 4 * cgp) = o[k];
+                *reinterpret_cast<uint32_t*>(xb + (64 * h + 4 * pq + k) * INF_PITCH + 4 * cgp) = o[k];
         }
-        const int now = tile, cnow = cc;
-        if (++cc == nch) {
-            cc = 0;
-            tile += (int)gridDim.x;
-        }
-        if (tile < a.tiles) fetch(tile, cc);
         __syncthreads();      // this tile's codes are there (the first time: the filters' too), the other tile has been read
 #pragma unroll
         for (int kk = 0; kk < INF_CH / 32; ++kk) {
-            const infer_v4i fb = *reinterpret_cast<const infer_v4i*>(rx + buf * INF_TILE + 32 * kk);
+            const infer_v4i fb = *reinterpret_cast<const infer_v4i*>(rb + 32 * kk);
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
-                const infer_v4i fa = *reinterpret_cast<const infer_v4i*>(rw + r * 32 * wpitch + cnow * INF_CH + 32 * kk);
+                const infer_v4i fa = *reinterpret_cast<const infer_v4i*>(rw + r * 32 * wpitch + cc * INF_CH + 32 * kk);
                 acc[r] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa, fb, acc[r], 0, 0, 0);
             }
         }
-        buf ^= 1;
-        if (cnow + 1 < nch) continue;
-        const int n = now / a.tiles_img, p = (now - n * a.tiles_img) * INF_PIX + wave * 32 + (lane & 31);
+        if (cc + 1 == nch) {
+            const int n = tile / a.tiles_img, p = (tile - n * a.tiles_img) * INF_PIX + wave * 32 + (lane & 31);
+            const __amdgpu_buffer_rsrc_t img = __builtin_amdgcn_make_buffer_rsrc(a.y + (size_t)n * a.K * a.HW, 0, y_bytes, 0x00020000);
+            const uint32_t at = p < a.HW ? (uint32_t)(4 * (lane >> 5)) * plane + 4u * (uint32_t)p : kOut;
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+            for (int r = 0; r < RT; ++r)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int k = 32 * r + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (k < a.K && p < a.HW) a.y[((size_t)n * a.K + k) * a.HW + p] = __fmul_rn((float)acc[r][v], scale);
-                acc[r][v] = 0;
-            }
+                for (int v = 0; v < 16; ++v) {
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(__fmul_rn((float)acc[r][v], scale)), img,
+                                                          at + (uint32_t)(32 * r + 8 * (v >> 2) + (v & 3)) * plane, 0, 0);
+                    acc[r][v] = 0;
+                }
+        }
+        // (behind the results: a wait for the next round then does not wait for these loads)
+        after(tile2, cc2);
+        fetch(f, tile2, cc2);
+        tile = tile1;
+        cc = cc1;
+        tile1 = tile2;
+        cc1 = cc2;
+    };
+    while (tile < a.tiles) {                             // (uniform over the block)
+        round(f0, xt, rx);
+        if (tile >= a.tiles) break;
+        round(f1, xt + INF_TILE, rx + INF_TILE);
     }
 }
 
@@ -150,6 +173,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
 // of 64 channels (40 -> 8 at 19 x 19, batch 55: 12.7, 8.5; 8 -> 8 at 47 x 47, batch 256, 4608 tiles: 35.1, 47.2).
 bool infer_1x1_applies(const InferArgs& a) {
     if (a.K > 64 || a.C > 4 * INF_CH || a.HW < 64) return false;
+    if (4ll * a.HW * std::max(a.C, a.K) >= 1ll << 31) return false;       // (one image's descriptor)
     const long long tiles = (long long)a.N * ((a.HW + INF_PIX - 1) / INF_PIX);
     if ((a.HW & 3) == 0) return (long long)a.K * a.C <= 8192 || tiles >= 512;
     return a.C <= INF_CH && a.K <= 32 && tiles <= 1024;
