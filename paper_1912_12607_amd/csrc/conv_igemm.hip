@@ -382,6 +382,13 @@ static int igemm_colrun(const IgemmArgs& a, const IgemmShape& g, unsigned ctiles
     return (ragged && g.gran <= (cells ? 32 : 16) && ctiles >= 96) ? (int)((ctiles + 7) / 8) : 0;
 }
 
+// The divisors a tile of `bm` rows sees (columns: pixels, or cells of cls_h x cls_w pixels).
+static void igemm_divisors(IgemmArgs* a, int bm, bool cells) {
+    const int oh = cells ? (a->OH + a->cls_h - 1) / a->cls_h : a->OH, ow = cells ? (a->OW + a->cls_w - 1) / a->cls_w : a->OW;
+    a->by_rtiles = fast_div((unsigned)((a->rows + bm - 1) / bm));
+    a->by_image = fast_div((unsigned)(oh * ow));
+    a->by_row = fast_div((unsigned)ow);
+}
 template <bool DGRAD, int WM, int KG, int NSTAGE, bool CLS, bool CELL, int BNT = IGD_BN, bool ALLC = false, bool STG = false>
 static hipError_t launch_igemm_dma(const IgemmArgs& a_in, const IgemmShape& g, hipStream_t st, const KernelTimer& kt) {
     IgemmArgs a = a_in;
@@ -394,6 +401,7 @@ static hipError_t launch_igemm_dma(const IgemmArgs& a_in, const IgemmShape& g, h
     const unsigned ctiles = (unsigned)((g.ncols + BNT - 1) / BNT), rtiles = (unsigned)((a.rows + 64 * WM - 1) / (64 * WM));
     dim3 grid(((ctiles + 7) / 8) * 8 * rtiles * (unsigned)g.ncls);
     a.colrun = igemm_colrun(a, g, ctiles, CELL);
+    igemm_divisors(&a, 64 * WM, CELL);
     launch_timed(kt, (igemm_dma_kernel<DGRAD, WM, KG, NSTAGE, CLS, CELL, BNT, ALLC, STG>), grid, dim3(128 * WM), lds, st, a);
     return hipGetLastError();
 }
@@ -446,6 +454,7 @@ unsigned igemm_plain_blocks(IgemmArgs* a, int bm, int bn) {
     a->ksplit = 1;
     const unsigned ctiles = (unsigned)((g.ncols + bn - 1) / bn), rtiles = (unsigned)((a->rows + bm - 1) / bm);
     a->colrun = igemm_colrun(*a, g, ctiles, false);
+    igemm_divisors(a, bm, false);
     return ((ctiles + 7) / 8) * 8 * rtiles;
 }
 
@@ -467,6 +476,7 @@ unsigned igemm_strided_blocks(IgemmArgs* a, int* form) {
     a->ksplit = 1;
     const unsigned ctiles = (unsigned)((g.ncols + 63) / 64), rtiles = (unsigned)((a->rows + 127) / 128);
     a->colrun = igemm_colrun(*a, g, ctiles, *form == STRIDED_CELL || *form == STRIDED_CELLS);
+    igemm_divisors(a, 128, *form == STRIDED_CELL || *form == STRIDED_CELLS);
     return ((ctiles + 7) / 8) * 8 * rtiles * (unsigned)g.ncls;
 }
 

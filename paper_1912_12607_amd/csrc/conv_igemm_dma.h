@@ -23,9 +23,11 @@ struct DgradClass {
     int r0, s0, nr, ns;
     int bh, bw;
 };
+// CS: the strides, where they are known to be CS x CS.
+template <int CS = 0>
 __device__ __forceinline__ DgradClass dgrad_class(const IgemmArgs& a, int cls) {
     DgradClass c;
-    const int csh = a.cls_h, csw = a.cls_w;     // the stride, or 1 where that direction is not split
+    const int csh = CS ? CS : a.cls_h, csw = CS ? CS : a.cls_w;     // the stride, or 1 where that direction is not split
     c.ch = cls / csw;
     c.cw = cls - c.ch * csw;
     c.OHc = (a.OH - c.ch + csh - 1) / csh;
@@ -76,6 +78,12 @@ __device__ __forceinline__ void store_cell(T* __restrict__ dst, size_t o, int OW
 //   <WM=2, KG=8, NSTAGE=2, BNT=64>: 128 x 64 (waves of 64 x 32), 48 KB: twice the tiles for layers with few columns
 //   (7 x 7 and 8 x 8 images), which otherwise leave more than half of the compute units idle
 // ---------------------------------------------------------------------------------------------
+// What a stage costs a block alone on its compute unit (cycles, 128 x 64 tile): 780; its 12 operand reads, 8 matrix products and the barrier
+// 500, its 6 loads with nothing beside them 620 (latency).  Before the offsets were worked out a stage ahead and operands and loads took
+// turns it was 1150, of which 350 were the arithmetic between the products.  A block's fixed cost is as large as three stages: 2000 before
+// the first load (it was 2900: divisors come from the host), 1200 - 2000 for the first stage, 3000 - 5000 for the results.  us per pass alone:
+// 3x3, 256 channels, 14 x 14, batch 64: 17.7 -> 15.6; 1x1, 1024 -> 256, 14 x 14, batch 128, forward 16.5 -> 14.7; fully connected
+// 2048 -> 1000, batch 256, forward 14.7 -> 11.5; 3x3 under stride 2, 128 channels, 56 x 56, backward-data 35.1 -> 33.0.
 //   ALLC (with CLS and CELL, stride 2 x 2, every class with taps): the columns are the 2 x 2 cells of pixels and the
 //   block runs the four classes one after the other, each into accumulators of its own, then writes every cell
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class
@@ -113,12 +121,13 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     // CLS: the residue classes of a column tile follow each other on the same XCD as well (they read
     // the same gradient pixels and write interleaved floats of the same cache lines).
     const int rtiles = (a.rows + BM - 1) / BM;
-    const int wg_i = block >> 3;
-    int cgroup = wg_i / rtiles;
+    const int wg_i = (int)(block >> 3);
+    const int row_group = div_by(wg_i, a.by_rtiles);
+    int cgroup = row_group;
     DgradClass dc;
     if (CLS) {
         if (CELL) {
-            dc = dgrad_class(a, ALLC ? 0 : a.cell - 1);
+            dc = dgrad_class<ALLC ? 2 : 0>(a, ALLC ? 0 : a.cell - 1);
             dc.OHc = (a.OH + a.cls_h - 1) / a.cls_h;      // cells, not pixels of the class
             dc.OWc = (a.OW + a.cls_w - 1) / a.cls_w;
         } else {
@@ -131,13 +140,16 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     const int OWc = CLS ? dc.OWc : a.OW;
     const int OHW = CLS ? dc.OHc * dc.OWc : OHWfull;     // columns per image
     const int ncols = a.N * OHW;
+    // (a class's columns are known here only)
+    auto image_of = [&](int col) { return CLS && !CELL ? col / OHW : div_by(col, a.by_image); };
+    auto row_of = [&](int pix) { return CLS && !CELL ? pix / OWc : div_by(pix, a.by_row); };
     int nr = CLS ? dc.nr : a.R, ns = CLS ? dc.ns : a.S;  // (ALLC: of the class being run)
     int gtot = nr * ns * Cg16;
     int nsteps = (gtot + KG - 1) / KG;
     // colrun (igemm_colrun): an XCD takes a run of column tiles instead of every eighth.
     const int ctile = a.colrun ? (int)(block & 7) * a.colrun + cgroup : (cgroup << 3) + (int)(block & 7);
     if (ctile * BN >= ncols) return;
-    const int rowbase = (wg_i % rtiles) * BM;
+    const int rowbase = (wg_i - row_group * rtiles) * BM;
     const int colbase = ctile * BN;
 
     const v4i wr = igd_rsrc(a.wgt, (uint32_t)((size_t)a.rows * gfull * 16));
@@ -160,82 +172,136 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         const int row = rowbase + RPL * (wave + NW * i) + lrow;
         aoff[i] = row < a.rows ? (uint32_t)row * (uint32_t)gfull * 16u : IGD_OOB;
     }
-    int bh[NLB], bw[NLB];
+    int bh[NLB], bw[NLB];                                    // a column beyond the last: a row that no tap brings inside the image
     int boh[NLB], bow[NLB];                                  // (ALLC) the column's cell, to which each class adds its offset
-    uint32_t bimg[NLB];                                      // byte offset of the column's image or OOB
+    uint32_t bimg[NLB];                                      // byte offset of the column's image
+    uint32_t bbase[NLB];                                     // ... of the pixel that tap (0,0) reads, modulo 2^32 (it may lie outside the image)
+    constexpr int kFar = 0x40000000;
 #pragma unroll
     for (int i = 0; i < NLB; ++i) {
         const int col = colbase + RPL * (wave + NW * i) + lrow;
         const bool cv = col < ncols;
         const int cc = cv ? col : 0;
-        const int n = cc / OHW, rem = cc - n * OHW;
-        const int oh = rem / OWc, ow = rem - oh * OWc;
-        boh[i] = oh;
+        const int n = image_of(cc), rem = cc - n * OHW;
+        const int oh = row_of(rem), ow = rem - oh * OWc;
+        boh[i] = cv ? oh : kFar;
         bow[i] = ow;
-        bh[i] = CLS ? (oh + dc.bh) : DGRAD ? (oh + a.pad_h) : (oh * a.stride_h - a.pad_h);
+        bh[i] = cv ? (CLS ? oh + dc.bh : DGRAD ? oh + a.pad_h : oh * a.stride_h - a.pad_h) : kFar;
         bw[i] = CLS ? (ow + dc.bw) : DGRAD ? (ow + a.pad_w) : (ow * a.stride_w - a.pad_w);
-        bimg[i] = cv ? (uint32_t)n * (uint32_t)(a.IH * a.IW * a.Ca) : IGD_OOB;
+        bimg[i] = (uint32_t)n * (uint32_t)(a.IH * a.IW * a.Ca);
+        bbase[i] = bimg[i] + (uint32_t)(bh[i] * a.IW + bw[i]) * (uint32_t)a.Ca;
     }
-    // reduction position of this lane's granule: filter tap (r,s) and channel granule cg
-    int r, s, cg;
-    int qnext;                                               // granule index of the next stage to issue
-    auto first_granule = [&]() {
-        const int tap = gsw / Cg16;
-        cg = gsw - tap * Cg16;
-        r = tap / (ns > 0 ? ns : 1);
-        s = tap - r * ns;
-        qnext = gsw;
-    };
-    first_granule();
-
-    auto issue_a = [&](int buf) {
-        const uint32_t boff = (uint32_t)buf * (STAGE_SLOTS * 16u);
-        const bool qv = qnext < gtot;
-        // granule of the filter row: the taps of a class are a sub-grid of the R x S filter
-        const int wq = CLS ? ((dc.r0 + a.cls_h * r) * a.S + dc.s0 + a.cls_w * s) * Cg16 + cg : qnext;
-#pragma unroll
-        for (int i = 0; i < NLA; ++i) {
-            const uint32_t off = (qv && aoff[i] != IGD_OOB) ? aoff[i] + (uint32_t)wq * 16u : IGD_OOB;
-            igd_load_lds(wr, lds_a0 + boff + (uint32_t)i * (NW * 64 * 16), off);
-        }
-    };
-    auto issue_b = [&](int buf) {
-        const uint32_t boff = (uint32_t)buf * (STAGE_SLOTS * 16u);
-        const bool qv = qnext < gtot;
+    // a direction split into classes is a stride-1 pass; otherwise only the taps that divide reach a pixel
+    const int dsh = CLS ? a.stride_h / a.cls_h : a.stride_h, dsw = CLS ? a.stride_w / a.cls_w : a.stride_w;
+    const bool unit = !DGRAD || (dsh == 1 && dsw == 1);
+    // Where the channels are whole stages, all lanes of a stage are at one filter tap: the position in the reduction is then the same for
+    // all of them and kept in scalar registers, the loads add it to offsets that stay (A) or change with the tap (B).
+    // (Not with ALLC: four copies of the loop, each run once or twice per block, wait for their instructions.)
+    const bool uni = !ALLC && Cg16 % KG == 0;
+    // Offsets of the next stage's loads, worked out a stage ahead: their arithmetic runs beside the matrix instructions, and no lane branches.
+    uint32_t na[NLA], nb[NLB];
+    uint32_t soff_a = 0, soff_b = 0;
+    auto tap_b = [&](int r, int s, uint32_t tapoff, int cg, uint32_t past) {       // nb: granule cg of this lane's pixels under tap (r,s)
 #pragma unroll
         for (int i = 0; i < NLB; ++i) {
-            int ih, iw;
-            bool ok = qv && bimg[i] != IGD_OOB;
-            if (DGRAD) {
-                const int th = bh[i] - r, tw = bw[i] - s;
-                // a direction split into classes is a stride-1 pass; otherwise only the taps that divide reach a pixel
-                const int dsh = CLS ? a.stride_h / a.cls_h : a.stride_h, dsw = CLS ? a.stride_w / a.cls_w : a.stride_w;
-                if (dsh == 1 && dsw == 1) {
-                    ih = th;
-                    iw = tw;
-                } else {
-                    ih = th / dsh;
-                    iw = tw / dsw;
-                    ok = ok && th >= 0 && tw >= 0 && (ih * dsh == th) && (iw * dsw == tw);
-                }
+            bool ok;
+            uint32_t off;
+            if (unit) {
+                const int ih = DGRAD ? bh[i] - r : bh[i] + r, iw = DGRAD ? bw[i] - s : bw[i] + s;
+                ok = ((unsigned)ih < (unsigned)a.IH) & ((unsigned)iw < (unsigned)a.IW);
+                off = bbase[i] + tapoff;
             } else {
-                ih = bh[i] + r;
-                iw = bw[i] + s;
+                const int th = bh[i] - r, tw = bw[i] - s;
+                const int ih = th / dsh, iw = tw / dsw;
+                ok = (th >= 0) & (tw >= 0) & (ih * dsh == th) & (iw * dsw == tw) & ((unsigned)ih < (unsigned)a.IH) & ((unsigned)iw < (unsigned)a.IW);
+                ok = ok & (bh[i] < kFar);
+                off = bimg[i] + (uint32_t)((ih * a.IW + iw) * a.Ca + cg * 16);
             }
-            ok = ok && (unsigned)ih < (unsigned)a.IH && (unsigned)iw < (unsigned)a.IW;
-            const uint32_t off = ok ? bimg[i] + (uint32_t)((ih * a.IW + iw) * a.Ca + cg * 16) : IGD_OOB;
-            igd_load_lds(xr, lds_b0 + boff + (uint32_t)i * (NW * 64 * 16), off);
+            nb[i] = (ok ? off : IGD_OOB) | past;
         }
-        // advance this lane's reduction position by one stage (KG granules)
-        qnext += KG;
-        cg += KG;
-        while (cg >= Cg16) {
-            cg -= Cg16;
-            if (++s == ns) {
-                s = 0;
-                ++r;
+    };
+    // granule of the filter row: the taps of a class are a sub-grid of the R x S filter
+    auto filter_granule = [&](int r, int s, int cg, int q) { return CLS ? ((dc.r0 + a.cls_h * r) * a.S + dc.s0 + a.cls_w * s) * Cg16 + cg : q; };
+    // position of the next stage: filter tap (r,s), channel granule cg, granule index q in the reduction, byte offset from tap (0,0)'s pixel
+    int r, s, cg, q;                                         // of this lane
+    int ur = 0, us = 0, ucg = 0, uq = 0;                     // uni: of the stage's first granule
+    uint32_t tapoff, utap = 0;
+    auto lane_offsets = [&]() {
+        const uint32_t past = q < gtot ? 0u : IGD_OOB;       // beyond the reduction: nothing is read
+        const uint32_t wq = (uint32_t)filter_granule(r, s, cg, q) * 16u;
+#pragma unroll
+        for (int i = 0; i < NLA; ++i) na[i] = (aoff[i] + wq) | past;      // (a row beyond the last: from 2^31 on)
+        tap_b(r, s, tapoff, cg, past);
+    };
+    auto first_stage = [&]() {
+        if (uni) {
+            ur = us = ucg = uq = 0;
+            utap = 0;
+            soff_b = 0;
+            soff_a = (uint32_t)filter_granule(0, 0, 0, 0) * 16u;
+#pragma unroll
+            for (int i = 0; i < NLA; ++i) na[i] = aoff[i] + (uint32_t)(gsw * 16);
+            tap_b(0, 0, (uint32_t)(gsw * 16), gsw, 0u);
+        } else {
+            const int tap = gsw / Cg16;
+            cg = gsw - tap * Cg16;
+            r = tap / (ns > 0 ? ns : 1);
+            s = tap - r * ns;
+            q = gsw;
+            tapoff = (uint32_t)((DGRAD ? -1 : 1) * (r * a.IW + s) * a.Ca + cg * 16);
+            lane_offsets();
+        }
+    };
+    auto next_stage = [&]() {
+        // (forward: a tap's first granule follows the last one of the tap before it)
+        const uint32_t over_row = (uint32_t)((DGRAD ? ns - a.IW : a.IW - ns) * a.Ca);
+        if (uni) {
+            uq += KG;
+            ucg += KG;
+            soff_b += KG * 16;
+            if (ucg == Cg16) {
+                ucg = 0;
+                soff_b = 0;
+                utap += DGRAD ? 0u - (uint32_t)a.Ca : (uint32_t)a.Ca;
+                if (++us == ns) {
+                    us = 0;
+                    ++ur;
+                    utap += over_row;
+                }
+                tap_b(ur, us, utap + (uint32_t)(gsw * 16), gsw, 0u);
             }
+            soff_a = (uint32_t)filter_granule(ur, us, ucg, uq) * 16u;
+        } else {
+            q += KG;
+            cg += KG;
+            tapoff += KG * 16;
+            auto next_tap = [&](bool wrap) {
+                cg -= wrap ? Cg16 : 0;
+                s += wrap ? 1 : 0;
+                const bool row = s == ns;
+                s = row ? 0 : s;
+                r += row ? 1 : 0;
+                if (DGRAD) tapoff -= wrap ? 2u * (uint32_t)a.Ca : 0u;
+                tapoff += row ? over_row : 0u;
+            };
+            if (Cg16 >= KG) {
+                next_tap(cg >= Cg16);
+            } else {
+#pragma unroll 1
+                for (int left = KG; left > 0; left -= Cg16) next_tap(cg >= Cg16);       // (at most KG / Cg16 + 1 taps further)
+            }
+            lane_offsets();
         }
+    };
+    auto load = [&](int buf, int u) {                        // the u-th of this wave's NL loads of a stage
+        const uint32_t boff = (uint32_t)buf * (STAGE_SLOTS * 16u);
+        if (u < NLA) igd_load_lds(wr, lds_a0 + boff + (uint32_t)u * (NW * 64 * 16), na[u < NLA ? u : 0], (uint32_t)__builtin_amdgcn_readfirstlane((int)soff_a));
+        else igd_load_lds(xr, lds_b0 + boff + (uint32_t)(u - NLA) * (NW * 64 * 16), nb[u < NLA ? 0 : u - NLA], (uint32_t)__builtin_amdgcn_readfirstlane((int)soff_b));
+    };
+    auto issue = [&](int buf, bool next) {                   // a stage's loads at once; next: another one follows
+#pragma unroll
+        for (int u = 0; u < NL; ++u) load(buf, u);
+        if (next) next_stage();
     };
 
     v16i acc[NC][MI][NJ];
@@ -252,30 +318,25 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     for (int c = 0; c < NC; ++c) {
     if (ALLC && c > 0) {
         // the next class: its taps and offsets; the ring is free once every wave has read the last stage
-        dc = dgrad_class(a, c);
+        dc = dgrad_class<2>(a, c);
         nr = dc.nr;
         ns = dc.ns;
         gtot = nr * ns * Cg16;
         nsteps = (gtot + KG - 1) / KG;
 #pragma unroll
         for (int i = 0; i < NLB; ++i) {
-            bh[i] = boh[i] + dc.bh;
+            bh[i] = boh[i] == kFar ? kFar : boh[i] + dc.bh;
             bw[i] = bow[i] + dc.bw;
+            bbase[i] = bimg[i] + (uint32_t)(bh[i] * a.IW + bw[i]) * (uint32_t)a.Ca;
         }
-        first_granule();
         __syncthreads();
     }
     // prologue: the first NSTAGE-1 stages on their way
-    if (nsteps > 0) {     // (a class without taps has nothing to load: its pixels get zeros)
-        issue_a(0);
-        issue_b(0);
-    }
+    first_stage();
+    if (nsteps > 0) issue(0, nsteps > 1);     // (a class without taps has nothing to load: its pixels get zeros)
 #pragma unroll
     for (int p = 1; p < NSTAGE - 1; ++p) {
-        if (nsteps > p) {
-            issue_a(p);
-            issue_b(p);
-        }
+        if (nsteps > p) issue(p, nsteps > p + 1);
     }
     for (int step = 0; step < nsteps; ++step) {
         const int buf = step % NSTAGE;
@@ -285,34 +346,47 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         else if (NSTAGE >= 3 && step + 1 < nsteps) igd_wait_vmcnt<NSTAGE >= 3 ? NL : 0>();
         else igd_wait_vmcnt<0>();
         __syncthreads();   // every wave's part of this stage is in LDS; stage step-1 has been read by all
-        // the next loads go into the buffer read in stage step-1; the weight half is requested now,
-        // the pixel half in the middle of this stage's MFMAs, so the memory pipeline sees a steady
-        // stream instead of one burst per stage
-        const bool more = step + NSTAGE - 1 < nsteps;
+        // the next loads go into the buffer read in stage step-1
+        const bool more = step + NSTAGE - 1 < nsteps, after = step + NSTAGE < nsteps;
         const int nbuf = (step + NSTAGE - 1) % NSTAGE;
-        if (more) issue_a(nbuf);
         const uint4* __restrict__ sA = ring + buf * STAGE_SLOTS;
         const uint4* __restrict__ sB = sA + BM * KG;
-#pragma unroll
-        for (int kk = 0; kk < KG / 2; ++kk) {
+        // Operands of PRE steps of 32 reduction bytes are requested ahead of the products, in turn with the loads of the next stage: either
+        // keeps its pipe busy for hundreds of cycles (a wave's operands 16 reads of 1 KB at 128 bytes per cycle and compute unit, its loads
+        // 8 of 1 KB at 64), so neither should queue behind the other.
+        constexpr int KK = KG / 2, PRE = NJ * MI > 4 ? 2 : KK, RD = PRE * (MI + NJ);
+        v4i fa[PRE][MI], fb[PRE][NJ];
+        auto read = [&](int kk, int o) {                     // operand o of a step: MI filter fragments, then NJ pixel fragments
             const int g = kk * 2 + (lane >> 5);
-            v4i fa[MI], fb[NJ];
+            const uint4 t = o < MI ? sA[igd_slot<KG>(wm * 64 + o * 32 + (lane & 31), g)] : sB[igd_slot<KG>(wn * CW + (o - MI) * 32 + (lane & 31), g)];
+            const v4i v = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+            if (o < MI) fa[kk % PRE][o < MI ? o : 0] = v;
+            else fb[kk % PRE][o < MI ? 0 : o - MI] = v;
+        };
+        if (more && !ALLC) {
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                const uint4 t = sA[igd_slot<KG>(wm * 64 + i * 32 + (lane & 31), g)];
-                fa[i] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
-            }
+            for (int u = 0; u < NL; ++u) {
+                load(nbuf, u);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const uint4 t = sB[igd_slot<KG>(wn * CW + j * 32 + (lane & 31), g)];
-                fb[j] = v4i{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+                for (int v = u * RD / NL; v < (u + 1) * RD / NL; ++v) read(v / (MI + NJ), v % (MI + NJ));
             }
+            if (after) next_stage();
+        } else {
+            if (more) issue(nbuf, after);
+#pragma unroll
+            for (int v = 0; v < RD; ++v) read(v / (MI + NJ), v % (MI + NJ));
+        }
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
-                    acc[c][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[c][i][j], 0, 0, 0);
-            if (kk == (KG >= 8 ? KG / 4 - 1 : 0) && more) issue_b(nbuf);
+                    acc[c][i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[kk % PRE][i], fb[kk % PRE][j], acc[c][i][j], 0, 0, 0);
+            if (kk + PRE < KK) {
+#pragma unroll
+                for (int o = 0; o < MI + NJ; ++o) read(kk + PRE, o);
+            }
         }
     }
     }   // classes
@@ -332,7 +406,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         constexpr int QPR = BN / 4, RPI = 64 * NW / QPR;     // 16-byte groups per row, rows per pass of the block
         const int q = tid % QPR, r0 = tid / QPR;
         const int col = colbase + 4 * q;
-        const int n = col / OHW, opix = col - n * OHW;
+        const int n = image_of(col), opix = col - n * OHW;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             __syncthreads();
@@ -343,15 +417,24 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
                     stg[(wm * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * PITCH + wn * CW + j * 32 + (lane & 31)] = acc[0][i][j][v];
             __syncthreads();
             if (col >= ncols) continue;
-#pragma unroll 4
-            for (int r = r0; r < 32 * WM; r += RPI) {
-                const int row = rowbase + (r >> 5) * 64 + i * 32 + (r & 31);
-                if (row >= a.rows) continue;
-                const int4 t = *reinterpret_cast<const int4*>(stg + r * PITCH + 4 * q);
-                const size_t o = ((size_t)n * a.rows + row) * OHWfull + opix;
-                *reinterpret_cast<float4*>(a.out + o) = make_float4(__fmul_rn((float)t.x, scale), __fmul_rn((float)t.y, scale),
-                                                                    __fmul_rn((float)t.z, scale), __fmul_rn((float)t.w, scale));
-                if (a.acc) { a.acc[o] = t.x; a.acc[o + 1] = t.y; a.acc[o + 2] = t.z; a.acc[o + 3] = t.w; }
+            // all of a lane's pieces are read before the first is written, and one 64-bit address serves them
+            constexpr int PM = 32 / RPI;                      // pieces per 32 rows
+            static_assert(32 % RPI == 0, "whole passes");
+            int4 t[WM * PM];
+#pragma unroll
+            for (int u = 0; u < WM * PM; ++u) t[u] = *reinterpret_cast<const int4*>(stg + (u / PM * 32 + u % PM * RPI + r0) * PITCH + 4 * q);
+            const int row0 = rowbase + i * 32 + r0;
+            const size_t o0 = ((size_t)n * a.rows + row0) * OHWfull + opix;
+            const bool full = rowbase + BM <= a.rows;         // (uniform)
+#pragma unroll
+            for (int u = 0; u < WM * PM; ++u) {
+                const int dr = u / PM * 64 + u % PM * RPI;    // rows further on
+                if (full || row0 + dr < a.rows) {
+                    const size_t o = o0 + (size_t)dr * OHWfull;
+                    *reinterpret_cast<float4*>(a.out + o) = make_float4(__fmul_rn((float)t[u].x, scale), __fmul_rn((float)t[u].y, scale),
+                                                                        __fmul_rn((float)t[u].z, scale), __fmul_rn((float)t[u].w, scale));
+                    if (a.acc) { a.acc[o] = t[u].x; a.acc[o + 1] = t[u].y; a.acc[o + 2] = t[u].z; a.acc[o + 3] = t[u].w; }
+                }
             }
         }
         return;
@@ -360,11 +443,11 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     for (int j = 0; j < NJ; ++j) {
         const int col = colbase + wn * CW + j * 32 + (lane & 31);
         if (col >= ncols) continue;
-        const int n = col / OHW;
+        const int n = image_of(col);
         int opix = col - n * OHW;
         int ci = 0, cj = 0;
         if (CLS) {
-            ci = opix / OWc;
+            ci = row_of(opix);
             cj = opix - ci * OWc;
             opix = (dc.ch + a.cls_h * ci) * a.OW + dc.cw + a.cls_w * cj;
         }

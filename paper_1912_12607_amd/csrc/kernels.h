@@ -127,6 +127,22 @@ hipError_t launch_dsgc(const float* g, size_t n, const float* ratios, int n_cand
                        uint64_t seed, const DsgcWs& ws, int nparts_absmax, float* clip_out,
                        double* dev_out, double* dev_all_out, hipStream_t st);
 
+// Division by a number the host knows: q = floor(n / d) for 0 <= n < 2^31 as a high product and a shift.  With l = ceil(log2 d) and
+// m = floor(2^(31+l) / d) + 1 (below 2^32 for d >= 2), m d exceeds 2^(31+l) by at most 2^l, so n m / 2^(31+l) lies at or above
+// n / d by less than n / 2^31 / d < 1 / d.  d = 1: m = 0 stands for it.
+struct FastDiv {
+    uint32_t m, s;
+};
+inline FastDiv fast_div(unsigned d) {
+    if (d <= 1) return FastDiv{0u, 0u};
+    unsigned l = 0;
+    while ((1ull << l) < d) ++l;
+    return FastDiv{(uint32_t)((1ull << (31 + l)) / d + 1), l - 1};
+}
+__host__ __device__ __forceinline__ int div_by(int n, const FastDiv& f) {
+    return f.m ? (int)((uint32_t)(((unsigned long long)(uint32_t)n * f.m) >> 32) >> f.s) : n;
+}
+
 // ---- conv_igemm.hip (dense forward and backward-data) -----------------------------------------
 struct IgemmArgs {
     const int8_t* act;           // NHWC codes, channel pitch Ca
@@ -147,6 +163,7 @@ struct IgemmArgs {
     size_t partial_bytes;
     int ksplit;                  // filled by launch_igemm(): blocks per output tile along the reduction
     int variant;                 // ConvVariant: VAR_AUTO, or the kernel the caller selected for this layer
+    FastDiv by_rtiles, by_image, by_row;     // filled with the grid of the wide tiles: row tiles, columns per image and per image row (pixels, or cells)
     int colrun;                  // filled by launch_igemm(): column tiles an XCD takes in a run, 0 = every eighth tile
     // Quantization fused into the forward pass of a 1 x 1, stride-1, unpadded layer (launch_igemm_fused):
     const float* xf;             // fp32 activations N,C,H,W (act is not read)

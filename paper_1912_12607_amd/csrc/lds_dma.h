@@ -24,6 +24,11 @@ __device__ __forceinline__ void igd_load_lds(const lds_dma_v4i& rsrc, uint32_t l
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(lds_base_uniform), "v"(voff), "s"(rsrc) : "memory");
 }
+// The same, `soff` (wave-uniform) added to every lane's offset.
+__device__ __forceinline__ void igd_load_lds(const lds_dma_v4i& rsrc, uint32_t lds_base_uniform, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_base_uniform), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
 // slot of (row, granule) in a [rows][KG] tile; the xor makes the MFMA operand reads (16 consecutive
 // rows of one granule per LDS pass) hit 16 different slots mod 16, see lds_slot(): with 8 granules per
 // row, slot mod 16 = 8 * (row & 1) + position, so rows of equal parity need different positions

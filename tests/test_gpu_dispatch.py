@@ -663,3 +663,23 @@ def test_bands_and_backward_weight_in_one_launch(shape, ahead):
         assert bool(launches) == (ahead and parts != two)
         for i, t in enumerate(outs):
             assert torch.equal(t, want[i]) or (parts == two and i in (0, 3))
+
+
+# The wide tiles' position in the reduction: scalar where the channels are whole stages (of 128 or 64 bytes), per lane otherwise, down to
+# several taps in a stage; taps that wrap rows, padding wider than the image border, strides with and without pixel classes, images of a
+# single row or column, tiles that span images.
+@pytest.mark.parametrize("shape", [(3, 128, 7, 9, 136, 3, 3, 1, (1, 1)), (2, 256, 5, 11, 64, 5, 3, 1, (4, 0)), (5, 64, 6, 6, 192, 3, 3, 1, (0, 2)),
+                                   (3, 16, 9, 8, 130, 5, 5, 1, (2, 2)), (2, 48, 10, 7, 70, 1, 7, 1, (0, 3)), (4, 144, 1, 13, 128, 1, 3, 1, (0, 1)),
+                                   (3, 128, 13, 1, 128, 3, 1, 1, (1, 0)), (3, 128, 11, 12, 128, 3, 3, 2, (1, 1)), (2, 128, 9, 10, 256, 1, 1, 2, (0, 0)),
+                                   (2, 136, 12, 9, 72, 4, 3, 2, (1, 0)), (2, 128, 13, 11, 128, 5, 5, 3, (2, 2)), (9, 384, 1, 1, 130, 1, 1, 1, (0, 0))])
+def test_reduction_positions_of_wide_tiles(shape):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 21)
+    for op in (B.OP_CONV_FWD, B.OP_CONV_BWD_DATA):
+        for variant in (B.VARIANT_WIDE128, B.VARIANT_WIDE256, B.VARIANT_WIDE_SQ128, B.VARIANT_WIDE_SQ128_DEEP, B.VARIANT_WIDE_128X64, B.VARIANT_WIDE_CELLS):
+            if not B.int8t_conv_variant_ok(op, desc, variant):
+                continue
+            B.int8t_conv_select_variant(op, desc, variant)
+            try:
+                conv_pass_elementwise(op, desc, od, xq, wq, dyq, True)
+            finally:
+                B.int8t_conv_select_variant(op, desc, B.VARIANT_AUTO)
