@@ -306,7 +306,7 @@ size_t int8t_workspace_bytes(int8t_op op, const int8t_conv_desc* desc, size_t n,
             const size_t s2d_bytes = wgrad_s2d(&a);
             a.variant = selected_variant(INT8T_OP_CONV_BWD_WEIGHT, desc);
             wgrad_plan(&a);
-            return align256((size_t)a.splits * a.K * a.R * a.S * a.Cp * 4) + align256(s2d_bytes);
+            return wgrad_partial_bytes(a) + align256(s2d_bytes);
         }
         default: break;
     }
@@ -747,7 +747,7 @@ int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc* desc, const int8_t
     wgrad_plan(&a);
     a.x = xq_dev; a.dy = dyq_dev; a.sa = sx_dev; a.sb = sdy_dev; a.dw = dw_dev; a.acc = acc_dev;
     a.partial = (int32_t*)ws_dev;
-    a.xs = (int8_t*)ws_dev + align256((size_t)a.splits * a.K * a.R * a.S * a.Cp * 4);
+    a.xs = (int8_t*)ws_dev + wgrad_partial_bytes(a);
     const size_t fwd_bytes = fwd_s2d_bytes(desc, g);
     const bool apart = (uintptr_t)fwd_ws_dev + fwd_bytes <= (uintptr_t)ws_dev || (uintptr_t)ws_dev + ws_bytes <= (uintptr_t)fwd_ws_dev;
     if (fwd_ws_dev && fwd_bytes && fwd_ws_bytes >= fwd_bytes && apart) {

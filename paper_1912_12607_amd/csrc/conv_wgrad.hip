@@ -28,7 +28,7 @@ __device__ __forceinline__ void wgrad_result(const WgradArgs& a, int k, int rs, 
 }
 
 // Few weights under many shares (a share's partial tile set is a few hundred KB at most): a block owns Q quads of four
-// channels, side by side in the partial's own order whatever taps and filters they belong to, its threads are (quads) x (split
+// filters, side by side in the partial's own order whatever taps and channels they belong to, its threads are (quads) x (split
 // lanes); every thread has up to 8 shares' 16 bytes in flight at once, the lanes of a wave are combined by lane
 // exchanges, the four waves through LDS.
 // Bound: one round trip to memory and the launch.  Before, 4 or 16 quads x one tap with the shares one after the other and the lanes summed
@@ -38,7 +38,7 @@ template <int Q>
 __global__ __launch_bounds__(256) void wgrad_reduce_flat_kernel(const WgradArgs a) {
     constexpr int ZL = 256 / Q, ZU = 8;
     __shared__ int4 part[4][Q];
-    const unsigned quads = (unsigned)a.K * (unsigned)(a.R * a.S) * (unsigned)(a.Cp >> 2);
+    const unsigned ncolsp = (unsigned)(a.R * a.S) * (unsigned)a.Cp, quads = (unsigned)((a.K + 3) >> 2) * ncolsp;
     const unsigned q0 = blockIdx.x * Q;
     const int zl = threadIdx.x / Q;
     const unsigned qi = q0 + threadIdx.x % Q;
@@ -65,38 +65,36 @@ __global__ __launch_bounds__(256) void wgrad_reduce_flat_kernel(const WgradArgs 
     if ((int)(threadIdx.x & (kWave - 1)) < Q) part[threadIdx.x / kWave][threadIdx.x % Q] = sum;
     __syncthreads();
     if (threadIdx.x >= 4 * Q) return;
-    const unsigned e = 4 * q0 + threadIdx.x;     // element of the partial
-    if (e >= 4 * quads) return;
-    const int* const t = reinterpret_cast<const int*>(&part[0][0]) + threadIdx.x;
+    // (the filters of the quads one after the other: neighbouring threads then write neighbouring channels)
+    const unsigned f = threadIdx.x / Q, u = threadIdx.x % Q;
+    if (q0 + u >= quads) return;
+    const int* const t = reinterpret_cast<const int*>(&part[0][0]) + 4 * u + f;
     const int v = (t[0] + t[4 * Q]) + (t[8 * Q] + t[12 * Q]);
-    const unsigned kt = e / (unsigned)a.Cp;      // filter and tap
-    const int c = (int)(e - kt * (unsigned)a.Cp), RS = a.R * a.S;
-    const int k = (int)(kt / (unsigned)RS), rs = (int)(kt - (unsigned)k * (unsigned)RS);
-    wgrad_result(a, k, rs, c, v, __fmul_rn(a.sa[0], a.sb[0]));
+    const unsigned k4 = (q0 + u) / ncolsp, col = q0 + u - k4 * ncolsp;
+    const int k = (int)(4 * k4 + f), rs = (int)(col / (unsigned)a.Cp), c = (int)(col - (unsigned)rs * (unsigned)a.Cp);
+    if (k < a.K) wgrad_result(a, k, rs, c, v, __fmul_rn(a.sa[0], a.sb[0]));
 }
 
-// Sum the split partials, apply Eq.2 and scatter [k][(r,s,c)] -> K,C,R,S.  A block owns, for one filter k,
-// 4*QN channels x RSC taps; its 256 threads are 256/QN split lanes x QN channel quads.  Every thread adds up the
-// splits z = lane, lane + 256/QN, ... of its quad at each tap (independent 16-byte loads, RSC of them in flight
+// The same with all taps of a filter in a block, or rows of them: the sums then leave as contiguous runs of the result.  A block owns
+// four filters, QN channels x RSC taps; its 256 threads are 256/QN split lanes x QN channels.  Every thread adds up the
+// splits z = lane, lane + 256/QN, ... of its channel at each tap (independent 16-byte loads, RSC of them in flight
 // per split), the lanes are combined through LDS, and the sums leave in the order of the result tensor -- with
-// all taps of a filter in the block (RSC = R*S) that is one contiguous run of 4*QN*RSC floats.  LDS holds
-// [split lane][channel quad][channel][tap] with an odd quad pitch of 4*RSC + 1 words: the stores of a wave
-// (one word per quad at a time) then land in different banks for any RSC, and the final reads walk
-// consecutive words with one word skipped per quad.
+// all taps of a filter in the block (RSC = R*S) that is one contiguous run of QN*RSC floats per filter.  LDS holds
+// [split lane][filter][channel][tap]; an odd number of taps per channel puts the stores of a wave in different banks.
 template <int QN, int RSC>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a) {
-    constexpr int ZL = 256 / QN, CB = 4 * QN, QP = 4 * RSC + 1, PITCH = QN * QP;
+    constexpr int ZL = 256 / QN, RUN = QN * RSC, PITCH = 4 * RUN;
     __shared__ int sred[ZL * PITCH];
     const int RS = a.R * a.S;
     const int ncolsp = RS * a.Cp;
-    const size_t total = (size_t)a.K * ncolsp;
-    const int nrg = RS / RSC, nct = a.Cp / CB;
+    const size_t total = wgrad_partial_elems(a) >> 2;
+    const int nrg = RS / RSC, nct = a.Cp / QN;
     int b = blockIdx.x;
     const int rg = b % nrg;
     b /= nrg;
-    const int ct = b % nct, k = b / nct;
-    const int quad = threadIdx.x % QN, zl = threadIdx.x / QN;
-    const int32_t* __restrict__ p = a.partial + (size_t)k * ncolsp + (size_t)(rg * RSC) * a.Cp + ct * CB + 4 * quad;
+    const int ct = b % nct, k4 = b / nct;
+    const int qc = threadIdx.x % QN, zl = threadIdx.x / QN;
+    const int4* __restrict__ p = reinterpret_cast<const int4*>(a.partial) + (size_t)k4 * ncolsp + (size_t)(rg * RSC) * a.Cp + ct * QN + qc;
     int4 s4[RSC];
 #pragma unroll
     for (int j = 0; j < RSC; ++j) s4[j] = make_int4(0, 0, 0, 0);
@@ -108,8 +106,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a) {
 #pragma unroll
         for (int u = 0; u < ZU; ++u)
 #pragma unroll
-            for (int j = 0; j < RSC; ++j)
-                v[u][j] = *reinterpret_cast<const int4*>(p + (size_t)(z + u * ZL) * total + (size_t)j * a.Cp);
+            for (int j = 0; j < RSC; ++j) v[u][j] = p[(size_t)(z + u * ZL) * total + (size_t)j * a.Cp];
 #pragma unroll
         for (int u = 0; u < ZU; ++u)
 #pragma unroll
@@ -118,26 +115,26 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const WgradArgs a) {
     for (; z < a.splits; z += ZL) {
 #pragma unroll
         for (int j = 0; j < RSC; ++j) {
-            const int4 v = *reinterpret_cast<const int4*>(p + (size_t)z * total + (size_t)j * a.Cp);
+            const int4 v = p[(size_t)z * total + (size_t)j * a.Cp];
             s4[j].x += v.x; s4[j].y += v.y; s4[j].z += v.z; s4[j].w += v.w;
         }
     }
-    int* __restrict__ mine = sred + zl * PITCH + quad * QP;
+    int* __restrict__ mine = sred + zl * PITCH + qc * RSC;
 #pragma unroll
     for (int j = 0; j < RSC; ++j) {
         mine[j] = s4[j].x;
-        mine[RSC + j] = s4[j].y;
-        mine[2 * RSC + j] = s4[j].z;
-        mine[3 * RSC + j] = s4[j].w;
+        mine[RUN + j] = s4[j].y;
+        mine[2 * RUN + j] = s4[j].z;
+        mine[3 * RUN + j] = s4[j].w;
     }
     __syncthreads();
     const int nz = a.splits < ZL ? a.splits : ZL;
     const float scale = __fmul_rn(a.sa[0], a.sb[0]);
-    for (int t = threadIdx.x; t < CB * RSC; t += 256) {
-        const int cl = t / RSC;
+    for (int t = threadIdx.x; t < PITCH; t += 256) {
+        const int f = t / RUN, cl = (t - f * RUN) / RSC;
         int sum = 0;
-        for (int z = 0; z < nz; ++z) sum += sred[z * PITCH + t + (cl >> 2)];
-        wgrad_result(a, k, rg * RSC + (t - cl * RSC), ct * CB + cl, sum, scale);
+        for (int z = 0; z < nz; ++z) sum += sred[z * PITCH + t];
+        if (4 * k4 + f < a.K) wgrad_result(a, 4 * k4 + f, rg * RSC + (t - f * RUN - cl * RSC), ct * QN + cl, sum, scale);
     }
 }
 
@@ -363,25 +360,25 @@ static int wgrad_flat_quads(unsigned quads, int splits) {
 
 hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
     if (a.direct) return hipSuccess;       // (wgrad_lines_tile wrote the result)
-    // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (256, 64 or
-    // 16) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
+    // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (64, 16 or
+    // 4) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
     // loads of a small layer are latency, not bandwidth; the flat kernel if nothing does.  A block's
-    // threads are (channels / 4) x (split lanes): 256 channels leave 4 split lanes, which is what few splits
+    // threads are channels x (split lanes): 64 channels leave 4 split lanes, which is what few splits
     // can keep busy.
     const int RS = a.R * a.S;
-    const size_t elems = (size_t)a.K * RS * a.Cp;
+    const size_t elems = wgrad_partial_elems(a);
     int rsc = 1, qn = 4;
     {
         const int cand[3] = {9, 7, 3};
         const int qns[3] = {64, 16, 4};
         bool found = false;
         for (int w = 0; w < 3 && !found; ++w) {
-            if (a.Cp % (4 * qns[w]) != 0) continue;
+            if (a.Cp % qns[w] != 0) continue;
             if (qns[w] == 64 && a.splits > 6) continue;
             for (int i = 0; i < 4 && !found; ++i) {
                 const int r = i < 3 ? cand[i] : 1;
                 if (RS % r != 0) continue;
-                if ((long long)a.K * (a.Cp / (4 * qns[w])) * (RS / r) >= 1024) { rsc = r; qn = qns[w]; found = true; }
+                if ((long long)((a.K + 3) / 4) * (a.Cp / qns[w]) * (RS / r) >= 1024) { rsc = r; qn = qns[w]; found = true; }
             }
         }
     }
@@ -396,7 +393,7 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
         else launch_timed(kt, (wgrad_reduce_flat_kernel<8>), blocks, dim3(256), 0, st, a);
         return hipGetLastError();
     }
-    const dim3 blocks((unsigned)(a.K * (a.Cp / (4 * qn)) * (RS / rsc)));
+    const dim3 blocks((unsigned)((a.K + 3) / 4 * (a.Cp / qn) * (RS / rsc)));
 #define REDUCE(RSCv)                                                                                         \
     do {                                                                                                     \
         if (qn == 64) launch_timed(kt, (wgrad_reduce_kernel<64, RSCv>), blocks, dim3(256), 0, st, a);      \

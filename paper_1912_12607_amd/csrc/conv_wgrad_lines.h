@@ -330,24 +330,24 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
         }
         return;
     }
-    // partial[z][k][(tap,c)], channel fastest: 32 consecutive columns per store instruction
+    // partial[z][k / 4][(tap,c)][k % 4]: four registers, 32 consecutive columns per store instruction and half-wave
     const int ncolsp = a.R * a.S * a.Cp;
-    int32_t* __restrict__ part = a.partial + (size_t)zshare * a.K * ncolsp;
+    int4* __restrict__ part = reinterpret_cast<int4*>(a.partial + (size_t)zshare * wgrad_partial_elems(a));
 #pragma unroll
     for (int k2 = 0; k2 < WN; ++k2) {
         const int c = ct * (64 * WN) + (ch * WN + k2) * 32 + l32;
         if (c >= a.Cp) continue;
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            const int col = (t0 + s) * a.Cp + c;
+        for (int m = 0; m < WM; ++m)
 #pragma unroll
-            for (int m = 0; m < WM; ++m)
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int k = kt * (64 * WM) + (mt * WM + m) * 32 + 8 * g4 + 4 * half;
+                if (k >= a.K) continue;          // (filters beyond the last in its four are zeros)
+                int4* __restrict__ const p = part + ((size_t)(k >> 2) * ncolsp + t0 * a.Cp + c);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int k = kt * (64 * WM) + (mt * WM + m) * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                    if (k < a.K) part[(size_t)k * ncolsp + col] = acc[s][m][k2][v];
-                }
-        }
+                for (int s = 0; s < ST; ++s)
+                    p[s * a.Cp] = make_int4(acc[s][m][k2][4 * g4], acc[s][m][k2][4 * g4 + 1], acc[s][m][k2][4 * g4 + 2], acc[s][m][k2][4 * g4 + 3]);
+            }
     }
 }
 

@@ -302,9 +302,9 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs& a, const unsigned bl
         }
     }
 
-    // partial[z][k][(tap,c)], channel fastest: 32 consecutive columns per store instruction
+    // partial[z][k / 4][(tap,c)][k % 4]: four registers, 32 consecutive columns per store instruction and half-wave
     const int ncolsp = RS * a.Cp;
-    int32_t* __restrict__ part = a.partial + (size_t)zshare * a.K * ncolsp;
+    int4* __restrict__ part = reinterpret_cast<int4*>(a.partial + (size_t)zshare * wgrad_partial_elems(a));
 #pragma unroll
     for (int j = 0; j < TBA; ++j) {
         if (j >= nt) continue;
@@ -315,9 +315,10 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs& a, const unsigned bl
             if (!PK && c >= a.Cp) continue;
             const int col = (t0 + j) * a.Cp + c;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int k = kt * W2_BM + mt * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (k < a.K) part[(size_t)k * ncolsp + col] = acc[j][i][v];
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int k = kt * W2_BM + mt * 32 + 8 * g4 + 4 * half;
+                if (k < a.K)                     // (filters beyond the last in its four are zeros)
+                    part[(size_t)(k >> 2) * ncolsp + col] = make_int4(acc[j][i][4 * g4], acc[j][i][4 * g4 + 1], acc[j][i][4 * g4 + 2], acc[j][i][4 * g4 + 3]);
             }
         }
     }

@@ -247,7 +247,7 @@ struct WgradArgs {
     const float* sb;
     float* dw;                   // [K][C][R][S]
     int32_t* acc;                // nullable
-    int32_t* partial;            // scratch [splits][K][R*S*Cp]
+    int32_t* partial;            // scratch [splits][ceil(K / 4)][R*S*Cp][4 filters]
     int N, C, Cp, H, W, K, Kp, P, Q, R, S;
     int stride_h, stride_w, pad_h, pad_w;
     // filled by wgrad_plan():
@@ -284,6 +284,13 @@ hipError_t launch_wgrad_lines(const WgradArgs& a, hipStream_t st);
 unsigned wgrad_grid(const WgradArgs& a);         // blocks of wgrad_kernel
 unsigned wgrad_lines_grid(const WgradArgs& a);
 bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filters, stride 2 x 2
+// Partial tiles of the shares: four filters side by side, which a lane of a matrix product holds in four neighbouring registers (one 16-byte
+// store instead of four of 4 bytes; the address path of a compute unit takes 16 cycles for either, 3000 - 5000 at the end of a block with
+// the latter.  us for the pass, channel by channel / so: 7x1, 160 -> 192, 17 x 17, batch 64: 23.3, 19.7; 3x3, 96 channels, 35 x 35, batch 32:
+// 18.1, 16.5; 3x3, 64 channels, 56 x 56, batch 64: 21.5, 20.2; 1x1, 1024 -> 256, 14 x 14, batch 128: 26.3, 25.1).
+__host__ __device__ inline size_t wgrad_partial_elems(const WgradArgs& a) { return (size_t)((a.K + 3) / 4 * 4) * a.R * a.S * a.Cp; }      // of one share
+inline size_t wgrad_partial_bytes(const WgradArgs& a) { return (a.splits * wgrad_partial_elems(a) * 4 + 255) & ~(size_t)255; }
+
 // which kernel VAR_AUTO stands for: true = wgrad_lines_kernel
 bool wgrad_auto_lines(const WgradArgs& a);
 // Share z runs on XCD z mod 8 with all its output tiles (they read the same lines of both tensors, and every XCD fills
