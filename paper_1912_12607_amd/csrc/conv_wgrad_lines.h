@@ -73,30 +73,29 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
     int zshare, tg, ct, kt;
     if (a.xgk > 0) {
         const int xcd = (int)(block & 7), i = (int)(block >> 3);
-        const int pk = (a.ktiles + a.xgk - 1) / a.xgk, pc = (a.ctiles + a.xgc - 1) / a.xgc;
-        const int per_share = pk * pc * a.tapgroups;
-        zshare = i / per_share;
-        int l = i - zshare * per_share;
-        tg = l % a.tapgroups;
-        l /= a.tapgroups;
-        ct = (xcd % a.xgc) * pc + l % pc;
-        kt = (xcd / a.xgc) * pk + l / pc;
+        const int ck = __builtin_ctz(a.xgk), cc = __builtin_ctz(a.xgc);      // (powers of two)
+        const int pk = (a.ktiles + a.xgk - 1) >> ck, pc = (a.ctiles + a.xgc - 1) >> cc;
+        zshare = div_by(i, a.by_tiles);
+        const int l = i - zshare * pk * pc * a.tapgroups, m = div_by(l, a.by_taps), mk = div_by(m, a.by_ctiles);
+        tg = l - m * a.tapgroups;
+        ct = (xcd & (a.xgc - 1)) * pc + m - mk * pc;
+        kt = (xcd >> cc) * pk + mk;
         if (kt >= a.ktiles || ct >= a.ctiles) return;
     } else {
         int ot;
         if (wgrad_xcd_mapping(a.splits)) {
-            const int wg_i = block >> 3;
-            zshare = ((wg_i / out_tiles) << 3) + (int)(block & 7);
+            const int wg_i = (int)(block >> 3), g = div_by(wg_i, a.by_tiles);
+            zshare = (g << 3) + (int)(block & 7);
             if (zshare >= a.splits) return;
-            ot = wg_i % out_tiles;
+            ot = wg_i - g * out_tiles;
         } else {
-            zshare = block / out_tiles;
-            ot = block - zshare * out_tiles;
+            zshare = div_by((int)block, a.by_tiles);
+            ot = (int)block - zshare * out_tiles;
         }
-        tg = ot % a.tapgroups;
-        ot /= a.tapgroups;
-        ct = ot % a.ctiles;
-        kt = ot / a.ctiles;
+        const int m = div_by(ot, a.by_taps);
+        tg = ot - m * a.tapgroups;
+        kt = div_by(m, a.by_ctiles);
+        ct = m - kt * a.ctiles;
     }
 
     // Lines and positions.  along_w: a line is an image row, positions run along W, the block owns tap
@@ -124,8 +123,7 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
     const int U = S2 ? QL + 1 : WLn + pl;
     const int GC = (U + GP - 1) / GP;             // ring stages per chunk
     const int total_lines = a.N * NLI;
-    const int c_begin = (int)(((uint32_t)a.chunks * (uint32_t)zshare) / (uint32_t)a.splits);
-    const int c_end = (int)(((uint32_t)a.chunks * (uint32_t)(zshare + 1)) / (uint32_t)a.splits);
+    const int c_begin = div_by(a.chunks * zshare, a.by_splits), c_end = div_by(a.chunks * (zshare + 1), a.by_splits);      // (below 2^31: the plan)
     const int NS = (c_end - c_begin) * GC;
 
     // ---- loader role.  A wave-wide load fills 16 lines x 64 channels of one position (1 KB of LDS in lane
@@ -166,7 +164,7 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
     auto line_base = [&](int e, int chunk) -> uint32_t {
         const int L = chunk * WL_LINES + myline;
         if (chunk >= c_end || L >= total_lines || !ld_chan_ok[e]) return IGD_OOB;
-        const int n = L / NLI;
+        const int n = div_by(L, a.by_lines);
         const int l = (L - n * NLI) * ld_lmul + ld_lshift[e];
         if ((unsigned)l >= (unsigned)ld_nlines[e]) return IGD_OOB;
         return (uint32_t)n * ld_img[e] + (uint32_t)l * ld_ls[e] + (uint32_t)ld_chan[e];
@@ -174,32 +172,24 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
     int lc = c_begin, lg = 0;           // chunk and stage (of the chunk) that is fetched next
 #pragma unroll
     for (int e = 0; e < NLD; ++e) ld_base[e] = line_base(e, lc);
+    // The next stage, into ring slot `slot`.  A position is the same for all lanes: its offset goes into the load's scalar offset, and a
+    // position outside the line turns the lanes' offsets into ones beyond the tensor.
     auto issue = [&](int slot) {
+        auto one = [&](int e, int pos, uint32_t dst) {
+            const bool ok = (unsigned)pos < (unsigned)ld_npos[e];
+            igd_load_lds(rsrc[e], ld_dst[e] + (uint32_t)slot * STAGE + dst, ld_base[e] | (ok ? 0u : IGD_OOB),
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)(ok ? (uint32_t)pos * ld_ps[e] : 0u)));
+        };
 #pragma unroll
         for (int j = 0; j < GP; ++j) {
-            if (S2) {
-                if (ld_input) {
+            if (S2 && ld_input) {
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int pos = 2 * (lg * GP + j) - pl + h;
-                        const bool ok = ld_base[0] != IGD_OOB && (unsigned)pos < (unsigned)ld_npos[0];
-                        igd_load_lds(rsrc[0], ld_dst[0] + (uint32_t)slot * STAGE + (uint32_t)(2 * j + h) * XPOS,
-                                     ok ? ld_base[0] + (uint32_t)pos * ld_ps[0] : IGD_OOB);
-                    }
-                } else {
-                    const int pos = lg * GP + j;
-                    const bool ok = ld_base[0] != IGD_OOB && (unsigned)pos < (unsigned)ld_npos[0];
-                    igd_load_lds(rsrc[0], ld_dst[0] + (uint32_t)slot * STAGE + (uint32_t)j * YPOS,
-                                 ok ? ld_base[0] + (uint32_t)pos * ld_ps[0] : IGD_OOB);
-                }
-                continue;
-            }
+                for (int h = 0; h < 2; ++h) one(0, 2 * (lg * GP + j) - pl + h, (uint32_t)(2 * j + h) * XPOS);
+            } else if (S2) {
+                one(0, lg * GP + j, (uint32_t)j * YPOS);
+            } else {
 #pragma unroll
-            for (int e = 0; e < NLD; ++e) {
-                const int pos = lg * GP + j - ld_poff[e];
-                const bool ok = ld_base[e] != IGD_OOB && (unsigned)pos < (unsigned)ld_npos[e];
-                igd_load_lds(rsrc[e], ld_dst[e] + (uint32_t)slot * STAGE + (uint32_t)j * ld_pitch[e],
-                             ok ? ld_base[e] + (uint32_t)pos * ld_ps[e] : IGD_OOB);
+                for (int e = 0; e < NLD; ++e) one(e, lg * GP + j - ld_poff[e], (uint32_t)j * ld_pitch[e]);
             }
         }
         if (++lg == GC) {
@@ -241,6 +231,8 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
     for (int i = 0; i < NS; ++i) {
         igd_wait_vmcnt<0>();            // this wave's loads of stage i have landed ...
         __syncthreads();                // ... and everyone's; all waves are done with stage i-1's slot
+        // (All of the next stage's loads at once: dealt out between the products they came too late -- 3x3 under stride 2, 256 channels,
+        // 28 x 28: 25.9 us so, 27.2 -- though they keep the address path busy for 400 cycles of the 1700 of a stage.)
         if (i + 1 < NS) issue((i + 1) & 1);
         const uint32_t sbase = lds0 + (uint32_t)(i & 1) * STAGE;
         auto fetch = [&](uint32_t off, int bytes) -> wl_v4i {

@@ -78,6 +78,12 @@ void wgrad_plan_lines(WgradArgs* a) {
             if (cost < best) { best = cost; a->xgk = gk; a->xgc = gc; }
         }
     }
+    const int pk = a->xgk ? (a->ktiles + a->xgk - 1) / a->xgk : a->ktiles, pc = a->xgk ? (a->ctiles + a->xgc - 1) / a->xgc : a->ctiles;
+    a->by_tiles = fast_div((unsigned)(pk * pc * a->tapgroups));
+    a->by_taps = fast_div((unsigned)a->tapgroups);
+    a->by_ctiles = fast_div((unsigned)pc);
+    a->by_splits = fast_div((unsigned)a->splits);
+    a->by_lines = fast_div((unsigned)NLI);
 }
 
 unsigned wgrad_lines_grid(const WgradArgs& a) {

@@ -257,6 +257,7 @@ struct WgradArgs {
     int ngrp, chunks, splits;    // groups of 16 images, reduction chunks, split-K factor
     int ktiles, ctiles, tapgroups;
     int xt_slots;                // 16-byte granules of the staged input window
+    FastDiv by_tiles, by_taps, by_ctiles, by_splits, by_lines;     // image lines: output tiles (of a patch), tap groups, channel tiles (of a patch), splits, lines per image
     size_t lds_bytes;
     // set by the caller, who knows the buffers: one share on image lines, whose tiles are written as the result (dw and acc overlap nothing the pass reads)
     int direct;
