@@ -23,6 +23,11 @@ typedef int band_v16i __attribute__((ext_vector_type(16)));
 constexpr int BAND_MAXPIX = 256;             // output pixels per band, at most (NTW = 2: 8 tiles of 32)
 constexpr size_t BAND_LDS_MAX = 80 * 1024;   // two blocks per compute unit
 constexpr int BAND_STAGE = 12;               // staged 16-byte granules per thread and band, at most
+// ... and of layers whose window takes no more: two tiles of rows then need 176 registers instead of 224, fewer than the 192 that the clip
+// search leaves, so that these blocks start beside it (7x7 under stride 2 on 3 channels, 224 x 224, batch 64: they waited for its end).  With
+// the rows' descriptors below (36 registers of a slot's tests and addresses less), alone: 16 -> 16 channels, 32 x 32, batch 128, 9.2 -> 8.4 us;
+// 64 -> 48 at 112 x 112, batch 16, 21.4 -> 19.4; 3x3 under stride 2 on 3 channels, 224 x 224, batch 64, 28.6 -> 23.5; 7x7 at 400 x 400, 100 -> 91.
+constexpr int BAND_STAGE_FEW = 6;
 constexpr int BAND_MAXG = 64;                // reduction granules (16 bytes each) per output row, at most
 constexpr int BAND_WJ = BAND_MAXG / 4;       // weight granules per thread
 constexpr int BAND_REG_ROWS = 4;             // window rows of the register-weight variant, at most
@@ -35,7 +40,7 @@ __host__ __device__ inline int odd_pitch(int granules) { return (granules & 1) ?
 // the output offsets of a lane) is worked out once per block.
 // MT: 32-row tiles of output rows; NTW: 32-pixel tiles per wave; UNI: rows is a multiple of 8, so
 // the "row exists" test of the epilogue is the same for every lane.
-template <bool DGRAD, int MT, int NTW, bool UNI>
+template <bool DGRAD, int MT, int NTW, bool UNI, int STG = BAND_STAGE>
 __device__ __forceinline__ void band_walk(const IgemmArgs& a, int BP, int nbands_h, int nbands, int block, int nblocks) {
     raise_wave_priority();
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
@@ -98,21 +103,21 @@ __device__ __forceinline__ void band_walk(const IgemmArgs& a, int BP, int nbands
     // tid + 256*j of window row wy, k = wy * kw + j ----------------------------------------------------
     const int rowgran = WW * Cg16;
     const int kw = (rowgran + 255) >> 8;
-    int s_goff[BAND_STAGE], s_ldst[BAND_STAGE], s_wy[BAND_STAGE];
+    const int nslots = WH * kw;              // (at most STG)
+    uint32_t s_goff[STG];             // offset inside an image row
+    int s_ldst[STG];                  // -1: no column for this thread
     {
         int wy = 0, j = 0;
 #pragma unroll
-        for (int k = 0; k < BAND_STAGE; ++k) {
+        for (int k = 0; k < STG; ++k) {
             const int col = tid + 256 * j;
-            s_wy[k] = -1;
-            s_goff[k] = 0;
-            s_ldst[k] = 0;
+            s_goff[k] = 0x80000000u;
+            s_ldst[k] = -1;
             if (wy < WH && col < rowgran) {
                 const int wx = col / Cg16, cg = col - wx * Cg16;
                 const int iw = dsmin + wx;
                 s_ldst[k] = (wy * WW + wx) * PG + cg;
-                s_wy[k] = wy;
-                s_goff[k] = ((unsigned)iw < (unsigned)a.IW) ? (iw * a.Ca + cg * 16) : -1;   // -1: padding column
+                if ((unsigned)iw < (unsigned)a.IW) s_goff[k] = (uint32_t)(iw * a.Ca + cg * 16);      // (else a padding column)
             }
             if (++j == kw) {
                 j = 0;
@@ -140,18 +145,28 @@ __device__ __forceinline__ void band_walk(const IgemmArgs& a, int BP, int nbands
     const float scale = __fmul_rn(a.sa[0], a.sb[0]);
     const int aoff0 = l32 * GP, aoff1 = (32 + l32) * GP;
 
-    // Window loads of the NEXT band are in flight (in registers) while the current band computes.
-    uint4 pre[BAND_STAGE];
+    // Window loads of the NEXT band are in flight (in registers) while the current band computes.  Through a descriptor per image row
+    // (none for a row outside the image): what lies outside reads zeros, and a slot costs no test and no 64-bit address of its own.
+    const uint32_t rowbytes = (uint32_t)a.IW * a.Ca;
+    uint4 pre[STG];
     auto issue = [&](int band) {
         const int n = band / nbands_h;
         const int oh0 = (band - n * nbands_h) * BP;
         const int8_t* __restrict__ img = a.act + (size_t)n * a.IH * a.IW * a.Ca;
+        int ih = oh0 + drmin, j = 0;
 #pragma unroll
-        for (int k = 0; k < BAND_STAGE; ++k) {
-            pre[k] = make_uint4(0, 0, 0, 0);
-            const int ih = oh0 + drmin + s_wy[k];
-            if (s_wy[k] >= 0 && s_goff[k] >= 0 && (unsigned)ih < (unsigned)a.IH)
-                pre[k] = *reinterpret_cast<const uint4*>(img + (size_t)ih * a.IW * a.Ca + s_goff[k]);
+        for (int k = 0; k < STG; ++k) {
+            if (k < nslots) {                // (uniform)
+                const bool in = (unsigned)ih < (unsigned)a.IH;
+                const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<int8_t*>(img) + (in ? (size_t)ih * a.IW * a.Ca : (size_t)0), 0, in ? rowbytes : 0u, 0x00020000);
+                const auto t = __builtin_amdgcn_raw_buffer_load_b128(row, s_goff[k], 0, 0);
+                pre[k] = make_uint4(t[0], t[1], t[2], t[3]);
+                if (++j == kw) {
+                    j = 0;
+                    ++ih;
+                }
+            }
         }
     };
     if (block < nbands) issue(block);
@@ -177,8 +192,8 @@ __device__ __forceinline__ void band_walk(const IgemmArgs& a, int BP, int nbands
         const int oh0 = (band - n * nbands_h) * BP;
         __syncthreads();   // previous band's reads are done (and weights / tables are in place)
 #pragma unroll
-        for (int k = 0; k < BAND_STAGE; ++k)
-            if (s_wy[k] >= 0) xW[s_ldst[k]] = pre[k];
+        for (int k = 0; k < STG; ++k)
+            if (s_ldst[k] >= 0) xW[s_ldst[k]] = pre[k];
         __syncthreads();
         if (band + nblocks < nbands) issue(band + nblocks);
 
@@ -438,7 +453,7 @@ struct BandPlan {
     int BP, nbands_h, nbands;
     int nks;                    // k-steps of the register-weight body, 0: the LDS body
     int mt, ntw;                // LDS body: 32-row tiles, 32-pixel tiles per wave
-    bool uni;
+    bool uni, few;              // LDS body: whole groups of rows, few staged granules
     size_t lds;
     BandRegTab tab;
 };

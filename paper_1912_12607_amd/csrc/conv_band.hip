@@ -7,9 +7,9 @@
 namespace int8t {
 
 // A pass in a launch of its own.
-template <bool DGRAD, int MT, int NTW, bool UNI>
+template <bool DGRAD, int MT, int NTW, bool UNI, int STG>
 __global__ __launch_bounds__(256) void band_kernel(const IgemmArgs a, int BP, int nbands_h, int nbands) {
-    band_walk<DGRAD, MT, NTW, UNI>(a, BP, nbands_h, nbands, (int)blockIdx.x, (int)gridDim.x);
+    band_walk<DGRAD, MT, NTW, UNI, STG>(a, BP, nbands_h, nbands, (int)blockIdx.x, (int)gridDim.x);
 }
 template <bool DGRAD, int NKS>
 __global__ __launch_bounds__(256, 2) void band_reg_kernel(const IgemmArgs a, int BP, int nbands_h, int nbands, const BandRegTab tab) {
@@ -38,6 +38,7 @@ bool band_plan(const IgemmArgs& a, BandPlan* p) {
     p->ntw = ntw;
     p->mt = a.rows > 32 ? 2 : 1;
     p->uni = a.rows % 8 == 0;
+    p->few = WH * kw <= BAND_STAGE_FEW;
     p->lds = ((size_t)64 * odd_pitch(G) + (size_t)WH * WW * odd_pitch(Cg16) + 1) * 16 + (size_t)(G + 4) * sizeof(int2);
     if (p->lds > BAND_LDS_MAX) return false;
     p->nbands_h = (a.OH + BP - 1) / BP;
@@ -82,13 +83,13 @@ bool launch_band(const IgemmArgs& a, hipStream_t st, hipError_t* err, bool dry_r
         *err = hipGetLastError();
         return true;
     }
-    const int variant = (a.dgrad ? 8 : 0) + (p.mt - 1) * 4 + (p.ntw - 1) * 2 + (p.uni ? 1 : 0);
+    const int variant = (a.dgrad ? 16 : 0) + (p.mt - 1) * 8 + (p.ntw - 1) * 4 + (p.few ? 0 : 2) + (p.uni ? 1 : 0);
     typedef void (*kern_t)(const IgemmArgs, int, int, int);
-#define BK(D, M, N) band_kernel<D, M, N, false>, band_kernel<D, M, N, true>
-    static const kern_t kerns[16] = {BK(false, 1, 1), BK(false, 1, 2), BK(false, 2, 1), BK(false, 2, 2),
+#define BK(D, M, N) band_kernel<D, M, N, false, BAND_STAGE_FEW>, band_kernel<D, M, N, true, BAND_STAGE_FEW>, band_kernel<D, M, N, false, BAND_STAGE>, band_kernel<D, M, N, true, BAND_STAGE>
+    static const kern_t kerns[32] = {BK(false, 1, 1), BK(false, 1, 2), BK(false, 2, 1), BK(false, 2, 2),
                                      BK(true, 1, 1),  BK(true, 1, 2),  BK(true, 2, 1),  BK(true, 2, 2)};
 #undef BK
-    static std::atomic<unsigned long long> attr_done[16];
+    static std::atomic<unsigned long long> attr_done[32];
     {
         hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kerns[variant]), (int)BAND_LDS_MAX, attr_done[variant]);
         if (e != hipSuccess) { *err = e; return true; }

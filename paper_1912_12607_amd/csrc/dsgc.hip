@@ -38,7 +38,8 @@
 // blocks that share one the first was done in half the time of the last, and the last ran alone (205 M elements: blocks
 // between 237 and 448 us).  The waves of a block therefore take their wave-iterations from a counter in LDS as
 // they come.  616 -> 466 us at 205 M elements, 161 -> 118 at 51 M, 47.6 -> 38.6 at 12.8 M, 21.4 -> 18.3 at 3.2 M.
-// The block leaves half the wave slots, 66 KB of LDS and 7/16 of the registers to kernels of another stream; those raise their
+// The block leaves half the wave slots, 66 KB of LDS and 3/8 of the registers (192 of a lane's 512: a block of four waves that takes
+// more waits until this one is done) to kernels of another stream; those raise their
 // waves' priority (they are bound by HBM and issue little), which is what lets them run beside this kernel.
 //
 // The integer sums are exact and order independent; the only error against an fp64 evaluation is
