@@ -468,7 +468,8 @@ int batch_kind(const int8t_quantize_item& it) {
 }
 
 // Second launch: the codes and scales, from the clip values and the partials of the first.  (checked arguments)
-int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_dev, hipStream_t st) {
+// s2d (nullable): where the space-to-depth codes of the first item go, activations of at most 4 channels rounded to nearest.
+int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_dev, hipStream_t st, int8_t* s2d = nullptr) {
     QuantBatch qb{};
     qb.count = count;
     std::fill(std::begin(qb.block0), std::end(qb.block0), 0x7fffffff);
@@ -488,10 +489,15 @@ int8t_status batch_codes(int count, const int8t_quantize_item* items, void* ws_d
         q.seed_lo = seed_key_x(it.seed);
         q.seed_hi = seed_key_a(it.seed);
         quant_grid(q.kind, it.dims, &q.gx, &q.gy, &q.gz);
+        if (s2d && i == 0) {
+            q.kind = 3;
+            q.gx = (int)(((size_t)q.d0 * ((q.d2 + 1) / 2) * ((q.d3 + 1) / 2) + 255) / 256);      // (no more blocks than of kind 0)
+            q.gy = q.gz = 1;
+        }
         qb.block0[oi] = (int)qblocks;
         qblocks += (long long)q.gx * q.gy * q.gz;      // (batch_blocks_ok)
     }
-    return launch_quantize_batch(qb, (int)qblocks, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
+    return launch_quantize_batch(qb, (int)qblocks, st, s2d) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
 }
 
 // the codes' launch has one block index over all tensors of a batch
@@ -629,9 +635,17 @@ int8t_status int8t_dsgc_clip_static(const float* g_dev, size_t n, const float* r
                            kStaticDsgcBytes, stream);
 }
 
+static int8t_status conv_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, const float* sx_dev, const int8_t* wq_dev, const float* sw_dev,
+                             float* y_dev, int32_t* acc_dev, void* ws_dev, size_t ws_bytes, bool s2d_ready, void* stream);
 int8t_status int8t_conv_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, const float* sx_dev,
                             const int8_t* wq_dev, const float* sw_dev, float* y_dev, int32_t* acc_dev,
                             void* ws_dev, size_t ws_bytes, void* stream) {
+    return conv_fwd(desc, xq_dev, sx_dev, wq_dev, sw_dev, y_dev, acc_dev, ws_dev, ws_bytes, false, stream);
+}
+
+// s2d_ready: the space-to-depth codes of a lie in the scratch already
+static int8t_status conv_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, const float* sx_dev, const int8_t* wq_dev, const float* sw_dev,
+                             float* y_dev, int32_t* acc_dev, void* ws_dev, size_t ws_bytes, bool s2d_ready, void* stream) {
     Geo g;
     int8t_status s = desc_ok(desc, &g);
     if (s != INT8T_OK) return s;
@@ -655,6 +669,7 @@ int8t_status int8t_conv_fwd(const int8t_conv_desc* desc, const int8_t* xq_dev, c
         const size_t s2d_bytes = igemm_s2d(&t);
         if (s2d_bytes && a.partial_bytes >= s2d_bytes) {
             a.s2d = (int8_t*)ws_dev;
+            a.s2d_ready = s2d_ready;
             a.partial = (int32_t*)((int8_t*)ws_dev + s2d_bytes);
             a.partial_bytes -= s2d_bytes;
         }
@@ -780,6 +795,23 @@ static bool fwd_scratch_kept(const int8t_conv_desc* d, const Geo& g, const int8t
         if (p && p < q + bytes && q < p + t.n) return false;
     }
     return true;
+}
+
+// Where a step that forms the codes of a (and of g_z: quant_g) and runs the forward pass may put the space-to-depth codes of a with the ordinary
+// ones: the forward pass's scratch, if nothing that is read or written up to that pass lies in it.  nullptr: the pass rewrites the codes itself.
+static int8_t* s2d_with_codes(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool quant_g) {
+    const size_t bytes = fwd_s2d_bytes(d, g);
+    if (!bytes || !b->ws_fwd || b->ws_fwd_bytes < bytes) return nullptr;
+    struct Range { const void* p; size_t n; };
+    const size_t nx = (size_t)d->N * d->C * d->H * d->W * 4, ny = (size_t)d->N * d->K * g.P * g.Q * 4, nw = (size_t)d->K * d->C * d->R * d->S * 4;
+    const int xd[4] = {d->N, d->C, d->H, d->W}, wd[4] = {d->K, d->C, d->R, d->S}, yd[4] = {d->N, d->K, g.P, g.Q};
+    const Range r[] = {{b->x, nx}, {b->w, nw}, {b->ws_quant, b->ws_quant_bytes}, {b->xq, int8t_code_bytes(xd, INT8T_ACT)}, {b->sx, 4},
+                       {b->wq, int8t_code_bytes(wd, INT8T_WGT)}, {b->sw, 4}, {quant_g ? b->dy : nullptr, ny}, {quant_g ? b->clip : nullptr, 4},
+                       {quant_g ? b->dyq : nullptr, int8t_code_bytes(yd, INT8T_ACT)}, {quant_g ? b->sdy : nullptr, 4},
+                       {quant_g ? b->ws_dy : nullptr, b->ws_dy_bytes}, {quant_g ? b->dev_final : nullptr, 8}};
+    for (const Range& t : r)
+        if (t.p && overlap(t.p, t.n, b->ws_fwd, bytes)) return nullptr;
+    return (int8_t*)b->ws_fwd;
 }
 
 // Whether what the three passes of a step write overlaps nothing that one of them reads or writes, so that they may run
@@ -958,6 +990,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
     // overlaps what another part of the call reads or writes.
     bool dw_x = false, dw_g = false;
     const bool dw_fused = dw_fused_parts(desc, g, parts, &dw_x, &dw_g) && !(quant_g && b->dev_final) && disjoint_step(desc, g, b, dw_x, dw_g);
+    int8_t* const s2d = quant_xw && fwd ? s2d_with_codes(desc, g, b, quant_g) : nullptr;
     // ---- launches
     hipStream_t st = (hipStream_t)stream;
     if (absmax && batch_absmax(2, it, b->ws_quant, prepare ? b->dy : nullptr, n_y, b->ws_dy, st) != hipSuccess) return INT8T_ERR_RUNTIME;
@@ -1007,7 +1040,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         if (launch_dw_fused(f, w, st, &e)) return e == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;
     }
     if (quant_xw) {
-        s = batch_codes(g_in_batch ? 3 : 2, it, b->ws_quant, st);
+        s = batch_codes(g_in_batch ? 3 : 2, it, b->ws_quant, st, s2d);
         if (s != INT8T_OK) return s;
     }
     if (quant_g && !g_in_batch) {
@@ -1056,7 +1089,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         }
     }
     if (fwd_left) {
-        s = int8t_conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, stream);
+        s = conv_fwd(desc, b->xq, b->sx, b->wq, b->sw, b->y, b->y_acc, b->ws_fwd, b->ws_fwd_bytes, s2d != nullptr, stream);
         if (s != INT8T_OK) return s;
     }
     if (bwd_data) {

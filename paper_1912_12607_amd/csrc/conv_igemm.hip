@@ -592,7 +592,7 @@ hipError_t launch_igemm(const IgemmArgs& a_in, hipStream_t st) {
             const S2dGeo g = s2d_geometry(a.R, a.S, a.pad_h, a.pad_w);
             int8_t* const xs = a.s2d;
             int8_t* const ws = a.s2d + (((size_t)t.N * t.IH * t.IW * 16 + 255) & ~(size_t)255);
-            const hipError_t e = launch_s2d_repack(a.act, xs, a.N, a.IH, a.IW, a.C, a.wgt, ws, a.rows, a.R, a.S, g, st);
+            const hipError_t e = launch_s2d_repack(a.s2d_ready ? nullptr : a.act, xs, a.N, a.IH, a.IW, a.C, a.wgt, ws, a.rows, a.R, a.S, g, st);
             if (e != hipSuccess) return e;
             t.act = xs;
             t.wgt = ws;

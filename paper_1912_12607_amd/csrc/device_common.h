@@ -207,4 +207,22 @@ __device__ __forceinline__ uint32_t pack4(int q0, int q1, int q2, int q3) {
            ((uint32_t)q3 << 24);
 }
 
+// The first C bytes of four 32-bit words, packed back to back into 16 bytes (the rest zero).
+__device__ __forceinline__ uint4 s2d_pack(const uint32_t px[4], int C) {
+    const uint32_t keep = C >= 4 ? 0xffffffffu : ((1u << (8 * C)) - 1u);
+    unsigned long long lo = 0, hi = 0;        // a 128-bit shift register
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const unsigned long long v = px[b] & keep;
+        const int sh = 8 * C * b;             // 0 .. 96
+        if (sh < 64) {
+            lo |= v << sh;
+            if (sh > 32) hi |= v >> (64 - sh);
+        } else {
+            hi |= v << (sh - 64);
+        }
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
 }  // namespace int8t

@@ -90,7 +90,7 @@ struct QuantBatchItem {
     int nparts;
     int8_t* q;
     float* scale;
-    int kind;                    // 0 activations, 1 weights, 2 planar
+    int kind;                    // 0 activations, 1 weights, 2 planar, 3 activations of at most 4 channels with their space-to-depth codes
     int gx, gy, gz;              // its virtual grid inside the launch
     int stoch;                   // Eq.3 instead of Eq.1
     uint32_t seed_lo, seed_hi;   // seed_key_x(seed), seed_key_a(seed): the draw's two keys
@@ -104,7 +104,8 @@ int absmax_blocks(size_t n);
 int absmax_colsum_blocks(int cols);
 void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz);
 hipError_t launch_absmax_batch(const AbsmaxBatch& b, int total_blocks, hipStream_t st);
-hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStream_t st);
+// s2d: where an item of kind 3 puts the space-to-depth codes (s2d.hip)
+hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStream_t st, int8_t* s2d = nullptr);
 int quant_blocks_act(int N, int Cp, int HW);
 int quant_blocks_planar(size_t n);
 int quant_blocks_wgt(int K, int Cg, int R, int S);
@@ -157,6 +158,7 @@ struct IgemmArgs {
     int dgrad;                   // 0: ih = oh*stride + r - pad;  1: ih = (oh + pad - r)/stride
     int C;                       // forward: channels in use (<= Ca); lets the launch recognise a layer for s2d.hip
     int8_t* s2d;                 // nullable scratch of igemm_s2d_bytes() bytes for the rewritten codes
+    int s2d_ready;               // those of the input are there already
     int cell;                    // filled by launch_igemm(): 0, or 1 + the only residue class that has taps (cell form, conv_igemm.hip)
     int cls_h, cls_w;            // filled by launch_igemm(): strides of the residue classes a strided backward-data pass splits its pixels into (1 = not split)
     int32_t* partial;            // nullable scratch [ksplit][N][rows][OH*OW] of a split reduction

@@ -785,18 +785,9 @@ __global__ __launch_bounds__(256) void quantize_wgt_kernel(
 // all the blocks that fit (13 channels at 43 x 43, batch 256, a and g_z: 14.5 us; with four blocks 15.7).
 enum { ACTS_NONE, ACTS_EVEN, ACTS_RAGGED };
 template <bool ANYSTOCH, int ACTS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH && ACTS == ACTS_EVEN ? 4 : 8))) void quantize_batch_kernel(const QuantBatch b) {
+__device__ __forceinline__ void quantize_batch_item(const QuantBatchItem& t, const int local, float* const lds4, int8_t* const smem) {
     constexpr bool RAGGED = ACTS == ACTS_RAGGED;
-    raise_wave_priority();
-    // one LDS area for whichever pass this block runs, sized by the host for the tensors of this launch
-    // (a 3x3 weight tensor needs 2.3 KB of tile, not the 16 KB of the largest case: the kernel then fits
-    // beside other kernels' blocks on a compute unit)
-    __shared__ float lds4[4];
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     uint32_t (*const atile)[QA_CH / 4 + 1] = reinterpret_cast<uint32_t (*)[QA_CH / 4 + 1]>(smem);
-    const int i = batch_item(b.block0, (int)blockIdx.x);
-    const QuantBatchItem& t = b.it[i];
-    const int local = (int)blockIdx.x - b.block0[i];
     const bool side = ACTS != ACTS_NONE && t.kind == 0 && quant_act_side_by_side(t.d0, t.d2 * t.d3, t.gx, t.gy);
     const int gxy = t.gx * t.gy, at = side ? local >> 3 : local;
     const int z = at / gxy, rem = at - z * gxy;
@@ -831,6 +822,78 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH
     }
 }
 
+template <bool ANYSTOCH, int ACTS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, ANYSTOCH && ACTS == ACTS_EVEN ? 4 : 8))) void quantize_batch_kernel(const QuantBatch b) {
+    raise_wave_priority();
+    // one LDS area for whichever pass this block runs, sized by the host for the tensors of this launch
+    // (a 3x3 weight tensor needs 2.3 KB of tile, not the 16 KB of the largest case: the kernel then fits
+    // beside other kernels' blocks on a compute unit)
+    __shared__ float lds4[4];
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    const int i = batch_item(b.block0, (int)blockIdx.x);
+    quantize_batch_item<ANYSTOCH, ACTS>(b.it[i], (int)blockIdx.x - b.block0[i], lds4, smem);
+}
+
+// Activations of at most 4 channels whose layer runs on space-to-depth codes (the image of a stem under stride 2 x 2): a thread takes the
+// 2 x 2 pixels of one rewritten pixel, so that the codes of all four and the rewritten granule come out of one read of the image.
+// Bound: HBM, 16 bytes of codes per pixel written (the layout's, of which C are in use).  Against two passes -- a thread per pixel with up
+// to 16 guarded loads, then a copy that read 16 bytes of codes per pixel for 4 -- on 3 channels at 224 x 224, batch 64: 70 + 14 us beside
+// the clip search -> 31 + 4 (the filters' copy); the step of a 7x7 stem 331 -> 303 (376 instead of 397 on one stream), 3x3 on 32 channels at 299 x 299,
+// batch 16: 131 -> 108.
+__device__ __forceinline__ void quantize_s2d_pixels(const QuantBatchItem& t, int8_t* __restrict__ xs, const int block, float* lds4) {
+    const int N = t.d0, C = t.d1, H = t.d2, W = t.d3, H2 = (H + 1) >> 1, W2 = (W + 1) >> 1;
+    absmax_partials_begin(t.absmax_part, t.nparts, lds4);
+    const size_t i = (size_t)block * 256 + threadIdx.x;
+    const bool here = i < (size_t)N * H2 * W2;
+    const size_t nh = (here ? i : 0) / W2;
+    const int w2 = (int)((here ? i : 0) - nh * W2);
+    const size_t n = nh / H2;
+    const int h2 = (int)(nh - n * H2);
+    const bool pairs = (W & 1) == 0;                                  // (uniform) pixels 2 w2 and 2 w2 + 1 of a row start on 8 bytes (api.hip: x on 16)
+    const bool right = 2 * w2 + 1 < W, below = 2 * h2 + 1 < H;        // the block's second column / row exists
+    const float* __restrict__ const x0 = t.x + (n * C * H + 2 * h2) * (size_t)W + 2 * w2;
+    float v[4][4];                                                    // [pixel][channel]
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float* __restrict__ const p = x0 + (c < C ? (size_t)c * H * W : (size_t)0), *const q = p + (below ? W : 0);      // (unconditional loads)
+        if (pairs) {
+            const float2 a = *reinterpret_cast<const float2*>(p), b = *reinterpret_cast<const float2*>(q);
+            v[0][c] = a.x; v[1][c] = a.y; v[2][c] = b.x; v[3][c] = b.y;
+        } else {
+            v[0][c] = p[0]; v[1][c] = p[right ? 1 : 0]; v[2][c] = q[0]; v[3][c] = q[right ? 1 : 0];
+        }
+    }
+    const float m = absmax_partials_end(lds4), inv = inv_scale_of(m);
+    if (block == 0 && threadIdx.x == 0) *t.scale = scale_of(m);
+    if (!here) return;
+    uint32_t px[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        int code[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) code[c] = c < C ? quantize_one<false>(v[k][c], inv, 0u, 0u, 0u) : 0;
+        px[k] = pack4(code[0], code[1], code[2], code[3]);
+    }
+    uint4* __restrict__ const row0 = reinterpret_cast<uint4*>(t.q) + (n * H + 2 * h2) * (size_t)W + 2 * w2, *const row1 = row0 + W;
+    row0[0] = make_uint4(px[0], 0u, 0u, 0u);
+    if (right) row0[1] = make_uint4(px[1], 0u, 0u, 0u);
+    if (below) row1[0] = make_uint4(px[2], 0u, 0u, 0u);
+    if (right && below) row1[1] = make_uint4(px[3], 0u, 0u, 0u);
+    if (!right) px[1] = px[3] = 0u;
+    if (!below) px[2] = px[3] = 0u;
+    reinterpret_cast<uint4*>(xs)[i] = s2d_pack(px, C);
+}
+template <bool ANYSTOCH>
+__global__ __launch_bounds__(256) void quantize_batch_s2d_kernel(const QuantBatch b, int8_t* const xs) {
+    raise_wave_priority();
+    __shared__ float lds4[4];
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    const int i = batch_item(b.block0, (int)blockIdx.x), local = (int)blockIdx.x - b.block0[i];
+    const QuantBatchItem& t = b.it[i];
+    if (t.kind == 3) quantize_s2d_pixels(t, xs, local, lds4);
+    else quantize_batch_item<ANYSTOCH, ACTS_RAGGED>(t, local, lds4, smem);
+}
+
 // grid of one tensor's quantize pass, by layout (0 activations, 1 weights, else planar)
 void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz) {
     if (kind == 0) {
@@ -844,7 +907,7 @@ void quant_grid(int kind, const int d[4], int* gx, int* gy, int* gz) {
     }
 }
 
-hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStream_t st) {
+hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStream_t st, int8_t* s2d) {
     size_t lds = 16;
     for (int i = 0; i < b.count; ++i) {
         const QuantBatchItem& t = b.it[i];
@@ -864,6 +927,11 @@ hipError_t launch_quantize_batch(const QuantBatch& b, int total_blocks, hipStrea
     for (int i = 0; i < b.count; ++i) {
         any_stoch = any_stoch || b.it[i].stoch;
         if (b.it[i].kind == 0) acts = std::max(acts, ((b.it[i].d2 * b.it[i].d3) & 3) != 0 ? (int)ACTS_RAGGED : (int)ACTS_EVEN);
+    }
+    if (s2d) {
+        if (any_stoch) launch_timed(kt, quantize_batch_s2d_kernel<true>, dim3(total_blocks), dim3(256), lds, st, b, s2d);
+        else launch_timed(kt, quantize_batch_s2d_kernel<false>, dim3(total_blocks), dim3(256), lds, st, b, s2d);
+        return hipGetLastError();
     }
 #define LAUNCH(ST, ACTSv) launch_timed(kt, (quantize_batch_kernel<ST, ACTSv>), dim3(total_blocks), dim3(256), lds, st, b)
 #define LAUNCH_ACTS(ST)                                             \

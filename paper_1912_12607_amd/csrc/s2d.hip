@@ -4,29 +4,12 @@
 // on padding.  The rewritten layer has 4 C channels in the granule and a quarter of the taps; the
 // dense kernels then run on it unchanged.  Forward and backward-weight need the same form of the input codes: a step makes it once
 // where the forward pass's scratch is known to hold it (int8t_conv_bwd_weight_fwd): 7x7 on 3 channels, 224 x 224, batch 64, the
-// whole step 345 -> 331 us; the copy reads 51 MB for 10 MB of codes, 10 us alone and 14 beside other kernels.
+// whole step 345 -> 331 us; the copy reads 51 MB for 10 MB of codes, 10 us alone and 14 beside other kernels.  A step that forms the
+// codes as well writes both forms at once (quantize_s2d_pixels()): only the filters are left to rewrite then.
 #include "device_common.h"
 #include "kernels.h"
 
 namespace int8t {
-
-// The first C bytes of four 32-bit words, packed back to back into 16 bytes (the rest zero).
-__device__ __forceinline__ uint4 s2d_pack(const uint32_t px[4], int C) {
-    const uint32_t keep = C >= 4 ? 0xffffffffu : ((1u << (8 * C)) - 1u);
-    unsigned long long lo = 0, hi = 0;        // a 128-bit shift register
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const unsigned long long v = px[b] & keep;
-        const int sh = 8 * C * b;             // 0 .. 96
-        if (sh < 64) {
-            lo |= v << sh;
-            if (sh > 32) hi |= v >> (64 - sh);
-        } else {
-            hi |= v << (sh - 64);
-        }
-    }
-    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
-}
 
 // Input codes: byte (2 dy + dx) * C + c of pixel (h', w') is channel c of pixel (2 h' + dy, 2 w' + dx),
 // zero where that pixel lies beyond an odd image.
@@ -75,7 +58,7 @@ __global__ __launch_bounds__(256) void s2d_repack_kernel(const int8_t* __restric
 
 hipError_t launch_s2d_repack(const int8_t* x, int8_t* xs, int N, int H, int W, int C, const int8_t* w, int8_t* ws, int K, int R, int S,
                              const S2dGeo& g, hipStream_t st) {
-    const size_t npix = (size_t)N * ((H + 1) / 2) * ((W + 1) / 2);
+    const size_t npix = x ? (size_t)N * ((H + 1) / 2) * ((W + 1) / 2) : 0;
     const unsigned filter_blocks = w ? (unsigned)((K * g.R2 * g.S2 + 255) / 256) : 0u;
     KernelTimer kt(KID_S2D_REPACK, st);
     launch_timed(kt, s2d_repack_kernel, dim3(filter_blocks + (unsigned)((npix + 255) / 256)), dim3(256), 0, st, x, xs, N, H, W, C, w, ws, K, R, S, g,

@@ -321,7 +321,8 @@ class LayerStep:
             self._k_w(sp)
             self._k_fwd_fused(sp)               # writes the codes of a
             self._ev_side.record(side)
-        elif one_pass:
+        elif one_pass or (not early and self.desc.groups == 1):
+            # (a stem's codes then come in both forms from one pass over the image)
             self._k_step(B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_FWD, seed, sp)
             self._ev_side.record(side)
         else:

@@ -486,6 +486,43 @@ def test_backward_weight_on_the_forward_passes_codes(shape):
     check(lambda: B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, shared, shared), 1)
 
 
+# A stem's codes in both forms from one pass over the image: every count of channels, odd and even rows and columns, a last block of one
+# pixel, with g_z's codes in the same launch and without, against the codes and the forward pass in calls of their own, bit for bit; and
+# with the scratch of the forward pass over the partial maxima, which the codes' pass still reads.
+@pytest.mark.parametrize("shape", [(3, 1, 1, 1, 8, 1, 1, 0), (2, 2, 16, 32, 24, 3, 3, 1), (1, 3, 33, 30, 8, 7, 7, 3), (257, 4, 2, 1, 130, 2, 3, 1),
+                                   (5, 3, 30, 33, 16, 5, 5, 2), (4, 1, 15, 17, 40, 1, 1, 0)])
+def test_stem_codes_in_both_forms(shape):
+    N, C, H, W, K, R, S, pad = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(2, 2), pad=(pad, pad), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False, input_grad=False)
+    g = torch.Generator(device=DEV).manual_seed(15)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    outs = [st.xq, st.sx, st.wq, st.sw, st.y, st.y_acc, st.dyq, st.sdy]
+    scratch = N * ((H + 1) // 2) * ((W + 1) // 2) * 16
+
+    def result(*calls, buf=st._layer_buffers):
+        for t in outs + [st.ws_fwd]:
+            t.fill_(7)
+        st.clip.fill_(1.5)
+        for parts in calls:
+            B.int8t_layer_step(st.desc, buf, parts, 3)
+        torch.cuda.synchronize()
+        return [t.clone() for t in outs + [st.ws_fwd[:scratch]]]
+
+    codes = B.STEP_ABSMAX | B.STEP_QUANT_XW
+    want = result(codes, B.STEP_QUANT_G, B.STEP_FWD)
+    for a, b in zip(result(codes | B.STEP_QUANT_G | B.STEP_FWD), want):
+        assert torch.equal(a, b)
+    for a, b in zip(result(codes | B.STEP_FWD, B.STEP_QUANT_G), want):
+        assert torch.equal(a, b)
+    buf = B.LayerBuffers.from_buffer_copy(st._layer_buffers)
+    shared = torch.empty(max(buf.ws_fwd_bytes, buf.ws_quant_bytes), dtype=torch.uint8, device=DEV)
+    buf.ws_quant = buf.ws_fwd = shared.data_ptr()
+    for a, b in list(zip(result(codes | B.STEP_QUANT_G | B.STEP_FWD, buf=buf), want))[:-1]:
+        assert torch.equal(a, b)
+
+
 # The forward pass without codes: one and two row tiles of filters, planes of whole 16-byte groups and others, ragged pixel tiles,
 # more tiles than resident blocks, channels that end inside 64, elements that are no number; layers just outside the rule, and
 # results over the input, which the calls one after the other allow.  Against the step's forward pass, bit for bit.
