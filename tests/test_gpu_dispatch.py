@@ -486,6 +486,25 @@ def test_backward_weight_on_the_forward_passes_codes(shape):
     check(lambda: B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, shared, shared), 1)
 
 
+# Bands whose window takes six staged granules a thread and seven, nine, twelve, a row in one part and in more, one and two tiles of rows
+# and of pixels, rows above and below the image, a last band that ends beyond it.
+@pytest.mark.parametrize("op,shape", [
+    (B.OP_CONV_FWD, (2, 16, 9, 130, 33, 6, 1, 1, (2, 0))), (B.OP_CONV_FWD, (2, 16, 9, 130, 24, 7, 1, 1, (3, 0))), (B.OP_CONV_FWD, (3, 40, 5, 120, 40, 3, 3, 1, (1, 1))),
+    (B.OP_CONV_FWD, (2, 48, 6, 250, 20, 3, 3, 1, (1, 1))), (B.OP_CONV_FWD, (2, 48, 7, 128, 64, 6, 1, 1, (5, 0))), (B.OP_CONV_FWD, (3, 5, 11, 21, 7, 5, 3, 1, (4, 2))),
+    (B.OP_CONV_BWD_DATA, (2, 33, 9, 130, 16, 6, 1, 1, (2, 0))), (B.OP_CONV_BWD_DATA, (2, 24, 9, 130, 16, 7, 1, 1, (3, 0))),
+    (B.OP_CONV_BWD_DATA, (3, 64, 5, 120, 40, 3, 3, 1, (1, 1))), (B.OP_CONV_BWD_DATA, (2, 20, 6, 250, 48, 3, 3, 1, (1, 1)))])
+@pytest.mark.parametrize("with_acc", [False, True])
+def test_bands_of_few_and_many_staged_granules(op, shape, with_acc):
+    desc, od, (xq, wq, dyq) = random_layer(shape, shape[3])
+    B.int8t_conv_select_variant(op, desc, B.VARIANT_BAND)
+    try:
+        B.int8t_profile_start("band_kernel")
+        conv_pass_elementwise(op, desc, od, xq, wq, dyq, with_acc)
+        assert B.int8t_profile_stop()["band_kernel"][0] == 1
+    finally:
+        B.int8t_conv_select_variant(op, desc, B.VARIANT_AUTO)
+
+
 # A stem's codes in both forms from one pass over the image: every count of channels, odd and even rows and columns, a last block of one
 # pixel, with g_z's codes in the same launch and without, against the codes and the forward pass in calls of their own, bit for bit; and
 # with the scratch of the forward pass over the partial maxima, which the codes' pass still reads.
