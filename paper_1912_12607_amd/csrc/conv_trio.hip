@@ -126,7 +126,97 @@ TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradA
     return TrioTile{5 * work >= (fwd ? 6 : 10) * 512 * longest ? 128 : 64, false};
 }
 
-hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile, hipStream_t st) {
+// When `count` blocks of one length after another have been dealt to the slots that are free first; returns the end of the last.
+namespace {
+struct SlotClock {
+    double at[64];       // the slots by the time they are free from
+    int n[64], size = 1;
+    explicit SlotClock(int slots) { at[0] = 0.0; n[0] = slots; }
+    double deal(long long count, double length) {
+        double end = 0.0;
+        while (count > 0) {
+            int i = 0;
+            for (int k = 1; k < size; ++k)
+                if (at[k] < at[i]) i = k;
+            if (size == 64 || count >= n[i]) {      // (a full table: the rest of the slots go along)
+                count -= n[i];
+                at[i] += length;
+            } else {
+                at[size] = at[i] + length;
+                n[size++] = (int)count;
+                n[i] -= (int)count;
+                end = std::max(end, at[size - 1]);
+                break;
+            }
+            end = std::max(end, at[i]);
+        }
+        return end;
+    }
+};
+}  // namespace
+
+// Backward-weight's shares in a shared launch: what it takes by itself, or fewer where the tiles of the other passes fill the chip anyway.
+// By itself the pass has to fill 512 block slots; in here every share costs a block's setup and a partial tile to write and to read, and the last
+// turn of the slots may hold a few blocks only.  One share leaves the reduction's launch out.  The estimate deals the blocks to the slots in
+// the order of the launch; its constants are fitted to the two and the three passes of 50 layers of 1 to 60 GOP with 1, 0.7, 0.5, 0.35 and 0.25 of the
+// shares (units of their own: only the order of the estimates counts).  Fewer where the estimate falls by a tenth, not below a half but for one: over
+// these layers 0.97 of the time with all the shares on average and 1.015 at most (from a fiftieth on 0.95, but 1.09 at most).  us with all and as chosen:
+//   3x3, 512 channels, 7 x 7, batch 64, two             40.5   28.6      3x3, 215 -> 197, 15 x 15, batch 6, three                   19.1   13.3
+//   7x1, 130 -> 959, 34 x 34, batch 7, two              53.5   44.8      3x3 under stride 2, 677 -> 365, 19 x 19, batch 10, three   54.8   39.6
+static int trio_shares(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, TrioTile tile) {
+    if (!w.lines || w.splits <= 1) return w.splits;
+    auto estimate = [&](int shares) {
+        SlotClock clock(512);
+        const double length = 2.38 + (double)((w.chunks + shares - 1) / shares) * w.t_chunk * 2.37;
+        double end = clock.deal((long long)w.ktiles * w.ctiles * w.tapgroups * shares, length);
+        for (const IgemmArgs* a : {fwd, &bwd}) {
+            if (!a) continue;
+            const bool half = tile.rows64 && a->rows <= 64;       // 64 x 128 tiles
+            const int cols = half ? 128 : tile.bn;
+            const long long tiles = (((long long)a->N * a->OH * a->OW + cols - 1) / cols) * ((a->rows + (half ? 63 : 127)) / (half ? 64 : 128));
+            const int taps = a->dgrad ? a->stride_h * a->stride_w : 1;      // (a pixel of a strided backward-data pass meets one class of taps)
+            const int stages = (a->R * a->S * (a->Ca >> 4) + 8 * taps - 1) / (8 * taps);
+            end = std::max(end, clock.deal(tiles, 1.46 + stages * 1.51 * (0.35 + 0.65 * (half ? 0.5 : tile.bn / 128.0))));
+        }
+        return end + shares * (double)w.t_partial * 1.11 + (shares > 1 ? 10.39 : 0.0);
+    };
+    int best = w.splits;
+    double least = estimate(w.splits);
+    const double all = least;
+    for (const int part : {70, 50, 35, 25}) {
+        const int shares = std::max(1, (w.splits * part + 50) / 100);
+        if (part < 50 && shares > 1) continue;
+        const double t = estimate(shares);
+        if (t * 1.1 < all && t < least) {
+            least = t;
+            best = shares;
+        }
+    }
+    return best;
+}
+
+// The estimate takes a few microseconds of the host, a step of a small layer twenty in all: the last layers' shares are kept, per thread.
+static void set_trio_shares(WgradArgs* w, const IgemmArgs* fwd, const IgemmArgs& bwd, TrioTile tile) {
+    struct Entry { int key[16], shares; };
+    static thread_local Entry table[64];        // (a key of zeros is no layer)
+    const int key[16] = {w->N, w->C, w->H, w->W, w->K, w->R, w->S, w->P, w->Q, w->stride_h, w->stride_w, w->pad_h, w->pad_w, w->splits,
+                         fwd ? 1 : 0, 2 * tile.bn + (tile.rows64 ? 1 : 0)};
+    unsigned h = 0;
+    for (const int k : key) h = (h ^ (unsigned)k) * 0x9E3779B1u;
+    Entry& e = table[h >> 26];
+    if (!std::equal(key, key + 16, e.key)) {
+        e.shares = trio_shares(fwd, bwd, *w, tile);
+        std::copy(key, key + 16, e.key);
+    }
+    if (e.shares == w->splits) return;
+    w->splits = e.shares;
+    w->by_splits = fast_div((unsigned)e.shares);
+    w->direct = e.shares == 1;                  // (passes that share a launch overlap nothing)
+}
+
+hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w_all, TrioTile tile, hipStream_t st) {
+    WgradArgs w = w_all;
+    set_trio_shares(&w, fwd, bwd, tile);
     const int bn = tile.bn;
     IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
     TrioBlocks n;
@@ -200,7 +290,9 @@ bool conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradAr
     return w.TB == 3 || tiles <= 4500;
 }
 
-hipError_t launch_conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w, hipStream_t st) {
+hipError_t launch_conv_trio_strided(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w_all, hipStream_t st) {
+    WgradArgs w = w_all;
+    set_trio_shares(&w, fwd, bwd, TrioTile{64, false});
     IgemmArgs f = fwd ? *fwd : bwd, b = bwd;
     TrioBlocks n{};
     n.wgrad = wgrad_lines_grid(w);

@@ -214,6 +214,7 @@ void wgrad_plan(WgradArgs* a) {
     a->ktiles = p.ktiles; a->ctiles = p.ctiles; a->tapgroups = p.tapgroups;
     a->xt_slots = p.xt_slots; a->lds_bytes = p.lds_bytes; a->lines = p.lines; a->xgk = p.xgk; a->xgc = p.xgc; a->pk = p.pk;
     a->by_tiles = p.by_tiles; a->by_taps = p.by_taps; a->by_ctiles = p.by_ctiles; a->by_splits = p.by_splits; a->by_lines = p.by_lines;
+    a->t_chunk = p.t_chunk; a->t_partial = p.t_partial;
 }
 
 namespace {

@@ -55,6 +55,8 @@ void wgrad_plan_lines(WgradArgs* a) {
     const double mfma_per_chunk = (double)QL * ST * WT * WT;   // per wave, a little less at the image border
     const double t_chunk = stages_per_chunk * 0.45 + 0.014 * 2.0 * mfma_per_chunk;
     const double t_partial = (double)a->K * a->R * a->S * a->Cp * 8.0 / 4.0e6;
+    a->t_chunk = (float)t_chunk;
+    a->t_partial = (float)t_partial;
     int splits = 1;
     double best = 1e30;
     for (int sp = 1; sp <= a->chunks && sp <= 4096; ++sp) {

@@ -271,6 +271,7 @@ struct WgradArgs {
     int variant;                 // VAR_AUTO or a VAR_WGRAD_*: set before wgrad_plan()
     int lines;                   // filled by wgrad_plan(): 1 = wgrad_lines_kernel runs (TB = taps along the line)
     int xgk, xgc;                // ... and its patches of output tiles per XCD: xgk x xgc = 8, or 0 0: tiles dealt by share
+    float t_chunk, t_partial;    // ... and its estimates, us: a chunk of a share, a share's partial tiles
 };
 // Rewrites the geometry into the space-to-depth form (s2d.hip) when it applies.  Returns the bytes of
 // the rewritten input codes (0: does not apply, the geometry is left alone).  Call before wgrad_plan().

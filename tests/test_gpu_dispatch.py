@@ -486,6 +486,40 @@ def test_backward_weight_on_the_forward_passes_codes(shape):
     check(lambda: B.int8t_conv_bwd_weight_fwd(st.desc, st.xq, st.sx, st.dyq, st.sdy, st.dw, st.dw_acc, shared, shared), 1)
 
 
+# Backward-weight with fewer shares beside other passes than by itself, one (no reduction) and several, for two passes and for three, stride 1 and 2:
+# bit for bit the calls one by one, whatever the scratch held; the same layer again, another one in between.
+@pytest.mark.parametrize("shape,reductions", [
+    ((64, 512, 7, 7, 512, 3, 3, 1, 1), (0, 1)), ((6, 215, 15, 15, 197, 3, 3, 1, 1), (0, 0)), ((10, 677, 19, 19, 365, 3, 3, 2, 1), (0, 0)),
+    ((32, 48, 35, 35, 64, 5, 5, 1, 2), (1, 1)), ((128, 1024, 14, 14, 256, 1, 1, 1, 0), (1, 1)), ((2, 16, 16, 16, 32, 3, 3, 1, 1), (0, 0))])
+def test_fewer_shares_beside_other_passes(shape, reductions):
+    N, C, H, W, K, R, S, stride, pad = shape
+    L = inputs.Layer("layer", N, C, H, W, K, R, S, stride=(stride, stride), pad=(pad, pad), groups=1)
+    st = LayerStep(L, keep_acc=True, requantize_deviation=False)
+    small = LayerStep(inputs.Layer("layer", 2, 32, 9, 9, 40, 3, 3, stride=(1, 1), pad=(1, 1), groups=1), requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(16)
+    for s in (st, small):
+        for t in (s.x, s.w, s.dy):
+            t.normal_(generator=g)
+        s.clip.fill_(1.5)
+        B.int8t_layer_step(s.desc, s._layer_buffers, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_QUANT_G, 3)
+    outs = [st.y, st.y_acc, st.dx, st.dx_acc, st.dw, st.dw_acc]
+    for parts in (B.STEP_FWD, B.STEP_BWD_DATA, B.STEP_BWD_WEIGHT):
+        B.int8t_layer_step(st.desc, st._layer_buffers, parts)
+    want = [t.clone() for t in outs]
+    two = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    for parts, count in ((two, reductions[0]), (two | B.STEP_FWD, reductions[1]), (two, reductions[0])):
+        for t in outs[2:] + [st.ws]:
+            t.fill_(7)
+        B.int8t_profile_start(None)
+        B.int8t_layer_step(st.desc, st._layer_buffers, parts)
+        torch.cuda.synchronize()
+        launches = B.int8t_profile_stop()
+        assert launches.pop("conv_trio_kernel")[0] == 1 and launches.pop("wgrad_reduce_kernel", (0,))[0] == count and not launches
+        for a, b in zip(outs, want):
+            assert torch.equal(a, b)
+        B.int8t_layer_step(small.desc, small._layer_buffers, parts)
+
+
 # Bands whose window takes six staged granules a thread and seven, nine, twelve, a row in one part and in more, one and two tiles of rows
 # and of pixels, rows above and below the image, a last band that ends beyond it.
 @pytest.mark.parametrize("op,shape", [
