@@ -772,7 +772,7 @@ int8t_status int8t_conv_bwd_weight_fwd(const int8t_conv_desc* desc, const int8_t
     // (the result of a reduction may go where the codes lay, that of a tile may not)
     const int xd[4] = {desc->N, desc->C, desc->H, desc->W}, yd[4] = {desc->N, desc->K, g.P, g.Q};
     const size_t nw = (size_t)desc->K * desc->C * desc->R * desc->S * 4;
-    a.direct = a.lines && a.splits == 1;
+    a.direct = wgrad_single_share(a);
     for (const void* out : {(const void*)dw_dev, (const void*)acc_dev})
         if (out && (overlap(out, nw, xq_dev, int8t_code_bytes(xd, INT8T_ACT)) || overlap(out, nw, dyq_dev, int8t_code_bytes(yd, INT8T_ACT)) ||
                     overlap(out, nw, sx_dev, 4) || overlap(out, nw, sdy_dev, 4)))
@@ -1067,7 +1067,7 @@ static int8t_status layer_step(const int8t_conv_desc* desc, const int8t_layer_bu
         d.sa = b->sdy; d.sb = b->sw; d.out = b->dx; d.acc = b->dx_acc;
         w.x = b->xq; w.dy = b->dyq; w.sa = b->sx; w.sb = b->sdy; w.dw = b->dw; w.acc = b->dw_acc;
         w.partial = (int32_t*)b->ws_bwd_weight;
-        w.direct = w.lines && w.splits == 1;        // (disjoint_results)
+        w.direct = wgrad_single_share(w);        // (disjoint_results)
         if (desc->stride_h != 1 || desc->stride_w != 1) {
             if (conv_trio_strided(fwd ? &f : nullptr, d, w))
                 return launch_conv_trio_strided(fwd ? &f : nullptr, d, w, st) == hipSuccess ? INT8T_OK : INT8T_ERR_RUNTIME;

@@ -180,30 +180,32 @@ size_t wgrad_s2d(WgradArgs* a) {
 // ---------------------------------------------------------------------------------------------
 namespace {
 // The plan of the most recent geometry, per host thread: a layer is planned once, not per call.
+constexpr int kPlanKey = 17;
 struct PlanCache {
-    int key[16];
+    int key[kPlanKey];
     WgradArgs plan;
     bool valid;
 };
 thread_local PlanCache g_plan_cache = {};
 
-void plan_key(const WgradArgs* a, int key[16]) {
-    const int k[16] = {a->N, a->C, a->Cp, a->H, a->W, a->K, a->Kp, a->P, a->Q, a->R, a->S,
-                       a->stride_h, a->stride_w, a->pad_h, a->pad_w, a->variant};
-    for (int i = 0; i < 16; ++i) key[i] = k[i];
+// (s2d: a stem in its space-to-depth form may have the geometry of a plain layer, and takes another kernel)
+void plan_key(const WgradArgs* a, int key[kPlanKey]) {
+    const int k[kPlanKey] = {a->N, a->C, a->Cp, a->H, a->W, a->K, a->Kp, a->P, a->Q, a->R, a->S,
+                             a->stride_h, a->stride_w, a->pad_h, a->pad_w, a->variant, a->s2d};
+    for (int i = 0; i < kPlanKey; ++i) key[i] = k[i];
 }
 void wgrad_plan_uncached(WgradArgs* a);
 }  // namespace
 
 void wgrad_plan(WgradArgs* a) {
-    int key[16];
+    int key[kPlanKey];
     plan_key(a, key);
     PlanCache& c = g_plan_cache;
     bool hit = c.valid;
-    for (int i = 0; hit && i < 16; ++i) hit = c.key[i] == key[i];
+    for (int i = 0; hit && i < kPlanKey; ++i) hit = c.key[i] == key[i];
     if (!hit) {
         wgrad_plan_uncached(a);
-        for (int i = 0; i < 16; ++i) c.key[i] = key[i];
+        for (int i = 0; i < kPlanKey; ++i) c.key[i] = key[i];
         c.plan = *a;
         c.valid = true;
         return;

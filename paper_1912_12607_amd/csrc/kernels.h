@@ -295,6 +295,9 @@ bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filte
 __host__ __device__ inline size_t wgrad_partial_elems(const WgradArgs& a) { return (size_t)((a.K + 3) / 4 * 4) * a.R * a.S * a.Cp; }      // of one share
 inline size_t wgrad_partial_bytes(const WgradArgs& a) { return (a.splits * wgrad_partial_elems(a) * 4 + 255) & ~(size_t)255; }
 
+// Whether the pass runs as one share on image lines, in the layer's own geometry: its tiles may then be the result (WgradArgs::direct).
+inline bool wgrad_single_share(const WgradArgs& a) { return a.lines && !a.s2d && a.splits == 1; }
+
 // which kernel VAR_AUTO stands for: true = wgrad_lines_kernel
 bool wgrad_auto_lines(const WgradArgs& a);
 // Share z runs on XCD z mod 8 with all its output tiles (they read the same lines of both tensors, and every XCD fills

@@ -5,6 +5,7 @@ import ctypes as C
 import math
 import os
 import re
+import threading
 
 import pytest
 
@@ -51,6 +52,30 @@ def test_binding_names_match_header():
     hdr = set(re.findall(r"\b(int8t_[a-z_0-9]+)\s*\(", open(HDR).read()))
     for n in hdr:
         assert f"def {n}(" in text, n
+
+
+# A stem in its space-to-depth form (C <= 4 under stride 2 x 2) may have the geometry of a plain layer on 4 C channels: the scratch
+# of either, which follows from its plan, does not depend on what the thread planned before.
+@pytest.mark.parametrize("stem,plain", [((3, 32, 32, 12, 5, 5, 2, 2), (12, 16, 16, 12, 3, 3, 1, 1)), ((3, 32, 32, 12, 6, 6, 2, 2), (12, 16, 16, 12, 3, 3, 1, 1)),
+                                        ((4, 48, 47, 24, 9, 9, 4, 4), (16, 24, 24, 24, 5, 5, 2, 2)), ((2, 28, 28, 40, 13, 1, 6, 0), (8, 14, 14, 40, 7, 1, 3, 0))])
+def test_plans_of_stems_and_plain_layers_of_one_geometry(lib, stem, plain):
+    layers = []
+    for (c, h, w, k, r, s, ph, pw), st in ((stem, 2), (plain, 1)):
+        layers.append(Desc(2, c, h, w, k, r, s, st, st, ph, pw, 1))
+
+    def sizes(*order):
+        out = {}
+
+        def plan():
+            for i in order:
+                out[i] = lib.int8t_workspace_bytes(4, C.byref(layers[i]), C.c_size_t(0), 0)
+        t = threading.Thread(target=plan)        # (plans are kept per thread)
+        t.start()
+        t.join()
+        return out
+    alone = {**sizes(0), **sizes(1)}
+    assert min(alone.values()) > 0
+    assert sizes(0, 1) == alone and sizes(1, 0) == alone
 
 
 def test_code_bytes(lib):

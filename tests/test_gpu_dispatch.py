@@ -773,3 +773,29 @@ def test_reduction_positions_of_wide_tiles(shape):
                 conv_pass_elementwise(op, desc, od, xq, wq, dyq, True)
             finally:
                 B.int8t_conv_select_variant(op, desc, B.VARIANT_AUTO)
+
+
+# Backward-weight of a stem, which runs in its space-to-depth form, and of a plain layer with that form's geometry, in turn on one thread,
+# each with the scratch it asked for at the start: either pass has its own plan (one share, whose tile is the result, belongs to the plain
+# layer), and nothing is written beyond dw.  5x5, 6x6 and 9x9 filters become 3x3 and 5x5, 2x2 ones 1x1.
+@pytest.mark.parametrize("stem,plain", [((2, 3, 32, 32, 12, 5, 5, 2, (2, 2)), (2, 12, 16, 16, 12, 3, 3, 1, (1, 1))),
+                                        ((2, 3, 32, 32, 12, 6, 6, 2, (2, 2)), (2, 12, 16, 16, 12, 3, 3, 1, (1, 1))),
+                                        ((2, 4, 23, 24, 24, 9, 9, 2, (4, 4)), (2, 16, 12, 12, 24, 5, 5, 1, (2, 2))),
+                                        ((2, 3, 32, 32, 12, 2, 2, 2, (0, 0)), (2, 12, 16, 16, 12, 1, 1, 1, (0, 0)))])
+def test_stems_and_plain_layers_of_one_geometry(stem, plain):
+    layers = []
+    for shape in (stem, plain):
+        desc, od, (xq, wq, dyq) = random_layer(shape, shape[5])
+        want, ov = oracle.wrap32(oracle.conv_bwd_weight(od, xq, dyq))
+        assert ov == 0
+        ws = torch.empty(B.int8t_workspace_bytes(B.OP_CONV_BWD_WEIGHT, desc), dtype=torch.uint8, device=DEV)
+        layers.append((desc, dev(pack_act(xq)), dev(pack_act(dyq)), want, ws))
+    one, guard = torch.ones(1, device=DEV), 4096
+    for i in (0, 1, 0, 1, 1, 0):
+        desc, xq, dyq, want, ws = layers[i]
+        dw = torch.full((want.size + guard,), 7.0, device=DEV)
+        acc = torch.full((want.size + guard,), 7, dtype=torch.int32, device=DEV)
+        B.int8t_conv_bwd_weight(desc, xq, one, dyq, one, dw[:want.size], acc[:want.size], ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(acc[:want.size].cpu().numpy().reshape(want.shape), want) and bool((acc[want.size:] == 7).all())
+        assert np.array_equal(dw[:want.size].cpu().numpy().reshape(want.shape), want.astype(np.float32)) and bool((dw[want.size:] == 7.0).all())
