@@ -195,23 +195,13 @@ static int trio_shares(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradAr
     return best;
 }
 
-// The estimate takes a few microseconds of the host, a step of a small layer twenty in all: the last layers' shares are kept, per thread.
+// (the estimate takes 0.2 us of the host for layers of a few hundred tiles, 1.4 us for tens of thousands)
 static void set_trio_shares(WgradArgs* w, const IgemmArgs* fwd, const IgemmArgs& bwd, TrioTile tile) {
-    struct Entry { int key[16], shares; };
-    static thread_local Entry table[64];        // (a key of zeros is no layer)
-    const int key[16] = {w->N, w->C, w->H, w->W, w->K, w->R, w->S, w->P, w->Q, w->stride_h, w->stride_w, w->pad_h, w->pad_w, w->splits,
-                         fwd ? 1 : 0, 2 * tile.bn + (tile.rows64 ? 1 : 0)};
-    unsigned h = 0;
-    for (const int k : key) h = (h ^ (unsigned)k) * 0x9E3779B1u;
-    Entry& e = table[h >> 26];
-    if (!std::equal(key, key + 16, e.key)) {
-        e.shares = trio_shares(fwd, bwd, *w, tile);
-        std::copy(key, key + 16, e.key);
-    }
-    if (e.shares == w->splits) return;
-    w->splits = e.shares;
-    w->by_splits = fast_div((unsigned)e.shares);
-    w->direct = e.shares == 1;                  // (passes that share a launch overlap nothing)
+    const int shares = trio_shares(fwd, bwd, *w, tile);
+    if (shares == w->splits) return;
+    w->splits = shares;
+    w->by_splits = fast_div((unsigned)shares);
+    w->direct = wgrad_single_share(*w);         // (passes that share a launch overlap nothing)
 }
 
 hipError_t launch_conv_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w_all, TrioTile tile, hipStream_t st) {

@@ -363,7 +363,7 @@ static int wgrad_flat_quads(unsigned quads, int splits) {
 }
 
 hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
-    if (a.direct) return hipSuccess;       // (wgrad_lines_tile wrote the result)
+    if (a.direct && a.lines) return hipSuccess;       // (wgrad_lines_tile wrote the result)
     // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (64, 16 or
     // 4) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
     // loads of a small layer are latency, not bandwidth; the flat kernel if nothing does.  A block's

@@ -799,3 +799,33 @@ def test_stems_and_plain_layers_of_one_geometry(stem, plain):
         torch.cuda.synchronize()
         assert np.array_equal(acc[:want.size].cpu().numpy().reshape(want.shape), want) and bool((acc[want.size:] == 7).all())
         assert np.array_equal(dw[:want.size].cpu().numpy().reshape(want.shape), want.astype(np.float32)) and bool((dw[want.size:] == 7.0).all())
+
+
+# A plain 1x1 layer whose shared launch takes one share of the two or four that the pass takes by itself, and in between a stem whose rewritten
+# geometry is the same, planned for the other kernel with as many shares: nothing of either is taken over by the other, bit for bit the
+# calls one by one.
+@pytest.mark.parametrize("N,H,W", [(32, 2, 1), (64, 2, 2), (50, 2, 3)])
+def test_shares_of_a_layer_after_a_stem_of_its_geometry(N, H, W):
+    plain = LayerStep(inputs.Layer("layer", N, 12, H, W, 4, 1, 1, stride=(1, 1), pad=(0, 0)), keep_acc=True, requantize_deviation=False)
+    stem = LayerStep(inputs.Layer("layer", N, 3, 2 * H, 2 * W, 4, 2, 2, stride=(2, 2), pad=(0, 0)), requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(17)
+    for st in (plain, stem):
+        for t in (st.x, st.w, st.dy):
+            t.normal_(generator=g)
+        st.clip.fill_(1.5)
+        B.int8t_layer_step(st.desc, st._layer_buffers, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_QUANT_G, 3)
+    outs = [plain.y, plain.y_acc, plain.dx, plain.dx_acc, plain.dw, plain.dw_acc]
+    plain.fwd()
+    plain.bwd_data()
+    plain.bwd_weight()
+    stem.bwd_weight()
+    want, stem_dw = [t.clone() for t in outs], stem.dw.clone()
+    two = B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT
+    for parts in (two, two | B.STEP_FWD, two):
+        for t in outs[2:] + [stem.dw]:
+            t.fill_(7)
+        B.int8t_layer_step(plain.desc, plain._layer_buffers, parts)
+        B.int8t_layer_step(stem.desc, stem._layer_buffers, B.STEP_BWD_WEIGHT)
+        torch.cuda.synchronize()
+        for a, b in zip(outs + [stem.dw], want + [stem_dw]):
+            assert torch.equal(a, b)
