@@ -370,7 +370,6 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
     // threads are channels x (split lanes): 64 channels leave 4 split lanes, which is what few splits
     // can keep busy.
     const int RS = a.R * a.S;
-    const size_t elems = wgrad_partial_elems(a);
     int rsc = 1, qn = 4;
     {
         const int cand[3] = {9, 7, 3};
@@ -387,8 +386,8 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
         }
     }
     KernelTimer kt(KID_WGRAD_REDUCE, st);
-    if (rsc == 1 && elems < ((size_t)1 << 31)) {
-        const unsigned quads = (unsigned)(elems >> 2);
+    if (rsc == 1) {
+        const unsigned quads = (unsigned)(wgrad_partial_elems(a) >> 2);       // (fewer than 2^31 weights with their padding: api.hip)
         const int q = wgrad_flat_quads(quads, a.splits);
         const dim3 blocks((quads + q - 1) / q);
         if (q == 64) launch_timed(kt, (wgrad_reduce_flat_kernel<64>), blocks, dim3(256), 0, st, a);
@@ -406,8 +405,7 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
     } while (0)
     if (rsc == 9) REDUCE(9);
     else if (rsc == 7) REDUCE(7);
-    else if (rsc == 3) REDUCE(3);
-    else launch_timed(kt, (wgrad_reduce_kernel<4, 1>), blocks, dim3(256), 0, st, a);
+    else REDUCE(3);
 #undef REDUCE
     return hipGetLastError();
 }
