@@ -307,7 +307,7 @@ void wgrad_plan_uncached(WgradArgs* a) {
     }
     // a caller may ask for half or twice the shares of this choice (per-layer tuning by measurement)
     if (a->variant == VAR_WGRAD_FEWER) splits = splits > 1 ? splits / 2 : 1;
-    if (a->variant == VAR_WGRAD_MORE) splits = (2 * splits <= a->chunks && 2 * splits <= 4096) ? 2 * splits : splits;
+    if (a->variant == VAR_WGRAD_MORE && 2 * splits <= a->chunks && 2 * splits <= 4096 && (long long)a->chunks * (2 * splits) < (1LL << 31)) splits *= 2;
     a->splits = splits;
 }
 }  // namespace

@@ -67,7 +67,7 @@ void wgrad_plan_lines(WgradArgs* a) {
         if (blocks > 8LL * slots || (long long)a->chunks * (sp + 2) >= (1LL << 31)) break;
     }
     if (a->variant == VAR_WGRAD_FEWER) splits = splits > 1 ? splits / 2 : 1;
-    if (a->variant == VAR_WGRAD_MORE) splits = (2 * splits <= a->chunks && 2 * splits <= 4096) ? 2 * splits : splits;
+    if (a->variant == VAR_WGRAD_MORE && 2 * splits <= a->chunks && 2 * splits <= 4096 && (long long)a->chunks * (2 * splits) < (1LL << 31)) splits *= 2;
     a->splits = splits;
     // XCD patches (see the kernel): the split of 8 into xgk x xgc whose patches read the fewest slices
     a->xgk = a->xgc = 0;

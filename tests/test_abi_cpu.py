@@ -78,6 +78,25 @@ def test_plans_of_stems_and_plain_layers_of_one_geometry(lib, stem, plain):
     assert sizes(0, 1) == alone and sizes(1, 0) == alone
 
 
+# The kernels deal chunks to shares as chunk = chunks * share / shares in 32 bits: twice the shares are only taken where that stays below 2^31
+# (2.6 million chunks of 32 lines, 512 shares by the library's own choice; an ordinary layer).
+@pytest.mark.parametrize("shape,chunks", [((40, 16, 1 << 21, 1, 16, 1, 3, 1, 1, 0, 1, 1), 40 * (1 << 21) // 32), ((64, 16, 40, 40, 16, 1, 3, 1, 1, 0, 1, 1), 80)])
+def test_twice_the_shares_stay_within_32_bits(lib, shape, chunks):
+    d = Desc(*shape)
+    share = 4 * d.K * d.C * d.R * d.S
+
+    def shares():
+        return lib.int8t_workspace_bytes(4, C.byref(d), C.c_size_t(0), 0) // share
+    own = shares()
+    assert lib.int8t_conv_select_variant(4, C.byref(d), 7) == 0
+    try:
+        more = shares()
+    finally:
+        assert lib.int8t_conv_select_variant(4, C.byref(d), 0) == 0
+    assert more == (2 * own if chunks * 2 * own < 1 << 31 and 2 * own <= chunks and 2 * own <= 4096 else own)
+    assert chunks * more < 1 << 31
+
+
 def test_code_bytes(lib):
     assert lib.int8t_code_bytes(dims(2, 16, 16, 16), 0) == 2 * 16 * 16 * 16
     assert lib.int8t_code_bytes(dims(64, 24, 56, 56), 0) == 64 * 56 * 56 * 32      # C padded to 32
