@@ -129,8 +129,8 @@ TrioTile conv_trio_tile(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradA
 // When `count` blocks of one length after another have been dealt to the slots that are free first; returns the end of the last.
 namespace {
 struct SlotClock {
-    double at[64];       // the slots by the time they are free from
-    int n[64], size = 1;
+    double at[4];        // the slots by the time they are free from: one more time per deal, three passes at most
+    int n[4], size = 1;
     explicit SlotClock(int slots) { at[0] = 0.0; n[0] = slots; }
     double deal(long long count, double length) {
         double end = 0.0;
@@ -138,7 +138,7 @@ struct SlotClock {
             int i = 0;
             for (int k = 1; k < size; ++k)
                 if (at[k] < at[i]) i = k;
-            if (size == 64 || count >= n[i]) {      // (a full table: the rest of the slots go along)
+            if (count >= n[i]) {
                 count -= n[i];
                 at[i] += length;
             } else {
