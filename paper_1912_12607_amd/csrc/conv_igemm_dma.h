@@ -177,6 +177,8 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
     uint32_t bimg[NLB];                                      // byte offset of the column's image
     uint32_t bbase[NLB];                                     // ... of the pixel that tap (0,0) reads, modulo 2^32 (it may lie outside the image)
     constexpr int kFar = 0x40000000;
+    // byte offset of pixel (y, x) in an image, modulo 2^32: y may be kFar, whose offset nothing uses
+    auto pixel = [&](int y, int x) { return ((uint32_t)y * (uint32_t)a.IW + (uint32_t)x) * (uint32_t)a.Ca; };
 #pragma unroll
     for (int i = 0; i < NLB; ++i) {
         const int col = colbase + RPL * (wave + NW * i) + lrow;
@@ -189,7 +191,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         bh[i] = cv ? (CLS ? oh + dc.bh : DGRAD ? oh + a.pad_h : oh * a.stride_h - a.pad_h) : kFar;
         bw[i] = CLS ? (ow + dc.bw) : DGRAD ? (ow + a.pad_w) : (ow * a.stride_w - a.pad_w);
         bimg[i] = (uint32_t)n * (uint32_t)(a.IH * a.IW * a.Ca);
-        bbase[i] = bimg[i] + (uint32_t)(bh[i] * a.IW + bw[i]) * (uint32_t)a.Ca;
+        bbase[i] = bimg[i] + pixel(bh[i], bw[i]);
     }
     // a direction split into classes is a stride-1 pass; otherwise only the taps that divide reach a pixel
     const int dsh = CLS ? a.stride_h / a.cls_h : a.stride_h, dsw = CLS ? a.stride_w / a.cls_w : a.stride_w;
@@ -215,7 +217,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
                 const int ih = th / dsh, iw = tw / dsw;
                 ok = (th >= 0) & (tw >= 0) & (ih * dsh == th) & (iw * dsw == tw) & ((unsigned)ih < (unsigned)a.IH) & ((unsigned)iw < (unsigned)a.IW);
                 ok = ok & (bh[i] < kFar);
-                off = bimg[i] + (uint32_t)((ih * a.IW + iw) * a.Ca + cg * 16);
+                off = bimg[i] + pixel(ih, iw) + (uint32_t)(cg * 16);
             }
             nb[i] = (ok ? off : IGD_OOB) | past;
         }
@@ -248,7 +250,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
             r = tap / (ns > 0 ? ns : 1);
             s = tap - r * ns;
             q = gsw;
-            tapoff = (uint32_t)((DGRAD ? -1 : 1) * (r * a.IW + s) * a.Ca + cg * 16);
+            tapoff = (DGRAD ? 0u - pixel(r, s) : pixel(r, s)) + (uint32_t)(cg * 16);
             lane_offsets();
         }
     };
@@ -327,7 +329,7 @@ __device__ __forceinline__ void igemm_dma_tile(const IgemmArgs& a, const unsigne
         for (int i = 0; i < NLB; ++i) {
             bh[i] = boh[i] == kFar ? kFar : boh[i] + dc.bh;
             bw[i] = bow[i] + dc.bw;
-            bbase[i] = bimg[i] + (uint32_t)(bh[i] * a.IW + bw[i]) * (uint32_t)a.Ca;
+            bbase[i] = bimg[i] + pixel(bh[i], bw[i]);
         }
         __syncthreads();
     }
