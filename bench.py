@@ -102,6 +102,24 @@ def roofline_of(nbytes, ops, kind, seconds, depthwise=False):
     return r
 
 
+# launches that passes of a step share, and the kernels that run one dense convolution by itself
+SHARED_KERNELS = ("conv_trio_kernel", "conv_band_trio_kernel", "dw_trio_kernel")
+CONV_KERNELS = ("igemm_kernel", "igemm_dma_kernel", "band_kernel", "band_reg_kernel")
+
+
+def shared_work(kernel, L, n_cand, kernels, two_streams):
+    """[algorithmic bytes, operations, kind, launches per step] of a launch that passes share; `kernels`: those of the
+    one-stream step.  The backward passes are in it, and the forward one in a one-stream step unless it ran ahead."""
+    alg = pass_algorithmic(L, n_cand)
+    fwd = not two_streams and not set(CONV_KERNELS) & set(kernels)
+    shared = [alg[p] for p in ("bwd_data", "bwd_weight") + (("fwd",) if fwd else ())]
+    if kernel == "dw_trio_kernel" and not {"quantize_batch_kernel", "quantize_planar_kernel"} & set(kernels):
+        # ... and the codes of a, W and g_z, which are not read back
+        # (two launches on two streams: the forward pass with the codes of a and W, the backward ones with those of g_z)
+        return [alg["quantize_xw"][0] + alg["quantize_gz"][0] + 4 * sum(sizes(L)), 6 * L.macs, "mfma", 2 if two_streams else 1]
+    return [sum(a[0] for a in shared), sum(a[1] for a in shared), "mfma", 1]
+
+
 def cpu_baseline(L, x, w, dy, ratios, n_img):
     """The oracle's full layer step on the first n_img images of the batch."""
     import numpy as np
@@ -314,16 +332,8 @@ def main():
     tops = 6 * L.macs / t_step / 1e12
 
     two_streams = overlap is None and period == 1 and two_stream_default(L)
-    if dom in ("conv_trio_kernel", "dw_trio_kernel"):
-        # one launch for the passes of a step, the backward ones in the two-stream step (pass_table() runs each by itself)
-        alg = pass_algorithmic(L, n_cand)
-        shared = [alg[p] for p in ("bwd_data", "bwd_weight") + (() if two_streams else ("fwd",))]
-        kernel_alg[dom] = [sum(a[0] for a in shared), sum(a[1] for a in shared), "mfma", 1]
-        if dom == "dw_trio_kernel" and not {"quantize_batch_kernel", "quantize_planar_kernel"} & set(per_kernel):
-            # ... and the codes of a, W and g_z, which are not read back
-            kernel_alg[dom][0] = alg["quantize_xw"][0] + alg["quantize_gz"][0] + 4 * sum(sizes(L))
-            # (two launches on two streams: the forward pass with the codes of a and W, the backward ones with those of g_z)
-            kernel_alg[dom][1], kernel_alg[dom][3] = 6 * L.macs, 2 if two_streams else 1
+    if dom in SHARED_KERNELS:
+        kernel_alg[dom] = shared_work(dom, L, n_cand, per_kernel, two_streams)
     nbytes, ops, kind, launches = kernel_alg.get(dom, [0, 0, None, per_kernel[dom][0]])
     launches = launches or per_kernel[dom][0]
     # per launch, as the duration is: the kernel's algorithmic work of the step / its launches per step
