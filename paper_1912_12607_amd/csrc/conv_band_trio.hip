@@ -84,14 +84,20 @@ kern_t band_trio_kernel(int nks, int mt, int st, int* slot) {
 //   3x3, 64 channels, 56 x 56, batch 64       38.3   59.1     34.4   47.4     1x1, 64 channels, 56 x 56, batch 64      32.4   48.2   22.1   42.2
 //   1x1, 24 -> 144, 56 x 56, batch 64         28.7   61.9     24.7   58.1     3x3, 32 channels, 56 x 56, batch 256     75.6  112.4   64.6   95.2
 //   3x3, 40 -> 60, 31 x 31, batch 200         38.8   62.8     33.6   57.9     1x3, 8 -> 16, 109 x 109, batch 26        29.7   43.8   23.9   33.3
-// Beyond 300 MB of codes and input gradient, which the last-level cache does not hold, HBM bounds both kinds of blocks and
-// nothing is gained (1x1, 64 -> 256, 56 x 56, batch 256, 463 MB: 142.7 apart, 146.1 here).
+// With more codes and input gradient than the last-level cache of 256 MB holds beside other data, HBM bounds both kinds of blocks, and side by
+// side they share it worse.  Time here over the time apart, 8 to 14 layers with batches that give the stated MB (geometric mean, and the
+// worst layer; two sets of buffers in turn):
+//   MB             60          120         180         210         240         270         290         340         500
+//   two passes   0.94 1.01   0.95 1.09   0.94 1.01   0.93 1.02   0.96 1.11   1.01 1.14   1.04 1.16   1.05 1.17   1.06 1.16
+//   three        0.87 1.00   0.91 0.99   0.96 1.01   0.98 1.02   0.99 1.04   1.00 1.09   1.02 1.11   1.03 1.07   1.03 1.09
+// (1x1, 64 channels, 56 x 56, two passes, us apart and here: 180 MB 0.85 of the time, 290 MB 83.3, 96.7; 1x1, 64 -> 256 at 56 x 56, 463 MB:
+// 142.7, 146.1.)
 int conv_band_trio(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradArgs& w) {
     BandPlan d, f;
     int slot;
     const int st = wgrad_form(w);
     const size_t pixels = (size_t)bwd.N * bwd.OH * bwd.OW;
-    if (4 * pixels * bwd.rows + pixels * (size_t)w.Cp + (size_t)w.N * w.P * w.Q * w.Kp > 300000000u) return 0;
+    if (4 * pixels * bwd.rows + pixels * (size_t)w.Cp + (size_t)w.N * w.P * w.Q * w.Kp > 220000000u) return 0;
     if (st < 0 || !band_auto(bwd, &d) || !band_trio_kernel(d.nks, d.mt, st, &slot)) return 0;
     return fwd && band_auto(*fwd, &f) && same_body(f, d) ? 3 : 2;
 }

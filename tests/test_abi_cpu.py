@@ -97,6 +97,15 @@ def test_twice_the_shares_stay_within_32_bits(lib, shape, chunks):
     assert chunks * more < 1 << 31
 
 
+# Bands and backward-weight share a launch up to 220 MB of codes and input gradient, which the last-level cache holds, and run apart above.
+@pytest.mark.parametrize("ch,K,R,batch,form", [(64, 64, 3, 180, 11), (64, 64, 3, 190, 0), (64, 64, 1, 180, 11), (64, 64, 1, 241, 0), (64, 256, 1, 121, 11), (64, 256, 1, 160, 0)])
+@pytest.mark.parametrize("parts", [192, 224])
+def test_large_band_layers_run_apart(lib, ch, K, R, batch, form, parts):
+    d = Desc(batch, ch, 56, 56, K, R, R, 1, 1, R // 2, R // 2, 1)
+    assert (batch * 3136 * (5 * ch + K) <= 220e6) == (form == 11)
+    assert lib.int8t_layer_step_form(C.byref(d), parts) == form
+
+
 def test_code_bytes(lib):
     assert lib.int8t_code_bytes(dims(2, 16, 16, 16), 0) == 2 * 16 * 16 * 16
     assert lib.int8t_code_bytes(dims(64, 24, 56, 56), 0) == 64 * 56 * 56 * 32      # C padded to 32
