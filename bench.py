@@ -45,16 +45,19 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 # STORED figures, not measured by this run: HBM bytes per launch from rocprofv3 counter runs
 # (FETCH_SIZE + WRITE_SIZE, each scaled by what the same counter reads for a copy kernel of known
-# size), keyed by (config, layer, kernel) -> (bytes, the profiles/ file that holds the run).
+# size), keyed by (config, layer, kernel) -- and, for a launch that passes share, their number -- ->
+# (bytes, the profiles/ file that holds the run).
 TRAFFIC = {
-    (4, 0, "igemm_dma_kernel"): (int((50.2 + 81.0) * 1e6), "profiles/step_config4_inception_1x7_kernels_and_counters.md"),
-    (4, 0, "wgrad_lines_kernel"): (int((101.6 + 49.5) * 1e6), "profiles/step_config4_inception_1x7_kernels_and_counters.md"),
-    (2, 1, "igemm_dma_kernel"): (int((12.8 + 33.6) * 1e6), "profiles/step_config2_resnet50_3x3_kernels_and_counters.md"),
-    (2, 1, "dsgc_sweep_kernel"): (int((25.9 + 0.6) * 1e6), "profiles/step_config2_resnet50_3x3_kernels_and_counters.md"),
-    (2, 0, "igemm_dma_kernel"): (int((20.9 + 72.8) * 1e6), "profiles/step_config2_resnet50_1x1_reduce_kernels_and_counters.md"),
-    (2, 0, "dsgc_sweep_kernel"): (int((25.9 + 0.6) * 1e6), "profiles/step_config2_resnet50_1x1_reduce_kernels_and_counters.md"),
-    (1, 0, "dsgc_sweep_kernel"): (int((51.6 + 0.6) * 1e6), "profiles/step_config1_resnet18_3x3_kernels_and_counters.md"),
-    (1, 0, "band_reg_kernel"): (int((13.3 + 51.4) * 1e6), "profiles/step_config1_resnet18_3x3_kernels_and_counters.md"),
+    (4, 0, "igemm_dma_kernel"): (int((50.3 + 80.7) * 1e6), "profiles/step_config4_inception_1x7_kernels_and_counters.md"),
+    (4, 0, "wgrad_lines_kernel"): (int((101.9 + 49.6) * 1e6), "profiles/step_config4_inception_1x7_kernels_and_counters.md"),
+    (2, 1, "conv_trio_kernel", 3): (int((82.3 + 63.4) * 1e6), "profiles/step_config2_resnet50_3x3_kernels_and_counters.md"),
+    (2, 1, "dsgc_sweep_kernel"): (int((25.9 + 0.2) * 1e6), "profiles/step_config2_resnet50_3x3_kernels_and_counters.md"),
+    (2, 0, "conv_trio_kernel", 2): (int((89.9 + 125.2) * 1e6), "profiles/step_config2_resnet50_1x1_reduce_kernels_and_counters.md"),
+    (2, 0, "conv_trio_kernel", 3): (int((117.4 + 152.6) * 1e6), "profiles/step_config2_resnet50_1x1_reduce_kernels_and_counters.md"),
+    (2, 0, "dsgc_sweep_kernel"): (int((25.9 + 0.2) * 1e6), "profiles/step_config2_resnet50_1x1_reduce_kernels_and_counters.md"),
+    (1, 0, "dsgc_sweep_kernel"): (int((51.6 + 0.2) * 1e6), "profiles/step_config1_resnet18_3x3_kernels_and_counters.md"),
+    (1, 0, "conv_band_trio_kernel", 2): (int((40.0 + 67.9) * 1e6), "profiles/step_config1_resnet18_3x3_kernels_and_counters.md"),
+    (1, 0, "conv_band_trio_kernel", 3): (int((53.9 + 119.4) * 1e6), "profiles/step_config1_resnet18_3x3_kernels_and_counters.md"),
 }
 
 MIN_STEPS_BEFORE_TIMING = 300
@@ -338,7 +341,7 @@ def main():
     launches = launches or per_kernel[dom][0]
     # per launch, as the duration is: the kernel's algorithmic work of the step / its launches per step
     roof = roofline_of(nbytes / launches, ops / launches, kind, dom_us * 1e-6, L.groups != 1)
-    tr = TRAFFIC.get((args.config, args.layer, dom))
+    tr = TRAFFIC.get((args.config, args.layer, dom) + ((2 if two_streams else 3,) if dom in SHARED_KERNELS else ()))
     roof["traffic"] = tr[0] if tr else None
     roof["traffic_source"] = ("stored figure, not measured by this run: " + tr[1]) if tr else None
     roof["kernel"] = dom
