@@ -798,7 +798,8 @@ static bool fwd_scratch_kept(const int8t_conv_desc* d, const Geo& g, const int8t
 }
 
 // Where a step that forms the codes of a (and of g_z: quant_g) and runs the forward pass may put the space-to-depth codes of a with the ordinary
-// ones: the forward pass's scratch, if nothing that is read or written up to that pass lies in it.  nullptr: the pass rewrites the codes itself.
+// ones: the forward pass's scratch, if nothing that is read or written up to that pass lies in it.  nullptr: the pass rewrites the codes itself (so
+// do the autograd modules, whose partial maxima and forward scratch are one buffer).
 static int8_t* s2d_with_codes(const int8t_conv_desc* d, const Geo& g, const int8t_layer_buffers* b, bool quant_g) {
     const size_t bytes = fwd_s2d_bytes(d, g);
     if (!bytes || !b->ws_fwd || b->ws_fwd_bytes < bytes) return nullptr;

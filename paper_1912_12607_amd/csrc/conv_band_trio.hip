@@ -22,6 +22,9 @@ struct BandWalk {
     int BP, nbands_h, nbands;
     BandRegTab tab;
 };
+// (The LDS body keeps its 12 staging slots.  6 where no window takes more would need ten instantiations more; with 12 / with 6, us for two and three
+// passes: 1x1, 24 -> 144, 56 x 56, batch 64: 23.2 49.1, 21.4 48.2; 1x3, 8 -> 16, 109 x 109, batch 26: 19.7 28.2, 18.3 26.0; 1x1, 16 -> 32,
+// 112 x 112, batch 64: 38.4 58.0, 36.6 55.8; 5x5, 3x3 and 7x1 on 16, 16 and 8 channels the same.)
 template <bool DGRAD, int NKS, int MT>
 __device__ __forceinline__ void band_pass(const IgemmArgs& a, const BandWalk& p, int block, int nblocks) {
     if constexpr (NKS > 0) band_reg_walk<DGRAD, NKS>(a, p.BP, p.nbands_h, p.nbands, p.tab, block, nblocks);

@@ -78,12 +78,12 @@ __device__ __forceinline__ void store_cell(T* __restrict__ dst, size_t o, int OW
 //   <WM=2, KG=8, NSTAGE=2, BNT=64>: 128 x 64 (waves of 64 x 32), 48 KB: twice the tiles for layers with few columns
 //   (7 x 7 and 8 x 8 images), which otherwise leave more than half of the compute units idle
 // ---------------------------------------------------------------------------------------------
-// What a stage costs a block alone on its compute unit (cycles, 128 x 64 tile): 780; its 12 operand reads, 8 matrix products and the barrier
-// 500, its 6 loads with nothing beside them 620 (latency).  Before the offsets were worked out a stage ahead and operands and loads took
-// turns it was 1150, of which 350 were the arithmetic between the products.  A block's fixed cost is as large as three stages: 2000 before
-// the first load (it was 2900: divisors come from the host), 1200 - 2000 for the first stage, 3000 - 5000 for the results.  us per pass alone:
-// 3x3, 256 channels, 14 x 14, batch 64: 17.7 -> 15.6; 1x1, 1024 -> 256, 14 x 14, batch 128, forward 16.5 -> 14.7; fully connected
-// 2048 -> 1000, batch 256, forward 14.7 -> 11.5; 3x3 under stride 2, 128 channels, 56 x 56, backward-data 35.1 -> 33.0.
+// What a stage of 128 bytes costs, us, by the times of 1x1 passes of 128 filters on 512 to 4096 channels (4 to 32 stages), before the offsets
+// were worked out a stage ahead and operands and loads took turns / so: 128 x 64 tile with 32 blocks 0.46, 0.32, with 256 blocks 0.62, 0.57;
+// 128 x 128 tile with 16 and 128 blocks 0.67, 0.45 and 0.76, 0.61.  (The matrix products of a stage, 8 and 16 of 32 cycles per wave, are 0.11 and
+// 0.21 us at 2.4 GHz; the rest is the chain of loads, operand reads and the barrier.)  us per pass alone: 3x3, 256 channels, 14 x 14,
+// batch 64: 17.7 -> 15.6; 1x1, 1024 -> 256, 14 x 14, batch 128, forward 16.5 -> 14.7; fully connected 2048 -> 1000, batch 256, forward
+// 14.7 -> 11.5; 3x3 under stride 2, 128 channels, 56 x 56, backward-data 35.1 -> 33.0.
 //   ALLC (with CLS and CELL, stride 2 x 2, every class with taps): the columns are the 2 x 2 cells of pixels and the
 //   block runs the four classes one after the other, each into accumulators of its own, then writes every cell
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class

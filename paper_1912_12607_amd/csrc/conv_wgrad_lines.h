@@ -232,7 +232,7 @@ __device__ __forceinline__ void wgrad_lines_tile(const WgradArgs& a, const unsig
         igd_wait_vmcnt<0>();            // this wave's loads of stage i have landed ...
         __syncthreads();                // ... and everyone's; all waves are done with stage i-1's slot
         // (All of the next stage's loads at once: dealt out between the products they came too late -- 3x3 under stride 2, 256 channels,
-        // 28 x 28: 25.9 us so, 27.2 -- though they keep the address path busy for 400 cycles of the 1700 of a stage.)
+        // 28 x 28: 25.9 us so, 27.2.)
         if (i + 1 < NS) issue((i + 1) & 1);
         const uint32_t sbase = lds0 + (uint32_t)(i & 1) * STAGE;
         auto fetch = [&](uint32_t off, int bytes) -> wl_v4i {

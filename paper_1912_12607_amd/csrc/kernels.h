@@ -289,9 +289,8 @@ unsigned wgrad_grid(const WgradArgs& a);         // blocks of wgrad_kernel
 unsigned wgrad_lines_grid(const WgradArgs& a);
 bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filters, stride 2 x 2
 // Partial tiles of the shares: four filters side by side, which a lane of a matrix product holds in four neighbouring registers (one 16-byte
-// store instead of four of 4 bytes; the address path of a compute unit takes 16 cycles for either, 3000 - 5000 at the end of a block with
-// the latter.  us for the pass, channel by channel / so: 7x1, 160 -> 192, 17 x 17, batch 64: 23.3, 19.7; 3x3, 96 channels, 35 x 35, batch 32:
-// 18.1, 16.5; 3x3, 64 channels, 56 x 56, batch 64: 21.5, 20.2; 1x1, 1024 -> 256, 14 x 14, batch 128: 26.3, 25.1).
+// store instead of four of 4 bytes: the address path of a compute unit takes 16 cycles for either.  us for the pass, channel by
+// channel / so: 7x1, 160 -> 192, 17 x 17, batch 64: 23.3, 19.7; 3x3, 96 channels, 35 x 35, batch 32: 18.1, 16.5; 3x3, 64 channels, 56 x 56, batch 64: 21.5, 20.2; 1x1, 1024 -> 256, 14 x 14, batch 128: 26.3, 25.1).
 __host__ __device__ inline size_t wgrad_partial_elems(const WgradArgs& a) { return (size_t)((a.K + 3) / 4 * 4) * a.R * a.S * a.Cp; }      // of one share
 inline size_t wgrad_partial_bytes(const WgradArgs& a) { return (a.splits * wgrad_partial_elems(a) * 4 + 255) & ~(size_t)255; }
 
