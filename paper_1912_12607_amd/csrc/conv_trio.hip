@@ -178,7 +178,9 @@ static int trio_shares(const IgemmArgs* fwd, const IgemmArgs& bwd, const WgradAr
             const int stages = (a->R * a->S * (a->Ca >> 4) + 8 * taps - 1) / (8 * taps);
             end = std::max(end, clock.deal(tiles, 1.46 + stages * 1.51 * (0.35 + 0.65 * (half ? 0.5 : tile.bn / 128.0))));
         }
-        return end + shares * (double)w.t_partial * 1.11 + (shares > 1 ? 10.39 : 0.0);
+        WgradArgs t = w;
+        t.splits = shares;
+        return end + shares * (double)w.t_partial * 1.11 + (wgrad_single_share(t) ? 0.0 : 10.39);
     };
     int best = w.splits;
     double least = estimate(w.splits);

@@ -294,8 +294,17 @@ bool wgrad_lines_s2(const WgradArgs& a);         // the stride-2 form: 3x3 filte
 __host__ __device__ inline size_t wgrad_partial_elems(const WgradArgs& a) { return (size_t)((a.K + 3) / 4 * 4) * a.R * a.S * a.Cp; }      // of one share
 inline size_t wgrad_partial_bytes(const WgradArgs& a) { return (a.splits * wgrad_partial_elems(a) * 4 + 255) & ~(size_t)255; }
 
-// Whether the pass runs as one share on image lines, in the layer's own geometry: its tiles may then be the result (WgradArgs::direct).
-inline bool wgrad_single_share(const WgradArgs& a) { return a.lines && !a.s2d && a.splits == 1; }
+// Whether the pass runs as one share on image lines, in the layer's own geometry, and its tiles are better written as the result
+// (WgradArgs::direct) than reduced: neighbouring lanes then store R S floats apart, the taps along the line as a run, where a reduction writes
+// whole filters but takes a launch.  us, as the result / with the reduction:
+//   3x3   64 -> 64 (0.15 MB of weights) 6.6, 8.9   640 -> 384 (8.8 MB) 12.7, 14.7
+//   5x5   33 -> 48 (0.16 MB) 7.5, 8.8   40 -> 64 (0.26 MB) 9.3, 8.7   64 -> 64 (0.4 MB) 12.7, 8.6   256 -> 128 (3.3 MB) 15.8, 13.8   320 -> 256 (8.2 MB) 22.1, 24.0
+//   7x7   16 -> 64 (0.2 MB) 7.9, 9.1    33 -> 48 (0.31 MB) 10.0, 9.3    64 -> 64 (0.8 MB) 18.7, 10.0   256 -> 128 (6.4 MB) 22.3, 14.4   640 -> 384 (48 MB) 69.5, 50.5
+inline bool wgrad_single_share(const WgradArgs& a) {
+    const int RS = a.R * a.S;
+    const long long bytes = 4ll * RS * a.C * a.K;
+    return a.lines && !a.s2d && a.splits == 1 && (RS <= 9 || bytes <= 200000 || (RS <= 25 && bytes >= 6000000));
+}
 
 // which kernel VAR_AUTO stands for: true = wgrad_lines_kernel
 bool wgrad_auto_lines(const WgradArgs& a);

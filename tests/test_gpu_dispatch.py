@@ -717,6 +717,36 @@ def test_backward_weight_over_its_codes():
         assert B.int8t_profile_stop() and np.array_equal(dw.cpu().numpy().reshape(want.shape), want.astype(np.float32))
 
 
+# One share of a large filter: its tile is the result where the weights are few, or 5x5 and many; reduced otherwise.  Both alone and
+# beside backward-data, whose launch may take fewer shares.
+@pytest.mark.parametrize("shape,one_share", [
+    ((1, 33, 8, 8, 33, 5, 5, 1, (2, 2)), True), ((1, 64, 8, 8, 64, 5, 5, 1, (2, 2)), False), ((1, 245, 6, 6, 245, 5, 5, 1, (2, 2)), True),
+    ((2, 64, 8, 9, 61, 7, 7, 1, (3, 3)), False), ((1, 16, 9, 8, 48, 7, 7, 1, (3, 3)), True), ((1, 70, 8, 8, 130, 3, 3, 1, (1, 1)), True),
+    ((1, 150, 7, 7, 130, 7, 7, 1, (3, 3)), False)])
+def test_single_share_of_large_filters(shape, one_share):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 19)
+    B.int8t_profile_start("wgrad_reduce_kernel")
+    conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
+    assert bool(B.int8t_profile_stop()) != one_share
+    N, C, H, W, K, R, S, stride, pad = shape
+    st = LayerStep(inputs.Layer("layer", N, C, H, W, K, R, S, stride=(stride, stride), pad=pad), keep_acc=True, requantize_deviation=False)
+    g = torch.Generator(device=DEV).manual_seed(23)
+    for t in (st.x, st.w, st.dy):
+        t.normal_(generator=g)
+    st.clip.fill_(1.5)
+    B.int8t_layer_step(st.desc, st._layer_buffers, B.STEP_ABSMAX | B.STEP_QUANT_XW | B.STEP_QUANT_G, 3)
+    st.bwd_data()
+    st.bwd_weight()
+    outs = [st.dx, st.dx_acc, st.dw, st.dw_acc]
+    want = [t.clone() for t in outs]
+    for t in outs:
+        t.fill_(7)
+    B.int8t_layer_step(st.desc, st._layer_buffers, B.STEP_BWD_DATA | B.STEP_BWD_WEIGHT)
+    torch.cuda.synchronize()
+    for a, b in zip(outs, want):
+        assert torch.equal(a, b)
+
+
 # Passes with the filter bank on chip in one launch with backward-weight: every body (weights in registers, in LDS with one and two
 # row tiles) with every form of backward-weight (image granules; 1, 3, 5, 7 taps along a line), all three passes or the
 # forward pass ahead, bands that end below the image, planes of odd sizes.  Bit for bit the calls one by one.
