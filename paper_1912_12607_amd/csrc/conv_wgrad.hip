@@ -364,26 +364,22 @@ static int wgrad_flat_quads(unsigned quads, int splits) {
 
 hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
     if (a.direct && a.lines) return hipSuccess;       // (wgrad_lines_tile wrote the result)
-    // Shape of the reducing blocks: the most taps (9, 7 or 3 where they divide R*S) and channels (64, 16 or
-    // 4) per block that still give the chip 1024 blocks -- few fat blocks leave compute units idle and the
-    // loads of a small layer are latency, not bandwidth; the flat kernel if nothing does.  A block's
-    // threads are channels x (split lanes): 64 channels leave 4 split lanes, which is what few splits
-    // can keep busy.
+    // Shape of the reducing blocks: taps (9, 7 or 3 where they divide R*S; they leave as runs) x channels (64 or 16), the flat kernel, which
+    // stores single floats R*S apart, if nothing fits.  A block's threads are channels x (split lanes): 64 channels leave 4 lanes, which
+    // is what few shares can keep busy, and their longer runs want the chip just filled; of 16 channels few blocks do, but many
+    // shares are many loads for each, and flat blocks are more.  us, 64 channels / 16 / flat:
+    //   1x7, 192 -> 768, 4 shares   6.3  6.6  10.2     3x3, 512 -> 160, 3 shares   4.9  6.0   5.1     7x7, 160 -> 192, 3 shares     -   9.1  15.2
+    //   3x3, 768 -> 320, 2 shares   7.6 11.7  12.3     3x3, 1024 -> 64, 8 shares   7.1  5.4   5.0     7x1, 512 -> 192, 13 shares  8.8  8.0   7.1
+    // Over 260 layers of 3, 7, 9 and 49 taps and 2 to 24 shares this takes 1.010 of the time of the best shape of each (1.13 at most); channels
+    // before taps and 1024 blocks for any shape, as it was, 1.074 (2.0 at most).
     const int RS = a.R * a.S;
-    int rsc = 1, qn = 4;
-    {
-        const int cand[3] = {9, 7, 3};
-        const int qns[3] = {64, 16, 4};
-        bool found = false;
-        for (int w = 0; w < 3 && !found; ++w) {
-            if (a.Cp % qns[w] != 0) continue;
-            if (qns[w] == 64 && a.splits > 6) continue;
-            for (int i = 0; i < 4 && !found; ++i) {
-                const int r = i < 3 ? cand[i] : 1;
-                if (RS % r != 0) continue;
-                if ((long long)((a.K + 3) / 4) * (a.Cp / qns[w]) * (RS / r) >= 1024) { rsc = r; qn = qns[w]; found = true; }
-            }
-        }
+    int rsc = 1, qn = 0;
+    for (const int taps : {9, 7, 3}) {
+        if (RS % taps != 0 || rsc > 1) continue;
+        auto blocks = [&](int channels) { return a.Cp % channels == 0 ? (long long)((a.K + 3) / 4) * (a.Cp / channels) * (RS / taps) : 0ll; };
+        if (a.splits <= 6 && blocks(64) >= 320) qn = 64;
+        else if (blocks(16) >= (a.splits <= 12 ? 128 : 1024)) qn = 16;
+        if (qn) rsc = taps;
     }
     KernelTimer kt(KID_WGRAD_REDUCE, st);
     if (rsc == 1) {
@@ -400,8 +396,7 @@ hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t st) {
 #define REDUCE(RSCv)                                                                                         \
     do {                                                                                                     \
         if (qn == 64) launch_timed(kt, (wgrad_reduce_kernel<64, RSCv>), blocks, dim3(256), 0, st, a);      \
-        else if (qn == 16) launch_timed(kt, (wgrad_reduce_kernel<16, RSCv>), blocks, dim3(256), 0, st, a); \
-        else launch_timed(kt, (wgrad_reduce_kernel<4, RSCv>), blocks, dim3(256), 0, st, a);                \
+        else launch_timed(kt, (wgrad_reduce_kernel<16, RSCv>), blocks, dim3(256), 0, st, a);               \
     } while (0)
     if (rsc == 9) REDUCE(9);
     else if (rsc == 7) REDUCE(7);

@@ -717,6 +717,23 @@ def test_backward_weight_over_its_codes():
         assert B.int8t_profile_stop() and np.array_equal(dw.cpu().numpy().reshape(want.shape), want.astype(np.float32))
 
 
+# The reduction in blocks of 9, 7 and 3 taps x 64 and 16 channels, with few and with many shares, and the flat one; filters and channels
+# that fill neither their last four nor their last sixteen.
+@pytest.mark.parametrize("shape,variant", [
+    ((8, 250, 7, 7, 515, 3, 3, 1, (1, 1)), B.VARIANT_WGRAD_MORE), ((8, 320, 7, 10, 410, 1, 7, 1, (0, 3)), 0), ((16, 254, 7, 7, 382, 1, 3, 1, (0, 1)), 0),
+    ((16, 190, 7, 7, 190, 3, 3, 1, (1, 1)), 0), ((24, 100, 10, 10, 110, 1, 7, 1, (0, 3)), 0), ((64, 100, 6, 6, 110, 1, 3, 1, (0, 1)), 0),
+    ((16, 40, 12, 14, 61, 5, 5, 1, (2, 2)), 0), ((64, 120, 14, 14, 519, 3, 1, 1, (1, 0)), 0), ((60, 30, 9, 9, 66, 3, 3, 1, (1, 1)), 0)])
+def test_reductions_of_few_and_many_shares(shape, variant):
+    desc, od, (xq, wq, dyq) = random_layer(shape, 29)
+    B.int8t_conv_select_variant(B.OP_CONV_BWD_WEIGHT, desc, variant)
+    try:
+        B.int8t_profile_start("wgrad_reduce_kernel")
+        conv_pass_elementwise(B.OP_CONV_BWD_WEIGHT, desc, od, xq, wq, dyq, True)
+        assert B.int8t_profile_stop()
+    finally:
+        B.int8t_conv_select_variant(B.OP_CONV_BWD_WEIGHT, desc, B.VARIANT_AUTO)
+
+
 # One share of a large filter: its tile is the result where the weights are few, or 5x5 and many; reduced otherwise.  Both alone and
 # beside backward-data, whose launch may take fewer shares.
 @pytest.mark.parametrize("shape,one_share", [
