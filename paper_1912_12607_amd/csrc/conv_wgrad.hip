@@ -34,6 +34,8 @@ __device__ __forceinline__ void wgrad_result(const WgradArgs& a, int k, int rs, 
 // Bound: one round trip to memory and the launch.  Before, 4 or 16 quads x one tap with the shares one after the other and the lanes summed
 // in LDS, and now, us: 3x3, 64 channels at 56 x 56, batch 64 (112 shares) 7.2, 4.7; 1x1, 64 -> 256 at 56 x 56, batch 256 (224) 7.2, 4.6;
 // 1x1, 1024 -> 256 at 14 x 14, batch 128 (19) 6.8, 5.5; 5x5, 48 -> 64 at 35 x 35, batch 32 (35) 5.4, 4.5.
+// Few shares of many weights are bandwidth: 1x1, 1024 -> 2048 at 4 x 4, batch 256 (3 shares, 34 MB), all 8 loads of a lane / the one it needs:
+// 10.4, 9.4; 2048 -> 512 at 7 x 7, batch 64 (3) 6.3, 5.7.
 template <int Q>
 __global__ __launch_bounds__(256) void wgrad_reduce_flat_kernel(const WgradArgs a) {
     constexpr int ZL = 256 / Q, ZU = 8;
@@ -44,16 +46,17 @@ __global__ __launch_bounds__(256) void wgrad_reduce_flat_kernel(const WgradArgs 
     const unsigned qi = q0 + threadIdx.x % Q;
     const int4* __restrict__ p = reinterpret_cast<const int4*>(a.partial) + (qi < quads ? qi : 0u);
     int4 sum = make_int4(0, 0, 0, 0);
-    for (int z0 = zl; z0 < a.splits; z0 += ZU * ZL) {
+    for (int z0 = 0; z0 < a.splits; z0 += ZU * ZL) {       // (the block's lanes together: no load that none of them needs)
         int4 v[ZU];
 #pragma unroll
-        for (int u = 0; u < ZU; ++u) {           // (unconditional: past the end the last share again, not added)
-            const int z = z0 + u * ZL;
-            v[u] = p[(size_t)(z < a.splits ? z : a.splits - 1) * quads];
+        for (int u = 0; u < ZU; ++u) {           // (a lane past the end takes the last share again, not added)
+            v[u] = make_int4(0, 0, 0, 0);
+            const int z = z0 + u * ZL + zl;
+            if (z0 + u * ZL < a.splits) v[u] = p[(size_t)(z < a.splits ? z : a.splits - 1) * quads];
         }
 #pragma unroll
         for (int u = 0; u < ZU; ++u) {
-            const int keep = z0 + u * ZL < a.splits ? -1 : 0;
+            const int keep = z0 + u * ZL + zl < a.splits ? -1 : 0;
             sum.x += v[u].x & keep; sum.y += v[u].y & keep; sum.z += v[u].z & keep; sum.w += v[u].w & keep;
         }
     }
