@@ -11,6 +11,9 @@
 // reads); the next two rounds of 64 channels are on their way meanwhile, two tiles alternate, one barrier per 64 channels.  (With one round
 // ahead, zeroed where it was loaded -- which waited for it on the spot -- and addresses of 64 bits, us per call: 144 -> 24 at 56 x 56, batch 64:
 // 53.3, now 49.8; 32 -> 16 at 112 x 112: 55.8, 48.1; 16 -> 34 at 96 x 96, batch 43: 33.6, 26.8.  Five blocks per compute unit: no gain.)
+// Planes of no whole 16-byte groups: blocks with one round each (infer_1x1_applies(), the grid), whose 32 loads of a float are what they
+// wait for; one round ahead, and only if there is one.  150 layers with two empty rounds of loads / so: 1.12 and 0.92 of the time with 64-bit addresses
+// (16 -> 8 at 61 x 61, batch 32: 13.3, 9.6 us; 40 -> 24 at 81 x 81, batch 16: 16.0, 12.3; 8 -> 8 at 73 x 73, batch 8: 7.9, 6.2).
 #include <algorithm>
 
 #include "device_common.h"
@@ -86,7 +89,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
     after(tile1, cc1);
     int tile2 = tile1, cc2 = cc1;
     fetch(f0, tile, 0);
-    fetch(f1, tile1, cc1);
+    if (VEC) fetch(f1, tile1, cc1);
     __syncthreads();
     const float inv_x = inv_scale_of(s_max[0]), inv_w = inv_scale_of(s_max[1]);
     const float scale = __fmul_rn(scale_of(s_max[0]), scale_of(s_max[1]));
@@ -127,6 +130,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
             for (int k = 0; k < 4; ++k)
                 *reinterpret_cast<uint32_t*>(xb + (64 * h + 4 * pq + k) * INF_PITCH + 4 * cgp) = o[k];
         }
+        if (!VEC && tile1 < a.tiles) fetch(f, tile1, cc1);      // (uniform)
         __syncthreads();      // this tile's codes are there (the first time: the filters' too), the other tile has been read
 #pragma unroll
         for (int kk = 0; kk < INF_CH / 32; ++kk) {
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
         }
         // (behind the results: a wait for the next round then does not wait for these loads)
         after(tile2, cc2);
-        fetch(f, tile2, cc2);
+        if (VEC) fetch(f, tile2, cc2);
         tile = tile1;
         cc = cc1;
         tile1 = tile2;
@@ -161,7 +165,7 @@ __global__ __launch_bounds__(256, inf_blocks(RT)) void infer_1x1_kernel(const In
     while (tile < a.tiles) {                             // (uniform over the block)
         round(f0, xt, rx);
         if (tile >= a.tiles) break;
-        round(f1, xt + INF_TILE, rx + INF_TILE);
+        round(VEC ? f1 : f0, xt + INF_TILE, rx + INF_TILE);
     }
 }
 
