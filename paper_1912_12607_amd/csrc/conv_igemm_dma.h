@@ -83,7 +83,10 @@ __device__ __forceinline__ void store_cell(T* __restrict__ dst, size_t o, int OW
 // 128 x 128 tile with 16 and 128 blocks 0.67, 0.45 and 0.76, 0.61.  (The matrix products of a stage, 8 and 16 of 32 cycles per wave, are 0.11 and
 // 0.21 us at 2.4 GHz; the rest is the chain of loads, operand reads and the barrier.)  us per pass alone: 3x3, 256 channels, 14 x 14,
 // batch 64: 17.7 -> 15.6; 1x1, 1024 -> 256, 14 x 14, batch 128, forward 16.5 -> 14.7; fully connected 2048 -> 1000, batch 256, forward
-// 14.7 -> 11.5; 3x3 under stride 2, 128 channels, 56 x 56, backward-data 35.1 -> 33.0.
+// 14.7 -> 11.5; 3x3 under stride 2, 128 channels, 56 x 56, backward-data 35.1 -> 33.0.  Over 620 forward and backward-data passes of random layers 0.94 of the
+// time: 0.87 - 0.93 where the channels are whole stages; elsewhere 0.93 - 0.95 up to two blocks per compute unit and 0.97 - 1.0 above, where the arithmetic
+// of the lanes and loads of two half lines per pixel bound (3x3, 850 -> 1024, 12 x 12, batch 32, 576 tiles: 65, 78; the others 1.13 at most).  Dealing
+// the loads out between the products gains 2 - 3 % there and costs 3 % below two blocks per compute unit.
 //   ALLC (with CLS and CELL, stride 2 x 2, every class with taps): the columns are the 2 x 2 cells of pixels and the
 //   block runs the four classes one after the other, each into accumulators of its own, then writes every cell
 //   whole -- two neighbouring floats per lane and image row, whole cache lines per wave -- where the per-class
